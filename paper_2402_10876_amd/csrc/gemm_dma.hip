@@ -11,9 +11,14 @@
 //   gather  : lane l of a copy instruction fetches one 16-byte chunk of row
 //             row_idx[...] of A (Listing 1: CTO_k); the four (TM=128) rows an
 //             instruction covers come from one scalar load of the index list.
-//   LDS     : k-major tiles, 64-byte units XOR-swizzled (see swz_mask); the
-//             swizzle is applied on the global side, the LDS side of a copy
-//             instruction is always 1 KiB contiguous.
+//   LDS     : k-major tiles of A (and of the dense baseline's B), 64-byte units
+//             XOR-swizzled (see swz_mask); the swizzle is applied on the global
+//             side, the LDS side of a copy instruction is always 1 KiB contiguous.
+//             A packed weight is stored in the register order of the matrix
+//             instruction (see the packer) and copied as it lies: one 16-byte
+//             LDS read per operand instead of two transposing ones (1-2 % of
+//             every TW launch: 8192 x 1024 x 4096 and 8192 x 4096 x 1024 at 50 %
+//             together 91.0 -> 89.4 us, a BERT-base layer at 75 % 39.0 -> 38.4).
 //   MFMA    : operands come from ds_read_b64_tr_b16 issued from inline
 //             assembly.  The compiler orders every LDS read it knows about
 //             behind all earlier asynchronous copies (vmcnt(0)), which would
@@ -30,6 +35,8 @@ namespace twg {
 
 namespace {
 
+typedef int int4v __attribute__((ext_vector_type(4)));
+
 template <int OFF>
 __device__ __forceinline__ int2v tr_read(uint32_t addr) {
   int2v v;
@@ -45,27 +52,32 @@ __device__ __forceinline__ half8 as_half8(const Frag& f) {
   u.s[0] = f.lo; u.s[1] = f.hi;
   return u.h;
 }
+// The same operand where the tile is stored in the matrix core's register order.
+template <int OFF>
+__device__ __forceinline__ int4v read128(uint32_t addr) {
+  int4v v;
+  asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(v) : "v"(addr), "n"(OFF));
+  return v;
+}
+__device__ __forceinline__ half8 as_half8(const int4v& f) {
+  union { int4v s; half8 h; } u;
+  u.s = f;
+  return u.h;
+}
 
-template <int N>
-__device__ __forceinline__ void wait_lds(Frag* f) {
-  // s_waitcnt tied to the fragments so that no use can be moved above it
-  if constexpr (N == 2)
-    asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(f[0].lo), "+v"(f[0].hi), "+v"(f[1].lo), "+v"(f[1].hi));
-  else if constexpr (N == 3)
-    asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(f[0].lo), "+v"(f[0].hi), "+v"(f[1].lo), "+v"(f[1].hi),
-                 "+v"(f[2].lo), "+v"(f[2].hi));
-  else if constexpr (N == 4)
-    asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(f[0].lo), "+v"(f[0].hi), "+v"(f[1].lo), "+v"(f[1].hi),
-                 "+v"(f[2].lo), "+v"(f[2].hi), "+v"(f[3].lo), "+v"(f[3].hi));
-  else if constexpr (N == 6)
-    asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(f[0].lo), "+v"(f[0].hi), "+v"(f[1].lo), "+v"(f[1].hi),
-                 "+v"(f[2].lo), "+v"(f[2].hi), "+v"(f[3].lo), "+v"(f[3].hi), "+v"(f[4].lo),
-                 "+v"(f[4].hi), "+v"(f[5].lo), "+v"(f[5].hi));
-  else static_assert(N == 2, "unsupported fragment count");
+// s_waitcnt tied to the fragments so that no use can be moved above it: MB blocks of A, NB of B.
+__device__ __forceinline__ void tie(Frag& f) { asm volatile("" : "+v"(f.lo), "+v"(f.hi)); }
+__device__ __forceinline__ void tie(int4v& f) { asm volatile("" : "+v"(f)); }
+template <int MB, int NB, class FB>
+__device__ __forceinline__ void wait_lds(Frag* a, FB* b) {
+  asm volatile("s_waitcnt lgkmcnt(0)");
+#pragma unroll
+  for (int i = 0; i < MB; ++i) tie(a[i]);
+#pragma unroll
+  for (int j = 0; j < NB; ++j) tie(b[j]);
 }
 
 // Wave-uniform 16-byte record through the scalar cache, complete on return.
-typedef int int4v __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ int4v scalar_load4(const void* p) {
   int4v r;
   asm volatile("s_load_dwordx4 %0, %1, 0x0\n\ts_waitcnt lgkmcnt(0)" : "=s"(r) : "s"(p));
@@ -311,6 +323,7 @@ void tw_gemm_km_dma_kernel(GemmArgs g_arg) {
     const int row = (wave * NIB + j) * RPIB + b_rloc;
     b_el[j] = ((lb % RBB) ^ swz_mask<RBB>(row)) / 2;
     if constexpr (DENSE) { if (t * TN + b_el[j] >= g.N) b_el[j] = 0; }
+    else b_el[j] = (lb % RBB) / 2;            // the packed image is copied as it lies
   }
   // Addresses are a wave-uniform base plus an unsigned 32-bit byte offset per
   // lane (the host checks that A fits): one multiply-add per copy instruction.
@@ -416,30 +429,36 @@ void tw_gemm_km_dma_kernel(GemmArgs g_arg) {
     fa[i] = lds0 + grp * (KS * RBA) + swz<RBA>(frow, (wm * WM + i * 32 + 16 * (q & 1) + 4 * (p & 3)) * 2);
 #pragma unroll
   for (int j = 0; j < NB; ++j)
-    fb[j] = lds0 + STAGE_A + grp * (KS * RBB) + swz<RBB>(frow, (wn * WN + j * 32 + 16 * (q & 1) + 4 * (p & 3)) * 2);
+    fb[j] = lds0 + STAGE_A + grp * (KS * RBB) +
+            (DENSE ? swz<RBB>(frow, (wn * WN + j * 32 + 16 * (q & 1) + 4 * (p & 3)) * 2) : (wn * NB + j) * 1024 + lane * 16);
 
-  constexpr int NF = MB + NB;
-  Frag f0[NF], f1[NF];       // operands of k-steps 0 and 1 of a stage
-  auto read_step = [&](uint32_t boff, auto KK_, Frag* f) {
+  // operands of k-steps 0 and 1 of a stage; a packed weight is stored in register order (one
+  // 16-byte read per lane), the dense baseline's B needs the transposing reads
+  struct Ops { Frag a[MB]; std::conditional_t<DENSE, Frag, int4v> b[NB]; };
+  Ops f0, f1;
+  auto read_step = [&](uint32_t boff, auto KK_, Ops& f) {
     constexpr int KK = decltype(KK_)::value;
 #pragma unroll
     for (int i = 0; i < MB; ++i) {
-      f[i].lo = tr_read<KK * RBA>(fa[i] + boff);
-      f[i].hi = tr_read<(KK + 4) * RBA>(fa[i] + boff);
+      f.a[i].lo = tr_read<KK * RBA>(fa[i] + boff);
+      f.a[i].hi = tr_read<(KK + 4) * RBA>(fa[i] + boff);
     }
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
-      f[MB + j].lo = tr_read<KK * RBB>(fb[j] + boff);
-      f[MB + j].hi = tr_read<(KK + 4) * RBB>(fb[j] + boff);
+      if constexpr (DENSE) {
+        f.b[j].lo = tr_read<KK * RBB>(fb[j] + boff);
+        f.b[j].hi = tr_read<(KK + 4) * RBB>(fb[j] + boff);
+      } else {
+        f.b[j] = read128<KK * RBB>(fb[j] + boff);
+      }
     }
   };
-  auto mfma_step = [&](const Frag* f) {
+  auto mfma_step = [&](const Ops& f) {
 #pragma unroll
     for (int i = 0; i < MB; ++i)
 #pragma unroll
       for (int j = 0; j < NB; ++j)
-        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(as_half8(f[i]), as_half8(f[MB + j]),
-                                                           acc[i][j], 0, 0, 0);
+        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(as_half8(f.a[i]), as_half8(f.b[j]), acc[i][j], 0, 0, 0);
   };
   using K0 = std::integral_constant<int, 0>;
   using K16 = std::integral_constant<int, 16>;
@@ -481,7 +500,7 @@ void tw_gemm_km_dma_kernel(GemmArgs g_arg) {
     read_step(boff, K0{}, f0);
     if (s > 0 && live_prev) mfma_step(f1);   // second k-step of the previous stage
     const bool live = s * KSPLIT + grp < ns32;   // false only for group 1 on an odd tail
-    wait_lds<NF>(f0);                    // full wait: the index fetch above is in as well
+    wait_lds<MB, NB>(f0.a, f0.b);        // full wait: the index fetch above is in as well
     tie_rows(rows_next);
     // the copies of stage sn = s+D-1 go into the buffer of stage s-1, which every wave has
     // finished reading; when sn opens chunk c >= 1 of the list, chunk c+1 follows it into the
@@ -495,7 +514,7 @@ void tw_gemm_km_dma_kernel(GemmArgs g_arg) {
     if (live) mfma_step(f0);
     live_prev = live;
     rows_cur = rows_next;
-    wait_lds<NF>(f1);
+    wait_lds<MB, NB>(f1.a, f1.b);
   }
   if (ns > 0 && live_prev) mfma_step(f1);
 

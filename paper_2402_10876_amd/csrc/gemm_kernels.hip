@@ -103,7 +103,7 @@ __global__ __launch_bounds__(NTHREADS) void tw_gemm_km_kernel(GemmArgs g) {
   for (int i = 0; i < NBK; ++i) {
     const int id = (tid + i * NTHREADS) % (KS * CB);
     b_row[i] = id / CB; b_c[i] = id % CB;
-    b_slot[i] = swz<RBB>(b_row[i], b_c[i] * 16);
+    b_slot[i] = DENSE ? swz<RBB>(b_row[i], b_c[i] * 16) : id * 16;
     b_live[i] = true;
     if constexpr (DENSE) {
       if (t * TN + b_c[i] * 8 >= g.N) { b_live[i] = false; b_c[i] = 0; }  // past the last column
@@ -217,7 +217,10 @@ __global__ __launch_bounds__(NTHREADS) void tw_gemm_km_kernel(GemmArgs g) {
 #pragma unroll
       for (int i = 0; i < MB; ++i) a[i] = lds_operand<RBA>(As, wm * WM + i * 32, kk, lane);
 #pragma unroll
-      for (int j = 0; j < NB; ++j) b[j] = lds_operand<RBB>(Bs, wn * WN + j * 32, kk, lane);
+      for (int j = 0; j < NB; ++j) {
+        if constexpr (DENSE) b[j] = lds_operand<RBB>(Bs, wn * WN + j * 32, kk, lane);
+        else b[j] = *(const half8*)(Bs + (kk / 16 * (TN / 32) + wn * NB + j) * 1024 + lane * 16);   // register order
+      }
 #pragma unroll
       for (int i = 0; i < MB; ++i)
 #pragma unroll

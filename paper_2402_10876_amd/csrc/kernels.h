@@ -9,7 +9,8 @@ struct GemmArgs {
   const _Float16* A;   // KM kernels: K x M, element (i,k) at A[k*lda + i]; MK: A[i*lda + k]
   _Float16* C;         // KM kernels: N x M, element (i,n) at C[n*ldc + i]; MK: C[i*ldc + n]
   int M, lda, ldc;
-  // TW: condensed weight image [sum Kp_t][G]; dense: B, K x N row-major
+  // TW: condensed weight image, register order of the matrix instruction (see the packer);
+  // dense: B, K x N row-major
   const _Float16* vals;
   int ldb;                       // dense only
   const int32_t* row_idx;        // TW: padded kept-row lists (CTO_k as indices)

@@ -281,8 +281,11 @@ tw_status concat_host(const tw_handle_s* const* parts, int n, tw_handle_s* h) tr
 // ---------------------------------------------------------------------------
 // Device image.
 //
-// TW : per tile, Kp_t = K_t rounded up to KSTEP_TW rows of G halves, row-major,
-//      zero filled (rows past K_t and columns past W_t).
+// TW : per tile, Kp_t = K_t rounded up to KSTEP_TW rows of G halves, zero filled (rows past
+//      K_t and columns past W_t), in the register order of v_mfma_f32_32x32x16_f16's second
+//      operand: for k-step s (16 condensed rows), column block nb (32 columns) and lane l the 8
+//      halves of column 32 nb + l%32, rows 16 s + 8 (l/32) .. +7.  A lane's halves are
+//      contiguous (one 16-byte load), a wave's 64 lanes are contiguous (1 KiB).
 // TVW: per tile, Kp_t = K_t rounded up to KSTEP_TVW.  The compressed tile is
 //      stored in the register order of v_smfmac_f32_32x32x32_f16's sparse
 //      operand: for K-stage s (64 rows), half u (32 rows), column block nb
@@ -436,8 +439,12 @@ void build_device_values(tw_handle_s* h) {
       const int w = h->tile_col_off[t + 1] - h->tile_col_off[t];
       const uint16_t* v = h->values.data() + h->val_off[t];
       uint16_t* o = d.vals.data() + (size_t)d.tile_kp_off[t] * G;
-      for (int j = 0; j < kt; ++j)
-        std::copy(v + (size_t)j * w, v + (size_t)(j + 1) * w, o + (size_t)j * G);
+      for (int j0 = 0; j0 < kt; j0 += 8) {               // 8 rows of a column at a time
+        uint16_t* ob = o + (size_t)(j0 / 16) * G * 16 + (j0 % 16) * 32;
+        const int jn = std::min(8, kt - j0);
+        for (int c = 0; c < w; ++c)
+          for (int j = 0; j < jn; ++j) ob[(c / 32) * 512 + (c % 32) * 8 + j] = v[(size_t)(j0 + j) * w + c];
+      }
     }
     d.meta.clear();
     return;

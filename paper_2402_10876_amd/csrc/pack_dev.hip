@@ -73,7 +73,8 @@ struct TileTables {           // device pointers, per tile t (n_tiles + 1 entrie
   const int32_t* col_idx;     // device image: [t * G + c], -1 = none
 };
 
-// TW: logical values V[t][j][c] and the image [kp0 + j][c] (zero padded), one thread per image element
+// TW: logical values V[t][j][c] and the image (zero padded, register order of the matrix
+// instruction: see the host packer's build_device_values), one thread per image element
 __global__ void gather_tw(const uint16_t* B, int ldb, int G, TileTables tt, uint16_t* logical, uint16_t* image) {
   const int t = blockIdx.y;
   const int kp0 = tt.tile_kp_off[t], kp = tt.tile_kp_off[t + 1] - kp0;
@@ -87,7 +88,7 @@ __global__ void gather_tw(const uint16_t* B, int ldb, int G, TileTables tt, uint
     v = B[(size_t)tt.row_idx[kp0 + j] * ldb + tt.col_idx[t * G + c]];
     logical[tt.val_off[t] + (size_t)j * w + c] = v;
   }
-  image[(size_t)(kp0 + j) * G + c] = v;
+  image[(size_t)kp0 * G + (size_t)(j / 16) * (16 * G) + (c / 32) * 512 + ((j % 16) / 8) * 256 + (c % 32) * 8 + j % 8] = v;
 }
 
 // TVW, logical form: per (tile, group of 4 kept rows, column) the two stored positions, which

@@ -29,7 +29,7 @@ struct DeviceImage {
   std::vector<int32_t> zero_cols;    // original indices of pruned columns
   std::vector<int32_t> tile_order;   // tiles by descending K_t (longest first)
   std::vector<int32_t> tile_sched;   // per launch position: {tile, kp offset, Kp_t, width}
-  std::vector<uint16_t> vals;        // TW: [sum Kp_t][G]; TVW: swizzled compressed values
+  std::vector<uint16_t> vals;        // TW: condensed rows, TVW: compressed values; both in register order
   std::vector<int8_t> vals8;         // int8: TW [sum Kp_t][G] bytes, TVW swizzled compressed bytes (vals is empty then)
   std::vector<uint32_t> meta;        // TVW: swizzled 2-bit position words
   std::vector<int32_t> ew_ptr;       // TEW: N+1 offsets into ew_pairs, by original column
