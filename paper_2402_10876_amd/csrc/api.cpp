@@ -592,7 +592,7 @@ tw_status tw_dense_gemm(const void* A, const void* B, void* C, int M, int K, int
   g.xcd_map = o.xcd_map;
   g.wg_split = 1;
   if (layout == TW_LAYOUT_MK) {
-    hipError_t em = twg::launch_dense_mk(tn, g, (hipStream_t)stream);
+    hipError_t em = twg::launch_dense_mk(g, (hipStream_t)stream);
     return em == hipSuccess ? TW_OK : TW_ERR_HIP;
   }
   const int tm = pick_tile_m(o, M, g.n_tiles, tn, K, true);

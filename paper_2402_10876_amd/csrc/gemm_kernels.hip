@@ -38,11 +38,10 @@ __device__ __forceinline__ half8 lds_operand(const char* tile, int x0, int k0, i
   return u.h;
 }
 
-// MK = true: A is M x K and C is M x N, both row-major (the layout Section V
-// calls uncoalesced once rows are pruned).  Only the global accesses differ:
-// the gather reads single halves A[m][row_idx[k]] and the scatter writes single
-// halves C[m][col_idx[n]]; LDS tiles, MFMA feeding and staging are unchanged.
-// It is a compatibility path and is not tuned.
+// MK = true (dense baseline only): A is M x K and C is M x N, both row-major.
+// Only the global accesses differ: A is read and C written in single halves;
+// LDS tiles, MFMA feeding and staging are unchanged.  It is not tuned; tile-wise
+// weights in this layout have a kernel of their own (gemm_mk.hip).
 template <int TM, int TN, int WAVES_M, bool DENSE, bool MK>
 __global__ __launch_bounds__(NTHREADS) void tw_gemm_km_kernel(GemmArgs g) {
   constexpr int WAVES_N = 4 / WAVES_M;
@@ -65,12 +64,7 @@ __global__ __launch_bounds__(NTHREADS) void tw_gemm_km_kernel(GemmArgs g) {
 
   // ---- extra workgroups: +0 into the pruned columns of C -----------------
   if ((int)blockIdx.x >= n_gemm) {
-    if constexpr (MK) {
-      const int col = g.zero_cols[blockIdx.x - n_gemm];
-      for (int i = tid; i < g.M; i += NTHREADS) g.C[(size_t)i * g.ldc + col] = (_Float16)0.f;
-    } else {
-      zero_fill_column(g, blockIdx.x - n_gemm);
-    }
+    zero_fill_column(g, blockIdx.x - n_gemm);
     return;
   }
 
@@ -318,15 +312,6 @@ static hipError_t dispatch(int G, int tm, GemmArgs& g, hipStream_t stream) {
   return hipErrorInvalidValue;
 }
 
-template <bool DENSE>
-static hipError_t dispatch_mk(int G, GemmArgs& g, hipStream_t stream) {
-  g.n_mtiles = (g.M + 127) / 128;
-  if (G == 128) return launch<128, 128, 2, DENSE, true>(g, stream);
-  if (G == 64) return launch<128, 64, 2, DENSE, true>(g, stream);
-  if (G == 32) return launch<128, 32, 4, DENSE, true>(g, stream);
-  return hipErrorInvalidValue;
-}
-
 
 hipError_t launch_tw_km(int G, int tm, GemmArgs g, hipStream_t stream) {
   return dispatch<false>(G, tm, g, stream);
@@ -334,7 +319,9 @@ hipError_t launch_tw_km(int G, int tm, GemmArgs g, hipStream_t stream) {
 hipError_t launch_dense_km(int tn, int tm, GemmArgs g, hipStream_t stream) {
   return dispatch<true>(tn, tm, g, stream);
 }
-hipError_t launch_tw_mk(int G, GemmArgs g, hipStream_t stream) { return dispatch_mk<false>(G, g, stream); }
-hipError_t launch_dense_mk(int tn, GemmArgs g, hipStream_t stream) { return dispatch_mk<true>(tn, g, stream); }
+hipError_t launch_dense_mk(GemmArgs g, hipStream_t stream) {
+  g.n_mtiles = (g.M + 127) / 128;
+  return launch<128, 128, 2, true, true>(g, stream);
+}
 
 }  // namespace twg

@@ -75,9 +75,10 @@ hipError_t launch_tvw_i8(int G, int tm, GemmI8Args g, hipStream_t stream);
 // hipErrorInvalidValue when no instance exists for (G, tm).
 hipError_t launch_tw_km(int G, int tm, GemmArgs g, hipStream_t stream);
 hipError_t launch_dense_km(int tn, int tm, GemmArgs g, hipStream_t stream);
-// Row-major A (M x K) and C (M x N): compatibility path on the register-staged kernel.
+// Row-major A (M x K) and C (M x N): tile-wise weights (gemm_mk.hip), and the dense baseline on
+// the register-staged kernel (128 columns per tile).
 hipError_t launch_tw_mk(int G, GemmArgs g, hipStream_t stream);
-hipError_t launch_dense_mk(int tn, GemmArgs g, hipStream_t stream);
+hipError_t launch_dense_mk(GemmArgs g, hipStream_t stream);
 // Asynchronous-copy pipeline (gemm_dma.hip): G / tn in {64, 128}, depth = stages
 // in flight (3 or 4); the dense variant needs K % 32 == 0.
 // variant: DMA_WAVES4 = 4 waves per workgroup; DMA_WAVES8 = 8 waves splitting the tile

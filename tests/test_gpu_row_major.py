@@ -1,0 +1,35 @@
+"""Row-major activations and outputs (TW_LAYOUT_MK) against the oracle at the edges of the kernel's
+bands: K around one and two bands of 768 columns, M around the 64-row band, column ranges of a tile
+wider than one staged segment, tile widths 32, 64 and 128 (-m gpu)."""
+import numpy as np
+import pytest
+
+import paper_2402_10876_amd as tw
+from oracle import gemm as og
+from tests.helpers import assert_C_close, random_tw_mask
+from tests import gpu_util as gu
+import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+CASES = [  # M, K, N, G, col_keep, row_keep
+    (1, 1, 1, 32, 1.0, 1.0), (1, 767, 130, 128, 0.9, 0.3), (63, 768, 384, 128, 0.9, 0.25),
+    (64, 769, 257, 64, 0.9, 0.5), (65, 1535, 300, 32, 0.8, 0.6), (130, 1536, 640, 128, 0.3, 0.9),
+    (200, 1537, 400, 64, 0.2, 0.05), (70, 2500, 900, 128, 0.9, 1.0), (129, 800, 2048, 128, 0.1, 0.02),
+    (66, 3072, 768, 128, 0.9, 0.28), (1000, 96, 1200, 32, 0.9, 0.4), (5, 40, 700, 64, 0.02, 0.1),
+]
+
+
+@pytest.mark.parametrize("M,K,N,G,col_keep,row_keep", CASES)
+def test_row_major_edges(M, K, N, G, col_keep, row_keep):
+    rng = np.random.default_rng(M * 7919 + K)
+    mask = random_tw_mask(rng, K, N, G, col_keep, row_keep)
+    A, B = wl.make_A(K, M, K), wl.make_B(K, K, N, 0.1)
+    print(f"case row-major M={M} K={K} N={N} G={G} keep={col_keep}/{row_keep}", flush=True)
+    p = tw.tw_pack(B, mask, G, tw.PATTERN_TW)
+    ldc = (N + 7) // 8 * 8 + 8
+    C, raw = gu.run_tw_mk(tw, p, A, N, ldc=ldc, fill=5.0)
+    p.free()
+    assert_C_close(C, og.gemm_oracle(A, B, mask), og.abs_bound(A, B, mask))
+    assert not raw[:, :N][:, ~mask.any(0)].view(np.uint16).any()       # pruned columns: exactly +0
+    assert (raw[:, N:] == 5.0).all()                                   # nothing written past column N
