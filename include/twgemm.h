@@ -194,10 +194,11 @@ tw_status tw_prune_dev_static(const void* B_dev, int K, int N, int ldb, int G, i
  * tw_pack_dev - tw_pack for a weight and masks in device memory (Algorithm 3's Condense and
  * Section V's offline condensing, run by kernels on `stream`).  TW and TVW: the kept-column
  * list, the per-tile kept-row lists, the condensed values, the 2:4 positions and the
- * kernel-facing image are all produced on the device; only the index lists (a few KB) visit
+ * kernel-facing image are all produced on the device; only the kept-row counts of the tiles visit
  * the host, which lays out offsets, padding and the launch order of the tiles exactly as for
- * tw_pack.  The result is the same handle bit for bit; its logical values are copied to the
- * host only when tw_export, tw_unpack or tw_concat ask for them.  TEW goes through the host
+ * tw_pack.  The result is the same handle bit for bit; its lists and logical values are read back
+ * to the host only when tw_export, tw_unpack, tw_concat, tw_conv_bind or tw_flop_counts ask for
+ * them.  TEW goes through the host
  * packer (the weight and masks are copied to the host).  Allocates device memory and waits
  * for `stream`: an offline step like tw_pack.  Arguments and errors as tw_pack_host, B with
  * leading dimension ldb >= N; TW_ERR_HIP for a failed runtime call.

@@ -117,8 +117,6 @@ int pick_tile_m_tvw(const Opts& o, int G, int M, int n_tiles, int max_k) {
   return (wgs128 <= 1536 && tail != 0 && tail <= 256) ? 64 : 128;
 }
 
-size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
-
 // K-split inside the workgroup pays when 128-row tiles cannot give every CU a
 // workgroup and the K loop is long enough to amortise the final reduction.  64-row tiles
 // only where 128-row tiles would leave more than half of the CUs idle: they move half as much
@@ -202,41 +200,24 @@ tw_status tw_upload(tw_handle_t h) {
   if (d.blob) return TW_OK;
   int dev = -1;
   if (hipGetDevice(&dev) != hipSuccess) return TW_ERR_HIP;
-  // one allocation, 256-byte aligned parts
-  // (value parts are sized by n_vals / n_meta: a device-packed weight has no host copy of them)
-  struct Part { const void* src; size_t bytes; size_t off; bool copy; };
-  const bool i8 = h->dtype == TW_DTYPE_I8;
-  const bool have_vals = i8 ? !d.vals8.empty() : !d.vals.empty();
-  Part parts[10] = {
-      {d.col_idx.data(), d.col_idx.size() * 4, 0, true},   {d.tile_kp_off.data(), d.tile_kp_off.size() * 4, 0, true},
-      {d.row_idx.data(), d.row_idx.size() * 4, 0, true},   {d.zero_cols.data(), d.zero_cols.size() * 4, 0, true},
-      {d.tile_order.data(), d.tile_order.size() * 4, 0, true},
-      i8 ? Part{d.vals8.data(), d.n_vals, 0, have_vals} : Part{d.vals.data(), d.n_vals * 2, 0, have_vals},
-      {d.meta.data(), d.n_meta * 4, 0, !d.meta.empty()}, {d.tile_sched.data(), d.tile_sched.size() * 4, 0, true},
-      {d.ew_ptr.data(), d.ew_ptr.size() * 4, 0, true}, {d.ew_pairs.data(), d.ew_pairs.size() * 4, 0, true}};
-  size_t total = 0;
-  for (auto& p : parts) { p.off = total; total += align_up(p.bytes ? p.bytes : 1, 256); }
+  twg::ImageLayout L;
+  twg::layout_image(h, &L);
+  const void* src[twg::IMG_PARTS] = {};
+  src[twg::IMG_TILE_KP_OFF] = d.tile_kp_off.data(); src[twg::IMG_TILE_ORDER] = d.tile_order.data();
+  src[twg::IMG_TILE_SCHED] = d.tile_sched.data(); src[twg::IMG_COL_IDX] = d.col_idx.data();
+  src[twg::IMG_ROW_IDX] = d.row_idx.data(); src[twg::IMG_ZERO_COLS] = d.zero_cols.data();
+  src[twg::IMG_VALS] = h->dtype == TW_DTYPE_I8 ? (const void*)d.vals8.data() : (const void*)d.vals.data();
+  src[twg::IMG_META] = d.meta.data(); src[twg::IMG_EW_PTR] = d.ew_ptr.data(); src[twg::IMG_EW_PAIRS] = d.ew_pairs.data();
   void* blob = nullptr;
-  if (hipMalloc(&blob, total) != hipSuccess) { (void)hipGetLastError(); return TW_ERR_ALLOC; }
-  for (auto& p : parts) {
-    if (!p.bytes || !p.copy) continue;
-    if (hipMemcpy((char*)blob + p.off, p.src, p.bytes, hipMemcpyHostToDevice) != hipSuccess) {
+  if (hipMalloc(&blob, L.total) != hipSuccess) { (void)hipGetLastError(); return TW_ERR_ALLOC; }
+  for (int i = 0; i < twg::IMG_PARTS; ++i) {
+    if (!L.bytes[i]) continue;
+    if (hipMemcpy((char*)blob + L.off[i], src[i], L.bytes[i], hipMemcpyHostToDevice) != hipSuccess) {
       (void)hipFree(blob);
       return TW_ERR_HIP;
     }
   }
-  char* b = (char*)blob;
-  d.d_col_idx = (const int32_t*)(b + parts[0].off);
-  d.d_tile_kp_off = (const int32_t*)(b + parts[1].off);
-  d.d_row_idx = (const int32_t*)(b + parts[2].off);
-  d.d_zero_cols = (const int32_t*)(b + parts[3].off);
-  d.d_tile_order = (const int32_t*)(b + parts[4].off);
-  d.d_vals = (const uint16_t*)(b + parts[5].off);
-  d.d_meta = (const uint32_t*)(b + parts[6].off);
-  d.d_tile_sched = (const int32_t*)(b + parts[7].off);
-  d.d_ew_ptr = (const int32_t*)(b + parts[8].off);
-  d.d_ew_pairs = (const uint32_t*)(b + parts[9].off);
-  d.blob = blob; d.blob_bytes = total; d.device = dev;
+  twg::bind_image(h, blob, L, dev);
   return TW_OK;
 }
 
@@ -358,7 +339,7 @@ tw_status tw_concat(const tw_handle_t* parts, int n, int upload, tw_handle_t* ou
   if (!parts || n < 1) return TW_ERR_ARG;
   for (int i = 0; i < n; ++i) {
     if (!parts[i]) return TW_ERR_ARG;
-    const tw_status sf = twg::fetch_logical_values(parts[i]);   // a device-packed member
+    const tw_status sf = twg::fetch_logical(parts[i]);          // a device-packed member
     if (sf != TW_OK) return sf;
   }
   tw_handle_s* h = new (std::nothrow) tw_handle_s();
@@ -384,7 +365,7 @@ static tw_status gemm_launch(const Opts& o, const void* A, int M, int lda, int l
   }
   g.col_idx = h->img.d_col_idx; g.tile_order = h->img.d_tile_order;
   g.tile_sched = h->img.d_tile_sched; g.uniform_kp = h->img.uniform_kp;
-  g.zero_cols = h->img.d_zero_cols; g.n_zero = (int)h->img.zero_cols.size();
+  g.zero_cols = h->img.d_zero_cols; g.n_zero = h->img.n_zero;
   g.meta = h->img.d_meta;
   g.ew_ptr = h->img.d_ew_ptr; g.ew_pairs = h->img.d_ew_pairs;
   g.ew_last = h->img.ew_pairs.empty() ? 0 : (int)h->img.ew_pairs.size() - 1;
@@ -530,6 +511,8 @@ tw_status tw_conv_bind(tw_handle_t h, const tw_conv_geom* cg, int64_t ldx, tw_co
   int dev = -1;
   if (hipGetDevice(&dev) != hipSuccess) return TW_ERR_HIP;
   if (dev != h->img.device) return TW_ERR_STATE;
+  const tw_status sf = twg::fetch_lists(h);            // the padded kept-row lists of a device-packed weight
+  if (sf != TW_OK) return sf;
   std::vector<int32_t> off;
   tw_conv_s* b = new (std::nothrow) tw_conv_s();
   if (!b) return TW_ERR_ALLOC;
@@ -640,7 +623,7 @@ static tw_status gemm_i8_launch(const void* A, int M, int lda, tw_handle_t h, vo
     g.row_idx = conv->d_off;
     g.conv_P = conv->geom.P; g.conv_L = conv->geom.L; g.conv_H = conv->geom.H; g.conv_W = conv->geom.W;
   }
-  g.zero_cols = h->img.d_zero_cols; g.n_zero = (int)h->img.zero_cols.size();
+  g.zero_cols = h->img.d_zero_cols; g.n_zero = h->img.n_zero;
   g.n_tiles = h->n_tiles; g.K = h->K; g.N = h->N; g.xcd_map = o.xcd_map ? 1 : 0;
   g.meta = h->img.d_meta;
   hipError_t e;
@@ -714,7 +697,7 @@ tw_status tw_dense_gemm_i8(const void* A, const void* B, void* C, int M, int K, 
 tw_status tw_export(tw_handle_t h, tw_packed_view* out) {
   if (!h || !out) return TW_ERR_ARG;
   std::memset(out, 0, sizeof(*out));
-  const tw_status sf = twg::fetch_logical_values(h);   // device-packed: the values come over now
+  const tw_status sf = twg::fetch_logical(h);          // device-packed: lists and values come over now
   if (sf != TW_OK) return sf;
   out->K = h->K; out->N = h->N; out->G = h->G; out->pattern = h->pattern;
   out->n_kept = h->n_kept; out->n_tiles = h->n_tiles; out->dtype = h->dtype;
@@ -734,7 +717,7 @@ tw_status tw_export(tw_handle_t h, tw_packed_view* out) {
 
 tw_status tw_unpack(tw_handle_t h, uint16_t* Bm, uint8_t* mask) {
   if (!h) return TW_ERR_ARG;
-  const tw_status sf = twg::fetch_logical_values(h);
+  const tw_status sf = twg::fetch_logical(h);
   if (sf != TW_OK) return sf;
   return twg::unpack_host(h, Bm, mask);
 }
@@ -743,7 +726,6 @@ tw_status tw_free(tw_handle_t h) {
   if (!h) return TW_OK;
   tw_status st = TW_OK;
   if (h->img.blob && hipFree(h->img.blob) != hipSuccess) st = TW_ERR_HIP;
-  if (h->dev_logical && hipFree(h->dev_logical) != hipSuccess) st = TW_ERR_HIP;
   delete h;
   return st;
 }
@@ -767,7 +749,11 @@ tw_status tw_flop_counts(tw_handle_t h, int64_t* sum_kw, int64_t* sum_k, int64_t
   if (!h) return TW_ERR_ARG;
   if (sum_kw) *sum_kw = h->sum_kw;
   if (sum_k) *sum_k = h->sum_k;
-  if (k_union) *k_union = h->k_union;
+  if (k_union) {
+    const tw_status sf = twg::fetch_lists(h);          // counted from the lists
+    if (sf != TW_OK) return sf;
+    *k_union = h->k_union;
+  }
   return TW_OK;
 }
 

@@ -302,17 +302,19 @@ void build_device_image(tw_handle_s* h) {
   build_device_values(h);
 }
 
-// The integer parts of the device image: they follow from the logical lists alone.
-void build_device_lists(tw_handle_s* h) {
+static int kstep_of(const tw_handle_s* h) {
+  const bool tvw = h->pattern == TW_PATTERN_TVW;
+  return h->dtype == TW_DTYPE_I8 ? (tvw ? KSTEP_I8_TVW : KSTEP_I8) : tvw ? KSTEP_TVW : KSTEP_TW;
+}
+
+// What follows from the tiles' kept-row counts and widths alone: padded heights, launch order,
+// sizes of the parts (so that a device image can be allocated before its contents exist).
+void plan_tiles(tw_handle_s* h) {
   DeviceImage& d = h->img;
   const int G = h->G, nt = h->n_tiles;
   const bool tvw = h->pattern == TW_PATTERN_TVW;
   const bool i8 = h->dtype == TW_DTYPE_I8;
-  const int kstep = i8 ? (tvw ? KSTEP_I8_TVW : KSTEP_I8) : tvw ? KSTEP_TVW : KSTEP_TW;
-  d.col_idx.assign((size_t)nt * G, -1);
-  for (int t = 0; t < nt; ++t)
-    std::copy(h->col_idx.begin() + h->tile_col_off[t], h->col_idx.begin() + h->tile_col_off[t + 1],
-              d.col_idx.begin() + (size_t)t * G);
+  const int kstep = kstep_of(h);
   d.tile_kp_off.assign(nt + 1, 0);
   h->max_kp = 0;
   for (int t = 0; t < nt; ++t) {
@@ -321,6 +323,42 @@ void build_device_lists(tw_handle_s* h) {
     d.tile_kp_off[t + 1] = d.tile_kp_off[t] + kp;
     h->max_kp = std::max(h->max_kp, kp);
   }
+  d.n_zero = h->N - h->n_kept;
+  d.tile_order.resize(nt);
+  for (int t = 0; t < nt; ++t) d.tile_order[t] = t;
+  if (longest_first.load())
+    std::stable_sort(d.tile_order.begin(), d.tile_order.end(), [&](int a, int b) {
+      return h->tile_k_off[a + 1] - h->tile_k_off[a] > h->tile_k_off[b + 1] - h->tile_k_off[b];
+    });
+  d.tile_sched.resize((size_t)nt * 4);
+  for (int pos = 0; pos < nt; ++pos) {
+    const int t = d.tile_order[pos];
+    d.tile_sched[4 * pos + 0] = t;
+    d.tile_sched[4 * pos + 1] = d.tile_kp_off[t];
+    d.tile_sched[4 * pos + 2] = d.tile_kp_off[t + 1] - d.tile_kp_off[t];
+    d.tile_sched[4 * pos + 3] = h->tile_col_off[t + 1] - h->tile_col_off[t];
+  }
+  // equal tiles launched in column order: the kernels can form the record from the position
+  d.uniform_kp = nt > 0 ? d.tile_sched[2] : 0;
+  for (int pos = 0; pos < nt && d.uniform_kp; ++pos)
+    if (d.tile_sched[4 * pos] != pos || d.tile_sched[4 * pos + 2] != d.uniform_kp ||
+        d.tile_sched[4 * pos + 1] != pos * d.uniform_kp)
+      d.uniform_kp = 0;
+  if (i8) { d.n_vals = tvw ? (size_t)d.tile_kp_off[nt] / 2 * G : ((size_t)d.tile_kp_off[nt] + KSTEP_I8) * G; }
+  else d.n_vals = tvw ? (size_t)d.tile_kp_off[nt] / 2 * G : ((size_t)d.tile_kp_off[nt] + KSTEP_TW) * G;
+  d.n_meta = !tvw ? 0 : i8 ? (size_t)d.tile_kp_off[nt] / 64 * (G / 32) * 64
+                           : (size_t)d.tile_kp_off[nt] / KSTEP_TVW * (G / 32) * 64;
+}
+
+// The integer parts of the device image: they follow from the logical lists alone.
+void build_device_lists(tw_handle_s* h) {
+  plan_tiles(h);
+  DeviceImage& d = h->img;
+  const int G = h->G, nt = h->n_tiles;
+  d.col_idx.assign((size_t)nt * G, -1);
+  for (int t = 0; t < nt; ++t)
+    std::copy(h->col_idx.begin() + h->tile_col_off[t], h->col_idx.begin() + h->tile_col_off[t + 1],
+              d.col_idx.begin() + (size_t)t * G);
   // slack behind the last tile (valid row 0): the K-split kernel copies stages of 64 rows and
   // may run one 32-row stage past a tile's end (it never multiplies it), and the TW kernel
   // stages the list through LDS in chunks of 8 stages, up to two chunks past a short tile
@@ -343,32 +381,46 @@ void build_device_lists(tw_handle_s* h) {
   d.ew_pairs.resize(h->ew_row.size());
   for (size_t e = 0; e < h->ew_row.size(); ++e)
     d.ew_pairs[e] = (uint32_t)h->ew_row[e] << 16 | h->ew_val[e];
-  d.tile_order.resize(nt);
-  for (int t = 0; t < nt; ++t) d.tile_order[t] = t;
-  if (longest_first.load())
-    std::stable_sort(d.tile_order.begin(), d.tile_order.end(), [&](int a, int b) {
-      return h->tile_k_off[a + 1] - h->tile_k_off[a] > h->tile_k_off[b + 1] - h->tile_k_off[b];
-    });
-  d.tile_sched.resize((size_t)nt * 4);
-  for (int pos = 0; pos < nt; ++pos) {
-    const int t = d.tile_order[pos];
-    d.tile_sched[4 * pos + 0] = t;
-    d.tile_sched[4 * pos + 1] = d.tile_kp_off[t];
-    d.tile_sched[4 * pos + 2] = d.tile_kp_off[t + 1] - d.tile_kp_off[t];
-    d.tile_sched[4 * pos + 3] = h->tile_col_off[t + 1] - h->tile_col_off[t];
+}
+
+// Where the parts lie in the one allocation of an image, 256-byte aligned.
+void layout_image(const tw_handle_s* h, ImageLayout* L) {
+  const DeviceImage& d = h->img;
+  const size_t nt = (size_t)h->n_tiles;
+  size_t* b = L->bytes;
+  b[IMG_TILE_KP_OFF] = (nt + 1) * 4;
+  b[IMG_TILE_ORDER] = nt * 4;
+  b[IMG_TILE_SCHED] = nt * 16;
+  b[IMG_COL_IDX] = nt * h->G * 4;
+  b[IMG_ROW_IDX] = ((size_t)d.tile_kp_off[nt] + ROW_IDX_SLACK) * 4;
+  b[IMG_ZERO_COLS] = (size_t)d.n_zero * 4;
+  b[IMG_VALS] = h->dtype == TW_DTYPE_I8 ? d.n_vals : d.n_vals * 2;
+  b[IMG_META] = d.n_meta * 4;
+  b[IMG_EW_PTR] = d.ew_ptr.size() * 4;
+  b[IMG_EW_PAIRS] = d.ew_pairs.size() * 4;
+  b[IMG_VALID] = h->host_values_ready ? 0 : d.n_meta * 2;      // only where the host has no valid bits of its own
+  L->total = 0;
+  for (int i = 0; i < IMG_PARTS; ++i) {
+    L->off[i] = L->total;
+    L->total += ((b[i] ? b[i] : 1) + 255) / 256 * 256;
   }
-  // equal tiles launched in column order: the kernels can form the record from the position
-  d.uniform_kp = nt > 0 ? d.tile_sched[2] : 0;
-  for (int pos = 0; pos < nt && d.uniform_kp; ++pos)
-    if (d.tile_sched[4 * pos] != pos || d.tile_sched[4 * pos + 2] != d.uniform_kp ||
-        d.tile_sched[4 * pos + 1] != pos * d.uniform_kp)
-      d.uniform_kp = 0;
-  // sizes of the value parts (elements), so that a device image can be allocated before its
-  // values exist (device-side packing)
-  if (i8) { d.n_vals = tvw ? (size_t)d.tile_kp_off[nt] / 2 * G : ((size_t)d.tile_kp_off[nt] + KSTEP_I8) * G; }
-  else d.n_vals = tvw ? (size_t)d.tile_kp_off[nt] / 2 * G : ((size_t)d.tile_kp_off[nt] + KSTEP_TW) * G;
-  d.n_meta = !tvw ? 0 : i8 ? (size_t)d.tile_kp_off[nt] / 64 * (G / 32) * 64
-                           : (size_t)d.tile_kp_off[nt] / KSTEP_TVW * (G / 32) * 64;
+}
+
+void bind_image(tw_handle_s* h, void* blob, const ImageLayout& L, int device) {
+  DeviceImage& d = h->img;
+  const char* p = (const char*)blob;
+  d.d_tile_kp_off = (const int32_t*)(p + L.off[IMG_TILE_KP_OFF]);
+  d.d_tile_order = (const int32_t*)(p + L.off[IMG_TILE_ORDER]);
+  d.d_tile_sched = (const int32_t*)(p + L.off[IMG_TILE_SCHED]);
+  d.d_col_idx = (const int32_t*)(p + L.off[IMG_COL_IDX]);
+  d.d_row_idx = (const int32_t*)(p + L.off[IMG_ROW_IDX]);
+  d.d_zero_cols = (const int32_t*)(p + L.off[IMG_ZERO_COLS]);
+  d.d_vals = (const uint16_t*)(p + L.off[IMG_VALS]);
+  d.d_meta = (const uint32_t*)(p + L.off[IMG_META]);
+  d.d_ew_ptr = (const int32_t*)(p + L.off[IMG_EW_PTR]);
+  d.d_ew_pairs = (const uint32_t*)(p + L.off[IMG_EW_PAIRS]);
+  d.d_valid = (const uint8_t*)(p + L.off[IMG_VALID]);
+  d.blob = blob; d.blob_bytes = L.total; d.device = device;
 }
 
 // The value parts of the device image, from the logical values (layouts above).

@@ -35,6 +35,7 @@ struct DeviceImage {
   std::vector<int32_t> ew_ptr;       // TEW: N+1 offsets into ew_pairs, by original column
   std::vector<uint32_t> ew_pairs;    // TEW: restored elements, row << 16 | fp16 bits
   int32_t uniform_kp = 0;            // > 0: all tiles have this padded K_t and are launched in column order
+  int32_t n_zero = 0;                // pruned columns
   size_t n_vals = 0, n_meta = 0;     // elements of the value / position-word parts (set with the lists)
   // device copies (one allocation, sub-pointers)
   void* blob = nullptr;
@@ -50,7 +51,14 @@ struct DeviceImage {
   const uint32_t* d_meta = nullptr;
   const int32_t* d_ew_ptr = nullptr;
   const uint32_t* d_ew_pairs = nullptr;
+  const uint8_t* d_valid = nullptr;  // device-packed TVW: valid bits of the 2:4 positions, 2 per group, one byte per
+                                     // 16-bit half of a position word
 };
+
+// Parts of the device image in the order they lie in the blob (the tables the host makes first).
+enum { IMG_TILE_KP_OFF, IMG_TILE_ORDER, IMG_TILE_SCHED, IMG_COL_IDX, IMG_ROW_IDX, IMG_ZERO_COLS, IMG_VALS, IMG_META,
+       IMG_EW_PTR, IMG_EW_PAIRS, IMG_VALID, IMG_PARTS };
+struct ImageLayout { size_t bytes[IMG_PARTS], off[IMG_PARTS], total; };
 
 }  // namespace twg
 
@@ -68,12 +76,9 @@ struct tw_handle_s {
   int32_t k_union = 0;  // K rows kept by at least one tile
   int32_t max_kp = 0;  // largest padded K_t
   twg::DeviceImage img;
-  // device-side packing (tw_pack_dev): the logical values / 2:4 bytes live in this device
-  // allocation (values first, then meta and valid at the offsets below) until somebody asks for
-  // them on the host
-  void* dev_logical = nullptr;
-  size_t dev_logical_meta_off = 0, dev_logical_valid_off = 0;
-  bool host_values_ready = true;     // false: `values` / `meta` / `valid` still have to be fetched
+  // device-side packing (tw_pack_dev): the lists and the values live in the device image alone until
+  // somebody asks for them on the host
+  bool host_lists_ready = true, host_values_ready = true;
 };
 
 namespace twg {
@@ -88,6 +93,7 @@ extern std::atomic<int> longest_first;
 // Builds h->img host staging from the logical form: the integer parts (from the lists alone),
 // the value parts, or both.
 void build_device_image(tw_handle_s* h);
+void plan_tiles(tw_handle_s* h);         // padded tile heights, launch order and sizes, from the kept-row counts
 void build_device_lists(tw_handle_s* h);
 void build_device_values(tw_handle_s* h);
 // From h->col_idx / tile_k_off / row_idx: tiles of G over the kept columns; then offsets,
@@ -97,6 +103,10 @@ void finish_lists(tw_handle_s* h);
 // Device-side packer (pack_dev.hip): fills *h from device buffers, image included (fp16, TW / TVW).
 tw_status pack_device(const uint16_t* B, int ldb, const uint8_t* mask, const uint8_t* tile_mask, int K, int N,
                       int G, int pattern, hipStream_t stream, tw_handle_s* h);
-// Copies the logical values of a device-packed handle to the host if they are not there yet.
-tw_status fetch_logical_values(tw_handle_s* h);
+// Reads the lists (and the values) of a device-packed handle back to the host if they are not there yet.
+tw_status fetch_lists(tw_handle_s* h);
+tw_status fetch_logical(tw_handle_s* h);
+// Sizes and offsets of the image's parts; pointers of the parts once the blob exists.
+void layout_image(const tw_handle_s* h, ImageLayout* L);
+void bind_image(tw_handle_s* h, void* blob, const ImageLayout& L, int device);
 }  // namespace twg

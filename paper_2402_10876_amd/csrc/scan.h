@@ -1,40 +1,31 @@
-// Internal: stream compaction shared by the device pruner and the device packer.
+// Internal: order-preserving counting inside a workgroup, shared by the device pruner and the
+// device packer.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
 namespace twg {
 
-// Condense: positions of the kept entries of each segment, in ascending order.
-// One workgroup per segment (blockIdx.x); pos[i] = index among the kept (or -1), list[pos] = i.
-static __global__ void compact(const int32_t* keep, int len, int32_t* pos, int32_t* list) {
-  __shared__ int part[1024];
-  __shared__ int base;
-  const int32_t* kp = keep + (size_t)blockIdx.x * len;
-  int32_t* ps = pos + (size_t)blockIdx.x * len;
-  int32_t* ls = list + (size_t)blockIdx.x * len;
-  if (threadIdx.x == 0) base = 0;
+constexpr int SCAN_T = 1024;                    // threads of the workgroups that count
+constexpr int SCAN_WAVES = SCAN_T / 64;
+
+// Number of lanes with `v` set in front of this thread, over the workgroup's SCAN_T threads in
+// order; *total: over all of them.  `part` is SCAN_WAVES ints of LDS; the caller puts a barrier
+// between two uses of the same array.
+__device__ __forceinline__ int count_before(bool v, int* part, int* total) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const unsigned long long b = __ballot(v);
+  if (lane == 0) part[wave] = __popcll(b);
   __syncthreads();
-  for (int c0 = 0; c0 < len; c0 += (int)blockDim.x) {
-    const int i = c0 + threadIdx.x;
-    const int v = i < len ? (kp[i] != 0) : 0;
-    part[threadIdx.x] = v;
-    __syncthreads();
-    for (int d = 1; d < (int)blockDim.x; d <<= 1) {          // inclusive scan
-      const int add = (int)threadIdx.x >= d ? part[threadIdx.x - d] : 0;
-      __syncthreads();
-      part[threadIdx.x] += add;
-      __syncthreads();
-    }
-    if (i < len) {
-      const int p = base + part[threadIdx.x] - v;
-      ps[i] = v ? p : -1;
-      if (v) ls[p] = i;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) base += part[blockDim.x - 1];
-    __syncthreads();
+  int before = 0, all = 0;
+#pragma unroll
+  for (int w = 0; w < SCAN_WAVES; ++w) {
+    const int n = part[w];
+    before += w < wave ? n : 0;
+    all += n;
   }
+  *total = all;
+  return before + __popcll(b & ((1ull << lane) - 1ull));
 }
 
 }  // namespace twg
