@@ -9,7 +9,10 @@ the load statement (register coalescing of a loop-carried value does exactly
 that).  This script compiles each kernel source to assembly and walks every
 kernel in layout order (fall-through paths; the pending set is dropped at a label
 that follows an unconditional jump): a register written by a load inside an
-inline-assembly block is "pending" until the next `s_waitcnt` with `lgkmcnt(0)`;
+inline-assembly block is "pending" until the next `s_waitcnt` with `lgkmcnt(0)`, or
+for a `global_load` until the next `s_waitcnt vmcnt(..)` in an inline-assembly block
+(the kernels place these loads so that this wait covers them; the compiler's own
+waits count other loads);
 any instruction that names a pending register before that wait is reported.
 
     python -m paper_2402_10876_amd.check_async_asm          # exit status 1 on a finding
@@ -32,6 +35,7 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-Xclang", "-target-featu
 
 _REG = re.compile(r"\b([vsa])(?:(\d+)|\[(\d+):(\d+)\])")
 _ASYNC = re.compile(r"^(ds_read\w*|ds_load\w*|s_load_\w+|s_buffer_load_\w+)$")
+_ASYNC_VM = re.compile(r"^global_load_dword\w*$")
 
 
 def _regs(text):
@@ -47,7 +51,7 @@ def _regs(text):
 def check_assembly(asm_text: str):
     """Returns a list of (kernel, line number, instruction, registers) findings."""
     findings = []
-    kernel, in_app, pending, prev_op = None, False, {}, ""
+    kernel, in_app, pending, pending_vm, prev_op = None, False, {}, {}, ""
     for ln, raw in enumerate(asm_text.split("\n"), 1):
         line = raw.strip()
         if line.startswith(";;#ASMSTART"):
@@ -64,9 +68,9 @@ def check_assembly(asm_text: str):
                 continue
             if code.startswith("."):               # a local label: reached by fall-through unless the
                 if prev_op in ("s_branch", "s_endpgm", "s_setpc_b64"):   # block before it ends in a jump
-                    pending = {}
+                    pending, pending_vm = {}, {}
             else:
-                kernel, pending = code[:-1], {}    # a new function
+                kernel, pending, pending_vm = code[:-1], {}, {}    # a new function
             continue
         if code.startswith("."):
             continue
@@ -76,19 +80,21 @@ def check_assembly(asm_text: str):
         if op == "s_waitcnt":
             if "lgkmcnt(0)" in args:
                 pending = {}
+            if in_app and "vmcnt" in args:
+                pending_vm = {}
             continue
         if op == "s_endpgm":
-            pending = {}
+            pending, pending_vm = {}, {}
             continue
-        if in_app and _ASYNC.match(op):
+        if in_app and (_ASYNC.match(op) or _ASYNC_VM.match(op)):
             dst_txt, _, src_txt = args.partition(",")
-            bad = _regs(src_txt) & set(pending)
+            bad = _regs(src_txt) & (set(pending) | set(pending_vm))
             if bad:
                 findings.append((kernel, ln, code, sorted(bad)))
             for r in _regs(dst_txt):
-                pending[r] = ln
+                (pending if _ASYNC.match(op) else pending_vm)[r] = ln
             continue
-        bad = _regs(args) & set(pending)
+        bad = _regs(args) & (set(pending) | set(pending_vm))
         if bad:
             findings.append((kernel, ln, code, sorted(bad)))
     return findings

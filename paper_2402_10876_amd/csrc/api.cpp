@@ -423,22 +423,12 @@ static tw_status gemm_launch(const Opts& o, const void* A, int M, int lda, int l
     if (ks == 2 || (ks == 0 && use_ksplit(M, h->n_tiles, h->max_kp, &tmk))) variant = twg::DMA_KSPLIT2;
     if (variant == twg::DMA_KSPLIT2 && ks == 2) tmk = tm == 256 ? 128 : tm;
     if (variant == twg::DMA_KSPLIT2 && h->G == 64) tmk = 128;   // the one K-split instance for G = 64
-    // kept-row lists through LDS where at most one and a half 4-wave workgroups per CU run
-    // (nothing else there hides the scalar loads' round trip: -6...-22 %) or one 8-wave
-    // workgroup; by scalar loads for fuller CUs (two workgroups per CU: 3-7 % ahead of the LDS route, unless
-    // the lists are long: 4096 x 1024 at M = 8192 and 50 %, 46.3 with LDS against 50.0 us)
     const int tmu = variant == twg::DMA_KSPLIT2 ? tmk : tm;
-    auto lidx_for = [&](int v, int t) {
-      if (o.idx_route) return o.idx_route == 2;
-      const long wgs = (long)((M + t - 1) / t) * h->n_tiles;
-      if (v == twg::DMA_WAVES8) return wgs <= 256;       // alone on its CU: nothing else hides the round trip
-      return wgs <= 384 || (wgs <= 512 && h->max_kp >= 2048);
-    };
     // several tiles per workgroup (plain TW, 4 waves, 64- or 128-row tiles of G = 128, 3 stages): on request
     if (!tew && variant == twg::DMA_WAVES4 && o.tiles_per_wg > 1) g.tiles_per_wg = o.tiles_per_wg;
-    e = launch_dma(h->G, tmu, depth, variant, lidx_for(variant, tmu), g, (hipStream_t)stream);
+    e = launch_dma(h->G, tmu, depth, variant, g, (hipStream_t)stream);
     if (e == hipErrorInvalidValue && variant != twg::DMA_WAVES4)
-      e = launch_dma(h->G, tm, depth, twg::DMA_WAVES4, lidx_for(twg::DMA_WAVES4, tm), g, (hipStream_t)stream);
+      e = launch_dma(h->G, tm, depth, twg::DMA_WAVES4, g, (hipStream_t)stream);
   }
   if (e == hipErrorInvalidValue && o.kernel != 2 && !tew && !conv)
     e = twg::launch_tw_km(h->G, tm, g, (hipStream_t)stream);

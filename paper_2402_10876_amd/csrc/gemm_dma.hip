@@ -9,8 +9,7 @@
 // per stage is one vmcnt wait and one s_barrier.
 //
 //   gather  : lane l of a copy instruction fetches one 16-byte chunk of row
-//             row_idx[...] of A (Listing 1: CTO_k); the four (TM=128) rows an
-//             instruction covers come from one scalar load of the index list.
+//             row_idx[...] of A (Listing 1: CTO_k).
 //   LDS     : k-major tiles of A (and of the dense baseline's B), 64-byte units
 //             XOR-swizzled (see swz_mask); the swizzle is applied on the global
 //             side, the LDS side of a copy instruction is always 1 KiB contiguous.
@@ -88,6 +87,17 @@ template <int N>
 __device__ __forceinline__ void wait_vm() {
   static_assert(N >= 0 && N <= 63, "vmcnt is a 6-bit counter");
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+
+// row * lda in 32 bits.  OPAQUE: as an instruction of its own: the compiler's 64-bit multiply-add takes
+// a register pair as addend whose unused half may be one that a load is on its way to, which the
+// check of the split loads would have to tell from a real use.
+template <bool OPAQUE>
+__device__ __forceinline__ uint32_t row_offset(int row, uint32_t lda) {
+  if constexpr (!OPAQUE) return (uint32_t)row * lda;
+  uint32_t r;
+  asm("v_mul_lo_u32 %0, %1, %2" : "=v"(r) : "v"(row), "s"(lda));
+  return r;
 }
 
 // Waits until at most `newer` stages of NPS copies each are outstanding (newer <= MAXN; in the
@@ -198,7 +208,6 @@ __device__ __forceinline__ void ew_fill_column(const GemmArgs& g, int which) {
 // workspace and takes a ticket at the pair's counter; the one that arrives last adds all partial
 // tiles in split order (so the sum does not depend on who was last), runs the epilogue and puts
 // the counter back to zero.  Nobody waits for anybody: a workgroup that is not last is done.
-// LIDX: the kept-row list reaches the lanes through LDS (see fetch_rows) instead of scalar loads.
 // MULTI: a workgroup computes g.tiles_per_wg jobs one after the other (job ids blockIdx.x,
 // + gridDim.x, ..; gridDim.x is a multiple of 8, so every job keeps the workgroup's XCD).  The
 // next job's first copies are issued as soon as every wave has read its staged chunks: the
@@ -207,11 +216,12 @@ __device__ __forceinline__ void ew_fill_column(const GemmArgs& g, int which) {
 // arguments are read again through a pointer the compiler cannot see through and the lane id is
 // made opaque, so that nothing derived from them stays in registers across jobs.
 template <int TM, int TN, int WAVES_M, int D, bool DENSE, int NWAVES = 4, int KSPLIT = 1, bool EW = false,
-          bool SPLIT = false, bool LIDX = true, bool MULTI = false>
-// (the TEW epilogue and the loop over jobs must not cost an instance a wave per SIMD: the second
-// launch-bound asks the compiler to keep the register count within that occupancy)
-__global__ __launch_bounds__(NWAVES * 64, (MULTI && TM * TN <= 64 * 128) ? 4 : ((EW || MULTI) && TM <= 128 && TN <= 128 && NWAVES == 4) ? 3 : 1)
+          bool SPLIT = false, bool MULTI = false>
+// (the TEW epilogue, the loop over jobs and the rows in flight must not cost an instance a wave per
+// SIMD: the second launch-bound asks the compiler to keep the register count within that occupancy)
+__global__ __launch_bounds__(NWAVES * 64, ((MULTI && TM * TN <= 64 * 128) || (!DENSE && !EW && KSPLIT == 1 && NWAVES == 8 && TM == 256)) ? 4 : ((EW || MULTI) && TM <= 128 && TN <= 128 && NWAVES == 4) ? 3 : 1)
 void tw_gemm_km_dma_kernel(GemmArgs g_arg) {
+  constexpr bool LIDX = D > 3;             // how the kept-row list reaches the lanes (see fetch_rows)
   constexpr int NT = NWAVES * 64;          // threads of the workgroup
   constexpr int WPG = NWAVES / KSPLIT;     // waves per group
   constexpr int KSS = KS * KSPLIT;         // condensed rows per pipeline stage
@@ -335,23 +345,23 @@ void tw_gemm_km_dma_kernel(GemmArgs g_arg) {
   for (int j = 0; j < NIB; ++j)
     b_off[j] = (uint32_t)((wave * NIB + j) * RPIB + b_rloc) * ldb2 + (uint32_t)b_el[j] * 2u;
 
-  // Row indices (Listing 1: CTO_k), two ways, both issued right after a stage barrier and
-  // waited for with the first operand reads of that stage (one lgkmcnt(0) wait covers both).
+  // Row indices (Listing 1: CTO_k), one per lane and copy instruction, two ways:
   // LIDX: through LDS.  Chunk c of a tile's kept-row list (8 stages' worth) is copied into
   //   half c % 2 of a small ring by the same asynchronous copies as the operand tiles, so it
   //   is tracked by the same in-order counter and has landed, at no extra wait, long before
   //   its first stage is issued; every lane then picks the index of the row it copies with
-  //   one ds_read_b32 per copy instruction.
-  // else: scalar loads of the RPIA consecutive entries a copy instruction covers (wave-uniform
-  //   address), the lane selects its own.  They miss the scalar cache on every stage and
-  //   return out of order, so their whole round trip to L2 sits in the iteration.
-  // Measured on the same box: with at most two 4-wave workgroups per CU (or the K-split
-  // instances) the LDS route is 5-22 % faster, since nothing else on the CU hides that round
-  // trip; with many workgroups per CU it is hidden anyway and the ring's extra barrier and
-  // reads cost 3-5 %.  The host picks per launch.
-  typedef int sidx_t __attribute__((ext_vector_type(RPIA)));
-  struct Rows { std::conditional_t<LIDX, int, sidx_t> r[NIA]; };
+  //   one ds_read_b32 per copy instruction, waited for with the first operand reads.
+  // else (three stages in flight): by one vector load per stage, two iterations ahead of its use
+  //   and right ahead of the copies of the stage before: the wait for those copies, by the
+  //   in-order counter, has it in at no extra cost.  The four lanes of a quad copy from the same
+  //   row; lane j of the quad loads the index for copy instruction j and the quad shares it.
+  //   Measured against the LDS ring (few workgroups per CU) and scalar loads waited for in every
+  //   iteration (many): 8192 x 4096 x 1024 47.0 -> 44.3 us at 50 %, 16.1 -> 14.7 at 87.5 %;
+  //   128 x 3072 x 768 at 75 % 7.9 -> 7.3; launches of several workgroups per CU within 2 %.
+  struct Rows { int r[NIA]; };
+  static_assert(LIDX || D == 3 || DENSE, "a deeper pipeline would wait for its index loads");
   const uint32_t idx_lds0 = (uint32_t)(uintptr_t)LDS_PTR(char, lds) + IDX_OFF;
+  const uint32_t idx_lane = (uint32_t)((wave * NIA + (lane & (NIA - 1))) * RPIA + a_rloc) * 4u;
   auto issue_chunk = [&](int c) {        // waves 0 .. NCI-1: 1 KiB of the list each
     if constexpr (!DENSE && LIDX) {
       if (wave < NCI)
@@ -359,31 +369,29 @@ void tw_gemm_km_dma_kernel(GemmArgs g_arg) {
                                          LDS_PTR(void, lds + IDX_OFF + (c & 1) * (CH * 4) + wave * 1024), 16, 0, 0);
     }
   };
-  auto fetch_rows = [&](int s, Rows& dst) {      // rows of stage s; valid after the next lgkmcnt(0) wait
-    if constexpr (!DENSE) {
+  auto fetch_rows = [&](int s, Rows& dst) {      // LIDX: rows of stage s; valid after the next lgkmcnt(0) wait
+    if constexpr (!DENSE && LIDX) {
 #pragma unroll
       for (int j = 0; j < NIA; ++j) {
-        if constexpr (LIDX) {
-          const uint32_t pos = (uint32_t)(s * KSS + (wave * NIA + j) * RPIA + a_rloc) & (2 * CH - 1);
-          asm volatile("ds_read_b32 %0, %1" : "=v"(dst.r[j]) : "v"(idx_lds0 + pos * 4));
-        } else {
-          const int* rp = g.row_idx + kp0 + s * KSS + (wave * NIA + j) * RPIA;
-          if constexpr (RPIA == 2) asm volatile("s_load_dwordx2 %0, %1, 0x0" : "=s"(dst.r[j]) : "s"(rp));
-          else if constexpr (RPIA == 4) asm volatile("s_load_dwordx4 %0, %1, 0x0" : "=s"(dst.r[j]) : "s"(rp));
-          else asm volatile("s_load_dwordx8 %0, %1, 0x0" : "=s"(dst.r[j]) : "s"(rp));
-        }
+        const uint32_t pos = (uint32_t)(s * KSS + (wave * NIA + j) * RPIA + a_rloc) & (2 * CH - 1);
+        asm volatile("ds_read_b32 %0, %1" : "=v"(dst.r[j]) : "v"(idx_lds0 + pos * 4));
       }
     }
   };
+  auto fetch_quad = [&](int s, int& dst) {       // else: of the quad; valid once the load has been waited for
+    if constexpr (!DENSE && !LIDX)
+      asm volatile("global_load_dword %0, %1, %2" : "=v"(dst) : "v"(idx_lane), "s"(g.row_idx + kp0 + s * KSS));
+  };
+  auto share_quad = [&](int& src, Rows& dst) {   // (instructions of their own, behind the wait for the load)
+    asm volatile("s_nop 1\n\tv_mov_b32_dpp %0, %1 quad_perm:[0,0,0,0] row_mask:0xf bank_mask:0xf" : "=v"(dst.r[0]) : "v"(src));
+    if constexpr (NIA > 1) asm volatile("v_mov_b32_dpp %0, %1 quad_perm:[1,1,1,1] row_mask:0xf bank_mask:0xf" : "=v"(dst.r[1]) : "v"(src));
+    if constexpr (NIA > 2) asm volatile("v_mov_b32_dpp %0, %1 quad_perm:[2,2,2,2] row_mask:0xf bank_mask:0xf" : "=v"(dst.r[2]) : "v"(src));
+    if constexpr (NIA > 2) asm volatile("v_mov_b32_dpp %0, %1 quad_perm:[3,3,3,3] row_mask:0xf bank_mask:0xf" : "=v"(dst.r[3]) : "v"(src));
+  };
   auto tie_rows = [&](Rows& x) {      // after a wait: no use of x may be moved above this point
-    if constexpr (!DENSE && LIDX) {
-      if constexpr (NIA == 1) asm volatile("" : "+v"(x.r[0]));
-      else if constexpr (NIA == 2) asm volatile("" : "+v"(x.r[0]), "+v"(x.r[1]));
-      else asm volatile("" : "+v"(x.r[0]), "+v"(x.r[1]), "+v"(x.r[2]), "+v"(x.r[3]));
-    } else if constexpr (!DENSE) {
-      if constexpr (NIA == 1) asm volatile("" : "+s"(x.r[0]));
-      else if constexpr (NIA == 2) asm volatile("" : "+s"(x.r[0]), "+s"(x.r[1]));
-      else asm volatile("" : "+s"(x.r[0]), "+s"(x.r[1]), "+s"(x.r[2]), "+s"(x.r[3]));
+    if constexpr (!DENSE) {
+#pragma unroll
+      for (int j = 0; j < NIA; ++j) asm volatile("" : "+v"(x.r[j]));
     }
   };
   auto issue = [&](int s, const Rows& rows) {     // copies of stage s; rows = its kept-row indices
@@ -398,13 +406,8 @@ void tw_gemm_km_dma_kernel(GemmArgs g_arg) {
     for (int j = 0; j < NIA; ++j) {
       int row;
       if constexpr (DENSE) row = s * KSS + (wave * NIA + j) * RPIA + a_rloc;
-      else if constexpr (LIDX) row = rows.r[j];
-      else {
-        row = rows.r[j][0];
-#pragma unroll
-        for (int q = 1; q < RPIA; ++q) row = (a_rloc == q) ? rows.r[j][q] : row;
-      }
-      __builtin_amdgcn_global_load_lds(GLOBAL_PTR(Abase + ((uint32_t)row * lda2 + (uint32_t)a_el[j] * 2u)),
+      else row = rows.r[j];
+      __builtin_amdgcn_global_load_lds(GLOBAL_PTR(Abase + (row_offset<!DENSE && !LIDX>(row, lda2) + (uint32_t)a_el[j] * 2u)),
                                        LDS_PTR(void, dstA + (wave * NIA + j) * 1024), 16, 0, 0);
     }
   };
@@ -463,60 +466,106 @@ void tw_gemm_km_dma_kernel(GemmArgs g_arg) {
   using K0 = std::integral_constant<int, 0>;
   using K16 = std::integral_constant<int, 16>;
 
-  Rows rows_cur, rows_next;
-  if (ns > 0) {
-    // (LIDX: the first two chunks of the kept-row list,) the indices of the first D stages in
-    // one round trip, then the copies of D-1 stages
-    issue_chunk(0);
-    if (ns > 8) issue_chunk(1);
-    Rows pro[D];
-    if constexpr (!DENSE && LIDX) {
-      wait_vm<0>();
-      asm volatile("s_barrier" ::: "memory");
-    }
-#pragma unroll
-    for (int d = 0; d < D; ++d) fetch_rows(d < ns ? d : ns - 1, pro[d]);
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-#pragma unroll
-    for (int d = 0; d < D; ++d) tie_rows(pro[d]);
-#pragma unroll
-    for (int d = 0; d < D - 1; ++d)
-      if (d < ns) issue(d, pro[d]);
-    rows_cur = pro[D - 1];
-  }
   bool live_prev = false;
-  for (int s = 0; s < ns; ++s) {
-    // own copies of stage s have landed: at most the copies of the newer stages remain
-    // (a wave that also copies list chunks waits for one copy more at times: harmless)
-    int newer = ns - 1 - s;
-    if (newer > D - 2) newer = D - 2;
-    wait_stage<NPS, D - 2>(newer);
-    // everybody's copies of stage s have landed, everybody is done reading stage s-1
-    asm volatile("s_barrier" ::: "memory");
-    // rows of stage s+D: needed by the next iteration, so that the addresses of its copies
-    // can be formed ahead of the wait that completes this fetch
-    fetch_rows(s + D < ns ? s + D : ns - 1, rows_next);
+  // What an iteration does once stage s is in LDS: `cur` are the rows of stage s+D-1.
+  auto consume = [&](int s, const Rows& cur, auto after_first_reads) {
     const uint32_t boff = (uint32_t)((s % D) * STAGE);
     read_step(boff, K0{}, f0);
-    if (s > 0 && live_prev) mfma_step(f1);   // second k-step of the previous stage
-    const bool live = s * KSPLIT + grp < ns32;   // false only for group 1 on an odd tail
-    wait_lds<MB, NB>(f0.a, f0.b);        // full wait: the index fetch above is in as well
-    tie_rows(rows_next);
+    if (KSPLIT == 1 ? s > 0 : live_prev) mfma_step(f1);   // second k-step of the previous stage
+    const bool live = KSPLIT == 1 || s * KSPLIT + grp < ns32;   // false only for group 1 on an odd tail
+    wait_lds<MB, NB>(f0.a, f0.b);
+    after_first_reads();
     // the copies of stage sn = s+D-1 go into the buffer of stage s-1, which every wave has
-    // finished reading; when sn opens chunk c >= 1 of the list, chunk c+1 follows it into the
+    // finished reading; LIDX: when sn opens chunk c >= 1 of the list, chunk c+1 follows it into the
     // half of the ring whose last reader (stage 8c-1, two iterations ago) is behind this barrier
     const int sn = s + D - 1;
     if (sn < ns) {
-      issue(sn, rows_cur);
-      if ((sn & 7) == 0 && sn >= 8 && sn + 8 < ns) issue_chunk((sn >> 3) + 1);
+      issue(sn, cur);
+      if (LIDX && (sn & 7) == 0 && sn >= 8 && sn + 8 < ns) issue_chunk((sn >> 3) + 1);
     }
     read_step(boff, K16{}, f1);
     if (live) mfma_step(f0);
     live_prev = live;
-    rows_cur = rows_next;
     wait_lds<MB, NB>(f1.a, f1.b);
+  };
+  if constexpr (LIDX || DENSE) {
+    Rows rows_cur, rows_next;            // of the next stage to copy and of the one after
+    if (ns > 0) {
+      // (LIDX: the first two chunks of the kept-row list,) the indices of the first D stages in
+      // one round trip, then the copies of D-1 stages
+      issue_chunk(0);
+      if (ns > 8) issue_chunk(1);
+      Rows pro[D];
+      if constexpr (!DENSE) {
+        wait_vm<0>();
+        asm volatile("s_barrier" ::: "memory");
+      }
+#pragma unroll
+      for (int d = 0; d < D; ++d) fetch_rows(d < ns ? d : ns - 1, pro[d]);
+      if constexpr (!DENSE) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+      for (int d = 0; d < D; ++d) tie_rows(pro[d]);
+#pragma unroll
+      for (int d = 0; d < D - 1; ++d)
+        if (d < ns) issue(d, pro[d]);
+      rows_cur = pro[D - 1];
+    }
+    for (int s = 0; s < ns; ++s) {
+      // own copies of stage s have landed: at most the copies of the newer stages remain
+      // (a wave that also copies list chunks waits for one copy more at times: harmless)
+      int newer = ns - 1 - s;
+      if (newer > D - 2) newer = D - 2;
+      wait_stage<NPS, D - 2>(newer);
+      // everybody's copies of stage s have landed, everybody is done reading stage s-1
+      asm volatile("s_barrier" ::: "memory");
+      // rows of stage s+D: needed by the next iteration, so that the addresses of its copies
+      // can be formed ahead of the wait that completes this fetch
+      fetch_rows(s + D < ns ? s + D : ns - 1, rows_next);
+      consume(s, rows_cur, [&] { tie_rows(rows_next); });      // (the full wait has the index fetch in)
+      rows_cur = rows_next;
+    }
+  } else {
+    // Two row fetches in flight, in two registers by turns (iterations in pairs, a single one last if
+    // their number is odd), because no register may be copied while its load is under way.
+    static_assert(LIDX || DENSE || D == 3, "");
+    int even, odd;
+    auto iteration = [&](int s, int& q, auto LAST) {   // q: rows of stage s+2; receives those of stage s+4
+      constexpr bool last = decltype(LAST)::value;     // the tile's last stage
+      // own copies of stage s and the rows of stage s+2, issued ahead of them, have landed: newer are
+      // the rows of stage s+3 and the copies of stage s+1
+      if (!last && s + 3 < ns) wait_vm<NPS + 1>();
+      else if (!last && s + 1 < ns) wait_vm<NPS>();
+      else wait_vm<0>();
+      Rows cur;
+      if constexpr (!last) share_quad(q, cur);
+      // everybody's copies of stage s have landed, everybody is done reading stage s-1
+      asm volatile("s_barrier" ::: "memory");
+      // (behind the operand reads: a copy unit with its queue full would hold them up)
+      consume(s, cur, [&] { if (!last && s + 4 < ns) fetch_quad(s + 4, q); });
+    };
+    if (ns > 0) {
+      int q0, q1;
+      fetch_quad(0, q0);
+      fetch_quad(ns > 1 ? 1 : 0, q1);
+      fetch_quad(ns > 2 ? 2 : 0, even);
+      wait_vm<0>();
+      Rows r0, r1;
+      share_quad(q0, r0);
+      share_quad(q1, r1);
+      issue(0, r0);
+      fetch_quad(ns > 3 ? 3 : 0, odd);
+      if (ns > 1) issue(1, r1);
+      int s = 0;
+      for (; s + 1 < ns; s += 2) {
+        iteration(s, even, std::false_type{});
+        iteration(s + 1, odd, std::false_type{});
+      }
+      wait_vm<NPS>();                    // (no row fetch is under way past this point; nothing is waited for)
+      if (s < ns) iteration(s, even, std::true_type{});
+    }
+    wait_vm<0>();                        // (nothing is outstanding: every copy has been waited for)
   }
-  if (ns > 0 && live_prev) mfma_step(f1);
+  if (KSPLIT == 1 ? ns > 0 : live_prev) mfma_step(f1);
 
   if constexpr (SPLIT) {
     if (S > 1) {
@@ -725,14 +774,14 @@ void tw_gemm_km_dma_kernel(GemmArgs g_arg) {
 }
 
 template <int TM, int TN, int WAVES_M, int D, bool DENSE, int NWAVES = 4, int KSPLIT = 1, bool EW = false,
-          bool SPLIT = false, bool LIDX = true, bool MULTI = false>
+          bool SPLIT = false, bool MULTI = false>
 static hipError_t launch(const GemmArgs& g, hipStream_t stream) {
   const int jobs = g.n_mtiles * g.n_tiles * (SPLIT ? g.wg_split : 1) + g.n_zero;
   if (jobs <= 0) return hipSuccess;
   const int tpw = MULTI && g.tiles_per_wg > 1 ? g.tiles_per_wg : 1;
   const int grid = MULTI ? ((jobs + tpw - 1) / tpw + 7) / 8 * 8 : jobs;
   (void)hipGetLastError();   // an error left behind by an earlier call of this thread is not this launch's
-  hipLaunchKernelGGL((tw_gemm_km_dma_kernel<TM, TN, WAVES_M, D, DENSE, NWAVES, KSPLIT, EW, SPLIT, LIDX, MULTI>), dim3(grid),
+  hipLaunchKernelGGL((tw_gemm_km_dma_kernel<TM, TN, WAVES_M, D, DENSE, NWAVES, KSPLIT, EW, SPLIT, MULTI>), dim3(grid),
                      dim3(NWAVES * 64), 0, stream, g);
   return hipGetLastError();
 }
@@ -756,23 +805,19 @@ static hipError_t dispatch_ew(int G, int tm, int variant, GemmArgs& g, hipStream
   return hipErrorInvalidValue;
 }
 
-// Both index routes of an instance (the dense baseline has no kept-row list: one instance).
-template <int TM, int TN, int WAVES_M, int D, bool DENSE, int NWAVES = 4, bool MULTI_OK = false>
-static hipError_t launch2(bool lidx, const GemmArgs& g, hipStream_t stream) {
-  if constexpr (MULTI_OK && !DENSE) {
-    if (g.tiles_per_wg > 1)
-      return lidx ? launch<TM, TN, WAVES_M, D, false, NWAVES, 1, false, false, true, true>(g, stream)
-                  : launch<TM, TN, WAVES_M, D, false, NWAVES, 1, false, false, false, true>(g, stream);
+// The instances that can compute several tiles per workgroup, and the others.
+template <int TM, int TN, int WAVES_M, int D, bool DENSE, int NWAVES = 4>
+static hipError_t launch_multi(const GemmArgs& g, hipStream_t stream) {
+  if constexpr (!DENSE) {
+    if (g.tiles_per_wg > 1) return launch<TM, TN, WAVES_M, D, false, NWAVES, 1, false, false, true>(g, stream);
   }
-  if constexpr (DENSE) return launch<TM, TN, WAVES_M, D, true, NWAVES>(g, stream);
-  else if (lidx) return launch<TM, TN, WAVES_M, D, false, NWAVES, 1, false, false, true>(g, stream);
-  else return launch<TM, TN, WAVES_M, D, false, NWAVES, 1, false, false, false>(g, stream);
+  return launch<TM, TN, WAVES_M, D, DENSE, NWAVES>(g, stream);
 }
 
 template <bool DENSE>
-static hipError_t dispatch(int G, int tm, int depth, int variant, bool lidx, GemmArgs& g, hipStream_t stream) {
+static hipError_t dispatch(int G, int tm, int depth, int variant, GemmArgs& g, hipStream_t stream) {
   g.n_mtiles = (g.M + tm - 1) / tm;
-  if (variant == DMA_KSPLIT2) {   // two K-split groups of four waves (kept-row list through LDS)
+  if (variant == DMA_KSPLIT2) {   // two K-split groups of four waves
     if (G == 128 && tm == 128 && depth == 3) return launch<128, 128, 2, 3, DENSE, 8, 2>(g, stream);
     if (G == 128 && tm == 64 && depth == 3) return launch<64, 128, 1, 3, DENSE, 8, 2>(g, stream);
     if (G == 128 && tm == 64 && depth == 4) return launch<64, 128, 1, 4, DENSE, 8, 2>(g, stream);
@@ -780,31 +825,28 @@ static hipError_t dispatch(int G, int tm, int depth, int variant, bool lidx, Gem
     return hipErrorInvalidValue;
   }
   if (variant == DMA_WAVES8) {    // 512-thread workgroups: 64 x 32 (m x n) per wave
-    if (G == 128 && tm == 128 && depth == 3) return launch2<128, 128, 2, 3, DENSE, 8>(lidx, g, stream);
-    if (G == 128 && tm == 128 && depth == 4) return launch2<128, 128, 2, 4, DENSE, 8>(lidx, g, stream);
-    if (G == 128 && tm == 256 && depth == 3) return launch2<256, 128, 4, 3, DENSE, 8>(lidx, g, stream);
+    if (G == 128 && tm == 128 && depth == 3) return launch<128, 128, 2, 3, DENSE, 8>(g, stream);
+    if (G == 128 && tm == 128 && depth == 4) return launch<128, 128, 2, 4, DENSE, 8>(g, stream);
+    if (G == 128 && tm == 256 && depth == 3) return launch<256, 128, 4, 3, DENSE, 8>(g, stream);
     return hipErrorInvalidValue;
   }
 #define TWG_CASE(TM_, TN_, WM_, D_) \
-  if (G == TN_ && tm == TM_ && depth == D_) return launch2<TM_, TN_, WM_, D_, DENSE>(lidx, g, stream);
-  if (G == 128 && tm == 64 && depth == 3) return launch2<64, 128, 1, 3, DENSE, 4, true>(lidx, g, stream);
-  if (G == 128 && tm == 128 && depth == 3) return launch2<128, 128, 2, 3, DENSE, 4, true>(lidx, g, stream);
+  if (G == TN_ && tm == TM_ && depth == D_) return launch<TM_, TN_, WM_, D_, DENSE>(g, stream);
+  if (G == 128 && tm == 64 && depth == 3) return launch_multi<64, 128, 1, 3, DENSE>(g, stream);
+  if (G == 128 && tm == 128 && depth == 3) return launch_multi<128, 128, 2, 3, DENSE>(g, stream);
   TWG_CASE(256, 128, 2, 3)
   TWG_CASE(64, 128, 1, 4) TWG_CASE(128, 128, 2, 4) TWG_CASE(256, 128, 2, 4)
   TWG_CASE(128, 64, 2, 3) TWG_CASE(256, 64, 4, 3)
   TWG_CASE(128, 64, 2, 4) TWG_CASE(256, 64, 4, 4)
-#undef TWG_CASE
-  // deep pipelines for launches with about one workgroup per CU (kept-row list through LDS)
-#define TWG_CASE(TM_, TN_, WM_, D_) \
-  if (G == TN_ && tm == TM_ && depth == D_) return launch<TM_, TN_, WM_, D_, DENSE>(g, stream);
+  // deep pipelines for launches with about one workgroup per CU
   TWG_CASE(64, 128, 1, 6) TWG_CASE(128, 128, 2, 6) TWG_CASE(128, 64, 2, 6)
   TWG_CASE(64, 128, 1, 8) TWG_CASE(128, 128, 2, 8) TWG_CASE(128, 64, 2, 8)
 #undef TWG_CASE
   return hipErrorInvalidValue;
 }
 
-hipError_t launch_tw_km_dma(int G, int tm, int depth, int variant, bool lidx, GemmArgs g, hipStream_t stream) {
-  return dispatch<false>(G, tm, depth, variant, lidx, g, stream);
+hipError_t launch_tw_km_dma(int G, int tm, int depth, int variant, GemmArgs g, hipStream_t stream) {
+  return dispatch<false>(G, tm, depth, variant, g, stream);
 }
 
 static __global__ void zero_words(uint32_t* p, int n) {
@@ -826,12 +868,12 @@ hipError_t launch_tw_km_dma_split(int G, int tm, GemmArgs g, hipStream_t stream)
   if (G == 64 && tm == 128) return launch<128, 64, 2, 3, false, 4, 1, false, true>(g, stream);
   return hipErrorInvalidValue;
 }
-hipError_t launch_tew_km_dma(int G, int tm, int depth, int variant, bool, GemmArgs g, hipStream_t stream) {
+hipError_t launch_tew_km_dma(int G, int tm, int depth, int variant, GemmArgs g, hipStream_t stream) {
   if (depth != 3) return hipErrorInvalidValue;
   return dispatch_ew(G, tm, variant, g, stream);
 }
 hipError_t launch_dense_km_dma(int tn, int tm, int depth, int variant, GemmArgs g, hipStream_t stream) {
-  return dispatch<true>(tn, tm, depth, variant, true, g, stream);
+  return dispatch<true>(tn, tm, depth, variant, g, stream);
 }
 
 }  // namespace twg
