@@ -55,6 +55,12 @@ bool opts_from(const tw_launch_opts* in, Opts* o) {
   return true;
 }
 
+// Nothing was asked for: the library chooses the kernel and its shape.
+bool automatic(const Opts& o) {
+  return o.tile_m == 0 && o.kernel == 0 && o.depth == 3 && o.waves == 4 && o.ksplit == 0 && o.wg_split < 2 &&
+         o.idx_route == 0 && o.tiles_per_wg < 2 && o.xcd_map == 1;
+}
+
 // Workspace of the K split across workgroups: 1024 counters, then the fp32 partial tiles.
 constexpr size_t WS_COUNTER_BYTES = 4096;
 constexpr int WS_MAX_PAIRS = (int)(WS_COUNTER_BYTES / 4);
@@ -377,6 +383,16 @@ static tw_status gemm_launch(const Opts& o, const void* A, int M, int lda, int l
     if (e == hipErrorInvalidValue) return TW_ERR_UNSUPPORTED;
     return e == hipSuccess ? TW_OK : TW_ERR_HIP;
   }
+  // the asynchronous kernel addresses A with 32-bit byte offsets
+  const bool a_fits32 = conv || (unsigned long long)h->K * (unsigned long long)lda * 2ull < (1ull << 32);
+  // Few output blocks.  A weight with nothing pruned adds up in the order of the dense baseline (same
+  // bits), and a TEW weight without restored elements in the order of its TW twin.
+  const bool plain = h->pattern != TW_PATTERN_TEW || (h->img.ew_pairs.empty() && h->G != 32 && a_fits32);
+  if (plain && automatic(o) && h->sum_kw < (int64_t)h->K * h->N &&
+      twg::small_km_pays(h->G, h->pattern == TW_PATTERN_TVW, M, h->n_tiles, h->max_kp)) {
+    hipError_t e = twg::launch_small_km(h->G, h->pattern == TW_PATTERN_TVW, h->max_kp, g, (hipStream_t)stream);
+    return e == hipSuccess ? TW_OK : TW_ERR_HIP;
+  }
   if (h->pattern == TW_PATTERN_TVW) {
     const int tvw_tm = pick_tile_m_tvw(o, h->G, M, h->n_tiles > 0 ? h->n_tiles : 1, h->max_kp);
     hipError_t e = twg::launch_tvw_km(h->G, tvw_tm, o.depth > 4 ? 4 : o.depth, g, (hipStream_t)stream);
@@ -392,8 +408,6 @@ static tw_status gemm_launch(const Opts& o, const void* A, int M, int lda, int l
   const bool tew = h->pattern == TW_PATTERN_TEW;
   auto launch_dma = tew ? twg::launch_tew_km_dma : twg::launch_tw_km_dma;
   const int depth = tew ? 3 : o.depth;
-  // the asynchronous kernel addresses A with 32-bit byte offsets
-  const bool a_fits32 = conv || (unsigned long long)h->K * (unsigned long long)lda * 2ull < (1ull << 32);
   // K split across workgroups: few tiles, long kept-row lists, and a workspace to reduce through
   if (!tew && o.kernel != 1 && h->G != 32 && a_fits32 && o.ws && o.wg_split != 1 && h->n_tiles > 0) {
     int stm = 0, S = 0;

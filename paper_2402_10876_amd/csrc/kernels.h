@@ -96,5 +96,8 @@ hipError_t launch_dense_km_dma(int tn, int tm, int depth, int variant, GemmArgs 
 hipError_t launch_zero_words(uint32_t* p, int n, hipStream_t stream);
 // TVW (2:4 inside the kept rows) on the sparse matrix instruction (gemm_tvw.hip).
 hipError_t launch_tvw_km(int G, int tm, int depth, GemmArgs g, hipStream_t stream);
+// Few 32 x 32 blocks of C: TW and TVW (sparse), any G (gemm_small.hip); max_kp: longest padded kept-row list.
+hipError_t launch_small_km(int G, bool sparse, int max_kp, GemmArgs g, hipStream_t stream);
+bool small_km_pays(int G, bool sparse, int M, int n_tiles, int max_kp);
 
 }  // namespace twg
