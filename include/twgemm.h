@@ -249,7 +249,7 @@ tw_status tw_gemm(const void* A_dev, int M, int lda, int layout, tw_handle_t h,
  *                   xcd_map -1 (default) | 0 | 1 | 2,
  *                   wg_split 0 = automatic when a workspace is given, 1 = never,
  *                            2..8 = that many workgroups per (M-tile, N-tile) pair,
- *                   idx_route 0..2, accepted and without effect (see tw_set_option),
+ *                   idx_route 0 = automatic, 1, 2 (see tw_set_option),
  *                   tiles_per_wg 0 = automatic (one: more never measured faster), 1..8 = tiles a
  *                            workgroup of the asynchronous TW kernel computes one after the
  *                            other (same results bit for bit)
@@ -389,9 +389,9 @@ const char* tw_status_str(int status);
  *              of a workgroup (long K, few tiles)
  *   "depth"    stages in flight of the asynchronous pipeline: 3 (default) .. 8 (6 and 8 exist for
               4-wave tiles of 64 x 128, 128 x 128 and 128 x 64 only; TVW: 3 or 4)
-   "idx_route" 0..2; had chosen how the asynchronous TW kernel reads a tile's kept-row list.
-              Accepted and without effect: launches of three stages in flight read it with vector
-              loads two stages ahead, which measured best or equal everywhere, deeper ones through LDS
+   "idx_route" how a 4-wave launch with three stages in flight reads a tile's kept-row list: 0 =
+              automatic, 1 = scalar loads (128 x 128 and 256 x 64 tiles), 2 = one vector load per stage,
+              two stages ahead; everything else has one way and ignores it
    "wg_split" K split across workgroups (tw_gemm_ex with a workspace): 0 / 1 = off,
               2..8 = workgroups per (M-tile, N-tile) pair
  *   "tiles_per_wg" tiles a workgroup of the asynchronous TW kernel computes one after the other

@@ -123,6 +123,21 @@ int pick_tile_m_tvw(const Opts& o, int G, int M, int n_tiles, int max_k) {
   return (wgs128 <= 1536 && tail != 0 && tail <= 256) ? 64 : 128;
 }
 
+// Kept-row indices by scalar loads instead of one vector load per stage (4-wave workgroups, three
+// stages in flight).  128 x 128 tiles with more than one and a half and at most two and three quarter
+// workgroups per CU, same buffers, vector against scalar: 768 x 2304 at M = 4096 9.5 / 9.0 us at 75 %,
+// 16.3 / 13.6 at 50 %; 1024 x 1024 at M = 8192 11.4 / 10.4; 768 x 3072 at M = 3000 11.9 / 10.0, at 4096
+// 10.1 / 9.8; 1500 x 3000 at 80 % 15.5 / 14.6.  With more the vector load wins (768 x 2304 at M = 7000
+// 16.8 / 19.9, 8192 19.5 / 20.6), with fewer too (2048 x 768 x 3072 at 60 % 8.5 / 9.3).  256 x 64 tiles
+// only on convolutions with long lists, whose misaligned rows keep the copy unit busy (256 -> 256 at
+// 56 x 56, batch 8: 16.7 / 16.1; a plain 1024 x 2048 at 60 % 12.6 / 14.0).
+bool scalar_rows(const Opts& o, int M, int n_tiles, int G, int tm, int max_k, bool conv) {
+  if (o.idx_route) return o.idx_route == 1;
+  const long wgs = (long)((M + tm - 1) / tm) * n_tiles;
+  if (G == 128 && tm == 128) return wgs > 384 && wgs <= 704;
+  return conv && G == 64 && tm == 256 && wgs > 384 && max_k > 256;
+}
+
 // K-split inside the workgroup pays when 128-row tiles cannot give every CU a
 // workgroup and the K loop is long enough to amortise the final reduction.  64-row tiles
 // only where 128-row tiles would leave more than half of the CUs idle: they move half as much
@@ -438,6 +453,7 @@ static tw_status gemm_launch(const Opts& o, const void* A, int M, int lda, int l
     if (variant == twg::DMA_KSPLIT2 && ks == 2) tmk = tm == 256 ? 128 : tm;
     if (variant == twg::DMA_KSPLIT2 && h->G == 64) tmk = 128;   // the one K-split instance for G = 64
     const int tmu = variant == twg::DMA_KSPLIT2 ? tmk : tm;
+    g.scalar_rows = !tew && variant == twg::DMA_WAVES4 && scalar_rows(o, M, h->n_tiles, h->G, tmu, h->max_kp, conv);
     // several tiles per workgroup (plain TW, 4 waves, 64- or 128-row tiles of G = 128, 3 stages): on request
     if (!tew && variant == twg::DMA_WAVES4 && o.tiles_per_wg > 1) g.tiles_per_wg = o.tiles_per_wg;
     e = launch_dma(h->G, tmu, depth, variant, g, (hipStream_t)stream);

@@ -216,12 +216,13 @@ __device__ __forceinline__ void ew_fill_column(const GemmArgs& g, int which) {
 // arguments are read again through a pointer the compiler cannot see through and the lane id is
 // made opaque, so that nothing derived from them stays in registers across jobs.
 template <int TM, int TN, int WAVES_M, int D, bool DENSE, int NWAVES = 4, int KSPLIT = 1, bool EW = false,
-          bool SPLIT = false, bool MULTI = false>
+          bool SPLIT = false, bool MULTI = false, bool SCALAR = false>
 // (the TEW epilogue, the loop over jobs and the rows in flight must not cost an instance a wave per
 // SIMD: the second launch-bound asks the compiler to keep the register count within that occupancy)
 __global__ __launch_bounds__(NWAVES * 64, ((MULTI && TM * TN <= 64 * 128) || (!DENSE && !EW && KSPLIT == 1 && NWAVES == 8 && TM == 256)) ? 4 : ((EW || MULTI) && TM <= 128 && TN <= 128 && NWAVES == 4) ? 3 : 1)
 void tw_gemm_km_dma_kernel(GemmArgs g_arg) {
   constexpr bool LIDX = D > 3;             // how the kept-row list reaches the lanes (see fetch_rows)
+  static_assert(!SCALAR || (!LIDX && !DENSE && KSPLIT == 1), "");
   constexpr int NT = NWAVES * 64;          // threads of the workgroup
   constexpr int WPG = NWAVES / KSPLIT;     // waves per group
   constexpr int KSS = KS * KSPLIT;         // condensed rows per pipeline stage
@@ -345,20 +346,25 @@ void tw_gemm_km_dma_kernel(GemmArgs g_arg) {
   for (int j = 0; j < NIB; ++j)
     b_off[j] = (uint32_t)((wave * NIB + j) * RPIB + b_rloc) * ldb2 + (uint32_t)b_el[j] * 2u;
 
-  // Row indices (Listing 1: CTO_k), one per lane and copy instruction, two ways:
+  // Row indices (Listing 1: CTO_k), one per lane and copy instruction, three ways:
   // LIDX: through LDS.  Chunk c of a tile's kept-row list (8 stages' worth) is copied into
   //   half c % 2 of a small ring by the same asynchronous copies as the operand tiles, so it
   //   is tracked by the same in-order counter and has landed, at no extra wait, long before
   //   its first stage is issued; every lane then picks the index of the row it copies with
   //   one ds_read_b32 per copy instruction, waited for with the first operand reads.
+  // SCALAR: by scalar loads of the RPIA consecutive entries a copy instruction covers, the lane
+  //   selects its own; waited for with the first operand reads of the stage.
   // else (three stages in flight): by one vector load per stage, two iterations ahead of its use
   //   and right ahead of the copies of the stage before: the wait for those copies, by the
   //   in-order counter, has it in at no extra cost.  The four lanes of a quad copy from the same
   //   row; lane j of the quad loads the index for copy instruction j and the quad shares it.
-  //   Measured against the LDS ring (few workgroups per CU) and scalar loads waited for in every
-  //   iteration (many): 8192 x 4096 x 1024 47.0 -> 44.3 us at 50 %, 16.1 -> 14.7 at 87.5 %;
-  //   128 x 3072 x 768 at 75 % 7.9 -> 7.3; launches of several workgroups per CU within 2 %.
-  struct Rows { int r[NIA]; };
+  //   Measured against the LDS ring (few workgroups per CU) and scalar loads (many): 8192 x 4096 x
+  //   1024 44.8 -> 40.2 us at 50 %, 2048 x 768 x 3072 at 60 % 9.5 -> 8.5, 4096 x 1024 x 2048 with 64-wide
+  //   tiles 14.5 -> 12.6.  Where two to three 128 x 128 workgroups share a CU and all are resident,
+  //   their waves hide the scalar loads' round trip and the vector load, one more request to the
+  //   copy unit per stage, costs more than it saves (the host's rule has the figures).
+  typedef int sidx_t __attribute__((ext_vector_type(RPIA)));
+  struct Rows { std::conditional_t<SCALAR, sidx_t, int> r[NIA]; };
   static_assert(LIDX || D == 3 || DENSE, "a deeper pipeline would wait for its index loads");
   const uint32_t idx_lds0 = (uint32_t)(uintptr_t)LDS_PTR(char, lds) + IDX_OFF;
   const uint32_t idx_lane = (uint32_t)((wave * NIA + (lane & (NIA - 1))) * RPIA + a_rloc) * 4u;
@@ -369,8 +375,16 @@ void tw_gemm_km_dma_kernel(GemmArgs g_arg) {
                                          LDS_PTR(void, lds + IDX_OFF + (c & 1) * (CH * 4) + wave * 1024), 16, 0, 0);
     }
   };
-  auto fetch_rows = [&](int s, Rows& dst) {      // LIDX: rows of stage s; valid after the next lgkmcnt(0) wait
-    if constexpr (!DENSE && LIDX) {
+  auto fetch_rows = [&](int s, Rows& dst) {      // LIDX, SCALAR: rows of stage s; valid after the next lgkmcnt(0) wait
+    if constexpr (SCALAR) {
+#pragma unroll
+      for (int j = 0; j < NIA; ++j) {
+        const int* rp = g.row_idx + kp0 + s * KSS + (wave * NIA + j) * RPIA;
+        if constexpr (RPIA == 2) asm volatile("s_load_dwordx2 %0, %1, 0x0" : "=s"(dst.r[j]) : "s"(rp));
+        else if constexpr (RPIA == 4) asm volatile("s_load_dwordx4 %0, %1, 0x0" : "=s"(dst.r[j]) : "s"(rp));
+        else asm volatile("s_load_dwordx8 %0, %1, 0x0" : "=s"(dst.r[j]) : "s"(rp));
+      }
+    } else if constexpr (!DENSE && LIDX) {
 #pragma unroll
       for (int j = 0; j < NIA; ++j) {
         const uint32_t pos = (uint32_t)(s * KSS + (wave * NIA + j) * RPIA + a_rloc) & (2 * CH - 1);
@@ -379,17 +393,22 @@ void tw_gemm_km_dma_kernel(GemmArgs g_arg) {
     }
   };
   auto fetch_quad = [&](int s, int& dst) {       // else: of the quad; valid once the load has been waited for
-    if constexpr (!DENSE && !LIDX)
+    if constexpr (!DENSE && !LIDX && !SCALAR)
       asm volatile("global_load_dword %0, %1, %2" : "=v"(dst) : "v"(idx_lane), "s"(g.row_idx + kp0 + s * KSS));
   };
   auto share_quad = [&](int& src, Rows& dst) {   // (instructions of their own, behind the wait for the load)
+    if constexpr (!SCALAR) {
     asm volatile("s_nop 1\n\tv_mov_b32_dpp %0, %1 quad_perm:[0,0,0,0] row_mask:0xf bank_mask:0xf" : "=v"(dst.r[0]) : "v"(src));
     if constexpr (NIA > 1) asm volatile("v_mov_b32_dpp %0, %1 quad_perm:[1,1,1,1] row_mask:0xf bank_mask:0xf" : "=v"(dst.r[1]) : "v"(src));
     if constexpr (NIA > 2) asm volatile("v_mov_b32_dpp %0, %1 quad_perm:[2,2,2,2] row_mask:0xf bank_mask:0xf" : "=v"(dst.r[2]) : "v"(src));
     if constexpr (NIA > 2) asm volatile("v_mov_b32_dpp %0, %1 quad_perm:[3,3,3,3] row_mask:0xf bank_mask:0xf" : "=v"(dst.r[3]) : "v"(src));
+    }
   };
   auto tie_rows = [&](Rows& x) {      // after a wait: no use of x may be moved above this point
-    if constexpr (!DENSE) {
+    if constexpr (SCALAR) {
+#pragma unroll
+      for (int j = 0; j < NIA; ++j) asm volatile("" : "+s"(x.r[j]));
+    } else if constexpr (!DENSE) {
 #pragma unroll
       for (int j = 0; j < NIA; ++j) asm volatile("" : "+v"(x.r[j]));
     }
@@ -406,8 +425,12 @@ void tw_gemm_km_dma_kernel(GemmArgs g_arg) {
     for (int j = 0; j < NIA; ++j) {
       int row;
       if constexpr (DENSE) row = s * KSS + (wave * NIA + j) * RPIA + a_rloc;
-      else row = rows.r[j];
-      __builtin_amdgcn_global_load_lds(GLOBAL_PTR(Abase + (row_offset<!DENSE && !LIDX>(row, lda2) + (uint32_t)a_el[j] * 2u)),
+      else if constexpr (SCALAR) {
+        row = rows.r[j][0];
+#pragma unroll
+        for (int q = 1; q < RPIA; ++q) row = (a_rloc == q) ? rows.r[j][q] : row;
+      } else row = rows.r[j];
+      __builtin_amdgcn_global_load_lds(GLOBAL_PTR(Abase + (row_offset<!DENSE && !LIDX && !SCALAR>(row, lda2) + (uint32_t)a_el[j] * 2u)),
                                        LDS_PTR(void, dstA + (wave * NIA + j) * 1024), 16, 0, 0);
     }
   };
@@ -488,7 +511,7 @@ void tw_gemm_km_dma_kernel(GemmArgs g_arg) {
     live_prev = live;
     wait_lds<MB, NB>(f1.a, f1.b);
   };
-  if constexpr (LIDX || DENSE) {
+  if constexpr (LIDX || DENSE || SCALAR) {
     Rows rows_cur, rows_next;            // of the next stage to copy and of the one after
     if (ns > 0) {
       // (LIDX: the first two chunks of the kept-row list,) the indices of the first D stages in
@@ -496,7 +519,7 @@ void tw_gemm_km_dma_kernel(GemmArgs g_arg) {
       issue_chunk(0);
       if (ns > 8) issue_chunk(1);
       Rows pro[D];
-      if constexpr (!DENSE) {
+      if constexpr (!DENSE && LIDX) {
         wait_vm<0>();
         asm volatile("s_barrier" ::: "memory");
       }
@@ -774,14 +797,14 @@ void tw_gemm_km_dma_kernel(GemmArgs g_arg) {
 }
 
 template <int TM, int TN, int WAVES_M, int D, bool DENSE, int NWAVES = 4, int KSPLIT = 1, bool EW = false,
-          bool SPLIT = false, bool MULTI = false>
+          bool SPLIT = false, bool MULTI = false, bool SCALAR = false>
 static hipError_t launch(const GemmArgs& g, hipStream_t stream) {
   const int jobs = g.n_mtiles * g.n_tiles * (SPLIT ? g.wg_split : 1) + g.n_zero;
   if (jobs <= 0) return hipSuccess;
   const int tpw = MULTI && g.tiles_per_wg > 1 ? g.tiles_per_wg : 1;
   const int grid = MULTI ? ((jobs + tpw - 1) / tpw + 7) / 8 * 8 : jobs;
   (void)hipGetLastError();   // an error left behind by an earlier call of this thread is not this launch's
-  hipLaunchKernelGGL((tw_gemm_km_dma_kernel<TM, TN, WAVES_M, D, DENSE, NWAVES, KSPLIT, EW, SPLIT, MULTI>), dim3(grid),
+  hipLaunchKernelGGL((tw_gemm_km_dma_kernel<TM, TN, WAVES_M, D, DENSE, NWAVES, KSPLIT, EW, SPLIT, MULTI, SCALAR>), dim3(grid),
                      dim3(NWAVES * 64), 0, stream, g);
   return hipGetLastError();
 }
@@ -829,6 +852,12 @@ static hipError_t dispatch(int G, int tm, int depth, int variant, GemmArgs& g, h
     if (G == 128 && tm == 128 && depth == 4) return launch<128, 128, 2, 4, DENSE, 8>(g, stream);
     if (G == 128 && tm == 256 && depth == 3) return launch<256, 128, 4, 3, DENSE, 8>(g, stream);
     return hipErrorInvalidValue;
+  }
+  if constexpr (!DENSE) {
+    if (g.scalar_rows && depth == 3 && g.tiles_per_wg <= 1) {
+      if (G == 128 && tm == 128) return launch<128, 128, 2, 3, false, 4, 1, false, false, false, true>(g, stream);
+      if (G == 64 && tm == 256) return launch<256, 64, 4, 3, false, 4, 1, false, false, false, true>(g, stream);
+    }
   }
 #define TWG_CASE(TM_, TN_, WM_, D_) \
   if (G == TN_ && tm == TM_ && depth == D_) return launch<TM_, TN_, WM_, D_, DENSE>(g, stream);
