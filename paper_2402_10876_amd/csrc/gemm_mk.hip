@@ -1,18 +1,18 @@
 // Grouped TW kernel for row-major activations and outputs (TW_LAYOUT_MK): A is M x K, C is M x N.
 //
 // In this layout a kept row of a tile is a column of A: gathering it from memory would take 2-byte
-// accesses.  So a workgroup copies a band of A (64 rows x up to 768 columns) as it lies, 16 bytes
+// accesses.  So a workgroup copies a band of A (64 or 32 rows x up to 768 columns) as it lies, 16 bytes
 // per lane, turns it round on the way into LDS (8 x 8 blocks, in registers), and gathers from
-// there: the band is stored k-major, 128 bytes per k, and the transposing LDS read takes an
+// there: the band is stored k-major, 128 (64) bytes per k, and the transposing LDS read takes an
 // address per lane, so that the four k rows a 16-lane group reads are any four rows of the band.
 // The band is read from memory once per workgroup and serves all N-tiles of that workgroup.
 //
-//   slots   : 8 waves of 64 x 32 (m x n) each; G / 32 waves make a slot that owns one N-tile, so
+//   slots   : 8 waves of 64 (32) x 32 (m x n) each; G / 32 waves make a slot that owns one N-tile, so
 //             2 (G = 128), 4 (64) or 8 (32) tiles run side by side on the same band.
 //   weights : every wave loads its own 32 columns straight into registers (the packed image is in
 //             the register order of the matrix instruction), PF k-steps ahead and on into the next
 //             tile: the K loop has no barrier, and 64 KiB or more per CU are in flight.
-//   long K  : bands of 512 columns one after the other, the next one's loads in flight while this
+//   long K  : bands of 512 (768) columns one after the other, the next one's loads in flight while this
 //             one is multiplied; the k-steps around the end of a band run in both, with the other
 //             band's rows pointing at a row of zeros.
 //   output  : staged in LDS over the range of original columns that the tiles side by side answer
@@ -31,23 +31,26 @@ namespace twg {
 
 namespace {
 
-constexpr int MK_TM = 64;              // rows of A per band
 constexpr int MK_KC = 768;             // columns of A per band, at most
-constexpr int MK_KC_LONG = 512;        // columns per band when K needs several: one 64 x 64 block per wave
-constexpr int MK_ROWB = MK_TM * 2;     // LDS bytes per k
+template <int TM>
+constexpr int MK_KC_LONG = TM == 32 ? MK_KC : 512;   // columns per band when K needs several: one block per wave
 constexpr uint32_t MK_ZERO = MK_KC;    // row of zeros behind the band
 constexpr int MK_NW = 8, MK_NT = MK_NW * 64;
-constexpr int MK_A_BYTES = (MK_KC + 8) * MK_ROWB;
 
-// LDS offset of row k of the band, in units of 16 bytes (bit 3 up: row, bits 0..2: XOR mask of the
-// row's eight 16-byte chunks).  The 8 x 8 blocks are written with k = 8 kc + j, one j at a time for
-// kc = 0..7: bit 3 of k swaps neighbouring rows and bits 3..5 permute the chunks, so that a wave's
-// writes cover both halves of the 256-byte bank period evenly; bits 0 and 1 of k send four
-// consecutive rows to the four quarters of the period for the reads.
+// LDS offset of row k of the band, in units of 16 bytes (above: row, low bits: XOR mask of the
+// row's 16-byte chunks).  The 8 x 8 blocks are written with k = 8 kc + j, one j at a time for
+// consecutive kc: bits 3 and up of k permute neighbouring rows and the chunks inside a row, so that a
+// wave's writes cover the 256-byte bank period evenly; the low bits of k send the four
+// consecutive rows of a read to the four quarters of the period.
+template <int TM>
 __device__ __forceinline__ uint32_t mk_row_unit(uint32_t k) {
-  const uint32_t row = k ^ ((k >> 3) & 1u);
-  const uint32_t x = ((k >> 3) & 3u) | ((((k >> 5) ^ (k >> 1)) & 1u) << 2);
-  return row << 3 | x;
+  if constexpr (TM == 64) {
+    const uint32_t row = k ^ ((k >> 3) & 1u);
+    const uint32_t x = ((k >> 3) & 3u) | ((((k >> 5) ^ (k >> 1)) & 1u) << 2);
+    return row << 3 | x;
+  } else {
+    return (k ^ ((k >> 3) & 3u)) << 2 | ((k >> 5) & 3u);
+  }
 }
 
 __device__ __forceinline__ half8 mk_operand(const char* lo, const char* hi) {
@@ -62,15 +65,19 @@ __device__ __forceinline__ half8 mk_operand(const char* lo, const char* hi) {
 // LONG: K in several bands.  One band needs no registers for the next one, and PF = 14 k-steps hold
 // a whole tile of 75 % sparsity at K = 768: its products then wait for no load, and the stores of the
 // tiles before drain meanwhile.
-template <int G, bool LONG>
-__global__ __launch_bounds__(MK_NT) void tw_gemm_mk_kernel(GemmArgs g, int groups, int parts, int per_part, int kc_max) {
+template <int G, bool LONG, int TM>
+__global__ __launch_bounds__(MK_NT, TM == 32 ? 4 : 2) void tw_gemm_mk_kernel(GemmArgs g, int groups, int parts, int per_part, int kc_max) {
   constexpr int SW = G / 32;                        // waves per slot
   constexpr int SLOTS = MK_NW / SW;
-  constexpr int PF = LONG ? 8 : 14;                 // k-steps of weights and kept rows in flight
+  constexpr int NM = TM / 32;                       // blocks of 32 rows
+  constexpr int KB = TM == 64 ? 64 : 128;           // columns of A a wave turns round at a time
+  constexpr int A_BYTES = (MK_KC + 8) * TM * 2;     // LDS bytes of the band, TM * 2 per k
+  constexpr int RW = TM / MK_NW;                    // rows of C a wave stores
+  constexpr int PF = TM == 32 ? 6 : LONG ? 8 : 14;                 // k-steps of weights and kept rows in flight
   // output staging: 64 rows of 368 columns (256 kept ones and the pruned ones between them, usually);
   // 4 rows further on is half a bank period, so that the two halves of a wave do not collide
   constexpr int SEG = 368, PITCH = SEG * 2;
-  __shared__ __attribute__((aligned(1024))) char lds[MK_A_BYTES + MK_TM * PITCH];
+  __shared__ __attribute__((aligned(1024))) char lds[A_BYTES + TM * PITCH];
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -78,7 +85,7 @@ __global__ __launch_bounds__(MK_NT) void tw_gemm_mk_kernel(GemmArgs g, int group
   const int total = g.n_mtiles * parts;
   const int lid = g.xcd_map ? xcd_remap(blockIdx.x, total) : (int)blockIdx.x;
   const int mt = lid / parts, part = lid - mt * parts;
-  const int m0 = mt * MK_TM;
+  const int m0 = mt * TM;
   const int gr0 = part * per_part, gr_n = min(groups - gr0, per_part);
   const int bands = LONG ? (g.K + kc_max - 1) / kc_max : 1;
   // the bands of an XCD start on different groups: weights come from memory once per XCD, and
@@ -86,14 +93,14 @@ __global__ __launch_bounds__(MK_NT) void tw_gemm_mk_kernel(GemmArgs g, int group
   auto group_of = [&](int i) { return gr0 + (i + mt) % gr_n; };
 
   // ---- band of A: global rows as they lie -> k-major LDS rows ----------------------------------
-  // lane = (m block mg of 8 rows, chunk kc of 8 columns); a wave turns 64 x 64 round per step
+  // lane = (m block mg of 8 rows, chunk kc of 8 columns); a wave turns TM x KB round per step
   // (wave-uniform base, 32-bit byte offset per lane)
-  const int kc = lane & 7, mg = lane >> 3;
+  const int kc = lane % (KB / 8), mg = lane / (KB / 8);
   const char* A_band = (const char*)(g.A + (size_t)m0 * g.lda);
   const uint32_t lda2 = (uint32_t)g.lda * 2u;
-  const int m_last = min(MK_TM, g.M - m0) - 1;
+  const int m_last = min(TM, g.M - m0) - 1;
   auto load_block = [&](int k0, int kb, u32x4 (&v)[8]) {
-    int kg = k0 + kb * 64 + kc * 8;
+    int kg = k0 + kb * KB + kc * 8;
     if (kg > g.lda - 8) kg = g.lda - 8;             // columns past K: never referenced
 #pragma unroll
     for (int i = 0; i < 8; ++i)                     // rows past M: never stored
@@ -106,11 +113,11 @@ __global__ __launch_bounds__(MK_NT) void tw_gemm_mk_kernel(GemmArgs g, int group
       u32x4 w;
 #pragma unroll
       for (int d = 0; d < 4; ++d) w[d] = __builtin_amdgcn_perm(v[2 * d + 1][j >> 1], v[2 * d][j >> 1], sel);
-      const uint32_t unit = mk_row_unit((uint32_t)(kb * 64 + kc * 8 + j)) ^ (uint32_t)mg;
+      const uint32_t unit = mk_row_unit<TM>((uint32_t)(kb * KB + kc * 8 + j)) ^ (uint32_t)mg;
       *(u32x4*)(lds + unit * 16) = w;
     }
   };
-  char* stg = lds + MK_A_BYTES;
+  char* stg = lds + A_BYTES;
 
   // ---- this wave's operands --------------------------------------------------------------------
   const int p = lane & 15, q = lane >> 4;
@@ -167,7 +174,7 @@ __global__ __launch_bounds__(MK_NT) void tw_gemm_mk_kernel(GemmArgs g, int group
     }
   };
 
-  floatx16 acc[2];
+  floatx16 acc[NM];
   u32x4 v0[8];
   load_head(group_of(0));
   load_block(0, wave, v0);
@@ -175,7 +182,7 @@ __global__ __launch_bounds__(MK_NT) void tw_gemm_mk_kernel(GemmArgs g, int group
   int col;
   {
     u32x4 v1[8];
-    const bool two = !LONG && g.K > 512 + wave * 64;
+    const bool two = TM == 64 && !LONG && g.K > 512 + wave * 64;
     if (two) load_block(0, wave + 8, v1);
     cur = tile_of(group_of(0));
     load_first(cur);
@@ -183,9 +190,9 @@ __global__ __launch_bounds__(MK_NT) void tw_gemm_mk_kernel(GemmArgs g, int group
 #pragma unroll
     for (int u = 0; u < PF; ++u) fetch(cur, u < cur.nk ? u : 0, u);
     load_head(group_of(gr_n > 1 ? 1 : 0));
-    for (int i = tid; i < MK_TM * PITCH / 16; i += MK_NT) *(u32x4*)(stg + i * 16) = u32x4{0u, 0u, 0u, 0u};
-    if (tid < 8) *(u32x4*)(lds + (mk_row_unit(MK_ZERO) ^ (uint32_t)tid) * 16) = u32x4{0u, 0u, 0u, 0u};
-    store_block(wave, v0);
+    for (int i = tid; i < TM * PITCH / 16; i += MK_NT) *(u32x4*)(stg + i * 16) = u32x4{0u, 0u, 0u, 0u};
+    if (tid < TM / 8) *(u32x4*)(lds + (mk_row_unit<TM>(MK_ZERO) ^ (uint32_t)tid) * 16) = u32x4{0u, 0u, 0u, 0u};
+    if (wave * KB < (LONG ? kc_max : MK_KC)) store_block(wave, v0);
     if (two) store_block(wave + 8, v1);
   }
   __syncthreads();
@@ -195,7 +202,7 @@ __global__ __launch_bounds__(MK_NT) void tw_gemm_mk_kernel(GemmArgs g, int group
     const int gr_next = group_of(has_next ? i + 1 : i);
     const Tile next = tile_of(gr_next);
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+    for (int j = 0; j < NM; ++j)
 #pragma unroll
       for (int k = 0; k < 16; ++k) acc[j][k] = 0.f;
 
@@ -218,21 +225,21 @@ __global__ __launch_bounds__(MK_NT) void tw_gemm_mk_kernel(GemmArgs g, int group
         s1 = __builtin_amdgcn_readfirstlane(s1);
       }
       // operands of a k-step: rows of the other bands read the row of zeros
-      auto operands = [&](int u, half8 (&a)[2]) {
+      auto operands = [&](int u, half8 (&a)[NM]) {
         const uint32_t k = (uint32_t)(r[u] - k0);
-        const int unit = (int)(mk_row_unit(k < (uint32_t)kn ? k : MK_ZERO) << 4);
+        const int unit = (int)(mk_row_unit<TM>(k < (uint32_t)kn ? k : MK_ZERO) << 4);
         const uint32_t lo = (uint32_t)__builtin_amdgcn_mov_dpp(unit, 0xA0, 0xf, 0xf, false) ^ xa;   // lanes 0,0,2,2 of each four
         const uint32_t hi = (uint32_t)__builtin_amdgcn_mov_dpp(unit, 0xF5, 0xf, 0xf, false) ^ xa;   // lanes 1,1,3,3
         a[0] = mk_operand(lds + lo, lds + hi);
-        a[1] = mk_operand(lds + (lo ^ 64u), lds + (hi ^ 64u));
+        if constexpr (NM == 2) a[1] = mk_operand(lds + (lo ^ 64u), lds + (hi ^ 64u));
       };
-      auto multiply = [&](int u, const half8 (&a)[2]) {
+      auto multiply = [&](int u, const half8 (&a)[NM]) {
         acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[0], b[u], acc[0], 0, 0, 0);
-        acc[1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[1], b[u], acc[1], 0, 0, 0);
+        if constexpr (NM == 2) acc[1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[1], b[u], acc[1], 0, 0, 0);
       };
       // The reads of k-step u+1 are issued ahead of the products of k-step u.  Whole rounds of PF
       // refill the sets as they go; the tile's last (shorter) round fills them with the next tile's.
-      half8 a[2][2];
+      half8 a[2][NM];
       if (s < s1) operands(0, a[0]);
       for (; s + PF < s1; s += PF) {
 #pragma unroll
@@ -256,7 +263,7 @@ __global__ __launch_bounds__(MK_NT) void tw_gemm_mk_kernel(GemmArgs g, int group
       else last_round(std::false_type{});
       if constexpr (LONG) {
         __syncthreads();                            // everybody is done with the band
-        if (more) store_block(wave, v0);
+        if (more && wave * KB < kc_max) store_block(wave, v0);
         __syncthreads();
       }
     }
@@ -272,7 +279,7 @@ __global__ __launch_bounds__(MK_NT) void tw_gemm_mk_kernel(GemmArgs g, int group
       const int cl = my_col - c0;
       if (my_col >= 0 && cl >= 0 && cl < SEG) {
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
+        for (int i = 0; i < NM; ++i)
 #pragma unroll
           for (int k = 0; k < 16; ++k) {
             const int mm = i * 32 + 8 * (k >> 2) + 4 * (lane >> 5) + (k & 3);
@@ -291,22 +298,22 @@ __global__ __launch_bounds__(MK_NT) void tw_gemm_mk_kernel(GemmArgs g, int group
       const int f0 = (lo + 7) & ~7, f1 = max(hi & ~7, f0);            // its whole 16-byte pieces
       const int ch = (f0 - c0) / 8 + lane;
       const u32x4 zero = {0u, 0u, 0u, 0u};
-      if (f0 + lane * 8 < f1) {                     // a wave stores 8 rows, one at a time
-        u32x4 v[8];
+      if (f0 + lane * 8 < f1) {                     // a wave stores RW rows, one at a time
+        u32x4 v[RW];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) v[i] = *(const u32x4*)(stg + (wave * 8 + i) * PITCH + ch * 16);
+        for (int i = 0; i < RW; ++i) v[i] = *(const u32x4*)(stg + (wave * RW + i) * PITCH + ch * 16);
 #pragma unroll
-        for (int i = 0; i < 8; ++i) *(u32x4*)(stg + (wave * 8 + i) * PITCH + ch * 16) = zero;
-        _Float16* dst = g.C + (size_t)(m0 + wave * 8) * g.ldc + c0 + ch * 8;
+        for (int i = 0; i < RW; ++i) *(u32x4*)(stg + (wave * RW + i) * PITCH + ch * 16) = zero;
+        _Float16* dst = g.C + (size_t)(m0 + wave * RW) * g.ldc + c0 + ch * 8;
 #pragma unroll
-        for (int i = 0; i < 8; ++i)
-          if (m0 + wave * 8 + i < g.M) *(u32x4*)(dst + (size_t)i * g.ldc) = v[i];
+        for (int i = 0; i < RW; ++i)
+          if (m0 + wave * RW + i < g.M) *(u32x4*)(dst + (size_t)i * g.ldc) = v[i];
       }
       // the ends: wave 0 the piece that lo cuts, wave 1 the piece that hi cuts, a lane per row
       if (wave < 2) {
         const int cc = wave == 0 ? lo & ~7 : hi & ~7;
         const bool cut = wave == 0 ? (lo & 7) != 0 : (hi & 7) != 0 && (hi & ~7) >= f0;
-        if (cut) {
+        if (cut && lane < TM) {
           u32x4* at = (u32x4*)(stg + lane * PITCH + (cc - c0) * 2);
           const u32x4 v = *at;
           *at = zero;
@@ -327,33 +334,47 @@ static __global__ void zero_mk(_Float16* C, int M, int N, int ldc) {
   for (int m = blockIdx.y; m < M; m += gridDim.y) C[(size_t)m * ldc + n] = (_Float16)0.f;
 }
 
-template <int G>
+template <int G, int TM>
 static hipError_t launch_mk(GemmArgs& g, hipStream_t stream) {
   constexpr int SLOTS = MK_NW / (G / 32);
-  g.n_mtiles = (g.M + MK_TM - 1) / MK_TM;
+  constexpr int RESIDENT = TM == 32 ? 512 : 256;         // workgroups the chip holds at once
+  g.n_mtiles = (g.M + TM - 1) / TM;
   const int groups = (g.n_tiles + SLOTS - 1) / SLOTS;    // SLOTS tiles side by side
-  // one workgroup per CU (150 KB of LDS): a band's groups are shared out so that about 256 exist
-  int parts = (256 + g.n_mtiles - 1) / g.n_mtiles;
+  int parts = (RESIDENT + g.n_mtiles - 1) / g.n_mtiles;
   if (g.K > MK_KC || parts > groups) parts = groups;     // (K in several bands: a group each)
   const int per = (groups + parts - 1) / parts;
   parts = (groups + per - 1) / per;
   const dim3 grid((unsigned)(g.n_mtiles * parts));
   if (g.K > MK_KC)
-    hipLaunchKernelGGL((tw_gemm_mk_kernel<G, true>), grid, dim3(MK_NT), 0, stream, g, groups, parts, per, MK_KC_LONG);
+    hipLaunchKernelGGL((tw_gemm_mk_kernel<G, true, TM>), grid, dim3(MK_NT), 0, stream, g, groups, parts, per, MK_KC_LONG<TM>);
   else
-    hipLaunchKernelGGL((tw_gemm_mk_kernel<G, false>), grid, dim3(MK_NT), 0, stream, g, groups, parts, per, MK_KC);
+    hipLaunchKernelGGL((tw_gemm_mk_kernel<G, false, TM>), grid, dim3(MK_NT), 0, stream, g, groups, parts, per, MK_KC);
   return hipGetLastError();
 }
 
-hipError_t launch_tw_mk(int G, GemmArgs g, hipStream_t stream) {
+// Rows of a band.  32: twice the workgroups, two per CU, which overlap their phases and give few blocks
+// a CU each, but read every weight twice as often.  They win where 64-row bands would leave half of
+// the CUs idle, and where the lists are short (band 64 / 32): 768 x 768 at 75 %, M = 2048 9.2 / 7.2 us,
+// M = 4096 9.8 / 11.0; 768 x 3072, M = 512 9.4 / 7.3, M = 1024 10.1 / 11.0; 3072 x 768, M = 2048 23.7 /
+// 21.3; 2000 x 1500 with G = 64, 144 of the larger blocks 16.2 / 20.4; lists of at most 96 rows at M = 4096:
+// 768 x 3072 at 90 % 20.8 / 18.4, 128 x 512 at 50 % 8.0 / 5.9; of 128 rows 9.3 / 9.8 (200 x 1000, 50 %).
+template <int G>
+static hipError_t launch_mk_rows(int max_kp, GemmArgs& g, hipStream_t stream) {
+  constexpr int SLOTS = MK_NW / (G / 32);
+  const long blocks64 = (long)((g.M + 63) / 64) * ((g.n_tiles + SLOTS - 1) / SLOTS);
+  if (blocks64 <= 128 || (g.K <= MK_KC && max_kp <= 96)) return launch_mk<G, 32>(g, stream);
+  return launch_mk<G, 64>(g, stream);
+}
+
+hipError_t launch_tw_mk(int G, int max_kp, GemmArgs g, hipStream_t stream) {
   (void)hipGetLastError();   // an error left behind by an earlier call of this thread is not this launch's
   if (g.n_tiles == 0) {
     hipLaunchKernelGGL(zero_mk, dim3((g.N + 255) / 256, g.M < 1024 ? g.M : 1024), dim3(256), 0, stream, g.C, g.M, g.N, g.ldc);
     return hipGetLastError();
   }
-  if (G == 128) return launch_mk<128>(g, stream);
-  if (G == 64) return launch_mk<64>(g, stream);
-  if (G == 32) return launch_mk<32>(g, stream);
+  if (G == 128) return launch_mk_rows<128>(max_kp, g, stream);
+  if (G == 64) return launch_mk_rows<64>(max_kp, g, stream);
+  if (G == 32) return launch_mk_rows<32>(max_kp, g, stream);
   return hipErrorInvalidValue;
 }
 

@@ -1,5 +1,5 @@
 """Row-major activations and outputs (TW_LAYOUT_MK) against the oracle at the edges of the kernel's
-bands: K around one and two bands of 768 columns, M around the 64-row band, column ranges of a tile
+bands: K around one and two bands of 768 columns, M around the 64- and 32-row bands, column ranges of a tile
 wider than one staged segment, tile widths 32, 64 and 128 (-m gpu)."""
 import numpy as np
 import pytest
@@ -17,6 +17,10 @@ CASES = [  # M, K, N, G, col_keep, row_keep
     (64, 769, 257, 64, 0.9, 0.5), (65, 1535, 300, 32, 0.8, 0.6), (130, 1536, 640, 128, 0.3, 0.9),
     (200, 1537, 400, 64, 0.2, 0.05), (70, 2500, 900, 128, 0.9, 1.0), (129, 800, 2048, 128, 0.1, 0.02),
     (66, 3072, 768, 128, 0.9, 0.28), (1000, 96, 1200, 32, 0.9, 0.4), (5, 40, 700, 64, 0.02, 0.1),
+    # 64-row bands (more than 128 blocks of them, lists of more than 96 rows), and 32-row ones by short lists
+    (1665, 768, 1300, 128, 0.9, 0.25), (1727, 769, 1300, 128, 0.9, 0.4), (1700, 1537, 1300, 64, 0.9, 0.2),
+    (1100, 767, 2300, 32, 0.9, 0.3), (1090, 513, 2300, 64, 0.9, 0.5), (2100, 700, 1300, 128, 0.9, 0.12),
+    (33, 1024, 257, 64, 0.9, 0.5), (31, 767, 257, 64, 0.9, 0.5),
 ]
 
 
