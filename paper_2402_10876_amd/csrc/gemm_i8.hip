@@ -93,7 +93,7 @@ constexpr int D8 = 3;        // stages in flight
 // KSPLIT = 2: two groups of four waves own the same output tile; a stage then holds 128
 // condensed rows, group g multiplies rows 64g..64g+63 of it and the partial sums are added
 // through LDS before the epilogue (long K with too few tiles to fill the chip).
-template <int TM, int TN, int WAVES_M, bool DENSE, bool OUT8, int NWAVES = 4, int KSPLIT = 1>
+template <int TM, int TN, int WAVES_M, bool DENSE, bool OUT8, int NWAVES = 4, int KSPLIT = 1, bool VEC = false>
 // (the 256 x 128 instance holds 128 accumulators per lane; its epilogue must not push the
 // register count past two waves per SIMD, which the 72 KiB of LDS allow)
 __global__ __launch_bounds__(NWAVES * 64, (TM * TN >= 256 * 128) ? 2 : 1) void tw_gemm_i8_kernel(GemmI8Args g) {
@@ -176,15 +176,17 @@ __global__ __launch_bounds__(NWAVES * 64, (TM * TN >= 256 * 128) ? 2 : 1) void t
   for (int j = 0; j < NIB; ++j)
     b_off[j] = (uint32_t)((wave * NIB + j) * RPIB + b_rloc) * ldb + (uint32_t)b_el[j];
 
-  // Kept-row indices of a stage for copy instruction j: RPIA consecutive entries of the
-  // list at a wave-uniform address, through scalar loads written in assembly (a vector
-  // load would share the in-order counter of the asynchronous copies).  Each fetch is
-  // issued right after a stage barrier and waited for together with the first operand
-  // reads of that stage, one iteration before its rows are needed.
+  // Kept-row indices of a stage for copy instruction j, two ways.
+  // VEC: one vector load per stage, two iterations ahead of its use and right ahead of the copies of the
+  //   stage before, so that the in-order wait for those copies has it in; lane j of a quad (whose
+  //   lanes copy from the same row) loads the index for copy instruction j and the quad shares it.
+  // else: RPIA consecutive entries of the list at a wave-uniform address, by scalar loads written in
+  //   assembly, issued right after a stage barrier and waited for together with the first operand reads
+  //   of that stage, one iteration before its rows are needed.
   typedef int sidx_t __attribute__((ext_vector_type(RPIA)));
-  struct Rows { sidx_t r[NIA]; };
+  struct Rows { std::conditional_t<VEC, int, sidx_t> r[NIA]; };
   auto fetch_rows = [&](int s, Rows& dst) {
-    if constexpr (!DENSE) {
+    if constexpr (!DENSE && !VEC) {
 #pragma unroll
       for (int j = 0; j < NIA; ++j) {
         const int* rp = g.row_idx + kp0 + s * KSS + (wave * NIA + j) * RPIA;
@@ -194,8 +196,21 @@ __global__ __launch_bounds__(NWAVES * 64, (TM * TN >= 256 * 128) ? 2 : 1) void t
       }
     }
   };
+  const uint32_t idx_lane = (uint32_t)((wave * NIA + (lane & (NIA - 1))) * RPIA + a_rloc) * 4u;
+  auto fetch_quad = [&](int s, int& dst) {       // VEC: of the quad; valid once the load has been waited for
+    if constexpr (VEC)
+      asm volatile("global_load_dword %0, %1, %2" : "=v"(dst) : "v"(idx_lane), "s"(g.row_idx + kp0 + s * KSS));
+  };
+  auto share_quad = [&](int& src, Rows& dst) {   // (instructions of their own, behind the wait for the load)
+    if constexpr (VEC) {
+      asm volatile("s_nop 1\n\tv_mov_b32_dpp %0, %1 quad_perm:[0,0,0,0] row_mask:0xf bank_mask:0xf" : "=v"(dst.r[0]) : "v"(src));
+      if constexpr (NIA > 1) asm volatile("v_mov_b32_dpp %0, %1 quad_perm:[1,1,1,1] row_mask:0xf bank_mask:0xf" : "=v"(dst.r[1]) : "v"(src));
+      if constexpr (NIA > 2) asm volatile("v_mov_b32_dpp %0, %1 quad_perm:[2,2,2,2] row_mask:0xf bank_mask:0xf" : "=v"(dst.r[2]) : "v"(src));
+      if constexpr (NIA > 2) asm volatile("v_mov_b32_dpp %0, %1 quad_perm:[3,3,3,3] row_mask:0xf bank_mask:0xf" : "=v"(dst.r[3]) : "v"(src));
+    }
+  };
   auto tie_rows = [&](Rows& x) {      // after a wait: no use of x may be moved above this point
-    if constexpr (!DENSE) {
+    if constexpr (!DENSE && !VEC) {
       if constexpr (NIA == 1) asm volatile("" : "+s"(x.r[0]));
       else if constexpr (NIA == 2) asm volatile("" : "+s"(x.r[0]), "+s"(x.r[1]));
       else asm volatile("" : "+s"(x.r[0]), "+s"(x.r[1]), "+s"(x.r[2]), "+s"(x.r[3]));
@@ -212,14 +227,22 @@ __global__ __launch_bounds__(NWAVES * 64, (TM * TN >= 256 * 128) ? 2 : 1) void t
                                        LDS_PTR(void, dstB + (wave * NIB + j) * 1024), 16, 0, 0);
 #pragma unroll
     for (int j = 0; j < NIA; ++j) {
-      int row;
-      if constexpr (DENSE) row = s * KSS + (wave * NIA + j) * RPIA + a_rloc;
-      else {
-        row = rows.r[j][0];
+      uint32_t off;
+      if constexpr (VEC) {
+        // (an instruction of its own: the compiler's multiply-add takes a register pair as addend whose
+        // unused half may be one that a load is on its way to)
+        asm("v_mul_lo_u32 %0, %1, %2" : "=v"(off) : "v"(rows.r[j]), "s"(lda));
+      } else {
+        int row;
+        if constexpr (DENSE) row = s * KSS + (wave * NIA + j) * RPIA + a_rloc;
+        else {
+          row = rows.r[j][0];
 #pragma unroll
-        for (int q = 1; q < RPIA; ++q) row = (a_rloc == q) ? rows.r[j][q] : row;
+          for (int q = 1; q < RPIA; ++q) row = (a_rloc == q) ? rows.r[j][q] : row;
+        }
+        off = (uint32_t)row * lda;
       }
-      __builtin_amdgcn_global_load_lds(GLOBAL_PTR(Abase + ((uint32_t)row * lda + (uint32_t)a_el[j])),
+      __builtin_amdgcn_global_load_lds(GLOBAL_PTR(Abase + (off + (uint32_t)a_el[j])),
                                        LDS_PTR(void, dstA + (wave * NIA + j) * 1024), 16, 0, 0);
     }
   };
@@ -273,42 +296,85 @@ __global__ __launch_bounds__(NWAVES * 64, (TM * TN >= 256 * 128) ? 2 : 1) void t
   using K0 = std::integral_constant<int, 0>;
   using K32 = std::integral_constant<int, 32>;
 
-  Rows rows_cur, rows_next;
-  if (ns > 0) {
-    // kept-row lists of the first D stages in one round trip, then D-1 stages of copies
-    Rows pro[D];
-#pragma unroll
-    for (int d = 0; d < D; ++d) fetch_rows(d < ns ? d : ns - 1, pro[d]);
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-#pragma unroll
-    for (int d = 0; d < D; ++d) tie_rows(pro[d]);
-#pragma unroll
-    for (int d = 0; d < D - 1; ++d)
-      if (d < ns) issue(d, pro[d]);
-    rows_cur = pro[D - 1];
-  }
   bool live_prev = false;
-  for (int s = 0; s < ns; ++s) {
-    // own copies of stage s have landed: at most the copies of the one newer stage remain
-    if (s + 1 < ns) wait_vm<NPS>();
-    else wait_vm<0>();
-    // everybody's copies of stage s have landed, everybody is done reading stage s-1
-    asm volatile("s_barrier" ::: "memory");
-    fetch_rows(s + D < ns ? s + D : ns - 1, rows_next);   // needed by the next iteration
+  // What an iteration does once stage s is in LDS: `cur` are the rows of stage s+D-1.
+  auto consume = [&](int s, const Rows& cur, auto after_first_reads) {
     const uint32_t boff = (uint32_t)((s % D) * STAGE);
     read_step(boff, K0{}, f0);
     if (KSPLIT == 1 ? s > 0 : live_prev) mfma_step(f1);   // second k-step of the previous stage
     const bool live = KSPLIT == 1 || s * KSPLIT + grp < ns64;   // false only for group 1 on an odd tail
-    wait_lds8<NF>(f0);                   // full wait: the scalar loads above are in as well
-    tie_rows(rows_next);
+    wait_lds8<NF>(f0);                   // full wait: scalar loads of rows are in as well
+    after_first_reads();
     // the copies of stage s+D-1 go into the buffer of stage s-1, which every wave has
     // finished reading
-    if (s + D - 1 < ns) issue(s + D - 1, rows_cur);
+    if (s + D - 1 < ns) issue(s + D - 1, cur);
     read_step(boff, K32{}, f1);
     if (live) mfma_step(f0);
     live_prev = live;
-    rows_cur = rows_next;
     wait_lds8<NF>(f1);
+  };
+  if constexpr (!VEC) {
+    Rows rows_cur, rows_next;
+    if (ns > 0) {
+      // kept-row lists of the first D stages in one round trip, then D-1 stages of copies
+      Rows pro[D];
+#pragma unroll
+      for (int d = 0; d < D; ++d) fetch_rows(d < ns ? d : ns - 1, pro[d]);
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+      for (int d = 0; d < D; ++d) tie_rows(pro[d]);
+#pragma unroll
+      for (int d = 0; d < D - 1; ++d)
+        if (d < ns) issue(d, pro[d]);
+      rows_cur = pro[D - 1];
+    }
+    for (int s = 0; s < ns; ++s) {
+      // own copies of stage s have landed: at most the copies of the one newer stage remain
+      if (s + 1 < ns) wait_vm<NPS>();
+      else wait_vm<0>();
+      // everybody's copies of stage s have landed, everybody is done reading stage s-1
+      asm volatile("s_barrier" ::: "memory");
+      fetch_rows(s + D < ns ? s + D : ns - 1, rows_next);   // needed by the next iteration
+      consume(s, rows_cur, [&] { tie_rows(rows_next); });
+      rows_cur = rows_next;
+    }
+  } else {
+    // Two row fetches in flight, in two registers by turns (iterations in pairs, a single one last if
+    // their number is odd), because no register may be copied while its load is under way.
+    int even, odd;
+    auto iteration = [&](int s, int& q, auto LAST) {   // q: rows of stage s+2; receives those of stage s+4
+      constexpr bool last = decltype(LAST)::value;     // the tile's last stage
+      // own copies of stage s and the rows of stage s+2, issued ahead of them, have landed: newer are
+      // the rows of stage s+3 and the copies of stage s+1
+      if (!last && s + 3 < ns) wait_vm<NPS + 1>();
+      else if (!last && s + 1 < ns) wait_vm<NPS>();
+      else wait_vm<0>();
+      Rows cur;
+      if constexpr (!last) share_quad(q, cur);
+      asm volatile("s_barrier" ::: "memory");
+      consume(s, cur, [&] { if (!last && s + 4 < ns) fetch_quad(s + 4, q); });
+    };
+    if (ns > 0) {
+      int q0, q1;
+      fetch_quad(0, q0);
+      fetch_quad(ns > 1 ? 1 : 0, q1);
+      fetch_quad(ns > 2 ? 2 : 0, even);
+      wait_vm<0>();
+      Rows r0, r1;
+      share_quad(q0, r0);
+      share_quad(q1, r1);
+      issue(0, r0);
+      fetch_quad(ns > 3 ? 3 : 0, odd);
+      if (ns > 1) issue(1, r1);
+      int s = 0;
+      for (; s + 1 < ns; s += 2) {
+        iteration(s, even, std::false_type{});
+        iteration(s + 1, odd, std::false_type{});
+      }
+      wait_vm<NPS>();                    // (no row fetch is under way past this point; nothing is waited for)
+      if (s < ns) iteration(s, even, std::true_type{});
+    }
+    wait_vm<0>();                        // (nothing is outstanding: every copy has been waited for)
   }
   if (KSPLIT == 1 ? ns > 0 : live_prev) mfma_step(f1);
 
@@ -464,12 +530,24 @@ static hipError_t launch8(const GemmI8Args& g, hipStream_t stream) {
   const int grid = g.n_mtiles * g.n_tiles + g.n_zero;
   if (grid <= 0) return hipSuccess;
   (void)hipGetLastError();   // an error left behind by an earlier call of this thread is not this launch's
-  if (g.c_i8)
-    hipLaunchKernelGGL((tw_gemm_i8_kernel<TM, TN, WAVES_M, DENSE, true, NWAVES, KSPLIT>), dim3(grid),
-                       dim3(NWAVES * 64), 0, stream, g);
-  else
-    hipLaunchKernelGGL((tw_gemm_i8_kernel<TM, TN, WAVES_M, DENSE, false, NWAVES, KSPLIT>), dim3(grid),
-                       dim3(NWAVES * 64), 0, stream, g);
+  auto go = [&](auto VEC_) {
+    constexpr bool VEC = decltype(VEC_)::value;
+    if (g.c_i8)
+      hipLaunchKernelGGL((tw_gemm_i8_kernel<TM, TN, WAVES_M, DENSE, true, NWAVES, KSPLIT, VEC>), dim3(grid),
+                         dim3(NWAVES * 64), 0, stream, g);
+    else
+      hipLaunchKernelGGL((tw_gemm_i8_kernel<TM, TN, WAVES_M, DENSE, false, NWAVES, KSPLIT, VEC>), dim3(grid),
+                         dim3(NWAVES * 64), 0, stream, g);
+  };
+  // Row indices by vector loads with at most two workgroups per CU (same buffers, scalar / vector, TW 75 %,
+  // int8 output: 3072 x 768 at M = 4096 9.2 / 8.4 us, 768 x 768 5.5 / 5.3, 2048 x 2048 x 2048 of G = 64 at 80 %
+  // 7.1 / 6.0, 64 x 4096 x 4096 8.5 / 6.7); with more the scalar round trip is hidden and the extra request to the
+  // copy unit is not (768 x 2304 at M = 4096, 576 workgroups 7.6 / 8.2; 768 x 3072 8.1 / 8.6; 750
+  // workgroups of 64-wide tiles 5.8 / 6.0).
+  if constexpr (DENSE) go(std::false_type{});
+  else if constexpr (KSPLIT > 1) go(std::true_type{});
+  else if ((long)g.n_mtiles * g.n_tiles <= 512) go(std::true_type{});
+  else go(std::false_type{});
   return hipGetLastError();
 }
 

@@ -15,7 +15,7 @@
 //   - one position word per (lane, column block): 2 bits per stored value.
 // The dense operand is read from the k-major A tile with ds_read_b64_tr_b16;
 // lane (m, g) of a 32-row half-stage needs rows 8g..8g+7 and 16+8g..16+8g+7.
-// Synchronisation, scalar index loads and the inline-assembly LDS reads are
+// Synchronisation, index loads and the inline-assembly LDS reads are
 // those of the asynchronous TW kernel.
 #include <type_traits>
 
@@ -73,7 +73,7 @@ __device__ __forceinline__ void wait_vm() {
 
 constexpr int KS2 = 64;   // condensed rows per stage (two sparse instructions deep)
 
-template <int TM, int TN, int WAVES_N, int D, int NW = 4>
+template <int TM, int TN, int WAVES_N, int D, int NW, bool VEC>
 __global__ __launch_bounds__(NW * 64) void tvw_gemm_km_kernel(GemmArgs g) {
   constexpr int NT = NW * 64;                            // threads of the workgroup
   constexpr int WAVES_M = NW / WAVES_N;
@@ -137,18 +137,41 @@ __global__ __launch_bounds__(NW * 64) void tvw_gemm_km_kernel(GemmArgs g) {
   }
   const _Float16* Abase = g.A + m0;
   typedef int sidx_t __attribute__((ext_vector_type(RPIA)));
-  struct Rows { sidx_t r[NIA]; };
+  // Kept-row indices.  VEC: one vector load per stage, two iterations ahead of its use and right ahead
+  // of the copies of the stage before, so that the in-order wait for those copies has it in; lane j of a
+  // quad (whose lanes copy from the same row) loads the index for copy instruction j and the quad shares
+  // it.  Else scalar loads, whose round trip sits in every iteration.  Same buffers, scalar / vector: 8192 x
+  // 4096 x 1024 at 75 % 35.9 / 33.3 us, 1200 x 3000 x 2000 18.1 / 16.0, 2048 x 2048 x 2048 of G = 64 at 80 %
+  // 12.6 / 11.2, 768 x 3072 at M = 4096 and 87.5 % 10.5 / 10.4 (3072 x 768 11.5 / 11.8).
+  struct Rows { std::conditional_t<VEC, int, sidx_t> r[NIA]; };
+  static_assert(!VEC || D == 3, "a deeper pipeline would wait for its index loads");
   auto fetch_rows = [&](int s, Rows& dst) {
+    if constexpr (!VEC) {
 #pragma unroll
-    for (int j = 0; j < NIA; ++j) {
-      const int* rp = g.row_idx + kp0 + s * KS2 + (wave * NIA + j) * RPIA;
-      if constexpr (RPIA == 2) asm volatile("s_load_dwordx2 %0, %1, 0x0" : "=s"(dst.r[j]) : "s"(rp));
-      else if constexpr (RPIA == 4) asm volatile("s_load_dwordx4 %0, %1, 0x0" : "=s"(dst.r[j]) : "s"(rp));
-      else asm volatile("s_load_dwordx8 %0, %1, 0x0" : "=s"(dst.r[j]) : "s"(rp));
+      for (int j = 0; j < NIA; ++j) {
+        const int* rp = g.row_idx + kp0 + s * KS2 + (wave * NIA + j) * RPIA;
+        if constexpr (RPIA == 2) asm volatile("s_load_dwordx2 %0, %1, 0x0" : "=s"(dst.r[j]) : "s"(rp));
+        else if constexpr (RPIA == 4) asm volatile("s_load_dwordx4 %0, %1, 0x0" : "=s"(dst.r[j]) : "s"(rp));
+        else asm volatile("s_load_dwordx8 %0, %1, 0x0" : "=s"(dst.r[j]) : "s"(rp));
+      }
+    }
+  };
+  const uint32_t idx_lane = (uint32_t)((wave * NIA + (lane & (NIA - 1))) * RPIA + a_rloc) * 4u;
+  auto fetch_quad = [&](int s, int& dst) {       // VEC: of the quad; valid once the load has been waited for
+    if constexpr (VEC)
+      asm volatile("global_load_dword %0, %1, %2" : "=v"(dst) : "v"(idx_lane), "s"(g.row_idx + kp0 + s * KS2));
+  };
+  auto share_quad = [&](int& src, Rows& dst) {   // (instructions of their own, behind the wait for the load)
+    if constexpr (VEC) {
+      asm volatile("s_nop 1\n\tv_mov_b32_dpp %0, %1 quad_perm:[0,0,0,0] row_mask:0xf bank_mask:0xf" : "=v"(dst.r[0]) : "v"(src));
+      if constexpr (NIA > 1) asm volatile("v_mov_b32_dpp %0, %1 quad_perm:[1,1,1,1] row_mask:0xf bank_mask:0xf" : "=v"(dst.r[1]) : "v"(src));
+      if constexpr (NIA > 2) asm volatile("v_mov_b32_dpp %0, %1 quad_perm:[2,2,2,2] row_mask:0xf bank_mask:0xf" : "=v"(dst.r[2]) : "v"(src));
+      if constexpr (NIA > 2) asm volatile("v_mov_b32_dpp %0, %1 quad_perm:[3,3,3,3] row_mask:0xf bank_mask:0xf" : "=v"(dst.r[3]) : "v"(src));
     }
   };
   auto tie_rows = [&](Rows& x) {      // after a wait: no use of x may be moved above this point
-    if constexpr (NIA == 2) asm volatile("" : "+s"(x.r[0]), "+s"(x.r[1]));
+    if constexpr (VEC) return;
+    else if constexpr (NIA == 2) asm volatile("" : "+s"(x.r[0]), "+s"(x.r[1]));
     else asm volatile("" : "+s"(x.r[0]), "+s"(x.r[1]), "+s"(x.r[2]), "+s"(x.r[3]));
   };
   auto issue = [&](int s, const Rows& rows) {     // copies of stage s; rows = its kept-row indices
@@ -171,10 +194,20 @@ __global__ __launch_bounds__(NW * 64) void tvw_gemm_km_kernel(GemmArgs g) {
     }
 #pragma unroll
     for (int j = 0; j < NIA; ++j) {
-      int row = rows.r[j][0];
+      size_t off;
+      if constexpr (VEC) {
+        // (an instruction of its own: the compiler's takes a register pair as addend whose unused half
+        // may be one that a load is on its way to)
+        uint64_t o;
+        asm("v_mad_u64_u32 %0, vcc, %1, %2, 0" : "=v"(o) : "v"(rows.r[j]), "s"(g.lda) : "vcc");
+        off = (size_t)o;
+      } else {
+        int row = rows.r[j][0];
 #pragma unroll
-      for (int q = 1; q < RPIA; ++q) row = (a_rloc == q) ? rows.r[j][q] : row;
-      __builtin_amdgcn_global_load_lds(GLOBAL_PTR(Abase + (size_t)row * g.lda + a_el[j]),
+        for (int q = 1; q < RPIA; ++q) row = (a_rloc == q) ? rows.r[j][q] : row;
+        off = (size_t)row * g.lda;
+      }
+      __builtin_amdgcn_global_load_lds(GLOBAL_PTR(Abase + off + a_el[j]),
                                        LDS_PTR(void, dstA + (wave * NIA + j) * 1024), 16, 0, 0);
     }
   };
@@ -240,45 +273,88 @@ __global__ __launch_bounds__(NW * 64) void tvw_gemm_km_kernel(GemmArgs g) {
   using U0 = std::integral_constant<int, 0>;
   using U1 = std::integral_constant<int, 1>;
 
-  Rows rows_cur{}, rows_next{};
-  if (ns > 0) {
-    // kept-row lists of the first D stages in one round trip, then D-1 stages of copies
-    Rows pro[D];
-#pragma unroll
-    for (int d = 0; d < D; ++d) fetch_rows(d < ns ? d : ns - 1, pro[d]);
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-#pragma unroll
-    for (int d = 0; d < D; ++d) tie_rows(pro[d]);
-#pragma unroll
-    for (int d = 0; d < D - 1; ++d)
-      if (d < ns) issue(d, pro[d]);
-    rows_cur = pro[D - 1];
-  }
   int idx_prev[NB] = {0, 0};
-  for (int s = 0; s < ns; ++s) {
-    int newer = ns - 1 - s;
-    if (newer > D - 2) newer = D - 2;
-    if (newer >= 2) wait_vm<2 * NPS>();
-    else if (newer == 1) wait_vm<NPS>();
-    else wait_vm<0>();
-    asm volatile("s_barrier" ::: "memory");
-    fetch_rows(s + D < ns ? s + D : ns - 1, rows_next);   // needed by the next iteration
+  // What an iteration does once stage s is in LDS: `cur` are the rows of stage s+D-1.
+  auto consume = [&](int s, const Rows& cur, auto after_first_reads) {
     const uint32_t boff = (uint32_t)((s % D) * STAGE);
     read_step(boff, U0{}, f0);
 #pragma unroll
     for (int i = 0; i < NB; ++i) idx[i] = lds_read32(fi[i] + boff);
     if (s > 0) smfmac_step(U1{}, f1, idx_prev);   // second half of the previous stage
-    wait_step(f0);                       // full wait: the scalar loads above are in as well
-    tie_rows(rows_next);
-    if (s + D - 1 < ns) issue(s + D - 1, rows_cur);
+    wait_step(f0);                       // full wait: scalar loads of rows are in as well
+    after_first_reads();
+    if (s + D - 1 < ns) issue(s + D - 1, cur);
     read_step(boff, U1{}, f1);
     smfmac_step(U0{}, f0, idx);
     // explicit moves behind the wait: a plain copy would make idx loop-carried, and
     // the compiler may then copy the read's destination before the wait
 #pragma unroll
     for (int i = 0; i < NB; ++i) asm volatile("v_mov_b32 %0, %1" : "=v"(idx_prev[i]) : "v"(idx[i]));
-    rows_cur = rows_next;
     wait_step(f1);
+  };
+  if constexpr (!VEC) {
+    Rows rows_cur{}, rows_next{};
+    if (ns > 0) {
+      // kept-row lists of the first D stages in one round trip, then D-1 stages of copies
+      Rows pro[D];
+#pragma unroll
+      for (int d = 0; d < D; ++d) fetch_rows(d < ns ? d : ns - 1, pro[d]);
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+      for (int d = 0; d < D; ++d) tie_rows(pro[d]);
+#pragma unroll
+      for (int d = 0; d < D - 1; ++d)
+        if (d < ns) issue(d, pro[d]);
+      rows_cur = pro[D - 1];
+    }
+    for (int s = 0; s < ns; ++s) {
+      int newer = ns - 1 - s;
+      if (newer > D - 2) newer = D - 2;
+      if (newer >= 2) wait_vm<2 * NPS>();
+      else if (newer == 1) wait_vm<NPS>();
+      else wait_vm<0>();
+      asm volatile("s_barrier" ::: "memory");
+      fetch_rows(s + D < ns ? s + D : ns - 1, rows_next);   // needed by the next iteration
+      consume(s, rows_cur, [&] { tie_rows(rows_next); });
+      rows_cur = rows_next;
+    }
+  } else {
+    // Two row fetches in flight, in two registers by turns (iterations in pairs, a single one last if
+    // their number is odd), because no register may be copied while its load is under way.
+    int even, odd;
+    auto iteration = [&](int s, int& q, auto LAST) {   // q: rows of stage s+2; receives those of stage s+4
+      constexpr bool last = decltype(LAST)::value;     // the tile's last stage
+      // own copies of stage s and the rows of stage s+2, issued ahead of them, have landed: newer are
+      // the rows of stage s+3 and the copies of stage s+1
+      if (!last && s + 3 < ns) wait_vm<NPS + 1>();
+      else if (!last && s + 1 < ns) wait_vm<NPS>();
+      else wait_vm<0>();
+      Rows cur;
+      if constexpr (!last) share_quad(q, cur);
+      asm volatile("s_barrier" ::: "memory");
+      consume(s, cur, [&] { if (!last && s + 4 < ns) fetch_quad(s + 4, q); });
+    };
+    if (ns > 0) {
+      int q0, q1;
+      fetch_quad(0, q0);
+      fetch_quad(ns > 1 ? 1 : 0, q1);
+      fetch_quad(ns > 2 ? 2 : 0, even);
+      wait_vm<0>();
+      Rows r0, r1;
+      share_quad(q0, r0);
+      share_quad(q1, r1);
+      issue(0, r0);
+      fetch_quad(ns > 3 ? 3 : 0, odd);
+      if (ns > 1) issue(1, r1);
+      int s = 0;
+      for (; s + 1 < ns; s += 2) {
+        iteration(s, even, std::false_type{});
+        iteration(s + 1, odd, std::false_type{});
+      }
+      wait_vm<NPS>();                    // (no row fetch is under way past this point; nothing is waited for)
+      if (s < ns) iteration(s, even, std::true_type{});
+    }
+    wait_vm<0>();                        // (nothing is outstanding: every copy has been waited for)
   }
   if (ns > 0) smfmac_step(U1{}, f1, idx_prev);
 
@@ -330,10 +406,11 @@ __global__ __launch_bounds__(NW * 64) void tvw_gemm_km_kernel(GemmArgs g) {
 
 template <int TM, int TN, int WAVES_N, int D, int NW = 4>
 static hipError_t launch(const GemmArgs& g, hipStream_t stream) {
+  constexpr bool VEC = D == 3;           // (a deeper pipeline would wait for its index loads)
   const int grid = g.n_mtiles * g.n_tiles + g.n_zero;
   if (grid <= 0) return hipSuccess;
   (void)hipGetLastError();   // an error left behind by an earlier call of this thread is not this launch's
-  hipLaunchKernelGGL((tvw_gemm_km_kernel<TM, TN, WAVES_N, D, NW>), dim3(grid), dim3(NW * 64), 0,
+  hipLaunchKernelGGL((tvw_gemm_km_kernel<TM, TN, WAVES_N, D, NW, VEC>), dim3(grid), dim3(NW * 64), 0,
                      stream, g);
   return hipGetLastError();
 }

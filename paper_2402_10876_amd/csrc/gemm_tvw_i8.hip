@@ -137,19 +137,22 @@ __global__ __launch_bounds__(256) void tvw_gemm_i8_kernel(GemmI8Args g) {
   }
   const char* Abase = (const char*)(g.A + m0);
   const uint32_t lda = (uint32_t)g.lda;         // the host checks that K * lda fits 32 bits
-  typedef int sidx_t __attribute__((ext_vector_type(RPIA)));
-  struct Rows { sidx_t r[NIA]; };
-  auto fetch_rows = [&](int s, Rows& dst) {
-#pragma unroll
-    for (int j = 0; j < NIA; ++j) {
-      const int* rp = g.row_idx + kp0 + s * KSV + (wave * NIA + j) * RPIA;
-      if constexpr (RPIA == 8) asm volatile("s_load_dwordx8 %0, %1, 0x0" : "=s"(dst.r[j]) : "s"(rp));
-      else asm volatile("s_load_dwordx16 %0, %1, 0x0" : "=s"(dst.r[j]) : "s"(rp));
-    }
+  // Kept-row indices: one vector load per stage, two iterations ahead of its use and right ahead of the
+  // copies of the stage before, so that the in-order wait for those copies has it in; lane j of a quad
+  // (whose lanes copy from the same row) loads the index for copy instruction j and the quad shares it.
+  // Scalar loads (32 registers per wave and stage) had their round trip in every iteration, the first
+  // three in two of them; same buffers, scalar / vector: 3072 x 768 at M = 4096 and 87.5 % 9.2 / 7.4 us,
+  // 768 x 768 5.9 / 5.0, 768 x 3072 10.6 / 10.3, 1200 x 3000 x 2000 at 75 % 15.1 / 11.9, 64 x 4096 x 4096 16.3 / 8.9.
+  struct Rows { int r[NIA]; };
+  const uint32_t idx_lane = (uint32_t)((wave * NIA + (lane & (NIA - 1))) * RPIA + a_rloc) * 4u;
+  auto fetch_quad = [&](int s, int& dst) {       // of the quad; valid once the load has been waited for
+    asm volatile("global_load_dword %0, %1, %2" : "=v"(dst) : "v"(idx_lane), "s"(g.row_idx + kp0 + s * KSV));
   };
-  auto tie_rows = [&](Rows& x) {      // after a wait: no use of x may be moved above this point
-    if constexpr (NIA == 2) asm volatile("" : "+s"(x.r[0]), "+s"(x.r[1]));
-    else asm volatile("" : "+s"(x.r[0]), "+s"(x.r[1]), "+s"(x.r[2]), "+s"(x.r[3]));
+  auto share_quad = [&](int& src, Rows& dst) {   // (instructions of their own, behind the wait for the load)
+    asm volatile("s_nop 1\n\tv_mov_b32_dpp %0, %1 quad_perm:[0,0,0,0] row_mask:0xf bank_mask:0xf" : "=v"(dst.r[0]) : "v"(src));
+    if constexpr (NIA > 1) asm volatile("v_mov_b32_dpp %0, %1 quad_perm:[1,1,1,1] row_mask:0xf bank_mask:0xf" : "=v"(dst.r[1]) : "v"(src));
+    if constexpr (NIA > 2) asm volatile("v_mov_b32_dpp %0, %1 quad_perm:[2,2,2,2] row_mask:0xf bank_mask:0xf" : "=v"(dst.r[2]) : "v"(src));
+    if constexpr (NIA > 2) asm volatile("v_mov_b32_dpp %0, %1 quad_perm:[3,3,3,3] row_mask:0xf bank_mask:0xf" : "=v"(dst.r[3]) : "v"(src));
   };
   auto issue = [&](int s, const Rows& rows) {     // copies of stage s; rows = its kept-row indices
     char* dstA = lds + (s % D) * STAGE;
@@ -167,10 +170,11 @@ __global__ __launch_bounds__(256) void tvw_gemm_i8_kernel(GemmI8Args g) {
                                        LDS_PTR(void, dstI + wave * (IB / 4)), 16, 0, 0);
 #pragma unroll
     for (int j = 0; j < NIA; ++j) {
-      int row = rows.r[j][0];
-#pragma unroll
-      for (int q = 1; q < RPIA; ++q) row = (a_rloc == q) ? rows.r[j][q] : row;
-      __builtin_amdgcn_global_load_lds(GLOBAL_PTR(Abase + ((uint32_t)row * lda + (uint32_t)a_el[j])),
+      // (an instruction of its own: the compiler's multiply-add takes a register pair as addend whose
+      // unused half may be one that a load is on its way to)
+      uint32_t off;
+      asm("v_mul_lo_u32 %0, %1, %2" : "=v"(off) : "v"(rows.r[j]), "s"(lda));
+      __builtin_amdgcn_global_load_lds(GLOBAL_PTR(Abase + (off + (uint32_t)a_el[j])),
                                        LDS_PTR(void, dstA + (wave * NIA + j) * 1024), 16, 0, 0);
     }
   };
@@ -239,42 +243,55 @@ __global__ __launch_bounds__(256) void tvw_gemm_i8_kernel(GemmI8Args g) {
   using U0 = std::integral_constant<int, 0>;
   using U1 = std::integral_constant<int, 1>;
 
-  Rows rows_cur{}, rows_next{};
-  if (ns > 0) {
-    // kept-row lists of the first two stages in one round trip and their copies, then the
-    // list of the third (a stage's list is 32 scalar registers per wave: three at once
-    // would not fit the scalar register file)
-    static_assert(D == 3, "");
-    {
-      Rows pro[2];
-      fetch_rows(0, pro[0]);
-      fetch_rows(ns > 1 ? 1 : 0, pro[1]);
-      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-      tie_rows(pro[0]);
-      tie_rows(pro[1]);
-      issue(0, pro[0]);
-      if (ns > 1) issue(1, pro[1]);
-    }
-    fetch_rows(ns > 2 ? 2 : ns - 1, rows_cur);
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    tie_rows(rows_cur);
-  }
-  for (int s = 0; s < ns; ++s) {
-    if (s + 1 < ns) wait_vm<NPS>();      // own copies of stage s have landed
-    else wait_vm<0>();
-    asm volatile("s_barrier" ::: "memory");
-    fetch_rows(s + D < ns ? s + D : ns - 1, rows_next);   // needed by the next iteration
+  // What an iteration does once stage s is in LDS: `cur` are the rows of stage s+D-1.
+  auto consume = [&](int s, const Rows& cur, auto after_first_reads) {
     const uint32_t boff = (uint32_t)((s % D) * STAGE);
     read_step(boff, U0{}, f0);
     if (s > 0) smfmac_step(f1);          // second half of the previous stage
-    wait_step(f0);                       // full wait: the scalar loads above are in as well
-    tie_rows(rows_next);
-    if (s + D - 1 < ns) issue(s + D - 1, rows_cur);
+    wait_step(f0);
+    after_first_reads();
+    if (s + D - 1 < ns) issue(s + D - 1, cur);
     read_step(boff, U1{}, f1);
     smfmac_step(f0);
-    rows_cur = rows_next;
     wait_step(f1);
+  };
+  static_assert(D == 3, "");
+  // Two row fetches in flight, in two registers by turns (iterations in pairs, a single one last if
+  // their number is odd), because no register may be copied while its load is under way.
+  int even, odd;
+  auto iteration = [&](int s, int& q, auto LAST) {   // q: rows of stage s+2; receives those of stage s+4
+    constexpr bool last = decltype(LAST)::value;     // the tile's last stage
+    // own copies of stage s and the rows of stage s+2, issued ahead of them, have landed: newer are
+    // the rows of stage s+3 and the copies of stage s+1
+    if (!last && s + 3 < ns) wait_vm<NPS + 1>();
+    else if (!last && s + 1 < ns) wait_vm<NPS>();
+    else wait_vm<0>();
+    Rows cur;
+    if constexpr (!last) share_quad(q, cur);
+    asm volatile("s_barrier" ::: "memory");
+    consume(s, cur, [&] { if (!last && s + 4 < ns) fetch_quad(s + 4, q); });
+  };
+  if (ns > 0) {
+    int q0, q1;
+    fetch_quad(0, q0);
+    fetch_quad(ns > 1 ? 1 : 0, q1);
+    fetch_quad(ns > 2 ? 2 : 0, even);
+    wait_vm<0>();
+    Rows r0, r1;
+    share_quad(q0, r0);
+    share_quad(q1, r1);
+    issue(0, r0);
+    fetch_quad(ns > 3 ? 3 : 0, odd);
+    if (ns > 1) issue(1, r1);
+    int s = 0;
+    for (; s + 1 < ns; s += 2) {
+      iteration(s, even, std::false_type{});
+      iteration(s + 1, odd, std::false_type{});
+    }
+    wait_vm<NPS>();                    // (no row fetch is under way past this point; nothing is waited for)
+    if (s < ns) iteration(s, even, std::true_type{});
   }
+  wait_vm<0>();                        // (nothing is outstanding: every copy has been waited for)
   if (ns > 0) smfmac_step(f1);
 
   // ---- epilogue: acc[i][j][r] is C^T(n, m) with m = lane % 32 and
