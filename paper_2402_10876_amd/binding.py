@@ -1,10 +1,13 @@
-"""ctypes binding with the same names as the C ABI.  Argument marshalling only:
+"""Binding with the same names as the C ABI (ctypes; the launch calls through a small CPython module
+over the same library).  Argument marshalling only:
 every step of the path runs inside libtwgemm.so.  The library is loaded from
 the package directory and is never built here; a missing library is an error
 (there is no fallback path)."""
 from __future__ import annotations
 
 import ctypes as C
+import importlib.machinery
+import importlib.util
 import os
 
 import numpy as np
@@ -22,6 +25,32 @@ EXPORTED_SYMBOLS = [
 ]
 
 _lib = None
+
+
+class _Unbound:
+    """Launch calls before the library is loaded: the ctypes route, which loads it."""
+
+    @staticmethod
+    def gemm(*_):
+        return None
+
+    gemm_i8 = conv = conv_i8 = gemm
+
+
+_call = _Unbound     # the launch calls as a CPython module; None for arguments that ctypes has to convert
+
+
+def _bind_call(L):
+    global _call
+    p = os.path.join(os.path.dirname(os.path.abspath(__file__)), "_twcall.so")
+    if not os.path.exists(p):
+        raise ImportError(f"{p} is missing: build it first (python -c 'import __graft_entry__ as g; g.build()')")
+    loader = importlib.machinery.ExtensionFileLoader("_twcall", p)
+    m = importlib.util.module_from_spec(importlib.util.spec_from_file_location("_twcall", p, loader=loader))
+    loader.exec_module(m)
+    m.bind(*(C.cast(f, C.c_void_p).value for f in (L.tw_gemm, L.tw_gemm_i8, L.tw_conv_gemm, L.tw_conv_gemm_i8)))
+    _call = m
+
 
 
 class TwError(RuntimeError):
@@ -100,6 +129,7 @@ def lib():
         for name in EXPORTED_SYMBOLS:
             if name != "tw_status_str":
                 getattr(L, name).restype = i
+        _bind_call(L)
         _lib = L
     return _lib
 
@@ -122,6 +152,7 @@ class PackedWeight:
 
     def __init__(self, handle: C.c_void_p):
         self._h = handle
+        self._addr = handle.value
 
     @property
     def handle(self):
@@ -194,7 +225,7 @@ class PackedWeight:
 
     def free(self):
         if self._h is not None:
-            h, self._h = self._h, None
+            h, self._h, self._addr = self._h, None, None
             _check(lib().tw_free(h), "tw_free")
 
     def __del__(self):
@@ -297,7 +328,11 @@ def tw_concat(parts, upload: bool = True) -> PackedWeight:
 def tw_gemm(A_ptr: int, M: int, lda: int, layout: int, packed: PackedWeight, C_ptr: int,
             ldc: int, stream: int = 0):
     """A_ptr / C_ptr: device addresses (e.g. torch.Tensor.data_ptr()), stream: hipStream_t."""
-    _check(lib().tw_gemm(A_ptr, M, lda, layout, packed.handle, C_ptr, ldc, stream), "tw_gemm")
+    st = _call.gemm(A_ptr, M, lda, layout, packed._addr, C_ptr, ldc, stream)
+    if st is None:
+        st = lib().tw_gemm(A_ptr, M, lda, layout, packed.handle, C_ptr, ldc, stream)
+    if st:
+        raise TwError(st, "tw_gemm")
 
 
 def tw_dense_gemm(A_ptr: int, B_ptr: int, C_ptr: int, M: int, K: int, N: int, lda: int,
@@ -309,7 +344,11 @@ def tw_dense_gemm(A_ptr: int, B_ptr: int, C_ptr: int, M: int, K: int, N: int, ld
 def tw_gemm_i8(A_ptr: int, M: int, lda: int, packed: PackedWeight, C_ptr: int, ldc: int,
                c_dtype: int = 0, scale: float = 1.0, stream: int = 0):
     """int8 A (K x M) times a packed int8 weight; C (N x M) int32 (c_dtype 0) or requantised int8 (1)."""
-    _check(lib().tw_gemm_i8(A_ptr, M, lda, packed.handle, C_ptr, ldc, c_dtype, scale, stream), "tw_gemm_i8")
+    st = _call.gemm_i8(A_ptr, M, lda, packed._addr, C_ptr, ldc, c_dtype, scale, stream)
+    if st is None:
+        st = lib().tw_gemm_i8(A_ptr, M, lda, packed.handle, C_ptr, ldc, c_dtype, scale, stream)
+    if st:
+        raise TwError(st, "tw_gemm_i8")
 
 
 def tw_dense_gemm_i8(A_ptr: int, B_ptr: int, C_ptr: int, M: int, K: int, N: int, lda: int, ldb: int,
@@ -323,6 +362,7 @@ class ConvBinding:
 
     def __init__(self, handle, packed):
         self._b, self._packed = handle, packed
+        self._addr = handle.value
 
     @property
     def handle(self):
@@ -332,7 +372,7 @@ class ConvBinding:
 
     def free(self):
         if self._b is not None:
-            b, self._b = self._b, None
+            b, self._b, self._addr = self._b, None, None
             _check(lib().tw_conv_free(b), "tw_conv_free")
 
     def __del__(self):
@@ -351,12 +391,20 @@ def tw_conv_bind(packed: PackedWeight, geom, ldx: int) -> ConvBinding:
 
 
 def tw_conv_gemm(X_ptr: int, binding: ConvBinding, C_ptr: int, ldc: int, stream: int = 0):
-    _check(lib().tw_conv_gemm(X_ptr, binding.handle, C_ptr, ldc, stream), "tw_conv_gemm")
+    st = _call.conv(X_ptr, binding._addr, C_ptr, ldc, stream)
+    if st is None:
+        st = lib().tw_conv_gemm(X_ptr, binding.handle, C_ptr, ldc, stream)
+    if st:
+        raise TwError(st, "tw_conv_gemm")
 
 
 def tw_conv_gemm_i8(X_ptr: int, binding: ConvBinding, C_ptr: int, ldc: int, c_dtype: int = 0, scale: float = 1.0,
                     stream: int = 0):
-    _check(lib().tw_conv_gemm_i8(X_ptr, binding.handle, C_ptr, ldc, c_dtype, scale, stream), "tw_conv_gemm_i8")
+    st = _call.conv_i8(X_ptr, binding._addr, C_ptr, ldc, c_dtype, scale, stream)
+    if st is None:
+        st = lib().tw_conv_gemm_i8(X_ptr, binding.handle, C_ptr, ldc, c_dtype, scale, stream)
+    if st:
+        raise TwError(st, "tw_conv_gemm_i8")
 
 
 def tw_launch_opts(**kw) -> LaunchOpts:

@@ -10,12 +10,14 @@ import glob
 import hashlib
 import os
 import subprocess
+import sysconfig
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 LIB = os.path.join(PKG, "libtwgemm.so")
 HASH_FILE = LIB + ".srchash"
 SOURCES = ["api.cpp", "pack.cpp", "gemm_kernels.hip", "gemm_dma.hip", "gemm_mk.hip", "gemm_small.hip", "gemm_tvw.hip", "gemm_i8.hip", "gemm_tvw_i8.hip", "prune.hip", "pack_dev.hip", "calibrate.hip"]
+CALL = os.path.join(PKG, "_twcall.so")       # the launch calls as a CPython module (csrc/pycall.cpp)
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 # packed-fp32 instruction selection is switched off for all device code
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
@@ -43,6 +45,16 @@ def built_hash() -> str | None:
         return f.read().strip()
 
 
+def build_call() -> str:
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-I" + sysconfig.get_paths()["include"],
+           os.path.join(PKG, "csrc", "pycall.cpp"), "-o", CALL + ".tmp"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("host compiler failed:\n" + " ".join(cmd) + "\n" + r.stdout + r.stderr)
+    os.replace(CALL + ".tmp", CALL)
+    return CALL
+
+
 def build(verbose: bool = False) -> str:
     srcs = [os.path.join(PKG, "csrc", s) for s in SOURCES]
     digest = source_hash()
@@ -50,6 +62,7 @@ def build(verbose: bool = False) -> str:
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError("hipcc failed:\n" + " ".join(cmd) + "\n" + r.stdout + r.stderr)
+    build_call()
     os.replace(LIB + ".tmp", LIB)
     with open(HASH_FILE, "w") as f:
         f.write(digest + "\n")
@@ -64,7 +77,7 @@ def ensure_built() -> str:
     library is missing).  A library named by TWGEMM_LIB is the caller's responsibility."""
     if os.environ.get("TWGEMM_LIB"):
         return os.environ["TWGEMM_LIB"]
-    if built_hash() == source_hash():
+    if built_hash() == source_hash() and os.path.exists(CALL):
         return LIB
     return build()
 
