@@ -124,8 +124,8 @@ int pick_tile_m_tvw(const Opts& o, int G, int M, int n_tiles, int max_k) {
 }
 
 // Kept-row indices by scalar loads instead of one vector load per stage (4-wave workgroups, three
-// stages in flight).  128 x 128 tiles with more than one and a half and at most two and three quarter
-// workgroups per CU, same buffers, vector against scalar: 768 x 2304 at M = 4096 9.5 / 9.0 us at 75 %,
+// stages in flight).  128 x 128 tiles, more than 384 and at most 720
+// workgroups, same buffers, vector against scalar: 768 x 2304 at M = 4096 9.5 / 9.0 us at 75 %,
 // 16.3 / 13.6 at 50 %; 1024 x 1024 at M = 8192 11.4 / 10.4; 768 x 3072 at M = 3000 11.9 / 10.0, at 4096
 // 10.1 / 9.8; 1500 x 3000 at 80 % 15.5 / 14.6.  With more the vector load wins (768 x 2304 at M = 7000
 // 16.8 / 19.9, 8192 19.5 / 20.6), with fewer too (2048 x 768 x 3072 at 60 % 8.5 / 9.3).  256 x 64 tiles
@@ -134,7 +134,7 @@ int pick_tile_m_tvw(const Opts& o, int G, int M, int n_tiles, int max_k) {
 bool scalar_rows(const Opts& o, int M, int n_tiles, int G, int tm, int max_k, bool conv) {
   if (o.idx_route) return o.idx_route == 1;
   const long wgs = (long)((M + tm - 1) / tm) * n_tiles;
-  if (G == 128 && tm == 128) return wgs > 384 && wgs <= 704;
+  if (G == 128 && tm == 128) return wgs > 384 && wgs <= 720;
   return conv && G == 64 && tm == 256 && wgs > 384 && max_k > 256;
 }
 

@@ -223,6 +223,11 @@ __global__ __launch_bounds__(NWAVES * 64, ((MULTI && TM * TN <= 64 * 128) || (!D
 void tw_gemm_km_dma_kernel(GemmArgs g_arg) {
   constexpr bool LIDX = D > 3;             // how the kept-row list reaches the lanes (see fetch_rows)
   static_assert(!SCALAR || (!LIDX && !DENSE && KSPLIT == 1), "");
+  // The products of a stage's two k-steps under a branch that is always taken: it keeps the compiler from
+  // mixing them into the operand reads, which two to three workgroups per CU prefer (768 x 3072 at M =
+  // 4096 13.9 -> 11.8 us, 1500 x 3000 at 80 % 14.5 -> 14.1, 768 x 2304 in a stream of layers 10.8 -> 10.2); not the
+  // 256 x 64 tiles of convolutions (16.6 / 16.9).
+  constexpr bool BRANCH = SCALAR && TM == 128;
   constexpr int NT = NWAVES * 64;          // threads of the workgroup
   constexpr int WPG = NWAVES / KSPLIT;     // waves per group
   constexpr int KSS = KS * KSPLIT;         // condensed rows per pipeline stage
@@ -494,8 +499,9 @@ void tw_gemm_km_dma_kernel(GemmArgs g_arg) {
   auto consume = [&](int s, const Rows& cur, auto after_first_reads) {
     const uint32_t boff = (uint32_t)((s % D) * STAGE);
     read_step(boff, K0{}, f0);
-    if (KSPLIT == 1 ? s > 0 : live_prev) mfma_step(f1);   // second k-step of the previous stage
-    const bool live = KSPLIT == 1 || s * KSPLIT + grp < ns32;   // false only for group 1 on an odd tail
+    if (KSPLIT == 1 && !BRANCH ? s > 0 : live_prev) mfma_step(f1);   // second k-step of the previous stage
+    // false only for group 1 on an odd tail (BRANCH: always true, and a branch all the same)
+    const bool live = (KSPLIT == 1 && !BRANCH) || s * KSPLIT + grp < ns32;
     wait_lds<MB, NB>(f0.a, f0.b);
     after_first_reads();
     // the copies of stage sn = s+D-1 go into the buffer of stage s-1, which every wave has
@@ -588,7 +594,7 @@ void tw_gemm_km_dma_kernel(GemmArgs g_arg) {
     }
     wait_vm<0>();                        // (nothing is outstanding: every copy has been waited for)
   }
-  if (KSPLIT == 1 ? ns > 0 : live_prev) mfma_step(f1);
+  if (KSPLIT == 1 && !BRANCH ? ns > 0 : live_prev) mfma_step(f1);
 
   if constexpr (SPLIT) {
     if (S > 1) {
