@@ -26,14 +26,12 @@
 #include <type_traits>
 
 #include "device_common.h"
+#include "mk_band.h"
 
 namespace twg {
 
 namespace {
 
-constexpr int MK_KC = 768;             // columns of A per band, at most
-template <int TM>
-constexpr int MK_KC_LONG = TM == 32 ? MK_KC : 512;   // columns per band when K needs several: one block per wave
 constexpr uint32_t MK_ZERO = MK_KC;    // row of zeros behind the band
 constexpr int MK_NW = 8, MK_NT = MK_NW * 64;
 
@@ -70,7 +68,7 @@ __global__ __launch_bounds__(MK_NT, TM == 32 ? 4 : 2) void tw_gemm_mk_kernel(Gem
   constexpr int SW = G / 32;                        // waves per slot
   constexpr int SLOTS = MK_NW / SW;
   constexpr int NM = TM / 32;                       // blocks of 32 rows
-  constexpr int KB = TM == 64 ? 64 : 128;           // columns of A a wave turns round at a time
+  constexpr int KB = MK_KB<TM>;                     // columns of A a wave turns round at a time
   constexpr int A_BYTES = (MK_KC + 8) * TM * 2;     // LDS bytes of the band, TM * 2 per k
   constexpr int RW = TM / MK_NW;                    // rows of C a wave stores
   constexpr int PF = TM == 32 ? 6 : LONG ? 8 : 14;                 // k-steps of weights and kept rows in flight
@@ -100,8 +98,7 @@ __global__ __launch_bounds__(MK_NT, TM == 32 ? 4 : 2) void tw_gemm_mk_kernel(Gem
   const uint32_t lda2 = (uint32_t)g.lda * 2u;
   const int m_last = min(TM, g.M - m0) - 1;
   auto load_block = [&](int k0, int kb, u32x4 (&v)[8]) {
-    int kg = k0 + kb * KB + kc * 8;
-    if (kg > g.lda - 8) kg = g.lda - 8;             // columns past K: never referenced
+    const int kg = mk_chunk<TM>(k0, kb, kc, g.K);   // (never past K, whatever lda is: A may be a slice of wider rows)
 #pragma unroll
     for (int i = 0; i < 8; ++i)                     // rows past M: never stored
       v[i] = *(const u32x4*)(A_band + ((uint32_t)min(mg * 8 + i, m_last) * lda2 + (uint32_t)kg * 2u));

@@ -37,3 +37,26 @@ def test_row_major_edges(M, K, N, G, col_keep, row_keep):
     assert_C_close(C, og.gemm_oracle(A, B, mask), og.abs_bound(A, B, mask))
     assert not raw[:, :N][:, ~mask.any(0)].view(np.uint16).any()       # pruned columns: exactly +0
     assert (raw[:, N:] == 5.0).all()                                   # nothing written past column N
+
+
+@pytest.mark.parametrize("M,K,N,G,lda", [(64, 64, 256, 128, 1024), (33, 61, 300, 64, 808), (70, 769, 257, 64, 4096),
+                                         (1665, 700, 1300, 128, 1472), (130, 1537, 640, 128, 2048)])
+def test_A_is_the_last_columns_of_a_wider_buffer(M, K, N, G, lda):
+    """lda > K and A's last row ends where the buffer ends; everything around A is NaN."""
+    import torch
+    rng = np.random.default_rng(M + K)
+    mask = random_tw_mask(rng, K, N, G, 0.9, 0.4)
+    A, B = wl.make_A(K, M, K), wl.make_B(K, K, N, 0.1)
+    print(f"case row-major slice M={M} K={K} N={N} G={G} lda={lda}", flush=True)
+    at = lda - (K + 7) // 8 * 8
+    wide = torch.full((M, lda), float("nan"), dtype=torch.float16, device="cuda")
+    wide[:, at:at + K] = torch.from_numpy(A).cuda()
+    ldc = (N + 7) // 8 * 8
+    C = torch.full((M, ldc), 5.0, dtype=torch.float16, device="cuda")
+    p = tw.tw_pack(B, mask, G, tw.PATTERN_TW)
+    tw.tw_gemm(wide.data_ptr() + 2 * at, M, lda, tw.LAYOUT_MK, p, C.data_ptr(), ldc, torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    p.free()
+    got = C.cpu().numpy()
+    assert_C_close(got[:, :N].astype(np.float64), og.gemm_oracle(A, B, mask), og.abs_bound(A, B, mask))
+    assert (got[:, N:] == 5.0).all()

@@ -1,0 +1,47 @@
+"""Which columns of A the row-major kernel reads: its own address arithmetic (csrc/mk_band.h), built for the
+host and followed over every block that a workgroup loads.  A may be the last columns of a wider buffer
+(lda > K), so nothing past the 16-byte chunk that holds column K - 1 may be touched (CPU)."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+DRIVER = r"""
+#include <cstdio>
+#include "mk_band.h"
+using namespace twg;
+static int fails = 0;
+// The blocks of a workgroup: 8 waves, a block each per band, and with one band of 64 rows a second one.
+template <int TM>
+void follow(int K) {
+  const bool is_long = K > MK_KC;
+  const int step = is_long ? MK_KC_LONG<TM> : MK_KC, bands = is_long ? (K + step - 1) / step : 1;
+  const int blocks = TM == 64 && !is_long ? 16 : 8;
+  for (int band = 0; band < bands; ++band)
+    for (int kb = 0; kb < blocks; ++kb)
+      for (int kc = 0; kc < MK_KB<TM> / 8; ++kc) {
+        const int own = band * step + kb * MK_KB<TM> + kc * 8, at = mk_chunk<TM>(band * step, kb, kc, K);
+        const bool ok = at >= 0 && at % 8 == 0 && at + 8 <= (K + 7) / 8 * 8 && (own >= K || at == own);
+        if (!ok && ++fails < 10) std::printf("TM %d K %d band %d block %d chunk %d: column %d\n", TM, K, band, kb, kc, at);
+      }
+}
+int main() {
+  for (int K = 1; K <= 3200; ++K) { follow<64>(K); follow<32>(K); }
+  std::printf("fails=%d\n", fails);
+  return fails != 0;
+}
+"""
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="g++ not available")
+def test_no_column_past_K_is_read(tmp_path):
+    src, exe = tmp_path / "driver.cpp", tmp_path / "driver"
+    src.write_text(DRIVER)
+    r = subprocess.run(["g++", "-std=c++17", "-O1", "-I", os.path.join(ROOT, "paper_2402_10876_amd", "csrc"), str(src), "-o", str(exe)],
+                       capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-2000:]
+    r = subprocess.run([str(exe)], capture_output=True, text=True, timeout=60)
+    assert r.returncode == 0 and "fails=0" in r.stdout, r.stdout[-2000:]
