@@ -92,16 +92,15 @@ __global__ __launch_bounds__(MK_NT, TM == 32 ? 4 : 2) void tw_gemm_mk_kernel(Gem
 
   // ---- band of A: global rows as they lie -> k-major LDS rows ----------------------------------
   // lane = (m block mg of 8 rows, chunk kc of 8 columns); a wave turns TM x KB round per step
-  // (wave-uniform base, 32-bit byte offset per lane)
+  // (wave-uniform base, byte offset per lane)
   const int kc = lane % (KB / 8), mg = lane / (KB / 8);
   const char* A_band = (const char*)(g.A + (size_t)m0 * g.lda);
-  const uint32_t lda2 = (uint32_t)g.lda * 2u;
   const int m_last = min(TM, g.M - m0) - 1;
   auto load_block = [&](int k0, int kb, u32x4 (&v)[8]) {
     const int kg = mk_chunk<TM>(k0, kb, kc, g.K);   // (never past K, whatever lda is: A may be a slice of wider rows)
 #pragma unroll
     for (int i = 0; i < 8; ++i)                     // rows past M: never stored
-      v[i] = *(const u32x4*)(A_band + ((uint32_t)min(mg * 8 + i, m_last) * lda2 + (uint32_t)kg * 2u));
+      v[i] = *(const u32x4*)(A_band + (mk_row_bytes(min(mg * 8 + i, m_last), g.lda) + (uint32_t)kg * 2u));
   };
   auto store_block = [&](int kb, const u32x4 (&v)[8]) {
 #pragma unroll

@@ -20,4 +20,7 @@ constexpr int mk_chunk(int k0, int kb, int kc, int K) {
   return kg < last ? kg : last;
 }
 
+// Byte offset of a row (0 .. 63) inside a band of rows of lda elements: past 32 bits from lda = 2^25 on.
+constexpr uint64_t mk_row_bytes(int row, int lda) { return (uint64_t)(uint32_t)row * ((uint32_t)lda * 2u); }
+
 }  // namespace twg

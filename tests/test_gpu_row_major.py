@@ -60,3 +60,23 @@ def test_A_is_the_last_columns_of_a_wider_buffer(M, K, N, G, lda):
     got = C.cpu().numpy()
     assert_C_close(got[:, :N].astype(np.float64), og.gemm_oracle(A, B, mask), og.abs_bound(A, B, mask))
     assert (got[:, N:] == 5.0).all()
+
+
+@pytest.mark.parametrize("M,K,N,G,lda", [(33, 96, 200, 64, 70_000_000),            # 32-row bands
+                                         (64, 200, 33200, 128, 35_000_000)])       # 64-row bands
+def test_last_row_of_a_band_past_32_bits(M, K, N, G, lda):
+    """The band's last row starts more than 2^32 bytes behind its first: A is a column slice of 4.5 GB."""
+    import torch
+    mask = random_tw_mask(np.random.default_rng(5), K, N, G, 1.0, 0.6)
+    A, B = wl.make_A(K, M, K), wl.make_B(K, K, N, 0.1)
+    print(f"case row-major M={M} N={N} lda={lda}", flush=True)
+    wide = torch.empty((M, lda), dtype=torch.float16, device="cuda")
+    wide[:, :K] = torch.from_numpy(A).cuda()
+    C = torch.full((M, N), 5.0, dtype=torch.float16, device="cuda")
+    p = tw.tw_pack(B, mask, G, tw.PATTERN_TW)
+    tw.tw_gemm(wide.data_ptr(), M, lda, tw.LAYOUT_MK, p, C.data_ptr(), N, torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    p.free()
+    del wide
+    torch.cuda.empty_cache()
+    assert_C_close(C.cpu().numpy().astype(np.float64), og.gemm_oracle(A, B, mask), og.abs_bound(A, B, mask))

@@ -1,6 +1,7 @@
-"""Which columns of A the row-major kernel reads: its own address arithmetic (csrc/mk_band.h), built for the
-host and followed over every block that a workgroup loads.  A may be the last columns of a wider buffer
-(lda > K), so nothing past the 16-byte chunk that holds column K - 1 may be touched (CPU)."""
+"""Which addresses of A the row-major kernel reads: its own arithmetic (csrc/mk_band.h), built for the host and
+followed over every block that a workgroup loads.  A may be the last columns of a wider buffer (lda > K),
+so nothing past the 16-byte chunk that holds column K - 1 may be touched, and lda goes up to the largest int
+(CPU)."""
 import os
 import shutil
 import subprocess
@@ -11,6 +12,7 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 DRIVER = r"""
 #include <cstdio>
+#include <initializer_list>
 #include "mk_band.h"
 using namespace twg;
 static int fails = 0;
@@ -30,6 +32,9 @@ void follow(int K) {
 }
 int main() {
   for (int K = 1; K <= 3200; ++K) { follow<64>(K); follow<32>(K); }
+  for (int row = 0; row < 64; ++row)
+    for (int lda : {8, 1 << 24, 1 << 25, 34087048, 1 << 30, 2147483640})
+      if (mk_row_bytes(row, lda) != 2ull * row * lda && ++fails < 10) std::printf("row %d lda %d\n", row, lda);
   std::printf("fails=%d\n", fails);
   return fails != 0;
 }
@@ -37,7 +42,7 @@ int main() {
 
 
 @pytest.mark.skipif(shutil.which("g++") is None, reason="g++ not available")
-def test_no_column_past_K_is_read(tmp_path):
+def test_addresses_of_A(tmp_path):
     src, exe = tmp_path / "driver.cpp", tmp_path / "driver"
     src.write_text(DRIVER)
     r = subprocess.run(["g++", "-std=c++17", "-O1", "-I", os.path.join(ROOT, "paper_2402_10876_amd", "csrc"), str(src), "-o", str(exe)],
