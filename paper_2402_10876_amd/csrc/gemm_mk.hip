@@ -62,8 +62,9 @@ __device__ __forceinline__ half8 mk_operand(const char* lo, const char* hi) {
 
 // LONG: K in several bands.  One band needs no registers for the next one, and PF = 14 k-steps hold
 // a whole tile of 75 % sparsity at K = 768: its products then wait for no load, and the stores of the
-// tiles before drain meanwhile.
-template <int G, bool LONG, int TM>
+// tiles before drain meanwhile.  WIDE: rows of A too far apart for 32-bit offsets, whose 64-bit sums cost
+// registers (3072 x 768 at M = 1000 17.0 -> 19.3 us with 32-row bands).
+template <int G, bool LONG, int TM, bool WIDE>
 __global__ __launch_bounds__(MK_NT, TM == 32 ? 4 : 2) void tw_gemm_mk_kernel(GemmArgs g, int groups, int parts, int per_part, int kc_max) {
   constexpr int SW = G / 32;                        // waves per slot
   constexpr int SLOTS = MK_NW / SW;
@@ -100,7 +101,7 @@ __global__ __launch_bounds__(MK_NT, TM == 32 ? 4 : 2) void tw_gemm_mk_kernel(Gem
     const int kg = mk_chunk<TM>(k0, kb, kc, g.K);   // (never past K, whatever lda is: A may be a slice of wider rows)
 #pragma unroll
     for (int i = 0; i < 8; ++i)                     // rows past M: never stored
-      v[i] = *(const u32x4*)(A_band + (mk_row_bytes(min(mg * 8 + i, m_last), g.lda) + (uint32_t)kg * 2u));
+      v[i] = *(const u32x4*)(A_band + mk_offset<WIDE>(min(mg * 8 + i, m_last), g.lda, kg));
   };
   auto store_block = [&](int kb, const u32x4 (&v)[8]) {
 #pragma unroll
@@ -330,7 +331,7 @@ static __global__ void zero_mk(_Float16* C, int M, int N, int ldc) {
   for (int m = blockIdx.y; m < M; m += gridDim.y) C[(size_t)m * ldc + n] = (_Float16)0.f;
 }
 
-template <int G, int TM>
+template <int G, int TM, bool WIDE = false>
 static hipError_t launch_mk(GemmArgs& g, hipStream_t stream) {
   constexpr int SLOTS = MK_NW / (G / 32);
   constexpr int RESIDENT = TM == 32 ? 512 : 256;         // workgroups the chip holds at once
@@ -342,9 +343,9 @@ static hipError_t launch_mk(GemmArgs& g, hipStream_t stream) {
   parts = (groups + per - 1) / per;
   const dim3 grid((unsigned)(g.n_mtiles * parts));
   if (g.K > MK_KC)
-    hipLaunchKernelGGL((tw_gemm_mk_kernel<G, true, TM>), grid, dim3(MK_NT), 0, stream, g, groups, parts, per, MK_KC_LONG<TM>);
+    hipLaunchKernelGGL((tw_gemm_mk_kernel<G, true, TM, WIDE>), grid, dim3(MK_NT), 0, stream, g, groups, parts, per, MK_KC_LONG<TM>);
   else
-    hipLaunchKernelGGL((tw_gemm_mk_kernel<G, false, TM>), grid, dim3(MK_NT), 0, stream, g, groups, parts, per, MK_KC);
+    hipLaunchKernelGGL((tw_gemm_mk_kernel<G, false, TM, WIDE>), grid, dim3(MK_NT), 0, stream, g, groups, parts, per, MK_KC);
   return hipGetLastError();
 }
 
@@ -358,6 +359,7 @@ template <int G>
 static hipError_t launch_mk_rows(int max_kp, GemmArgs& g, hipStream_t stream) {
   constexpr int SLOTS = MK_NW / (G / 32);
   const long blocks64 = (long)((g.M + 63) / 64) * ((g.n_tiles + SLOTS - 1) / SLOTS);
+  if (g.lda > MK_LDA_32) return launch_mk<G, 32, true>(g, stream);
   if (blocks64 <= 128 || (g.K <= MK_KC && max_kp <= 96)) return launch_mk<G, 32>(g, stream);
   return launch_mk<G, 64>(g, stream);
 }

@@ -20,7 +20,13 @@ constexpr int mk_chunk(int k0, int kb, int kc, int K) {
   return kg < last ? kg : last;
 }
 
-// Byte offset of a row (0 .. 63) inside a band of rows of lda elements: past 32 bits from lda = 2^25 on.
-constexpr uint64_t mk_row_bytes(int row, int lda) { return (uint64_t)(uint32_t)row * ((uint32_t)lda * 2u); }
+// Byte offset of column kg of a row (0 .. 63) inside a band of rows of lda elements.  WIDE: lda above
+// MK_LDA_32, where 32 bits do not hold it.
+constexpr int MK_LDA_32 = 1 << 25;
+template <bool WIDE>
+constexpr auto mk_offset(int row, int lda, int kg) {
+  if constexpr (WIDE) return (uint64_t)(uint32_t)row * ((uint32_t)lda * 2u) + (uint32_t)kg * 2u;
+  else return (uint32_t)row * ((uint32_t)lda * 2u) + (uint32_t)kg * 2u;
+}
 
 }  // namespace twg

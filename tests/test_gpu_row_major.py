@@ -62,10 +62,10 @@ def test_A_is_the_last_columns_of_a_wider_buffer(M, K, N, G, lda):
     assert (got[:, N:] == 5.0).all()
 
 
-@pytest.mark.parametrize("M,K,N,G,lda", [(33, 96, 200, 64, 70_000_000),            # 32-row bands
-                                         (64, 200, 33200, 128, 35_000_000)])       # 64-row bands
+@pytest.mark.parametrize("M,K,N,G,lda", [(33, 96, 200, 64, 70_000_000), (64, 200, 33200, 128, (1 << 25) + 8), (33, 1600, 200, 128, 70_000_000),
+                                         (64, 200, 33200, 128, 1 << 25)])       # the last one within 32 bits, 64-row bands
 def test_last_row_of_a_band_past_32_bits(M, K, N, G, lda):
-    """The band's last row starts more than 2^32 bytes behind its first: A is a column slice of 4.5 GB."""
+    """The band's last row starts up to 2^32 bytes and more behind its first: A is a column slice of 4.5 GB."""
     import torch
     mask = random_tw_mask(np.random.default_rng(5), K, N, G, 1.0, 0.6)
     A, B = wl.make_A(K, M, K), wl.make_B(K, K, N, 0.1)

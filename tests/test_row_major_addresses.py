@@ -33,8 +33,11 @@ void follow(int K) {
 int main() {
   for (int K = 1; K <= 3200; ++K) { follow<64>(K); follow<32>(K); }
   for (int row = 0; row < 64; ++row)
-    for (int lda : {8, 1 << 24, 1 << 25, 34087048, 1 << 30, 2147483640})
-      if (mk_row_bytes(row, lda) != 2ull * row * lda && ++fails < 10) std::printf("row %d lda %d\n", row, lda);
+    for (int lda : {8, 1 << 24, MK_LDA_32, MK_LDA_32 + 8, 1 << 30, 2147483640})
+      for (int kg : {0, lda - 8}) {
+        const uint64_t at = lda > MK_LDA_32 ? mk_offset<true>(row, lda, kg) : mk_offset<false>(row, lda, kg);
+        if (at != 2ull * row * lda + 2ull * kg && ++fails < 10) std::printf("row %d lda %d column %d\n", row, lda, kg);
+      }
   std::printf("fails=%d\n", fails);
   return fails != 0;
 }
