@@ -394,7 +394,7 @@ static tw_status gemm_launch(const Opts& o, const void* A, int M, int lda, int l
   g.wg_split = 1;
   g.tiles_per_wg = 1;
   if (layout == TW_LAYOUT_MK) {
-    hipError_t e = twg::launch_tw_mk(h->G, h->max_kp, g, (hipStream_t)stream);
+    hipError_t e = twg::launch_tw_mk(h->G, h->max_kp, h->nonfinite, g, (hipStream_t)stream);
     if (e == hipErrorInvalidValue) return TW_ERR_UNSUPPORTED;
     return e == hipSuccess ? TW_OK : TW_ERR_HIP;
   }

@@ -14,7 +14,7 @@
 //             tile: the K loop has no barrier, and 64 KiB or more per CU are in flight.
 //   long K  : bands of 512 (768) columns one after the other, the next one's loads in flight while this
 //             one is multiplied; the k-steps around the end of a band run in both, with the other
-//             band's rows pointing at a row of zeros.
+//             band's rows pointing at a row of zeros (CAREFUL: and their weights set to zero, for 0 x Inf is not 0).
 //   output  : staged in LDS over the range of original columns that the tiles side by side answer
 //             for, pruned ones as +0, and stored in whole 16-byte pieces of C's rows; a piece at
 //             the end of the range that belongs to two workgroups is stored element by element.
@@ -62,9 +62,10 @@ __device__ __forceinline__ half8 mk_operand(const char* lo, const char* hi) {
 
 // LONG: K in several bands.  One band needs no registers for the next one, and PF = 14 k-steps hold
 // a whole tile of 75 % sparsity at K = 768: its products then wait for no load, and the stores of the
-// tiles before drain meanwhile.  WIDE: rows of A too far apart for 32-bit offsets, whose 64-bit sums cost
-// registers (3072 x 768 at M = 1000 17.0 -> 19.3 us with 32-row bands).
-template <int G, bool LONG, int TM, bool WIDE>
+// tiles before drain meanwhile.  CAREFUL: for rows of A too far apart for 32-bit offsets and for weights with
+// infinities (or NaN) among them.  In every instance the wider sums and the masked weights would cost 5 to 14 %
+// of the launches with several bands (3072 x 768 at M = 4096 24.5 / 25.6 us, at M = 1000 16.9 / 19.3).
+template <int G, bool LONG, int TM, bool CAREFUL>
 __global__ __launch_bounds__(MK_NT, TM == 32 ? 4 : 2) void tw_gemm_mk_kernel(GemmArgs g, int groups, int parts, int per_part, int kc_max) {
   constexpr int SW = G / 32;                        // waves per slot
   constexpr int SLOTS = MK_NW / SW;
@@ -101,7 +102,7 @@ __global__ __launch_bounds__(MK_NT, TM == 32 ? 4 : 2) void tw_gemm_mk_kernel(Gem
     const int kg = mk_chunk<TM>(k0, kb, kc, g.K);   // (never past K, whatever lda is: A may be a slice of wider rows)
 #pragma unroll
     for (int i = 0; i < 8; ++i)                     // rows past M: never stored
-      v[i] = *(const u32x4*)(A_band + mk_offset<WIDE>(min(mg * 8 + i, m_last), g.lda, kg));
+      v[i] = *(const u32x4*)(A_band + mk_offset<CAREFUL>(min(mg * 8 + i, m_last), g.lda, kg));
   };
   auto store_block = [&](int kb, const u32x4 (&v)[8]) {
 #pragma unroll
@@ -206,6 +207,7 @@ __global__ __launch_bounds__(MK_NT, TM == 32 ? 4 : 2) void tw_gemm_mk_kernel(Gem
     // a k-step belongs to the band if its first row lies below the band's end; set u holds k-step
     // s + u throughout, so the last round of a band is the first of the next
     int s = 0;
+    u32x4 left = {0u, 0u, 0u, 0u};
     for (int band = 0; band < bands; ++band) {
       const int k0 = LONG ? band * kc_max : 0, kn = LONG ? min(g.K - k0, kc_max) : g.K;
       const bool more = LONG && band + 1 < bands;
@@ -246,12 +248,34 @@ __global__ __launch_bounds__(MK_NT, TM == 32 ? 4 : 2) void tw_gemm_mk_kernel(Gem
           fetch(cur, min(s + u + PF, cur.nk - 1), u);
         }
       }
+      // CAREFUL: the band's last k-step, which its end may cut: its 16 rows ascend, and the weights of those past
+      // the band, a suffix, are left for the bands behind it
+      auto cut_weights = [&](int u) {
+        constexpr unsigned long long ONCE = 0x0000333300003333ull;     // lanes that hold each of the rows once
+        const int ours = __popcll(__ballot(r[u] < k0 + kn) & ONCE) - 8 * (lane >> 5);   // (of the lane's 8 weights)
+        union { half8 h; u32x4 w; } x;
+        x.h = b[u];
+        left = x.w;
+#pragma unroll
+        for (int d = 0; d < 4; ++d)
+          x.w[d] &= (2 * d < ours ? 0x0000ffffu : 0u) | (2 * d + 1 < ours ? 0xffff0000u : 0u);
+        left ^= x.w;
+        b[u] = x.h;
+      };
       auto last_round = [&](auto FILL) {
 #pragma unroll
         for (int u = 0; u < PF; ++u) {
           if (s + u < s1) {
+            const bool end = LONG && CAREFUL && s + u == s1 - 1;
+            if (end) cut_weights(u);
             if (u + 1 < PF) operands(u + 1, a[(u + 1) & 1]);
             multiply(u, a[u & 1]);
+            if constexpr (LONG && CAREFUL) {        // what the next band, which runs this round again, may count
+              union { half8 h; u32x4 w; } x;
+#pragma unroll
+              for (int d = 0; d < 4; ++d) x.w[d] = end ? left[d] : 0u;
+              b[u] = x.h;
+            }
           }
           if constexpr (decltype(FILL)::value) fetch(next, u < next.nk ? u : 0, u);
         }
@@ -331,7 +355,7 @@ static __global__ void zero_mk(_Float16* C, int M, int N, int ldc) {
   for (int m = blockIdx.y; m < M; m += gridDim.y) C[(size_t)m * ldc + n] = (_Float16)0.f;
 }
 
-template <int G, int TM, bool WIDE = false>
+template <int G, int TM, bool CAREFUL = false>
 static hipError_t launch_mk(GemmArgs& g, hipStream_t stream) {
   constexpr int SLOTS = MK_NW / (G / 32);
   constexpr int RESIDENT = TM == 32 ? 512 : 256;         // workgroups the chip holds at once
@@ -343,9 +367,9 @@ static hipError_t launch_mk(GemmArgs& g, hipStream_t stream) {
   parts = (groups + per - 1) / per;
   const dim3 grid((unsigned)(g.n_mtiles * parts));
   if (g.K > MK_KC)
-    hipLaunchKernelGGL((tw_gemm_mk_kernel<G, true, TM, WIDE>), grid, dim3(MK_NT), 0, stream, g, groups, parts, per, MK_KC_LONG<TM>);
+    hipLaunchKernelGGL((tw_gemm_mk_kernel<G, true, TM, CAREFUL>), grid, dim3(MK_NT), 0, stream, g, groups, parts, per, MK_KC_LONG<TM>);
   else
-    hipLaunchKernelGGL((tw_gemm_mk_kernel<G, false, TM, WIDE>), grid, dim3(MK_NT), 0, stream, g, groups, parts, per, MK_KC);
+    hipLaunchKernelGGL((tw_gemm_mk_kernel<G, false, TM, CAREFUL>), grid, dim3(MK_NT), 0, stream, g, groups, parts, per, MK_KC);
   return hipGetLastError();
 }
 
@@ -356,23 +380,23 @@ static hipError_t launch_mk(GemmArgs& g, hipStream_t stream) {
 // 21.3; 2000 x 1500 with G = 64, 144 of the larger blocks 16.2 / 20.4; lists of at most 96 rows at M = 4096:
 // 768 x 3072 at 90 % 20.8 / 18.4, 128 x 512 at 50 % 8.0 / 5.9; of 128 rows 9.3 / 9.8 (200 x 1000, 50 %).
 template <int G>
-static hipError_t launch_mk_rows(int max_kp, GemmArgs& g, hipStream_t stream) {
+static hipError_t launch_mk_rows(int max_kp, bool nonfinite, GemmArgs& g, hipStream_t stream) {
   constexpr int SLOTS = MK_NW / (G / 32);
   const long blocks64 = (long)((g.M + 63) / 64) * ((g.n_tiles + SLOTS - 1) / SLOTS);
-  if (g.lda > MK_LDA_32) return launch_mk<G, 32, true>(g, stream);
+  if (g.lda > MK_LDA_32 || (nonfinite && g.K > MK_KC)) return launch_mk<G, 32, true>(g, stream);
   if (blocks64 <= 128 || (g.K <= MK_KC && max_kp <= 96)) return launch_mk<G, 32>(g, stream);
   return launch_mk<G, 64>(g, stream);
 }
 
-hipError_t launch_tw_mk(int G, int max_kp, GemmArgs g, hipStream_t stream) {
+hipError_t launch_tw_mk(int G, int max_kp, bool nonfinite, GemmArgs g, hipStream_t stream) {
   (void)hipGetLastError();   // an error left behind by an earlier call of this thread is not this launch's
   if (g.n_tiles == 0) {
     hipLaunchKernelGGL(zero_mk, dim3((g.N + 255) / 256, g.M < 1024 ? g.M : 1024), dim3(256), 0, stream, g.C, g.M, g.N, g.ldc);
     return hipGetLastError();
   }
-  if (G == 128) return launch_mk_rows<128>(max_kp, g, stream);
-  if (G == 64) return launch_mk_rows<64>(max_kp, g, stream);
-  if (G == 32) return launch_mk_rows<32>(max_kp, g, stream);
+  if (G == 128) return launch_mk_rows<128>(max_kp, nonfinite, g, stream);
+  if (G == 64) return launch_mk_rows<64>(max_kp, nonfinite, g, stream);
+  if (G == 32) return launch_mk_rows<32>(max_kp, nonfinite, g, stream);
   return hipErrorInvalidValue;
 }
 

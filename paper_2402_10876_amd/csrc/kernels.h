@@ -77,8 +77,8 @@ hipError_t launch_tvw_i8(int G, int tm, GemmI8Args g, hipStream_t stream);
 hipError_t launch_tw_km(int G, int tm, GemmArgs g, hipStream_t stream);
 hipError_t launch_dense_km(int tn, int tm, GemmArgs g, hipStream_t stream);
 // Row-major A (M x K) and C (M x N): tile-wise weights (gemm_mk.hip), and the dense baseline on
-// the register-staged kernel (128 columns per tile).
-hipError_t launch_tw_mk(int G, int max_kp, GemmArgs g, hipStream_t stream);
+// the register-staged kernel (128 columns per tile).  nonfinite: an infinity or NaN among the weights.
+hipError_t launch_tw_mk(int G, int max_kp, bool nonfinite, GemmArgs g, hipStream_t stream);
 hipError_t launch_dense_mk(GemmArgs g, hipStream_t stream);
 // Asynchronous-copy pipeline (gemm_dma.hip): G / tn in {64, 128}, depth = stages
 // in flight (3 or 4); the dense variant needs K % 32 == 0.

@@ -485,6 +485,7 @@ void build_device_values(tw_handle_s* h) {
     return;
   }
   if (!tvw) {
+    h->nonfinite = std::any_of(h->values.begin(), h->values.end(), [](uint16_t v) { return (v & 0x7c00) == 0x7c00; });
     d.vals.assign(((size_t)d.tile_kp_off[nt] + KSTEP_TW) * G, 0);
     for (int t = 0; t < nt; ++t) {
       const int kt = h->tile_k_off[t + 1] - h->tile_k_off[t];

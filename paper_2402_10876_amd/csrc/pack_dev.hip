@@ -41,7 +41,8 @@ struct Counts {
   unsigned long long nnz;      // entries of the structure mask
   int32_t outside;             // an element is kept outside the tile mask
   int32_t three;               // a 2:4 group keeps more than two
-  int32_t n_kept, pad;
+  int32_t n_kept;
+  int32_t nonfinite;           // TW: an infinity or NaN among the packed values
 };
 
 static __global__ void fill_zero(u32x4* p, size_t n) {
@@ -225,7 +226,8 @@ __global__ void image_lists(Structure st, int G, const int32_t* tile_kp_off, int
 
 // TW values (layout: see the host packer's build_device_values): 8 rows of a column per thread, one
 // 16-byte store; blockIdx.y == n_tiles: the slack behind the last tile.
-__global__ void image_tw(const uint16_t* B, int ldb, Structure st, int G, const int32_t* tile_kp_off, uint16_t* vals) {
+__global__ void image_tw(const uint16_t* B, int ldb, Structure st, int G, const int32_t* tile_kp_off, uint16_t* vals,
+                         Counts* counts) {
   const int t = blockIdx.y, i = blockIdx.x * blockDim.x + threadIdx.x;
   const int kp0 = tile_kp_off[t];
   u32x4* out = (u32x4*)(vals + (size_t)kp0 * G);
@@ -242,11 +244,14 @@ __global__ void image_tw(const uint16_t* B, int ldb, Structure st, int G, const 
   x.v = u32x4{0u, 0u, 0u, 0u};
   if (t * G + c < st.n_kept && j0 < kt) {
     const int n = st.kept[t * G + c];
+    bool nonfinite = false;
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
       const uint16_t v = B[(size_t)rows[min(j0 + j, kt - 1)] * ldb + n];
       x.e[j] = j0 + j < kt ? v : (uint16_t)0;
+      nonfinite |= (v & 0x7c00) == 0x7c00;
     }
+    if (nonfinite) counts->nonfinite = 1;              // racing writers all store 1
   }
   out[j0 / 16 * (2 * G) + (c / 32) * 64 + ((j0 % 16) / 8) * 32 + c % 32] = x.v;
 }
@@ -412,15 +417,14 @@ tw_status pack_device(const uint16_t* B, int ldb, const uint8_t* mask, const uin
              (int32_t*)d.d_col_idx, (int32_t*)d.d_zero_cols);
   if (!tvw) {
     const int most = std::max(h->max_kp / 8 * G, KSTEP_TW * G / 8);
-    TWG_LAUNCH(image_tw, dim3((most + T - 1) / T, n_tiles + 1), dim3(T), B, ldb, st, G, d.d_tile_kp_off, (uint16_t*)d.d_vals);
-    TWG_TRY(hipStreamSynchronize(s));    // the workspace goes away when this returns
-    return TW_OK;
-  }
-  if (n_tiles > 0 && h->max_kp > 0)
+    TWG_LAUNCH(image_tw, dim3((most + T - 1) / T, n_tiles + 1), dim3(T), B, ldb, st, G, d.d_tile_kp_off, (uint16_t*)d.d_vals, counts);
+  } else if (n_tiles > 0 && h->max_kp > 0) {
     TWG_LAUNCH(image_tvw, dim3((h->max_kp / 32 * G * 2 + T - 1) / T, n_tiles), dim3(T), B, ldb, mask, N, st, G,
                d.d_tile_kp_off, (uint16_t*)d.d_vals, (uint16_t*)d.d_meta, (uint8_t*)d.d_valid, counts);
-  Counts after;
+  }
+  Counts after;                          // (waits for the stream: the workspace goes away when this returns)
   TWG_TRY(hipMemcpyWithStream(&after, counts, sizeof after, hipMemcpyDeviceToHost, s));
+  h->nonfinite = after.nonfinite != 0;
   return after.three ? TW_ERR_MASK : TW_OK;
 } catch (const std::bad_alloc&) {
   return TW_ERR_ALLOC;

@@ -80,3 +80,50 @@ def test_last_row_of_a_band_past_32_bits(M, K, N, G, lda):
     del wide
     torch.cuda.empty_cache()
     assert_C_close(C.cpu().numpy().astype(np.float64), og.gemm_oracle(A, B, mask), og.abs_bound(A, B, mask))
+
+
+@pytest.mark.parametrize("M,K,N,G,row_keep", [(40, 1537, 300, 128, 0.3), (130, 3072, 640, 64, 0.05), (33, 1537, 200, 32, 1.0),
+                                              (1700, 1537, 1300, 64, 0.2), (1665, 3072, 1300, 128, 0.3)])
+def test_infinite_weights_at_the_ends_of_the_bands(M, K, N, G, row_keep):
+    """K in several bands: an infinite weight beside a band's end gives the infinity that its column's sum is, and
+    infinite activations likewise; no other column changes."""
+    import torch
+    rng = np.random.default_rng(M + K + G)
+    mask = random_tw_mask(rng, K, N, G, 0.9, row_keep)
+    A, B = wl.make_A(K, M, K), wl.make_B(K, K, N, 0.1)
+    A = np.where(A == 0, np.float16(0.5), A)
+    B = np.where(B == 0, np.float16(0.5), B)
+    cols = np.flatnonzero(mask.any(0))
+    ends = [e for e in range(256, K, 256)]                       # every band end of 512 and 768 columns among them
+    for i, c in enumerate(cols):                                 # one per column, within three kept rows of an end
+        kept = np.flatnonzero(mask[:, c])
+        at = np.searchsorted(kept, ends[i % len(ends)]) + i % 7 - 3
+        if i % 3 and 0 <= at < len(kept):
+            B[kept[at], c] = np.inf * (-1) ** i
+    tail = {int(np.flatnonzero(mask[:, c])[-1]) for c in cols}   # (a padded list repeats its last row with weights of 0)
+    free = [k for k in np.flatnonzero(mask.any(1)) if k not in tail and not np.isinf(B[k]).any()]
+    A[M // 2, free[len(free) // 2]] = np.inf
+    print(f"case row-major infinities M={M} K={K} N={N} G={G} keep={row_keep}", flush=True)
+    p = tw.tw_pack(B, mask, G, tw.PATTERN_TW)
+    C, raw = gu.run_tw_mk(tw, p, A, N)
+    # the same weight packed on the device, and as the second of two joined ones
+    Bd, md = torch.from_numpy(B).cuda(), torch.from_numpy(mask).cuda()
+    q = tw.tw_pack_dev(Bd.data_ptr(), N, md.data_ptr(), 0, K, N, G, tw.PATTERN_TW, torch.cuda.current_stream().cuda_stream)
+    one = tw.tw_pack(np.where(np.isinf(B), np.float16(1), B)[:, :64], mask[:, :64], G, tw.PATTERN_TW)
+    both = tw.tw_concat([one, q])
+    assert np.array_equal(gu.run_tw_mk(tw, q, A, N)[1].view(np.uint16), raw.view(np.uint16))
+    D = gu.run_tw_mk(tw, both, A, N + 64)[0][:, 64:]
+    assert np.array_equal(np.isnan(D), np.isnan(C)) and np.array_equal(np.isinf(D), np.isinf(C))
+    for x in (p, q, one, both):
+        x.free()
+    rows = np.unique(np.r_[0:8, M // 2 - 2:M // 2 + 3, M - 8:M])
+    A, C, kept = A[rows], C[rows], mask != 0
+    with np.errstate(invalid="ignore"):
+        want = np.stack([(A[:, kept[:, n]].astype(np.float64) * B[kept[:, n], n].astype(np.float64)).sum(1) for n in range(N)], 1)
+    inf, nan = np.isinf(want), np.isnan(want)
+    assert inf.sum() > len(rows) * len(cols) // 4
+    assert np.array_equal(np.isnan(C), nan) and np.array_equal(C[inf], want[inf])
+    fin = ~(inf | nan)
+    Af, Bf = np.where(np.isfinite(A), A, 0).astype(np.float16), np.where(np.isfinite(B), B, 0).astype(np.float16)
+    S = og.abs_bound(Af, Bf, mask)
+    assert_C_close(np.where(fin, C, 0), np.where(fin, want, 0), S)
