@@ -197,9 +197,9 @@ tw_status tw_prune_dev_static(const void* B_dev, int K, int N, int ldb, int G, i
  * kernel-facing image are all produced on the device; only the kept-row counts of the tiles visit
  * the host, which lays out offsets, padding and the launch order of the tiles exactly as for
  * tw_pack.  The result is the same handle bit for bit; its lists and logical values are read back
- * to the host only when tw_export, tw_unpack, tw_concat, tw_conv_bind or tw_flop_counts ask for
- * them.  TEW goes through the host
- * packer (the weight and masks are copied to the host).  Allocates device memory and waits
+ * to the host only when tw_export, tw_unpack, tw_concat or tw_conv_bind ask for them (under a lock
+ * of the library; launches and tw_flop_counts on other threads go on meanwhile).  TEW goes through
+ * the host packer (the weight and masks are copied to the host).  Allocates device memory and waits
  * for `stream`: an offline step like tw_pack.  Arguments and errors as tw_pack_host, B with
  * leading dimension ldb >= N; TW_ERR_HIP for a failed runtime call.
  */
@@ -336,8 +336,9 @@ tw_status tw_dense_gemm_i8(const void* A_dev, const void* B_dev, void* C_dev, in
  *
  * tw_conv_bind - bind a geometry to an uploaded TW or TVW handle (fp16 or int8) with
  *   K = C*R*S: *out receives a binding that owns the per-tile kept-row lists as element offsets
- *   on the device (allocates).  The handle is not changed: several bindings (geometries) of one
- *   handle may exist and launch at the same time; the handle must outlive them.  With c = 8
+ *   on the device (allocates; the lists of a device-packed handle are read back to the host the
+ *   first time).  What launches read of the handle is not changed: several bindings (geometries)
+ *   of one handle may exist and launch at the same time; the handle must outlive them.  With c = 8
  *   (fp16) or 16 (int8) elements per 16-byte copy: ldx a multiple of c,
  *   ldx >= roundup_c(B*L*P) + (R-1)*P + S-1 so that the windows of the last positions stay
  *   inside channel rows of ldx elements; C*ldx < 2^31.

@@ -769,11 +769,7 @@ tw_status tw_flop_counts(tw_handle_t h, int64_t* sum_kw, int64_t* sum_k, int64_t
   if (!h) return TW_ERR_ARG;
   if (sum_kw) *sum_kw = h->sum_kw;
   if (sum_k) *sum_k = h->sum_k;
-  if (k_union) {
-    const tw_status sf = twg::fetch_lists(h);          // counted from the lists
-    if (sf != TW_OK) return sf;
-    *k_union = h->k_union;
-  }
+  if (k_union) *k_union = h->k_union;
   return TW_OK;
 }
 

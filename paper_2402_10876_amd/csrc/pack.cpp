@@ -76,22 +76,20 @@ void set_tiles_of_G(tw_handle_s* h) {
   for (int t = 0; t <= h->n_tiles; ++t) h->tile_col_off[t] = std::min(t * h->G, h->n_kept);
 }
 
-// Everything that follows from the index lists alone: offsets (index minus position, Section V),
-// where each tile's values and 2:4 bytes start, the condensed work.
-void finish_lists(tw_handle_s* h) {
+// Offsets (index minus position, Section V) and where each tile's values and 2:4 bytes start, from the index
+// lists.  Writes nothing that a launch or tw_flop_counts reads: a device-packed handle comes here on its
+// first export, which other threads may be launching or counting beside.
+void derive_offsets(tw_handle_s* h) {
   const bool tvw = h->pattern == TW_PATTERN_TVW;
   h->cto_n.resize(h->n_kept);
   for (int j = 0; j < h->n_kept; ++j) h->cto_n[j] = h->col_idx[j] - j;
   h->cto_k.resize(h->row_idx.size());
   h->val_off.assign(h->n_tiles + 1, 0);
   h->meta_off.assign(h->n_tiles + 1, 0);
-  h->sum_kw = 0; h->sum_k = 0;
   for (int t = 0; t < h->n_tiles; ++t) {
     const int k0 = h->tile_k_off[t], kt = h->tile_k_off[t + 1] - k0;
     const int w = h->tile_col_off[t + 1] - h->tile_col_off[t];
     for (int j = 0; j < kt; ++j) h->cto_k[k0 + j] = h->row_idx[k0 + j] - j;
-    h->sum_kw += (int64_t)kt * w;
-    h->sum_k += kt;
     if (!tvw) {
       h->val_off[t + 1] = h->val_off[t] + (int64_t)kt * w;
     } else {
@@ -99,6 +97,17 @@ void finish_lists(tw_handle_s* h) {
       h->val_off[t + 1] = h->val_off[t] + (int64_t)ng * 2 * w;
       h->meta_off[t + 1] = h->meta_off[t] + (int64_t)ng * w;
     }
+  }
+}
+
+// Everything that follows from the index lists alone: the above and the condensed work.
+static void finish_lists(tw_handle_s* h) {
+  derive_offsets(h);
+  h->sum_kw = 0; h->sum_k = 0;
+  for (int t = 0; t < h->n_tiles; ++t) {
+    const int kt = h->tile_k_off[t + 1] - h->tile_k_off[t];
+    h->sum_kw += (int64_t)kt * (h->tile_col_off[t + 1] - h->tile_col_off[t]);
+    h->sum_k += kt;
   }
   std::vector<uint8_t> used(h->K, 0);
   for (int32_t r : h->row_idx) used[r] = 1;

@@ -43,6 +43,7 @@ struct Counts {
   int32_t three;               // a 2:4 group keeps more than two
   int32_t n_kept;
   int32_t nonfinite;           // TW: an infinity or NaN among the packed values
+  int32_t k_union, pad;        // rows that some tile keeps
 };
 
 static __global__ void fill_zero(u32x4* p, size_t n) {
@@ -174,10 +175,22 @@ __global__ void tile_row_any(const uint8_t* S, const uint8_t* element, int K, in
   if (outside) counts->outside = 1;      // racing writers all store 1
 }
 
-// Kept rows of tile blockIdx.x in order, and their number; the first workgroup adds up the entries.
-__global__ __launch_bounds__(SCAN_T) void compact_rows(const uint8_t* row_any, int K, int32_t* row_list, int32_t* k_t,
-                                                       const uint32_t* nnz_part, int n_part, Counts* counts) {
+// Kept rows of tile blockIdx.x in order, and their number; the first workgroup adds up the entries, those past
+// the n_lists tiles count the rows that some tile keeps, SCAN_T of them each.
+__global__ __launch_bounds__(SCAN_T) void compact_rows(const uint8_t* row_any, int n_lists, int K, int32_t* row_list,
+                                                       int32_t* k_t, const uint32_t* nnz_part, int n_part, Counts* counts) {
   __shared__ int part[SCAN_WAVES];
+  if ((int)blockIdx.x >= n_lists) {
+    const int k = ((int)blockIdx.x - n_lists) * SCAN_T + threadIdx.x;
+    const uint8_t* any = row_any + min(k, K - 1);
+    unsigned v = 0;
+#pragma unroll 16
+    for (int t = 0; t < n_lists; ++t) v |= any[(size_t)t * K];
+    int total;
+    count_before(k < K && v != 0, part, &total);
+    if (threadIdx.x == 0) atomicAdd(&counts->k_union, total);
+    return;
+  }
   if (blockIdx.x == 0 && threadIdx.x < 64) {
     unsigned long long sum = 0;
     for (int i = threadIdx.x; i < n_part; i += 64) sum += nnz_part[i];
@@ -372,7 +385,8 @@ tw_status pack_device(const uint16_t* B, int ldb, const uint8_t* mask, const uin
   const uint8_t* element = tvw && tile_mask ? mask : nullptr;
   if (vec) TWG_LAUNCH(tile_row_any<true>, dim3(nx, ny), dim3(T), S, element, K, N, lg, col_pos, row_any, nnz_part, counts);
   else TWG_LAUNCH(tile_row_any<false>, dim3(nx, ny), dim3(T), S, element, K, N, lg, col_pos, row_any, nnz_part, counts);
-  TWG_LAUNCH(compact_rows, dim3((unsigned)ntmax), dim3(SCAN_T), row_any, K, row_list, k_t, nnz_part, (int)(nx * ny), counts);
+  TWG_LAUNCH(compact_rows, dim3((unsigned)(ntmax + (K + SCAN_T - 1) / SCAN_T)), dim3(SCAN_T), row_any, (int)ntmax, K, row_list,
+             k_t, nnz_part, (int)(nx * ny), counts);
 
   // ---- plan: the counts visit the host ----------------------------------------------------
   std::vector<char> head(o_kt + ntmax * 4);
@@ -391,6 +405,7 @@ tw_status pack_device(const uint16_t* B, int ldb, const uint8_t* mask, const uin
     h->sum_kw += (int64_t)kt_h[t] * (h->tile_col_off[t + 1] - h->tile_col_off[t]);
   }
   h->sum_k = h->tile_k_off[n_tiles];
+  h->k_union = c.k_union;
   if (!tvw || tile_mask) {               // tile-wise: the structure mask is the union of its tiles' rows x columns
     if ((int64_t)c.nnz != h->sum_kw) return TW_ERR_MASK;
   }
@@ -448,7 +463,7 @@ static tw_status fetch_lists_locked(tw_handle_s* h) {
   for (int t = 0; t < nt; ++t)
     h->row_idx.insert(h->row_idx.end(), d.row_idx.begin() + d.tile_kp_off[t],
                       d.row_idx.begin() + d.tile_kp_off[t] + (h->tile_k_off[t + 1] - h->tile_k_off[t]));
-  finish_lists(h);
+  derive_offsets(h);
   h->host_lists_ready = true;
   return TW_OK;
 }

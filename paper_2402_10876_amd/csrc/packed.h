@@ -100,7 +100,7 @@ void build_device_values(tw_handle_s* h);
 // From h->col_idx / tile_k_off / row_idx: tiles of G over the kept columns; then offsets,
 // value offsets and the condensed work.
 void set_tiles_of_G(tw_handle_s* h);
-void finish_lists(tw_handle_s* h);
+void derive_offsets(tw_handle_s* h);
 // Device-side packer (pack_dev.hip): fills *h from device buffers, image included (fp16, TW / TVW).
 tw_status pack_device(const uint16_t* B, int ldb, const uint8_t* mask, const uint8_t* tile_mask, int K, int N,
                       int G, int pattern, hipStream_t stream, tw_handle_s* h);

@@ -134,3 +134,47 @@ def test_bert_base_ffn1_device_prune_then_pack_equals_host_pack():
     p_dev = _pack_dev(c.B, c.mask, c.G, tw.PATTERN_TVW, tile_mask=c.tile_mask)
     _same(p_dev.export(), opk.ref_pack(c.B, c.mask, c.G, opk.PATTERN_TVW, tile_mask=c.tile_mask))
     p_dev.free()
+
+
+@pytest.mark.parametrize("pattern", ["tw", "tvw"])
+def test_counts_without_the_lists_and_beside_their_reading(pattern):
+    """tw_flop_counts of a device-packed weight is the host-packed one's before anything has been read back (also
+    in a stream capture, where nothing could be), and while another thread has the lists read back."""
+    import threading
+    import torch
+    rng = np.random.default_rng(3)
+    K, N, G = 2500, 700, 64
+    if pattern == "tw":
+        mask, tmask, pat = random_tw_mask(rng, K, N, G, 0.8, 0.1), None, tw.PATTERN_TW
+    else:
+        mask, tmask = random_tvw_mask(rng, K, N, G, 0.8, 0.1)
+        pat = tw.PATTERN_TVW
+    B = wl.rng_fp16(3, (K, N))
+    h = tw.tw_pack_host(B, mask, G, pat, tile_mask=tmask)
+    want = h.flop_counts()
+    h.free()
+    assert 0 < want[2] < K
+    p = _pack_dev(B, mask, G, pat, tmask)
+    x = torch.zeros(8, device="cuda")
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        x += 1
+        assert p.flop_counts() == want
+    g.replay()
+    torch.cuda.synchronize()
+    assert float(x[0]) == 1.0
+    p.free()
+    for _ in range(10):
+        p = _pack_dev(B, mask, G, pat, tmask)
+        seen, stop = [], threading.Event()
+
+        def count():
+            while not stop.is_set():
+                seen.append(p.flop_counts())
+        th = threading.Thread(target=count)
+        th.start()
+        p.export()
+        stop.set()
+        th.join()
+        assert all(s == want for s in seen) and p.flop_counts() == want
+        p.free()

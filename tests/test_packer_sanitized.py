@@ -70,3 +70,35 @@ def test_packer_round_trip_under_asan_ubsan(tmp_path):
     r = subprocess.run([str(exe)], capture_output=True, text=True, env=env, timeout=120)
     assert r.returncode == 0, (r.stdout + r.stderr)[-2000:]
     assert "fails=0" in r.stdout
+
+
+SUMS_DRIVER = r"""
+#include <cstdio>
+#include <vector>
+#include "packed.h"
+int main() {
+  const int K = 100, N = 300;
+  std::vector<uint16_t> B((size_t)K * N, 0x3c00);
+  std::vector<uint8_t> mask((size_t)K * N, 1);
+  tw_handle_s h;
+  if (twg::pack_host(B.data(), mask.data(), nullptr, K, N, 128, TW_PATTERN_TW, &h) != TW_OK) return 2;
+  h.cto_n.clear(); h.cto_k.clear(); h.val_off.clear(); h.meta_off.clear();
+  h.sum_kw = -1; h.sum_k = -2; h.k_union = -3; h.max_kp = -4; h.nonfinite = true;      // (what other threads may be reading)
+  twg::derive_offsets(&h);
+  const bool made = h.cto_n.size() == (size_t)N && h.cto_k.size() == 300 && h.val_off[3] == (int64_t)K * N;
+  return made && h.sum_kw == -1 && h.sum_k == -2 && h.k_union == -3 && h.max_kp == -4 && h.nonfinite ? 0 : 1;
+}
+"""
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="g++ not available")
+def test_reading_the_lists_back_leaves_the_sums_alone(tmp_path):
+    """The lists of a device-packed handle are completed on first use, under a lock that launches and
+    tw_flop_counts do not take: the step may not write what those read."""
+    src, exe = tmp_path / "driver.cpp", tmp_path / "driver"
+    src.write_text(SUMS_DRIVER)
+    csrc = os.path.join(ROOT, "paper_2402_10876_amd", "csrc")
+    r = subprocess.run(["g++", "-std=c++17", "-O1", "-I", csrc, "-I", os.path.join(ROOT, "include"), str(src),
+                        os.path.join(csrc, "pack.cpp"), "-o", str(exe)], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-2000:]
+    assert subprocess.run([str(exe)], timeout=60).returncode == 0
