@@ -25,6 +25,7 @@
 #include <new>
 #include <vector>
 
+#include "mk_band.h"
 #include "packed.h"
 #include "scan.h"
 
@@ -42,7 +43,7 @@ struct Counts {
   int32_t outside;             // an element is kept outside the tile mask
   int32_t three;               // a 2:4 group keeps more than two
   int32_t n_kept;
-  int32_t nonfinite;           // TW: an infinity or NaN among the packed values
+  int32_t nonfinite;           // an infinity or NaN among the weights
   int32_t k_union, pad;        // rows that some tile keeps
 };
 
@@ -115,16 +116,33 @@ __global__ __launch_bounds__(SCAN_T) void compact_columns(const uint8_t* any, in
   if (threadIdx.x == 0) counts->n_kept = base;
 }
 
-// row_any[t][k] (bytes, zero on entry) = 1 if row k has an entry among the columns of tile t; counts
-// the entries of S, and (element != null) notes an entry of `element` that S lacks.  16 columns per
-// thread, which belong to two tiles at most.
+// An infinity or NaN among the 16 weights of row k from column n0 on whose mask bytes are set (columns past N:
+// not set).
 template <bool VEC>
-__global__ void tile_row_any(const uint8_t* S, const uint8_t* element, int K, int N, int lg, const int32_t* col_pos,
-                             uint8_t* row_any, uint32_t* nnz_part, Counts* counts) {
+__device__ __forceinline__ bool any_nonfinite(const uint16_t* B, int ldb, int vec_b, int k, int n0, int N, const u32x4& mask) {
+  union { u32x4 v[2]; uint16_t e[16]; } x;
+  const uint16_t* p = B + (size_t)k * ldb + n0;
+  if (VEC && vec_b) { x.v[0] = *(const u32x4*)p; x.v[1] = *(const u32x4*)(p + 8); }
+  else {
+#pragma unroll
+    for (int c = 0; c < 16; ++c) x.e[c] = p[min(c, N - 1 - n0)];
+  }
+  bool r = false;
+#pragma unroll
+  for (int c = 0; c < 16; ++c) r |= (x.e[c] & 0x7c00) == 0x7c00 && (mask[c >> 2] >> (8 * (c & 3)) & 1u);
+  return r;
+}
+
+// row_any[t][k] (bytes, zero on entry) = 1 if row k has an entry among the columns of tile t; counts
+// the entries of S, (element != null) notes an entry of `element` that S lacks and (B != null) an infinity
+// or NaN among the weights of S.  16 columns per thread, which belong to two tiles at most.
+template <bool VEC>
+__global__ void tile_row_any(const uint8_t* S, const uint8_t* element, const uint16_t* B, int ldb, int vec_b, int K, int N, int lg,
+                             const int32_t* col_pos, uint8_t* row_any, uint32_t* nnz_part, Counts* counts) {
   __shared__ int wave_sum[T / 64];
   const int n0 = (blockIdx.x * blockDim.x + threadIdx.x) * 16;
   int mine = 0;
-  bool outside = false;
+  bool outside = false, nonfinite = false;
   if (n0 < N) {
     int tile = -1;                       // the first tile; the other is the next one
     u32x4 first = {0u, 0u, 0u, 0u};      // bytes of its columns
@@ -164,6 +182,7 @@ __global__ void tile_row_any(const uint8_t* S, const uint8_t* element, int K, in
           const u32x4 o = e[i] & ~v[i];
           outside |= (o[0] | o[1] | o[2] | o[3]) != 0;
         }
+        if (B) nonfinite |= any_nonfinite<VEC>(B, ldb, vec_b, k, n0, N, v[i]);
       }
     }
   }
@@ -173,6 +192,7 @@ __global__ void tile_row_any(const uint8_t* S, const uint8_t* element, int K, in
   __syncthreads();
   if (threadIdx.x == 0) nnz_part[blockIdx.y * gridDim.x + blockIdx.x] = wave_sum[0] + wave_sum[1] + wave_sum[2] + wave_sum[3];
   if (outside) counts->outside = 1;      // racing writers all store 1
+  if (nonfinite) counts->nonfinite = 1;
 }
 
 // Kept rows of tile blockIdx.x in order, and their number; the first workgroup adds up the entries, those past
@@ -239,8 +259,7 @@ __global__ void image_lists(Structure st, int G, const int32_t* tile_kp_off, int
 
 // TW values (layout: see the host packer's build_device_values): 8 rows of a column per thread, one
 // 16-byte store; blockIdx.y == n_tiles: the slack behind the last tile.
-__global__ void image_tw(const uint16_t* B, int ldb, Structure st, int G, const int32_t* tile_kp_off, uint16_t* vals,
-                         Counts* counts) {
+__global__ void image_tw(const uint16_t* B, int ldb, Structure st, int G, const int32_t* tile_kp_off, uint16_t* vals) {
   const int t = blockIdx.y, i = blockIdx.x * blockDim.x + threadIdx.x;
   const int kp0 = tile_kp_off[t];
   u32x4* out = (u32x4*)(vals + (size_t)kp0 * G);
@@ -257,14 +276,11 @@ __global__ void image_tw(const uint16_t* B, int ldb, Structure st, int G, const 
   x.v = u32x4{0u, 0u, 0u, 0u};
   if (t * G + c < st.n_kept && j0 < kt) {
     const int n = st.kept[t * G + c];
-    bool nonfinite = false;
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
       const uint16_t v = B[(size_t)rows[min(j0 + j, kt - 1)] * ldb + n];
       x.e[j] = j0 + j < kt ? v : (uint16_t)0;
-      nonfinite |= (v & 0x7c00) == 0x7c00;
     }
-    if (nonfinite) counts->nonfinite = 1;              // racing writers all store 1
   }
   out[j0 / 16 * (2 * G) + (c / 32) * 64 + ((j0 % 16) / 8) * 32 + c % 32] = x.v;
 }
@@ -383,8 +399,11 @@ tw_status pack_device(const uint16_t* B, int ldb, const uint8_t* mask, const uin
   else TWG_LAUNCH(column_any<false>, any_grid, dim3(64, 4), S, K, N, col_any);
   TWG_LAUNCH(compact_columns, dim3(1), dim3(SCAN_T), col_any, N, col_pos, kept, dropped, counts);
   const uint8_t* element = tvw && tile_mask ? mask : nullptr;
-  if (vec) TWG_LAUNCH(tile_row_any<true>, dim3(nx, ny), dim3(T), S, element, K, N, lg, col_pos, row_any, nnz_part, counts);
-  else TWG_LAUNCH(tile_row_any<false>, dim3(nx, ny), dim3(T), S, element, K, N, lg, col_pos, row_any, nnz_part, counts);
+  // only the row-major kernel asks whether all weights are finite, of TW weights and where K takes several bands
+  const uint16_t* finite = !tvw && K > MK_KC ? B : nullptr;
+  const int vec_b = ldb % 8 == 0 && ((uintptr_t)B & 15) == 0;
+  if (vec) TWG_LAUNCH(tile_row_any<true>, dim3(nx, ny), dim3(T), S, element, finite, ldb, vec_b, K, N, lg, col_pos, row_any, nnz_part, counts);
+  else TWG_LAUNCH(tile_row_any<false>, dim3(nx, ny), dim3(T), S, element, finite, ldb, vec_b, K, N, lg, col_pos, row_any, nnz_part, counts);
   TWG_LAUNCH(compact_rows, dim3((unsigned)(ntmax + (K + SCAN_T - 1) / SCAN_T)), dim3(SCAN_T), row_any, (int)ntmax, K, row_list,
              k_t, nnz_part, (int)(nx * ny), counts);
 
@@ -406,6 +425,7 @@ tw_status pack_device(const uint16_t* B, int ldb, const uint8_t* mask, const uin
   }
   h->sum_k = h->tile_k_off[n_tiles];
   h->k_union = c.k_union;
+  h->nonfinite = c.nonfinite != 0;
   if (!tvw || tile_mask) {               // tile-wise: the structure mask is the union of its tiles' rows x columns
     if ((int64_t)c.nnz != h->sum_kw) return TW_ERR_MASK;
   }
@@ -432,14 +452,15 @@ tw_status pack_device(const uint16_t* B, int ldb, const uint8_t* mask, const uin
              (int32_t*)d.d_col_idx, (int32_t*)d.d_zero_cols);
   if (!tvw) {
     const int most = std::max(h->max_kp / 8 * G, KSTEP_TW * G / 8);
-    TWG_LAUNCH(image_tw, dim3((most + T - 1) / T, n_tiles + 1), dim3(T), B, ldb, st, G, d.d_tile_kp_off, (uint16_t*)d.d_vals, counts);
-  } else if (n_tiles > 0 && h->max_kp > 0) {
+    TWG_LAUNCH(image_tw, dim3((most + T - 1) / T, n_tiles + 1), dim3(T), B, ldb, st, G, d.d_tile_kp_off, (uint16_t*)d.d_vals);
+    TWG_TRY(hipStreamSynchronize(s));    // the workspace goes away when this returns
+    return TW_OK;
+  }
+  if (n_tiles > 0 && h->max_kp > 0)
     TWG_LAUNCH(image_tvw, dim3((h->max_kp / 32 * G * 2 + T - 1) / T, n_tiles), dim3(T), B, ldb, mask, N, st, G,
                d.d_tile_kp_off, (uint16_t*)d.d_vals, (uint16_t*)d.d_meta, (uint8_t*)d.d_valid, counts);
-  }
-  Counts after;                          // (waits for the stream: the workspace goes away when this returns)
+  Counts after;
   TWG_TRY(hipMemcpyWithStream(&after, counts, sizeof after, hipMemcpyDeviceToHost, s));
-  h->nonfinite = after.nonfinite != 0;
   return after.three ? TW_ERR_MASK : TW_OK;
 } catch (const std::bad_alloc&) {
   return TW_ERR_ALLOC;
