@@ -1,5 +1,5 @@
 """Binding with the same names as the C ABI (ctypes; the launch calls through a small CPython module
-over the same library).  Argument marshalling only:
+over the same library, where that has been built).  Argument marshalling only:
 every step of the path runs inside libtwgemm.so.  The library is loaded from
 the package directory and is never built here; a missing library is an error
 (there is no fallback path)."""
@@ -9,6 +9,7 @@ import ctypes as C
 import importlib.machinery
 import importlib.util
 import os
+import sysconfig
 
 import numpy as np
 
@@ -28,7 +29,7 @@ _lib = None
 
 
 class _Unbound:
-    """Launch calls before the library is loaded: the ctypes route, which loads it."""
+    """Launch calls before the library is loaded, or without the module: the ctypes route, which loads it."""
 
     @staticmethod
     def gemm(*_):
@@ -42,15 +43,14 @@ _call = _Unbound     # the launch calls as a CPython module; None for arguments 
 
 def _bind_call(L):
     global _call
-    p = os.path.join(os.path.dirname(os.path.abspath(__file__)), "_twcall.so")
-    if not os.path.exists(p):
-        raise ImportError(f"{p} is missing: build it first (python -c 'import __graft_entry__ as g; g.build()')")
+    p = os.path.join(os.path.dirname(os.path.abspath(__file__)), "_twcall" + (sysconfig.get_config_var("EXT_SUFFIX") or ".so"))
+    if not os.path.exists(p):        # no module for this interpreter (another library in a tree not built, no headers)
+        return
     loader = importlib.machinery.ExtensionFileLoader("_twcall", p)
     m = importlib.util.module_from_spec(importlib.util.spec_from_file_location("_twcall", p, loader=loader))
     loader.exec_module(m)
     m.bind(*(C.cast(f, C.c_void_p).value for f in (L.tw_gemm, L.tw_gemm_i8, L.tw_conv_gemm, L.tw_conv_gemm_i8)))
     _call = m
-
 
 
 class TwError(RuntimeError):

@@ -11,13 +11,16 @@ import hashlib
 import os
 import subprocess
 import sysconfig
+import warnings
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 LIB = os.path.join(PKG, "libtwgemm.so")
 HASH_FILE = LIB + ".srchash"
 SOURCES = ["api.cpp", "pack.cpp", "gemm_kernels.hip", "gemm_dma.hip", "gemm_mk.hip", "gemm_small.hip", "gemm_tvw.hip", "gemm_i8.hip", "gemm_tvw_i8.hip", "prune.hip", "pack_dev.hip", "calibrate.hip"]
-CALL = os.path.join(PKG, "_twcall.so")       # the launch calls as a CPython module (csrc/pycall.cpp)
+# the launch calls as a CPython module (csrc/pycall.cpp), for this interpreter (its tag is in the name); optional:
+# without it the binding makes these calls through ctypes
+CALL = os.path.join(PKG, "_twcall" + (sysconfig.get_config_var("EXT_SUFFIX") or ".so"))
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 # packed-fp32 instruction selection is switched off for all device code
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
@@ -45,12 +48,21 @@ def built_hash() -> str | None:
         return f.read().strip()
 
 
-def build_call() -> str:
+def build_call() -> str | None:
+    """Path of the module, or None (with a warning) where it cannot be compiled: no host compiler, no Python
+    headers.  Never leaves a module of older sources behind."""
     cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-I" + sysconfig.get_paths()["include"],
            os.path.join(PKG, "csrc", "pycall.cpp"), "-o", CALL + ".tmp"]
-    r = subprocess.run(cmd, capture_output=True, text=True)
-    if r.returncode != 0:
-        raise RuntimeError("host compiler failed:\n" + " ".join(cmd) + "\n" + r.stdout + r.stderr)
+    try:
+        r = subprocess.run(cmd, capture_output=True, text=True)
+        error = None if r.returncode == 0 else r.stdout + r.stderr
+    except OSError as e:
+        error = str(e)
+    if error is not None:
+        if os.path.exists(CALL):
+            os.remove(CALL)
+        warnings.warn("launch calls go through ctypes, their module was not built:\n" + " ".join(cmd) + "\n" + error)
+        return None
     os.replace(CALL + ".tmp", CALL)
     return CALL
 
@@ -77,9 +89,11 @@ def ensure_built() -> str:
     library is missing).  A library named by TWGEMM_LIB is the caller's responsibility."""
     if os.environ.get("TWGEMM_LIB"):
         return os.environ["TWGEMM_LIB"]
-    if built_hash() == source_hash() and os.path.exists(CALL):
-        return LIB
-    return build()
+    if built_hash() != source_hash():
+        return build()
+    if not os.path.exists(CALL):
+        build_call()
+    return LIB
 
 
 def describe() -> str:
