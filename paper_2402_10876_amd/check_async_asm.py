@@ -14,6 +14,9 @@ for a `global_load` until the next `s_waitcnt vmcnt(..)` in an inline-assembly b
 (the kernels place these loads so that this wait covers them; the compiler's own
 waits count other loads);
 any instruction that names a pending register before that wait is reported.
+The vector loads are also followed along every branch, up to the first wait for them on each
+path: there the compiler's own instructions are reported (whether a path can reach one of
+the kernels' own uses without a wait depends on the conditions of its branches).
 
     python -m paper_2402_10876_amd.check_async_asm          # exit status 1 on a finding
 """
@@ -100,6 +103,46 @@ def check_assembly(asm_text: str):
     return findings
 
 
+def check_branches(asm_text: str):
+    """Findings as check_assembly's, for inline-assembly global loads along the branches of a kernel."""
+    code, labels, kernel, in_app = [], {}, None, False
+    for ln, raw in enumerate(asm_text.split("\n"), 1):
+        line = raw.strip()
+        if line.startswith(";;#ASM"):
+            in_app = line.startswith(";;#ASMSTART")
+            continue
+        text = line.split(";")[0].strip()
+        if text.endswith(":"):
+            labels[text[:-1]] = len(code)
+            if not text.startswith("."):
+                kernel = text[:-1]
+        elif text and not text.startswith("."):
+            op, _, args = text.partition(" ")
+            code.append((kernel, ln, op, args.strip(), in_app, text))
+    findings = []
+    for i, (kernel, _, op, args, app, _) in enumerate(code):
+        if not (app and _ASYNC_VM.match(op)):
+            continue
+        regs, seen, todo = _regs(args.partition(",")[0]), set(), [i + 1]
+        while todo:
+            j = todo.pop()
+            while j < len(code) and j not in seen:
+                seen.add(j)
+                _, ln, op, args, app, text = code[j]
+                if op == "s_endpgm" or (app and op == "s_waitcnt" and "vmcnt" in args):
+                    break
+                if op == "s_branch":
+                    j = labels[args]
+                    continue
+                if op.startswith("s_cbranch"):
+                    todo.append(labels[args])
+                elif not app and _regs(args) & regs:
+                    findings.append((kernel, ln, text, sorted(_regs(args) & regs)))
+                    break
+                j += 1
+    return findings
+
+
 def compile_to_asm(src: str) -> str:
     with tempfile.TemporaryDirectory() as td:
         out = os.path.join(td, "k.s")
@@ -115,7 +158,7 @@ def check_sources(sources=KERNEL_SOURCES):
         texts = list(ex.map(compile_to_asm, sources))
     res = []
     for src, text in zip(sources, texts):
-        res += [(src,) + f for f in check_assembly(text)]
+        res += [(src,) + f for f in check_assembly(text) + check_branches(text)]
     return res
 
 

@@ -582,14 +582,16 @@ void tw_gemm_km_dma_kernel(GemmArgs g_arg) {
       share_quad(q0, r0);
       share_quad(q1, r1);
       issue(0, r0);
-      fetch_quad(ns > 3 ? 3 : 0, odd);
-      if (ns > 1) issue(1, r1);
+      if (ns > 1) {                        // (a single stage has no use for them: nothing may be under way then)
+        fetch_quad(ns > 3 ? 3 : 0, odd);
+        issue(1, r1);
+      }
       int s = 0;
       for (; s + 1 < ns; s += 2) {
         iteration(s, even, std::false_type{});
         iteration(s + 1, odd, std::false_type{});
       }
-      wait_vm<NPS>();                    // (no row fetch is under way past this point; nothing is waited for)
+      wait_vm<0>();                      // (nothing is under way, or the copies of the last stage, needed next)
       if (s < ns) iteration(s, even, std::true_type{});
     }
     wait_vm<0>();                        // (nothing is outstanding: every copy has been waited for)

@@ -39,6 +39,37 @@ _Z1kv:
 """
 
 
+# a single stage skips the wait of the loop: its accumulators may take the register of a row on its way
+BAD_SKIP = """
+_Z1kv:
+	;;#ASMSTART
+	global_load_dword v136, v134, s[4:5]
+	;;#ASMEND
+	s_cmp_lt_u32 s14, 2
+	s_cbranch_scc1 .LBB0_2
+	;;#ASMSTART
+	s_waitcnt vmcnt(8)
+	;;#ASMEND
+	;;#ASMSTART
+	v_mov_b32_dpp v119, v136 quad_perm:[0,0,0,0] row_mask:0xf bank_mask:0xf
+	;;#ASMEND
+	s_branch .LBB0_3
+.LBB0_2:
+	v_mov_b32_e32 v136, 0
+.LBB0_3:
+	;;#ASMSTART
+	s_waitcnt vmcnt(0)
+	;;#ASMEND
+	s_endpgm
+"""
+
+
+def test_scanner_follows_the_vector_loads_along_branches():
+    f = chk.check_branches(BAD_SKIP)
+    assert len(f) == 1 and f[0][0] == "_Z1kv" and "v136, 0" in f[0][2]
+    assert chk.check_branches(BAD_SKIP.replace("v_mov_b32_e32 v136", "v_mov_b32_e32 v137")) == []
+
+
 def test_scanner_flags_a_use_before_the_wait_and_nothing_else():
     f = chk.check_assembly(BAD)
     assert len(f) == 1 and f[0][0] == "_Z1kv" and "v76, v35" in f[0][2]
