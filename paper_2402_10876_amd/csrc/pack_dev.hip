@@ -378,6 +378,7 @@ tw_status pack_device(const uint16_t* B, int ldb, const uint8_t* mask, const uin
   (void)hipGetLastError();
 
   // ---- structure: kept columns, kept rows per tile --------------------------------------
+  std::vector<char> tables;              // (copied asynchronously: outlives the workspace, whose release waits for the device)
   DevBuf ws;
   const size_t o_kt = up(sizeof(Counts)), o_any = o_kt + up(ntmax * 4), o_rany = o_any + up((size_t)N + 16);
   const size_t zeroed = o_rany + up(ntmax * K), o_pos = zeroed, o_kept = o_pos + up((size_t)N * 4);
@@ -441,7 +442,7 @@ tw_status pack_device(const uint16_t* B, int ldb, const uint8_t* mask, const uin
   twg::DeviceImage& d = h->img;
 
   // ---- image: the host's tables, then the lists and values --------------------------------------
-  std::vector<char> tables(L.off[IMG_COL_IDX]);
+  tables.resize(L.off[IMG_COL_IDX]);
   std::copy_n((const char*)d.tile_kp_off.data(), L.bytes[IMG_TILE_KP_OFF], tables.data() + L.off[IMG_TILE_KP_OFF]);
   std::copy_n((const char*)d.tile_order.data(), L.bytes[IMG_TILE_ORDER], tables.data() + L.off[IMG_TILE_ORDER]);
   std::copy_n((const char*)d.tile_sched.data(), L.bytes[IMG_TILE_SCHED], tables.data() + L.off[IMG_TILE_SCHED]);
