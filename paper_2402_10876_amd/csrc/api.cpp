@@ -21,7 +21,7 @@ std::atomic<int> opt_waves{4};
 std::atomic<int> opt_ksplit{0};   // 0 = automatic, 1 = off, 2 = two K groups per workgroup
 std::atomic<int> opt_wg_split{0}; // 0 / 1 = off, 2..8 = workgroups per tile (needs a workspace)
 std::atomic<int> opt_tiles_per_wg{0};  // 0 = automatic, 1..8 = tiles a workgroup computes one after the other
-std::atomic<int> opt_idx_route{0};// kept-row lists: 0 = automatic, 1 = scalar loads, 2 = through LDS
+std::atomic<int> opt_idx_route{0};// kept-row lists: 0 = automatic, 1 = scalar loads, 2 = vector loads
 
 // What one launch runs with: the caller's tw_launch_opts, or the process defaults above
 // (tw_set_option) when there is none.  Read once per call, never shared between calls.
@@ -75,8 +75,9 @@ bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 
 // they are bound by the L2 -> LDS traffic, which is (tm + G) / (tm G) per product
 // (measured on the 3 x 3 convolution 256 -> 256 at 56 x 56: 17.0 against 21.7 us).
 // 256-row tiles of G = 128 (8 waves) need kept-row lists of at least 384 rows: with shorter
-// ones they lose 3-6 % to 128-row tiles (1024 x 4096 at M = 8192 from HBM: 23.5 against 22.2 us
-// at 87.5 %), with longer ones they win 10-25 % (44.5 against 49.1 us at 50 %).  `dense`: the
+// ones they lose 1-6 % to 128-row tiles (1024 x 4096 at M = 8192: 30.5 against 29.5 us at 75 %, 768 x
+// 4096 at 60 % 34.1 against 32.1), with longer ones they win (1024 x 4096: 43.9 against 46.5 us at 50 %)
+// or, on lists of 430 to 550 rows, come within 8 % either way (768 x 4096 at 50 % 37.2 against 36.0).  `dense`: the
 // dense kernel has no gather to hide and takes 256 rows from one workgroup per CU on when
 // K >= 1024 (2304 x 256 at M = 25088: 41.3 against 48.5 us), 128 rows for shorter K
 // (768 x 3072 at M = 4096: 23.8 against 25.5 us).
@@ -92,9 +93,9 @@ int pick_tile_m(const Opts& o, int M, int n_tiles, int G, int max_k, bool dense 
     if (need == 512 && (tm == 128 || (tm == 256 && G == 64))) need = 384;
     if (tm == 256 && G == 128 && max_k < 384) continue;
     if (tm == 256 && dense) need = max_k >= 1024 ? 192 : 512;
-    // one 256-row workgroup per CU with its kept-row lists through LDS: 3-9 % ahead of two
-    // 128-row ones when the lists are long (4096 x 1024 at M = 8192: 46.9 against 49.5 us at
-    // 50 %, 28.7 against 29.7 at 75 %; 2304 x 256 at M = 25088: 17.5 against 19.3 us)
+    // one 256-row workgroup per CU: 10-20 % ahead of two 128-row ones when the lists are long
+    // (4096 x 1024 at M = 8192: 40.0 against 48.0 us at 50 %, 24.4 against 27.6 at 75 %; 2304 x 256 at
+    // M = 25088 and 60 %: 18.7 against 23.0; 3072 x 768 at M = 8192, 192 workgroups: 28.3 against 32.9)
     if (tm == 256 && G == 128 && !dense && max_k >= 640) need = 192;
     const long wgs = (long)((M + tm - 1) / tm) * n_tiles;
     if (wgs >= need) return tm;
@@ -124,17 +125,20 @@ int pick_tile_m_tvw(const Opts& o, int G, int M, int n_tiles, int max_k) {
 }
 
 // Kept-row indices by scalar loads instead of one vector load per stage (4-wave workgroups, three
-// stages in flight).  128 x 128 tiles, more than 384 and at most 720
-// workgroups, same buffers, vector against scalar: 768 x 2304 at M = 4096 9.5 / 9.0 us at 75 %,
-// 16.3 / 13.6 at 50 %; 1024 x 1024 at M = 8192 11.4 / 10.4; 768 x 3072 at M = 3000 11.9 / 10.0, at 4096
-// 10.1 / 9.8; 1500 x 3000 at 80 % 15.5 / 14.6.  With more the vector load wins (768 x 2304 at M = 7000
-// 16.8 / 19.9, 8192 19.5 / 20.6), with fewer too (2048 x 768 x 3072 at 60 % 8.5 / 9.3).  256 x 64 tiles
-// only on convolutions with long lists, whose misaligned rows keep the copy unit busy (256 -> 256 at
-// 56 x 56, batch 8: 16.7 / 16.1; a plain 1024 x 2048 at 60 % 12.6 / 14.0).
+// stages in flight).  128 x 128 tiles, where more than two and nearly up to three workgroups share a CU: their
+// waves hide the scalar loads' round trip, and the vector load, one more request to the copy unit per
+// stage, is not hidden.  Time by scalar over time by vector loads, same buffers, grids of 6 to 29 column tiles
+// and 400 to 2000 rows: 384 to 512 workgroups 0.96 .. 1.16 (768 rows: 1.05 at 75 %, 1.13 at 50 %, 0.99 at 90 %),
+// 513 to 704 0.87 .. 1.03 (0.92, 0.95, 0.99), 720 to 736 0.93 .. 1.04 (0.98, 0.97, 0.99), 748 to 768 0.91 .. 1.03 (1.02,
+// 0.98, 0.99), more 1.01 .. 1.13 (1.05).  768 x 2304 at M = 4096, 75 %, 576 workgroups: 10.2 / 12.2 us.
+// 256 x 64 tiles only on convolutions with long lists, whose misaligned rows keep the copy unit busy:
+// nine of them 0 to 3.5 % (256 -> 256 at 56 x 56, batch 8, 16.9 / 17.5; 256 -> 512 at 28 x 28, batch 16, 16.8 / 17.3;
+// 128 -> 128 at 56 x 56 and 50 % 16.6 / 17.2); short lists are even (64 -> 256 at 80 x 80 14.6 / 14.5), and a plain
+// 1024 x 2048 at 60 % loses (14.0 / 12.6).
 bool scalar_rows(const Opts& o, int M, int n_tiles, int G, int tm, int max_k, bool conv) {
   if (o.idx_route) return o.idx_route == 1;
   const long wgs = (long)((M + tm - 1) / tm) * n_tiles;
-  if (G == 128 && tm == 128) return wgs > 384 && wgs <= 720;
+  if (G == 128 && tm == 128) return wgs > 512 && wgs <= 736;
   return conv && G == 64 && tm == 256 && wgs > 384 && max_k > 256;
 }
 
@@ -401,7 +405,8 @@ static tw_status gemm_launch(const Opts& o, const void* A, int M, int lda, int l
   // the asynchronous kernel addresses A with 32-bit byte offsets
   const bool a_fits32 = conv || (unsigned long long)h->K * (unsigned long long)lda * 2ull < (1ull << 32);
   // Few output blocks.  A weight with nothing pruned adds up in the order of the dense baseline (same
-  // bits), and a TEW weight without restored elements in the order of its TW twin.
+  // bits), and a TEW weight without restored elements in the order of its TW twin.  (sum_kw counts a TVW
+  // weight before its 2:4 step, so one that keeps every row and column stays with the pipelined kernel too.)
   const bool plain = h->pattern != TW_PATTERN_TEW || (h->img.ew_pairs.empty() && h->G != 32 && a_fits32);
   if (plain && automatic(o) && h->sum_kw < (int64_t)h->K * h->N &&
       twg::small_km_pays(h->G, h->pattern == TW_PATTERN_TVW, M, h->n_tiles, h->max_kp)) {

@@ -142,7 +142,8 @@ __global__ __launch_bounds__(NW * 64) void tvw_gemm_km_kernel(GemmArgs g) {
   // quad (whose lanes copy from the same row) loads the index for copy instruction j and the quad shares
   // it.  Else scalar loads, whose round trip sits in every iteration.  Same buffers, scalar / vector: 8192 x
   // 4096 x 1024 at 75 % 35.9 / 33.3 us, 1200 x 3000 x 2000 18.1 / 16.0, 2048 x 2048 x 2048 of G = 64 at 80 %
-  // 12.6 / 11.2, 768 x 3072 at M = 4096 and 87.5 % 10.5 / 10.4 (3072 x 768 11.5 / 11.8).
+  // 12.6 / 11.2, at M = 4096 and 87.5 % 768 x 3072 10.6 / 10.4, 3072 x 768 10.9 / 10.2, 768 x 768 5.3 / 5.2; one of
+  // nineteen launches slower (7448 x 2496 x 1280 at 79 % 32.2 / 32.9).
   struct Rows { std::conditional_t<VEC, int, sidx_t> r[NIA]; };
   static_assert(!VEC || D == 3, "a deeper pipeline would wait for its index loads");
   auto fetch_rows = [&](int s, Rows& dst) {
