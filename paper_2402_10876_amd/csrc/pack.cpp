@@ -11,6 +11,7 @@
 #include <cstring>
 #include <new>
 
+#include "mk_band.h"
 #include "packed.h"
 
 namespace twg {
@@ -74,6 +75,18 @@ void set_tiles_of_G(tw_handle_s* h) {
   h->n_tiles = (int32_t)h->tile_k_off.size() - 1;
   h->tile_col_off.resize(h->n_tiles + 1);
   for (int t = 0; t <= h->n_tiles; ++t) h->tile_col_off[t] = std::min(t * h->G, h->n_kept);
+}
+
+// An infinity or NaN among fp16 values, four at a time: an exponent of ones carries into the sign's bit.
+static bool any_nonfinite(const std::vector<uint16_t>& values) {
+  uint64_t bad = 0;
+  size_t i = 0;
+  for (uint64_t x; i + 4 <= values.size(); i += 4) {
+    std::memcpy(&x, values.data() + i, 8);
+    bad |= (x & 0x7c007c007c007c00ull) + 0x0400040004000400ull;
+  }
+  for (; i < values.size(); ++i) bad |= (values[i] & 0x7c00u) + 0x0400u;
+  return (bad & 0x8000800080008000ull) != 0;
 }
 
 // Offsets (index minus position, Section V) and where each tile's values and 2:4 bytes start, from the index
@@ -155,6 +168,7 @@ tw_status pack_host(const uint16_t* B, const uint8_t* mask, const uint8_t* tile_
         for (int c = 0; c < w; ++c) v[(size_t)j * w + c] = brow[cols[c]];
       }
     }
+    h->nonfinite = h->dtype == TW_DTYPE_F16 && K > MK_KC && any_nonfinite(h->values);
   } else {
     h->meta.assign((size_t)h->meta_off[h->n_tiles], 0);
     h->valid.assign((size_t)h->meta_off[h->n_tiles], 0);
@@ -246,7 +260,7 @@ tw_status unpack_host(const tw_handle_s* h, uint16_t* Bm, uint8_t* mask) {
 tw_status concat_host(const tw_handle_s* const* parts, int n, tw_handle_s* h) try {
   const tw_handle_s* p0 = parts[0];
   h->K = p0->K; h->G = p0->G; h->pattern = p0->pattern; h->dtype = p0->dtype;
-  h->N = 0; h->n_kept = 0; h->n_tiles = 0; h->sum_kw = 0; h->sum_k = 0;
+  h->N = 0; h->n_kept = 0; h->n_tiles = 0; h->sum_kw = 0; h->sum_k = 0; h->nonfinite = false;
   h->tile_col_off.assign(1, 0); h->tile_k_off.assign(1, 0);
   h->val_off.assign(1, 0); h->meta_off.assign(1, 0);
   if (h->pattern == TW_PATTERN_TEW) h->ew_col_ptr.assign(1, 0);
@@ -272,7 +286,7 @@ tw_status concat_host(const tw_handle_s* const* parts, int n, tw_handle_s* h) tr
       h->ew_val.insert(h->ew_val.end(), p->ew_val.begin(), p->ew_val.end());
     }
     h->N += p->N; h->n_kept += p->n_kept; h->n_tiles += p->n_tiles;
-    h->sum_kw += p->sum_kw; h->sum_k += p->sum_k;
+    h->sum_kw += p->sum_kw; h->sum_k += p->sum_k; h->nonfinite |= p->nonfinite;
   }
   h->cto_n.resize(h->n_kept);
   for (int j = 0; j < h->n_kept; ++j) h->cto_n[j] = h->col_idx[j] - j;
@@ -494,7 +508,6 @@ void build_device_values(tw_handle_s* h) {
     return;
   }
   if (!tvw) {
-    h->nonfinite = std::any_of(h->values.begin(), h->values.end(), [](uint16_t v) { return (v & 0x7c00) == 0x7c00; });
     d.vals.assign(((size_t)d.tile_kp_off[nt] + KSTEP_TW) * G, 0);
     for (int t = 0; t < nt; ++t) {
       const int kt = h->tile_k_off[t + 1] - h->tile_k_off[t];

@@ -75,7 +75,7 @@ struct tw_handle_s {
   int64_t sum_kw = 0, sum_k = 0;
   int32_t k_union = 0;  // K rows kept by at least one tile
   int32_t max_kp = 0;  // largest padded K_t
-  bool nonfinite = false;  // fp16 TW with K > MK_KC: an infinity or NaN among the values (known once they are packed)
+  bool nonfinite = false;  // fp16 TW with K > MK_KC: an infinity or NaN among the values
   twg::DeviceImage img;
   // device-side packing (tw_pack_dev): the lists and the values live in the device image alone until
   // somebody asks for them on the host
