@@ -52,8 +52,8 @@ PLAN = [(0, 4), (1, 1), (2, 1)]          # (shape index in the config, copies pe
 # they come from the two rocprofv3 --pmc runs (FETCH_SIZE, WRITE_SIZE) of this same command
 # summarised in the file named beside them, scaled by what the same counters read for a plain
 # 256 MiB device copy.  None where no such run has been made.
-PROFILED_TRAFFIC = {("tw", True): (32.46e6, "profiles/tw_gemm_km_dma_kernel_bert_base_tw75.md"),
-                    ("tvw", True): (29.45e6, "profiles/tvw_gemm_km_kernel_bert_base_tvw875.md")}
+PROFILED_TRAFFIC = {("tw", True): (32.45e6, "profiles/tw_gemm_km_dma_kernel_bert_base_tw75.md"),
+                    ("tvw", True): (29.33e6, "profiles/tvw_gemm_km_kernel_bert_base_tvw875.md")}
 
 
 def algorithmic_bytes(M, K_union, N, pattern, sum_kw, sum_k):
