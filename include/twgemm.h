@@ -389,12 +389,12 @@ const char* tw_status_str(int status);
  *   "ksplit"   0 = automatic, 1 = never, 2 = always split K between two wave groups
  *              of a workgroup (long K, few tiles)
  *   "depth"    stages in flight of the asynchronous pipeline: 3 (default) .. 8 (6 and 8 exist for
-              4-wave tiles of 64 x 128, 128 x 128 and 128 x 64 only; TVW: 3 or 4)
-   "idx_route" how a 4-wave launch with three stages in flight reads a tile's kept-row list: 0 =
-              automatic, 1 = scalar loads (128 x 128 and 256 x 64 tiles), 2 = one vector load per stage,
-              two stages ahead; everything else has one way and ignores it
-   "wg_split" K split across workgroups (tw_gemm_ex with a workspace): 0 / 1 = off,
-              2..8 = workgroups per (M-tile, N-tile) pair
+ *              4-wave tiles of 64 x 128, 128 x 128 and 128 x 64 only; TVW: 3 or 4)
+ *   "idx_route" how a 4-wave launch with three stages in flight reads a tile's kept-row list: 0 =
+ *              automatic, 1 = scalar loads (128 x 128 and 256 x 64 tiles), 2 = one vector load per
+ *              stage, two stages ahead; everything else has one way and ignores it
+ *   "wg_split" K split across workgroups (tw_gemm_ex with a workspace): 0 / 1 = off,
+ *              2..8 = workgroups per (M-tile, N-tile) pair
  *   "tiles_per_wg" tiles a workgroup of the asynchronous TW kernel computes one after the other
  *              (plain TW, 4 waves, G = 128, 64- or 128-row tiles, 3 stages; ignored elsewhere): the
  *              stores of a finished tile drain while the next one loads.  0 = automatic (one:

@@ -383,8 +383,8 @@ void build_device_lists(tw_handle_s* h) {
     std::copy(h->col_idx.begin() + h->tile_col_off[t], h->col_idx.begin() + h->tile_col_off[t + 1],
               d.col_idx.begin() + (size_t)t * G);
   // slack behind the last tile (valid row 0): the K-split kernel copies stages of 64 rows and
-  // may run one 32-row stage past a tile's end (it never multiplies it), and the TW kernel
-  // stages the list through LDS in chunks of 8 stages, up to two chunks past a short tile
+  // may run one 32-row stage past a tile's end (it never multiplies it), and the TW kernel with more than
+  // three stages in flight copies the list into LDS in chunks of 8 stages, up to two past a short tile
   d.row_idx.assign((size_t)d.tile_kp_off[nt] + ROW_IDX_SLACK, 0);
   for (int t = 0; t < nt; ++t) {
     const int k0 = h->tile_k_off[t], kt = h->tile_k_off[t + 1] - k0;

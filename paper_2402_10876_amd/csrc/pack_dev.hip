@@ -13,7 +13,7 @@
 //   image      one kernel writes the padded lists, one the values in the register order of the
 //              matrix instruction (TVW: with the 2:4 positions and the fill rule for short groups).
 // The image is the only copy; the lists and values of the logical form are read back from it if
-// somebody asks for them (tw_export, tw_unpack, tw_concat).
+// somebody asks for them (tw_export, tw_unpack, tw_concat; tw_conv_bind: the lists).
 //
 // What bounds it: two waits for the stream (11 us each), then launches of a few microseconds; the
 // masks (16 bytes per lane) and the weight are read once per pass.
