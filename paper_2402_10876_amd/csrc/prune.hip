@@ -12,14 +12,15 @@
 // by (score, index): the lowest n are pruned, equal scores lose the lower index
 // first.
 //
-// What bounds it: seven launches (TVW) one after the other on a weight of a few MB, each of them a
-// few dependent trips to memory.  1024 x 4096 at 87.5 % (TVW): 41 us of kernels, against 130 with
-// ranks by counting every pair, one thread per mask byte and 128-bit sums throughout.
+// What bounds it: three launches one after the other on a weight of a few MB, each of them a
+// few dependent trips to memory.  1024 x 4096 at 87.5 % (TVW): 35.4 us of kernels,
+// against 39.4 with seven launches; 64 x 64 20 against 25.5; 3136 x 192 30 against 59.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
 #include <mutex>
 
+#include "device_common.h"
 #include "prune.h"
 #include "scan.h"
 
@@ -36,36 +37,75 @@ __device__ __forceinline__ uint64_t magnitude24(uint16_t h) {   // |value| in un
   return e == 0 ? (uint64_t)m : (uint64_t)(m | 1024u) << (e - 1);
 }
 
-// Sum of squares.  Values below 1 have squares below 2^48: 2^15 of them fit a 64-bit sum, which
-// takes one multiply-add each; larger values go to a 128-bit sum of their own.
+// Sum of squares.  Values below 1 have squares below 2^48: 2^15 of them fit a 64-bit sum; larger values go
+// to a 128-bit sum of their own.  Up to 32 squares of values below 1 are added in fp64 first, exactly: a
+// square is a multiple of 2^-48 and their sum is below 2^5 (one full-rate instruction, where a 64-bit integer
+// multiply-add runs at a quarter of the rate).
 struct Sum {
   uint64_t lo = 0;
   u128 hi = 0;
+  double few = 0.0;
+  __device__ __forceinline__ void add_small(uint16_t h) {         // |value| < 1; flush() after 32 at the latest
+    union { uint16_t b; _Float16 f; } x;
+    x.b = h;
+    const double v = (double)(float)x.f;
+    few = __builtin_fma(v, v, few);
+  }
+  __device__ __forceinline__ void flush() {
+    lo += (uint64_t)(few * 281474976710656.0);                     // 2^48
+    few = 0.0;
+  }
   __device__ __forceinline__ void add(uint16_t h) {
     const uint64_t a = magnitude24(h);
     if (a < (1u << 24)) lo += (uint64_t)(uint32_t)a * (uint32_t)a;
     else hi += (u128)a * (u128)a;
   }
   __device__ __forceinline__ void carry() { hi += lo; lo = 0; }
-  __device__ __forceinline__ u128 total() const { return hi + lo; }
 };
+// Non-zero where one of the two halves of x is 1 or more (infinities and NaN among them).
+__device__ __forceinline__ uint32_t one_or_more(uint32_t x) { return ((x & 0x7fff7fffu) + 0x44004400u) & 0x80008000u; }
 
-// TW-C scores in two steps, exact and independent of any order (integer sums).  A workgroup takes
-// 256 columns and the rows 4 y + sub, + 4 gridDim.y, .. : 64 lanes of 4 columns x 4 rows; the four
-// rows' sums meet in LDS and the slice's sum goes to partial[y][column].
-__global__ void column_partial(const uint16_t* B, int K, int N, int ldb, int vec, u128* partial) {
-  __shared__ u128 part[4][256];
-  const int lane = threadIdx.x & 63, sub = threadIdx.x >> 6;
-  const int n = blockIdx.x * 256 + lane * 4;
+// Sum over the lanes whose ids differ in the bits FROM .. TO (powers of two), in every lane.  Their sums
+// in `lo` together stay below 2^64.
+template <int FROM, int TO>
+__device__ __forceinline__ u128 sum_over_lanes(const Sum& s) {
+  unsigned long long lo = s.lo;
+#pragma unroll
+  for (int d = FROM; d <= TO; d <<= 1) lo += __shfl_xor(lo, d);
+  u128 total = lo;
+  if (__any(s.hi != 0)) {                      // three 32-bit limbs, each in a 64-bit word
+    unsigned long long h0 = (uint32_t)s.hi, h1 = (uint32_t)(s.hi >> 32), h2 = (unsigned long long)(s.hi >> 64);
+#pragma unroll
+    for (int d = FROM; d <= TO; d <<= 1) {
+      h0 += __shfl_xor(h0, d);
+      h1 += __shfl_xor(h1, d);
+      h2 += __shfl_xor(h2, d);
+    }
+    total += (u128)h0 + ((u128)h1 << 32) + ((u128)h2 << 64);
+  }
+  return total;
+}
+
+// TW-C scores, exact and independent of any order (integer sums).  A workgroup of 1024 threads takes 16 columns
+// and all rows: 4 lanes of 4 columns, 256 rows at a time, 4 loads of 8 bytes in flight per thread.  Neighbouring
+// workgroups, which share the 128-byte lines, run on one XCD and meet in its L2.  One kernel, where slices of the
+// rows and a second kernel to add them up took 9.8 us and a launch more for 1024 x 4096.
+constexpr int SCORE_CW = 16, SCORE_LANES = SCORE_CW / 4, SCORE_STEP = 1024 / SCORE_LANES;
+__global__ __launch_bounds__(1024) void column_scores(const uint16_t* B, int K, int N, int ldb, int vec, u128* score) {
+  constexpr int CW = SCORE_CW, LANES = SCORE_LANES, ROWS = SCORE_STEP, U = 4;
+  __shared__ u128 part[16][CW];
+  const int tid = threadIdx.x, c4 = tid % LANES;
+  const int n_block = xcd_remap(blockIdx.x, gridDim.x) * CW;
+  const int n = n_block + c4 * 4;
   Sum s[4];
   int rows = 0;
-  const int step = 4 * gridDim.y;
-  for (int k0 = blockIdx.y * 4 + sub; k0 < K; k0 += 8 * step) {
-    union { uint2 v; uint16_t e[4]; } x[8];
+  for (int k0 = tid / LANES; k0 < K; k0 += U * ROWS) {
+    union { uint2 v; uint16_t e[4]; } x[U];
+    uint32_t big = 0;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
+    for (int i = 0; i < U; ++i) {
       x[i].v = uint2{0u, 0u};
-      const int k = k0 + i * step;
+      const int k = k0 + i * ROWS;
       if (k >= K) continue;
       const uint16_t* p = B + (size_t)k * ldb + n;
       if (vec && n + 4 <= N) x[i].v = *(const uint2*)p;
@@ -73,258 +113,428 @@ __global__ void column_partial(const uint16_t* B, int K, int N, int ldb, int vec
         for (int c = 0; c < 4; ++c) if (n + c < N) x[i].e[c] = p[c];
     }
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
+    for (int i = 0; i < U; ++i) big |= one_or_more(x[i].v.x) | one_or_more(x[i].v.y);
+    if (!__any(big != 0)) {
 #pragma unroll
-      for (int c = 0; c < 4; ++c) s[c].add(x[i].e[c]);
-    if ((rows += 8) >= (1 << 15)) {
+      for (int i = 0; i < U; ++i)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) s[c].add_small(x[i].e[c]);
+#pragma unroll
+      for (int c = 0; c < 4; ++c) s[c].flush();
+    } else {
+#pragma unroll
+      for (int i = 0; i < U; ++i)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) s[c].add(x[i].e[c]);
+    }
+    if ((rows += U) >= (1 << 15)) {
       rows = 0;
 #pragma unroll
       for (int c = 0; c < 4; ++c) s[c].carry();
     }
   }
 #pragma unroll
-  for (int c = 0; c < 4; ++c) part[sub][lane * 4 + c] = s[c].total();
+  for (int c = 0; c < 4; ++c) {
+    if (K > (1 << 15)) s[c].carry();           // (the lanes' 64-bit sums together would not fit)
+    const u128 w = sum_over_lanes<LANES, 32>(s[c]);
+    if ((tid & 63) < LANES) part[tid >> 6][c4 * 4 + c] = w;
+  }
   __syncthreads();
-  const int col = blockIdx.x * 256 + threadIdx.x;
-  if (col < N)
-    partial[(size_t)blockIdx.y * N + col] =
-        (part[0][threadIdx.x] + part[1][threadIdx.x]) + (part[2][threadIdx.x] + part[3][threadIdx.x]);
-}
-__global__ void column_score_finish(const u128* partial, int slices, int N, u128* score) {
-  const int n = blockIdx.x * blockDim.x + threadIdx.x;
-  if (n >= N) return;
-  u128 s = 0;
-#pragma unroll 8
-  for (int y = 0; y < slices; ++y) s += partial[(size_t)y * N + n];
-  score[n] = s;
+  const int col = n_block + tid;
+  if (tid >= CW || col >= N) return;
+  u128 t = 0;
+#pragma unroll
+  for (int w = 0; w < 16; ++w) t += part[w][tid];
+  score[col] = t;
 }
 
-// Which entries of a segment are kept: all but the n_pruned lowest in (score, index) order.  One
-// workgroup of SCAN_T threads per segment (blockIdx.x); R > 0: the segment has at most R * SCAN_T
-// entries and they stay in registers, R = 0: any length, read again in every pass.
+// Which entries of a segment of scores are kept: all but the n_pruned lowest in (score, index) order.  For the
+// SCAN_T threads of a workgroup, R rounds of SCAN_T entries at a time; REG: one such block holds the segment and
+// its scores stay in registers, else they are read again in every pass.
 //   1. the bits that all scores share at the top are skipped (OR of the differences to entry 0);
-//   2. the threshold is found 8 bits at a time from histograms in LDS; it is settled as soon as all
-//      scores with its leading bits are pruned, usually after two or three digits;
+//   2. the threshold is found 8 bits at a time from histograms in LDS, in windows of 32 bits of the
+//      score, so that a pass compares 32-bit numbers; every wave finds the digit's value by itself.  It is settled
+//      as soon as all scores with its leading bits are pruned, usually after two or three digits;
 //   3. scores equal to a threshold that had to be followed to its last bit are pruned in index
-//      order, and the kept entries are numbered in order:
-//      pos[i] = number among the kept or -1, list[pos] = i (each may be null).
-template <int R>
-__global__ __launch_bounds__(SCAN_T) void select_kept(const u128* scores, int len, int n_pruned, int32_t* pos, int32_t* list) {
-  __shared__ int hist[256], part[2][SCAN_WAVES];
-  __shared__ unsigned long long diff_w[2 * SCAN_WAVES];
-  __shared__ int found[3];                     // bin, entries in it, entries in front of it
+//      order, and the kept entries are numbered in order: out(i, number among the kept or -1) for every entry.
+// What bounds it: one CU's instruction rate (with 128-bit shifts and compares in every pass 9.7 us for 4096
+// entries, now 7.5 as a kernel of its own) and the chain of barriers.
+struct SelectLds {
+  __attribute__((aligned(16))) int hist[4][256];
+  int part[2][4 * SCAN_WAVES];
+  unsigned long long diff[2 * SCAN_WAVES];
+};
+template <int R, bool REG, class Out>
+__device__ __forceinline__ void select_entries(const u128* s, int len, int n_pruned, SelectLds& lds, Out out) {
+  static_assert(R * SCAN_WAVES <= 64, "a lane per count");
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const u128* s = scores + (size_t)blockIdx.x * len;
-  if (pos) pos += (size_t)blockIdx.x * len;
-  if (list) list += (size_t)blockIdx.x * len;
-  const int rounds = (len + SCAN_T - 1) / SCAN_T;
-  u128 key[R > 0 ? R : 1];
-  if constexpr (R > 0) {
+  const int blocks = REG ? 1 : (len - 1) / (R * SCAN_T) + 1;
+  u128 key[R];
+  auto load = [&](int b) {
 #pragma unroll
-    for (int r = 0; r < R; ++r) key[r] = r * SCAN_T + tid < len ? s[r * SCAN_T + tid] : 0;
-  }
-  auto each = [&](auto f) {                    // f(score, index) for this thread's entries, in order
-    if constexpr (R > 0) {
+    for (int r = 0; r < R; ++r) key[r] = s[min((b * R + r) * SCAN_T + tid, len - 1)];
+  };
+  auto there = [&](int b, int r) { return (b * R + r) * SCAN_T + tid < len; };
+  if constexpr (REG) load(0);
+  auto each = [&](auto f) {                    // f(score) for this thread's entries
+    for (int b = 0; b < blocks; ++b) {
+      if constexpr (!REG) load(b);
 #pragma unroll
       for (int r = 0; r < R; ++r)
-        if (r < rounds) f(key[r], r * SCAN_T + tid);
-    } else {
-      for (int r = 0; r < rounds; ++r) {
-        const int i = r * SCAN_T + tid;
-        f(i < len ? s[i] : (u128)0, i);
-      }
+        if (there(b, r)) f(key[r]);
     }
   };
+  // Scores whose bits above `shift` equal `prefix` are still open: the lowest `need` of them go.
   u128 prefix = 0;
-  int shift = 0, need = n_pruned;              // scores whose bits above `shift` equal `prefix`: the lowest `need` go
+  int shift = 0, need = n_pruned;
   bool all_equal_go = true;
-  if (n_pruned > 0 && n_pruned < len) {
+  const bool some = n_pruned > 0 && n_pruned < len;                  // (uniform over the workgroup)
+  if (some) {
     const u128 first = s[0];
     unsigned long long d0 = 0, d1 = 0;
-    each([&](u128 v, int i) {
-      if (i < len) { const u128 d = v ^ first; d0 |= (unsigned long long)d; d1 |= (unsigned long long)(d >> 64); }
-    });
+    each([&](u128 v) { const u128 d = v ^ first; d0 |= (unsigned long long)d; d1 |= (unsigned long long)(d >> 64); });
 #pragma unroll
     for (int k = 32; k >= 1; k >>= 1) { d0 |= __shfl_xor(d0, k); d1 |= __shfl_xor(d1, k); }
-    if (lane == 0) { diff_w[wave] = d0; diff_w[SCAN_WAVES + wave] = d1; }
+    if (lane == 0) { lds.diff[wave] = d0; lds.diff[SCAN_WAVES + wave] = d1; }
+    if (tid < 4 * 64) *(i32x4_t*)&lds.hist[0][tid * 4] = i32x4_t{0, 0, 0, 0};
     __syncthreads();
     d0 = d1 = 0;
 #pragma unroll
-    for (int w = 0; w < SCAN_WAVES; ++w) { d0 |= diff_w[w]; d1 |= diff_w[SCAN_WAVES + w]; }
+    for (int w = 0; w < SCAN_WAVES; ++w) { d0 |= lds.diff[w]; d1 |= lds.diff[SCAN_WAVES + w]; }
     shift = d1 ? 128 - __clzll((long long)d1) : d0 ? 64 - __clzll((long long)d0) : 0;
+    shift = __builtin_amdgcn_readfirstlane(shift);
     prefix = shift < 128 ? first >> shift : 0;
     all_equal_go = false;
-    while (shift > 0) {
-      const int bits = shift < 8 ? shift : 8, low = shift - bits;
-      for (int i = tid; i < 256; i += SCAN_T) hist[i] = 0;
-      __syncthreads();
-      each([&](u128 v, int i) {
-        if (i < len && (shift >= 128 || v >> shift == prefix)) atomicAdd(&hist[(int)(v >> low) & ((1 << bits) - 1)], 1);
-      });
-      __syncthreads();
-      if (wave == 0) {                         // four bins per lane: the bin that holds entry number `need`
-        int n[4], sum = 0;
+    while (shift > 0 && !all_equal_go) {       // a window of the 32 bits below `shift`, left-aligned
+      const int base = shift > 32 ? shift - 32 : 0, width = shift - base;
+      uint32_t win[R];
+      bool open[R];
+      auto window = [&](u128 v) { return (uint32_t)(v >> base) << (32 - width); };
+      auto is_open = [&](u128 v) { return shift >= 128 || v >> shift == prefix; };
+      if constexpr (REG) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) { n[j] = hist[lane * 4 + j]; sum += n[j]; }
+        for (int r = 0; r < R; ++r) { open[r] = there(0, r) && is_open(key[r]); win[r] = window(key[r]); }
+      }
+      uint32_t found = 0;                      // leading bits of the threshold's window
+      int done = 0;
+      for (int d = 0; done < width && !all_equal_go; ++d) {
+        const uint32_t lead = done ? ~0u << (32 - done) : 0u;
+        auto count = [&](uint32_t x) {
+          if ((x & lead) == found) atomicAdd(&lds.hist[d][(x << done) >> 24], 1);
+        };
+        if constexpr (REG) {
+#pragma unroll
+          for (int r = 0; r < R; ++r) if (open[r]) count(win[r]);
+        } else each([&](u128 v) { if (is_open(v)) count(window(v)); });
+        __syncthreads();
+        // four bins per lane: the bin that holds entry number `need`
+        const i32x4_t n = *(const i32x4_t*)&lds.hist[d][lane * 4];
+        const int sum = n[0] + n[1] + n[2] + n[3];
         int before = sum;
 #pragma unroll
         for (int k = 1; k < 64; k <<= 1) { const int t = __shfl_up(before, k); before += lane >= k ? t : 0; }
         before -= sum;
+        const int src = __ffsll(__ballot(before < need && need <= before + sum)) - 1;      // exactly one lane
+        int bin = lane * 4, in_bin = n[0];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          if (before < need && need <= before + n[j]) { found[0] = lane * 4 + j; found[1] = n[j]; found[2] = before; }
-          before += n[j];
-        }
+        for (int j = 1; j < 4; ++j)
+          if (need > before + in_bin) { before += in_bin; in_bin = n[j]; ++bin; }
+        found |= (uint32_t)__builtin_amdgcn_readlane(bin, src) << 24 >> done;
+        need -= __builtin_amdgcn_readlane(before, src);
+        done += 8;
+        all_equal_go = __builtin_amdgcn_readlane(in_bin, src) == need;
       }
-      __syncthreads();
-      prefix = prefix << bits | (unsigned)found[0];
-      need -= found[2];
-      shift = low;
-      if (found[1] == need) { all_equal_go = true; break; }
+      done = min(done, width);
+      prefix = prefix << done | found >> (32 - done);
+      shift -= done;
+      if (shift > 0 && !all_equal_go) {        // the next window's histograms
+        __syncthreads();
+        if (tid < 4 * 64) *(i32x4_t*)&lds.hist[0][tid * 4] = i32x4_t{0, 0, 0, 0};
+        __syncthreads();
+      }
     }
   }
-  int n_equal = 0, n_kept = 0;                 // entries equal to the threshold / kept, in the rounds before
-  each([&](u128 v, int i) {
-    bool keep = i < len && n_pruned < len;
-    if (n_pruned > 0 && n_pruned < len) {      // (uniform over the workgroup)
-      const u128 top = v >> shift;
-      const bool equal = i < len && top == prefix;
-      if (all_equal_go) keep = i < len && top > prefix;
-      else {
-        int total;
-        const int at = n_equal + count_before(equal, part[0], &total);
-        n_equal += total;
-        keep = i < len && (top > prefix || (equal && at >= need));
-      }
+  // In order: round after round, wave after wave.  Numbers of the entries of a kind in front of a wave's in each
+  // round of a block come from one scan over the waves' counts.
+  auto fronts = [&](const bool (&v)[R], int* p, int base, int (&front)[R]) {
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      front[r] = __popcll(__ballot(v[r]));
+      if (lane == 0) p[r * SCAN_WAVES + wave] = front[r];
     }
-    int total;
-    const int p = n_kept + count_before(keep, part[1], &total);
-    n_kept += total;
-    if (i < len) {
-      if (pos) pos[i] = keep ? p : -1;
-      if (list && keep) list[p] = i;
+    __syncthreads();
+    const int mine = lane < R * SCAN_WAVES ? p[lane] : 0;
+    int in = mine;
+#pragma unroll
+    for (int k = 1; k < 64; k <<= 1) { const int t = __shfl_up(in, k); in += lane >= k ? t : 0; }
+    const unsigned long long below = (1ull << lane) - 1ull;
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+      front[r] = base + __shfl(in - mine, r * SCAN_WAVES + wave) + __popcll(__ballot(v[r]) & below);
+    return base + __shfl(in, 63);
+  };
+  int n_equal = 0, n_kept = 0;                 // in the blocks before
+  for (int b = 0; b < blocks; ++b) {
+    if constexpr (!REG) load(b);
+    bool keep[R], equal[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const u128 top = key[r] >> shift;
+      keep[r] = there(b, r) && n_pruned < len && (!some || top > prefix);
+      equal[r] = there(b, r) && some && !all_equal_go && top == prefix;
     }
-    __syncthreads();                           // `part` may be used again
+    int at[R];
+    if (some && !all_equal_go) {
+      n_equal = fronts(equal, lds.part[0], n_equal, at);
+#pragma unroll
+      for (int r = 0; r < R; ++r) keep[r] |= equal[r] && at[r] >= need;
+    }
+    n_kept = fronts(keep, lds.part[1], n_kept, at);
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+      if (there(b, r)) out((b * R + r) * SCAN_T + tid, keep[r] ? at[r] : -1);
+    if (b + 1 < blocks) __syncthreads();       // `part` may be used again
+  }
+}
+
+// Segments too long for registers: a kernel of their own, one workgroup per segment.
+// pos[i] = number among the kept or -1, list[pos] = i.
+__global__ __launch_bounds__(SCAN_T) void select_kept(const u128* scores, int len, int n_pruned, int32_t* pos, int32_t* list) {
+  __shared__ SelectLds lds;
+  const size_t at = (size_t)blockIdx.x * len;
+  select_entries<4, false>(scores + at, len, n_pruned, lds, [&](int i, int p) {
+    pos[at + i] = p;
+    if (p >= 0) list[at + p] = i;
   });
 }
 
-// TW-R scores: tile t = kept columns [t*G, min((t+1)*G, n_kept)); 16 lanes per (tile, row), their
-// columns 16 apart; the lanes' sums meet in 64 bits, unless a value of 1 or more was among them.
-template <int G>
-__global__ void tile_row_scores(const uint16_t* B, int K, int ldb, int n_kept, const int32_t* kept_cols, u128* score) {
-  const int t = blockIdx.y, l = threadIdx.x & 15;
-  const int k = blockIdx.x * (blockDim.x >> 4) + (threadIdx.x >> 4);
-  const int w = min(G, n_kept - t * G);
-  Sum s;
-  if (k < K) {
-    const uint16_t* row = B + (size_t)k * ldb;
-    const int32_t* cols = kept_cols + t * G;
-    uint16_t v[G / 16];
-#pragma unroll
-    for (int i = 0; i < G / 16; ++i) v[i] = l + 16 * i < w ? row[cols[l + 16 * i]] : 0;
-#pragma unroll
-    for (int i = 0; i < G / 16; ++i) s.add(v[i]);
-  }
-  unsigned long long lo = s.lo;
-#pragma unroll
-  for (int d = 8; d >= 1; d >>= 1) lo += __shfl_xor(lo, d);
-  u128 total = lo;
-  if (__any(s.hi != 0)) {                      // three 32-bit limbs, each in a 64-bit word
-    unsigned long long h0 = (uint32_t)s.hi, h1 = (uint32_t)(s.hi >> 32), h2 = (unsigned long long)(s.hi >> 64);
-#pragma unroll
-    for (int d = 8; d >= 1; d >>= 1) {
-      h0 += __shfl_xor(h0, d);
-      h1 += __shfl_xor(h1, d);
-      h2 += __shfl_xor(h2, d);
-    }
-    total += (u128)h0 + ((u128)h1 << 32) + ((u128)h2 << 64);
-  }
-  if (k < K && l == 0) score[(size_t)t * K + k] = total;
+struct PruneArgs {
+  const uint16_t* B;
+  int K, N, ldb, n_kept, rows_kept;
+  const u128* col_score;
+  u128* row_score;
+  int32_t *col_pos, *kept_cols;        // number among the kept columns or -1; the kept columns
+  const int32_t *row_pos, *row_list;   // K > REG_MAX: the same for the rows of each tile
+  uint8_t *tiles, *element;            // masks (tiles: or null)
+  int blocks, rows;                    // workgroups per tile, rows of each (a multiple of 64)
+};
+constexpr int REG_MAX = 4 * SCAN_T;    // longest segment that is selected in registers
+// The workgroups of neighbouring tiles, which share 128-byte lines of the weight and the masks, run on one XCD: its L2
+// puts the lines together.
+__device__ __forceinline__ void tile_and_block(const PruneArgs& a, int& t, int& b) {
+  const int lid = xcd_remap(blockIdx.x, gridDim.x), tiles = (int)gridDim.x / a.blocks;
+  b = lid / tiles;
+  t = lid - b * tiles;
 }
 
-// out[k][n] = column n kept and row k kept in n's tile, into `a` and `b`; `zeroed` (TVW) starts as
-// zeros (each may be null).  A thread writes 16 columns, which belong to two tiles at most, of
-// EMIT_ROWS rows (VEC: 16-byte stores).
-constexpr int EMIT_ROWS = 4;
-template <bool VEC>
-__global__ void emit_tile_mask(int K, int N, int lg, int nt, const int32_t* col_pos, const int32_t* row_pos, uint8_t* a,
-                               uint8_t* b, uint8_t* zeroed) {
-  const int n0 = (blockIdx.y * blockDim.x + threadIdx.x) * 16;
-  const int k0 = blockIdx.x * EMIT_ROWS;
-  if (n0 >= N) return;
-  const int cnt = VEC ? 16 : min(16, N - n0);
-  int tile = -1;                               // the first tile; the other is the next one
-  u32x4_t first = {0u, 0u, 0u, 0u}, second = first;                  // bytes of their columns
-  if (a) {
-    i32x4_t pos[4];
-    if constexpr (VEC) {
+// TW-R scores: tile t = kept columns [t*G, min((t+1)*G, n_kept)); 16 lanes per (tile, row), their
+// columns 16 apart.  Workgroup (tile, block of rows).  R > 0: every workgroup first selects the kept columns for itself
+// (the first one writes them down): as long as a kernel that selects them alone on one CU, and a launch less.
+template <int G, int R>
+__global__ __launch_bounds__(1024) void tile_row_scores(PruneArgs a) {
+  constexpr int U = 2;                         // rows per thread and step
+  __shared__ SelectLds lds;
+  __shared__ int32_t list[R > 0 ? R * SCAN_T : 1];
+  int t, b;
+  tile_and_block(a, t, b);
+  const int l = threadIdx.x & 15, g = threadIdx.x >> 4;
+  const int32_t* cols = a.kept_cols + (size_t)t * G;
+  if constexpr (R > 0) {
+    select_entries<R, true>(a.col_score, a.N, a.N - a.n_kept, lds, [&](int i, int p) {
+      if (blockIdx.x == 0) a.col_pos[i] = p;
+      if (p < 0) return;
+      list[p] = i;
+      if (blockIdx.x == 0) a.kept_cols[p] = i;
+    });
+    __syncthreads();
+    cols = list + t * G;
+  }
+  const int w = min(G, a.n_kept - t * G);      // (nothing kept at all: one workgroup, which is done)
+  if (w <= 0) return;
+  int col[G / 16];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) pos[j] = *(const i32x4_t*)(col_pos + n0 + 4 * j);
-    } else {
+  for (int i = 0; i < G / 16; ++i) col[i] = cols[min(l + 16 * i, w - 1)];
+  const int k_end = min(a.K, (b + 1) * a.rows);
+  for (int k0 = b * a.rows + g; k0 < k_end; k0 += 64 * U) {
+    uint16_t v[U][G / 16];
 #pragma unroll
-      for (int c = 0; c < 16; ++c) pos[c >> 2][c & 3] = c < cnt ? col_pos[n0 + c] : -1;
+    for (int r = 0; r < U; ++r) {
+      const uint16_t* row = a.B + (size_t)min(k0 + 64 * r, a.K - 1) * a.ldb;
+#pragma unroll
+      for (int i = 0; i < G / 16; ++i) v[r][i] = row[col[i]];
     }
+    uint32_t big = 0;
 #pragma unroll
-    for (int c = 0; c < 16; ++c) {
-      const int p = pos[c >> 2][c & 3];
-      if (p < 0) continue;
-      if (tile < 0) tile = p >> lg;
-      if (p >> lg == tile) first[c >> 2] |= 1u << (8 * (c & 3));
-      else second[c >> 2] |= 1u << (8 * (c & 3));
+    for (int r = 0; r < U; ++r)
+#pragma unroll
+      for (int i = 0; i < G / 16; ++i) {
+        if (l + 16 * i >= w) v[r][i] = 0;
+        big |= one_or_more(v[r][i]);
+      }
+    const bool small = !__any(big != 0);
+#pragma unroll
+    for (int r = 0; r < U; ++r) {
+      Sum s;
+      if (small) {
+#pragma unroll
+        for (int i = 0; i < G / 16; ++i) s.add_small(v[r][i]);
+        s.flush();
+      } else {
+#pragma unroll
+        for (int i = 0; i < G / 16; ++i) s.add(v[r][i]);
+      }
+      const u128 total = sum_over_lanes<1, 8>(s);
+      const int k = k0 + 64 * r;
+      if (k < k_end && l == 0) a.row_score[(size_t)t * a.K + k] = total;
     }
   }
-  const int t0 = max(tile, 0), t1 = min(t0 + 1, max(nt - 1, 0));
-  bool keep0[EMIT_ROWS], keep1[EMIT_ROWS];
-#pragma unroll
-  for (int r = 0; r < EMIT_ROWS; ++r) {
-    const int k = min(k0 + r, K - 1);
-    keep0[r] = tile >= 0 && row_pos[(size_t)t0 * K + k] >= 0;
-    keep1[r] = tile >= 0 && row_pos[(size_t)t1 * K + k] >= 0;
+}
+
+// Bytes [from, to) of a 16-byte piece, aligned: one store, or up to four that the end leaves room for.
+__device__ __forceinline__ void store_piece(uint8_t* p, const u32x4_t& v, int from, int to) {
+  if (from <= 0 && to >= 16) { *(u32x4_t*)p = v; return; }
+  const uint64_t q0 = v[0] | (uint64_t)v[1] << 32, q1 = v[2] | (uint64_t)v[3] << 32;
+  // (arithmetic: a conditional of the two halves ends up as an indexed read of a copy in LDS)
+  auto bytes = [=](int o) { return (q0 ^ ((q0 ^ q1) & (0ull - (uint64_t)(o >> 3 & 1)))) >> (8 * (o & 7)); };
+  if (from > 0 && to < 16) {
+    for (int o = from; o < to; ++o) p[o] = (uint8_t)bytes(o);
+    return;
   }
-#pragma unroll
-  for (int r = 0; r < EMIT_ROWS; ++r) {
-    if (k0 + r >= K) break;
-    union { u32x4_t v; uint8_t e[16]; } x;
-    const u32x4_t none = {0u, 0u, 0u, 0u};
-    x.v = (keep0[r] ? first : none) | (keep1[r] ? second : none);
-    const size_t at = (size_t)(k0 + r) * N + n0;
-    if constexpr (VEC) {
-      if (a) *(u32x4_t*)(a + at) = x.v;
-      if (b) *(u32x4_t*)(b + at) = x.v;
-      if (zeroed) *(u32x4_t*)(zeroed + at) = none;
+  int o = from > 0 ? from : 0;
+  const int n = from > 0 ? 16 - from : to;
+  auto piece = [&](int size) {
+    if (!(n & size)) return;
+    if (size == 8) *(uint64_t*)(p + o) = bytes(o);
+    else if (size == 4) *(uint32_t*)(p + o) = (uint32_t)bytes(o);
+    else if (size == 2) *(uint16_t*)(p + o) = (uint16_t)bytes(o);
+    else p[o] = (uint8_t)bytes(o);
+    o += size;
+  };
+  if (from > 0) { piece(1); piece(2); piece(4); piece(8); }
+  else { piece(8); piece(4); piece(2); piece(1); }
+}
+
+// The masks.  tiles[k][n] = column n kept and row k kept in n's tile (may be null).  TVW: element[k][n], of those,
+// 2:4 along the condensed kept rows of the tile: in every group of 4 consecutive kept rows and every column
+// the 2 largest |w| stay; equal magnitudes: the lower position stays.
+// Workgroup (tile, block of rows): the tile answers for the columns from its first kept one (tile 0: from 0) to the next
+// tile's (the last: to N).  R > 0: the workgroup first selects the tile's kept rows for itself.  Then 16 lanes take
+// a row, 16 bytes of the mask each, aligned whatever N is; in a kept row (TVW) a lane reads the weights of the group's
+// four rows and ranks its own row among them.  1024 x 4096: 16 us; selection, masks of zeros and a kernel that filled in
+// single bytes took 6.7 + 5.4 + 4.1 us and two launches more.  1003 x 2491: 20 against 45.  What bounds it: the selection
+// (4 us), then the number of store instructions: the pieces that two tiles share are written in up to four parts.
+constexpr int COL_BITS = 8192;                 // columns a tile may answer for with their bits in LDS
+template <int R, bool TVW>
+__global__ __launch_bounds__(1024) void emit_masks(PruneArgs a, int lg) {
+  __shared__ SelectLds lds;
+  __shared__ int32_t pos_lds[R > 0 ? R * SCAN_T : 1], list_lds[R > 0 ? R * SCAN_T : 1];
+  __shared__ uint32_t bits[COL_BITS / 32 + 2];
+  const int K = a.K, N = a.N, tid = threadIdx.x;
+  int t, b;
+  tile_and_block(a, t, b);
+  const int c0 = t << lg, c1 = min((t + 1) << lg, a.n_kept);
+  const int lo = t == 0 ? 0 : a.kept_cols[c0], hi = c1 < a.n_kept ? a.kept_cols[c1] : N;
+  const bool few = hi - lo <= COL_BITS;        // (uniform)
+  for (int i = tid; i < COL_BITS / 32 + 2; i += 1024) bits[i] = 0;
+  __syncthreads();
+  if (few && c0 + tid < c1) {
+    const int at = a.kept_cols[c0 + tid] - lo;
+    atomicOr(&bits[at >> 5], 1u << (at & 31));
+  }
+  const int32_t *pos = pos_lds, *list = list_lds;
+  if constexpr (R > 0) {
+    if (c0 < c1)
+      select_entries<R, true>(a.row_score + (size_t)t * K, K, K - a.rows_kept, lds, [&](int i, int p) {
+        pos_lds[i] = p;
+        if (p >= 0) list_lds[p] = i;
+      });
+  } else {
+    pos = a.row_pos + (size_t)t * K;
+    list = a.row_list + (size_t)t * K;
+  }
+  __syncthreads();
+  // 16 columns from n on: which of them are kept ones of the tile
+  auto kept16 = [&](int n) {
+    uint32_t x = 0;
+    if (few) {
+      const int at = n - lo;
+      if (at < 0) x = bits[0] << -at;          // (n > lo - 16)
+      else {
+        const unsigned long long w = bits[at >> 5] | (unsigned long long)bits[(at >> 5) + 1] << 32;
+        x = (uint32_t)(w >> (at & 31));
+      }
     } else {
-      for (int c = 0; c < cnt; ++c) {
-        if (a) a[at + c] = x.e[c];
-        if (b) b[at + c] = x.e[c];
-        if (zeroed) zeroed[at + c] = 0;
+      for (int c = max(n, lo); c < min(n + 16, hi); ++c) x |= (a.col_pos[c] >= 0 ? 1u : 0u) << (c - n);
+    }
+    return x & 0xffffu;
+  };
+  struct __attribute__((packed, aligned(2))) Piece { u32x4_t v; };
+  // magnitudes of 16 weights of a row, order of finite fp16; columns outside the row are not used, but may be read where
+  // the matrix has them
+  const int64_t last_piece = (int64_t)(K - 1) * a.ldb + N - 16;
+  auto load16 = [&](int row, int n, uint32_t (&v)[8]) {
+    const int64_t first = (int64_t)row * a.ldb + n;
+    const uint16_t* p = a.B + first;
+    if (first >= 0 && first <= last_piece) {
+      const u32x4_t x = ((const Piece*)p)->v, y = ((const Piece*)(p + 8))->v;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) { v[j] = x[j] & 0x7fff7fffu; v[4 + j] = y[j] & 0x7fff7fffu; }
+    } else {
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const int c = n + 2 * j;
+        v[j] = (p[min(max(c, 0), N - 1) - n] | (uint32_t)p[min(max(c + 1, 0), N - 1) - n] << 16) & 0x7fff7fffu;
       }
     }
-  }
-}
-
-// 2:4 along the condensed kept rows of a tile: in every group of 4 consecutive kept rows
-// and every column keep the 2 largest |w|; equal magnitudes: the lower position stays.
-// Workgroup: 256 / G groups of a tile, G columns each.
-__global__ void two_of_four(const uint16_t* B, int K, int N, int ldb, int lg, int n_kept, int rows_kept,
-                            const int32_t* kept_cols, const int32_t* row_list, uint8_t* mask) {
-  const int t = blockIdx.y, c = (t << lg) + (int)(threadIdx.x & ((1u << lg) - 1u));
-  const int g = blockIdx.x * (blockDim.x >> lg) + (threadIdx.x >> lg);
-  if (c >= n_kept || 4 * g >= rows_kept) return;
-  const int n = kept_cols[c];
-  const int32_t* rows = row_list + (size_t)t * K + 4 * g;
-  const int cnt = min(4, rows_kept - 4 * g);
-  int row[4];
-  uint16_t v[4];
+  };
+  const bool same = !a.tiles || (((uintptr_t)a.tiles ^ (uintptr_t)a.element) & 15) == 0;
+  const int k_end = min(K, (b + 1) * a.rows);
+  for (int k = b * a.rows + (tid >> 4); k < k_end; k += 64) {
+    const int at = c0 < c1 ? pos[k] : -1;
+    uint8_t* row = a.element + (size_t)k * N;
+    const int off = (int)((uintptr_t)row & 15);
+    for (int n = ((lo + off) & ~15) - off + 16 * (tid & 15); n < hi; n += 256) {
+      const uint32_t x = at >= 0 ? kept16(n) : 0u;
+      u32x4_t tb, eb;
 #pragma unroll
-  for (int p = 0; p < 4; ++p) row[p] = rows[p < cnt ? p : 0];
+      for (int j = 0; j < 4; ++j) {            // four bits -> bytes 0 / 1
+        const uint32_t y = x >> (4 * j) & 15u;
+        tb[j] = (y * 0x00204081u) & 0x01010101u;
+      }
+      eb = tb;
+      if constexpr (TVW) {
+        if (x) {
+          const int g0 = at & ~3, mine = at & 3;
+          uint32_t own[8], v[4][8];
+          load16(k, n, own);
 #pragma unroll
-  for (int p = 0; p < 4; ++p) v[p] = B[(size_t)row[p] * ldb + n] & 0x7fffu;   // magnitude order of finite fp16
+          for (int q = 0; q < 4; ++q)          // past the end of the list: the row itself, which is not ahead of itself
+            load16(g0 + q < a.rows_kept ? list[g0 + q] : k, n, v[q]);
+          // top bit of a half: row q comes ahead, being larger, or (in front) as large
+          constexpr uint32_t H = 0x80008000u;
+          uint32_t keep[8];
 #pragma unroll
-  for (int p = 0; p < 4; ++p) {
-    int larger = 0;     // positions that come first: larger magnitude, or equal and lower
+          for (int j = 0; j < 8; ++j) {
+            uint32_t ahead[4];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) larger += q != p && q < cnt && (v[q] > v[p] || (v[q] == v[p] && q < p));
-    if (p < cnt && larger < 2) mask[(size_t)row[p] * N + n] = 1;
+            for (int q = 0; q < 4; ++q) ahead[q] = (v[q][j] | H) - (own[j] + (q >= mine ? 0x00010001u : 0u));
+            const uint32_t two = (ahead[0] & ahead[1]) | (ahead[2] & ahead[3]) | ((ahead[0] | ahead[1]) & (ahead[2] | ahead[3]));
+            keep[j] = ~two & H;
+          }
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+            eb[j] &= __builtin_amdgcn_perm(keep[2 * j + 1], keep[2 * j], 0x07050301u) >> 7;
+        }
+      }
+      const int from = lo - n, to = hi - n;
+      store_piece(row + n, eb, from, to);
+      if (a.tiles) {
+        uint8_t* other = a.tiles + (size_t)k * N + n;
+        if (same) store_piece(other, tb, from, to);
+        else
+          for (int c = max(from, 0); c < min(to, 16); ++c) other[c] = (uint8_t)(x >> c & 1u);
+      }
+    }
   }
 }
 
@@ -332,20 +542,14 @@ size_t align_up(size_t x) { return (x + 255) / 256 * 256; }
 
 }  // namespace
 
-// Row slices of the column scores: about 512 workgroups of 256 columns in all, so at most
-// 2 MiB of partial sums whatever the shape.
-static int column_slices(int K, int N) {
-  const int nbx = (N + 255) / 256;
-  const int want = 512 / nbx > 1 ? 512 / nbx : 1;
-  return K < want ? K : want;
-}
-
 size_t prune_workspace_bytes(int K, int N, int G) {
   const size_t nt = (size_t)(N + G - 1) / G;
-  // (one spare list per column and per row: the size is part of the interface)
+  // The size is part of the interface: more than the kernels use (one spare list per column and per row, and
+  // room for the column scores of `slices` slices of the rows).
+  const int blocks = (N + 255) / 256, slices = K < 512 / blocks ? K : 512 / blocks > 1 ? 512 / blocks : 1;
   return align_up((size_t)N * 16) + 3 * align_up((size_t)N * 4) +          // column score, pos, list
          align_up(nt * K * 16) + 3 * align_up(nt * K * 4) +                 // row score, pos, list
-         align_up((size_t)column_slices(K, N) * N * 16);                    // column scores per row slice
+         align_up((size_t)slices * N * 16);
 }
 
 hipError_t prune_device(const uint16_t* B, int K, int N, int ldb, int G, bool tvw, int n_cols_pruned,
@@ -360,9 +564,8 @@ hipError_t prune_device(const uint16_t* B, int K, int N, int ldb, int G, bool tv
   int32_t* kept_cols = (int32_t*)w;      w += align_up((size_t)N * 4);
   u128* row_score = (u128*)w;            w += align_up(ntmax * K * 16) + align_up(ntmax * K * 4);
   int32_t* row_pos = (int32_t*)w;        w += align_up(ntmax * K * 4);
-  int32_t* row_list = (int32_t*)w;       w += align_up(ntmax * K * 4);
-  u128* col_partial = (u128*)w;
-  const int T = 256, lg = G == 128 ? 7 : G == 64 ? 6 : 5;
+  int32_t* row_list = (int32_t*)w;
+  const int lg = G == 128 ? 7 : G == 64 ? 6 : 5;
   auto aligned = [](const void* p, size_t a) { return ((uintptr_t)p & (a - 1)) == 0; };
   (void)hipGetLastError();   // an error left behind by an earlier call of this thread is not this call's
   // a failed launch ends the call: later kernels would read workspace nobody wrote
@@ -372,37 +575,38 @@ hipError_t prune_device(const uint16_t* B, int K, int N, int ldb, int G, bool tv
     const hipError_t e_ = hipGetLastError();                                  \
     if (e_ != hipSuccess) return e_;                                          \
   } while (0)
-#define TWG_SELECT(segments, scores, len, n_pruned, pos, list)                                               \
-  do {                                                                                                       \
-    if ((len) <= SCAN_T) TWG_LAUNCH(select_kept<1>, dim3(segments), dim3(SCAN_T), scores, len, n_pruned, pos, list);           \
-    else if ((len) <= 4 * SCAN_T) TWG_LAUNCH(select_kept<4>, dim3(segments), dim3(SCAN_T), scores, len, n_pruned, pos, list);  \
-    else TWG_LAUNCH(select_kept<0>, dim3(segments), dim3(SCAN_T), scores, len, n_pruned, pos, list);         \
+  TWG_LAUNCH(column_scores, dim3((unsigned)((N + SCORE_CW - 1) / SCORE_CW)), dim3(1024), B, K, N, ldb,
+             (int)(ldb % 4 == 0 && aligned(B, 8)), col_score);
+  PruneArgs a{B, K, N, ldb, n_kept, rows_per_tile, col_score, row_score, col_pos, kept_cols, row_pos, row_list, tile_mask, mask, 0, 0};
+  // Workgroups of 1024 threads for the tiles, about one per CU: each selects for itself.
+  const int tiles = nt > 0 ? nt : 1;
+  a.blocks = 256 / tiles > 1 ? 256 / tiles : 1;
+  a.rows = ((K + a.blocks - 1) / a.blocks + 63) / 64 * 64;
+  a.blocks = (K + a.rows - 1) / a.rows;
+  const dim3 grid((unsigned)tiles * (unsigned)a.blocks), block(1024);
+  // Columns: entries per thread of a selection in registers, or (0) a kernel that selects.
+  const int rc = N <= SCAN_T ? 1 : N <= REG_MAX ? 4 : 0, rk = K <= SCAN_T ? 1 : K <= REG_MAX ? 4 : 0;
+  if (!rc) TWG_LAUNCH(select_kept, dim3(1), block, col_score, N, n_cols_pruned, col_pos, kept_cols);
+#define TWG_ROWS(G_)                                                             \
+  do {                                                                           \
+    if (rc == 1) TWG_LAUNCH((tile_row_scores<G_, 1>), grid, block, a);           \
+    else if (rc == 4) TWG_LAUNCH((tile_row_scores<G_, 4>), grid, block, a);      \
+    else TWG_LAUNCH((tile_row_scores<G_, 0>), grid, block, a);                   \
   } while (0)
-  const int ky = column_slices(K, N);
-  TWG_LAUNCH(column_partial, dim3((unsigned)((N + T - 1) / T), ky), dim3(T), B, K, N, ldb,
-             (int)(ldb % 4 == 0 && aligned(B, 8)), col_partial);
-  TWG_LAUNCH(column_score_finish, dim3((unsigned)((N + 63) / 64)), dim3(64), col_partial, ky, N, col_score);
-  TWG_SELECT(1, col_score, N, n_cols_pruned, col_pos, kept_cols);
-  if (nt > 0) {
-    const dim3 grid((K + 15) / 16, nt);
-    if (G == 128) TWG_LAUNCH(tile_row_scores<128>, grid, dim3(T), B, K, ldb, n_kept, kept_cols, row_score);
-    else if (G == 64) TWG_LAUNCH(tile_row_scores<64>, grid, dim3(T), B, K, ldb, n_kept, kept_cols, row_score);
-    else TWG_LAUNCH(tile_row_scores<32>, grid, dim3(T), B, K, ldb, n_kept, kept_cols, row_score);
-    TWG_SELECT(nt, row_score, K, K - rows_per_tile, row_pos, row_list);
+  if (G == 128) TWG_ROWS(128);
+  else if (G == 64) TWG_ROWS(64);
+  else TWG_ROWS(32);
+  if (!rk && nt > 0) TWG_LAUNCH(select_kept, dim3(nt), block, row_score, K, K - rows_per_tile, row_pos, row_list);
+  if (!tvw) {                                  // the element mask is the tile mask
+    if (rk == 1) TWG_LAUNCH((emit_masks<1, false>), grid, block, a, lg);
+    else if (rk == 4) TWG_LAUNCH((emit_masks<4, false>), grid, block, a, lg);
+    else TWG_LAUNCH((emit_masks<0, false>), grid, block, a, lg);
+  } else {
+    if (rk == 1) TWG_LAUNCH((emit_masks<1, true>), grid, block, a, lg);
+    else if (rk == 4) TWG_LAUNCH((emit_masks<4, true>), grid, block, a, lg);
+    else TWG_LAUNCH((emit_masks<0, true>), grid, block, a, lg);
   }
-  // TVW: the tile mask (if asked for) and an all-zero element mask for the 2:4 step to fill; TW: the
-  // element mask is the tile mask
-  const bool vec = N % 16 == 0 && aligned(mask, 16) && (!tile_mask || aligned(tile_mask, 16));
-  const unsigned ex = (unsigned)((N + 16 * T - 1) / (16 * T)), ey = (unsigned)((K + EMIT_ROWS - 1) / EMIT_ROWS);
-  uint8_t *out_a = tvw ? tile_mask : mask, *out_b = tvw ? nullptr : tile_mask, *zeroed = tvw ? mask : nullptr;
-  if (vec) TWG_LAUNCH(emit_tile_mask<true>, dim3(ey, ex), dim3(T), K, N, lg, nt, col_pos, row_pos, out_a, out_b, zeroed);
-  else TWG_LAUNCH(emit_tile_mask<false>, dim3(ey, ex), dim3(T), K, N, lg, nt, col_pos, row_pos, out_a, out_b, zeroed);
-  if (tvw && nt > 0 && rows_per_tile > 0) {
-    const int groups = (rows_per_tile + 3) / 4, per = T >> lg;
-    TWG_LAUNCH(two_of_four, dim3((groups + per - 1) / per, nt), dim3(T), B, K, N, ldb, lg, n_kept, rows_per_tile,
-               kept_cols, row_list, mask);
-  }
-#undef TWG_SELECT
+#undef TWG_ROWS
 #undef TWG_LAUNCH
   return hipSuccess;
 }
