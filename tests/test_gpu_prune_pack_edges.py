@@ -1,6 +1,7 @@
 """Device pruner and packer at the sizes where their kernels change path: segments around the register
-limits of the selection (1024 and 4096 entries), widths with and without 16-byte mask rows, scores that
-agree in all but their last bits (-m gpu)."""
+limits of the selection (1024 and 4096 entries), widths with and without 16-byte mask rows, masks at any
+address, a tile that answers for very many columns, counts that fill more than one block of host memory, several
+threads at once, scores that agree in all but their last bits (-m gpu)."""
 import numpy as np
 import pytest
 
@@ -17,6 +18,7 @@ pytestmark = pytest.mark.gpu
 CASES = [  # K, N, G, columns pruned, rows kept per tile
     (1024, 64, 64, 5, 300), (1025, 48, 32, 0, 256), (6, 4096, 128, 400, 4), (8, 4112, 64, 1, 8),
     (4100, 16, 32, 2, 1000), (33, 1040, 128, 1039, 1), (5, 17, 32, 3, 5), (64, 160, 32, 16, 32),
+    (1, 1, 32, 0, 1), (130, 3, 64, 1, 70), (4097, 5, 128, 0, 4097), (2, 9000, 64, 8990, 1), (70, 143, 128, 143, 5),
 ]
 
 
@@ -46,3 +48,106 @@ def test_scores_that_differ_in_the_last_bit_only():
     mask, _, _ = _prune_on_device(B, G, tw.PATTERN_TW, 0, 200)
     want = op.tw(B, G, n_cols_pruned=0, rows_kept_per_tile=200, exact=True)
     assert want[up].all() and np.array_equal(mask, want)
+
+
+@pytest.mark.parametrize("K,N,G,at,tile_at", [(37, 77, 32, 0, 0), (37, 77, 32, 3, 3), (64, 96, 32, 5, 12), (20, 200, 128, 15, 0)])
+def test_masks_at_any_address(K, N, G, at, tile_at):
+    """Masks that start `at` bytes behind a 16-byte boundary: what lies around them stays as it was, and they pack."""
+    import torch
+    B = wl.rng_fp16(K * N, (K, N), 0.5)
+    rk = K // 3
+    Bd = torch.from_numpy(B).cuda()
+    buf = [torch.full((K * N + 64,), 7, dtype=torch.uint8, device="cuda") for _ in range(2)]
+    md, td = buf[0][at:at + K * N], buf[1][tile_at:tile_at + K * N]
+    ws = torch.empty(tw.tw_prune_workspace_bytes(K, N, G), dtype=torch.uint8, device="cuda")
+    st = torch.cuda.current_stream().cuda_stream
+    print(f"case mask address K={K} N={N} at={at},{tile_at}", flush=True)
+    tw.tw_prune_dev(Bd.data_ptr(), K, N, N, G, tw.PATTERN_TVW, N // 8, rk, md.data_ptr(), td.data_ptr(), ws.data_ptr(),
+                    ws.numel(), st)
+    torch.cuda.synchronize()
+    want_t = op.tw(B, G, n_cols_pruned=N // 8, rows_kept_per_tile=rk, exact=True)
+    want = op.vw24_condensed(B, want_t, G)
+    assert np.array_equal(md.cpu().numpy().reshape(K, N), want) and np.array_equal(td.cpu().numpy().reshape(K, N), want_t)
+    for b, a in zip(buf, (at, tile_at)):
+        assert (b[:a] == 7).all() and (b[a + K * N:] == 7).all()
+    p = tw.tw_pack_dev(Bd.data_ptr(), N, md.data_ptr(), td.data_ptr(), K, N, G, tw.PATTERN_TVW, st)
+    _same(p.export(), opk.ref_pack(B, want, G, opk.PATTERN_TVW, tile_mask=want_t))
+    p.free()
+
+
+def test_a_tile_of_more_columns_than_fit_in_lds():
+    """100 kept columns among 20000: the last tile answers for more than 8192 columns."""
+    K, N, G = 6, 20000, 32
+    B = np.zeros((K, N), np.float16)
+    cols = np.r_[5:90, 9000:9015]
+    B[:, cols] = wl.rng_fp16(1, (K, len(cols)), 0.5)
+    B[:, cols] += np.sign(B[:, cols])
+    mask, tmask, _ = _prune_on_device(B, G, tw.PATTERN_TVW, N - len(cols), 5)
+    want_t = op.tw(B, G, n_cols_pruned=N - len(cols), rows_kept_per_tile=5, exact=True)
+    want = op.vw24_condensed(B, want_t, G)
+    assert np.array_equal(tmask, want_t) and np.array_equal(mask, want)
+    p = _pack_dev(B, want, G, tw.PATTERN_TVW, tile_mask=want_t)
+    _same(p.export(), opk.ref_pack(B, want, G, opk.PATTERN_TVW, tile_mask=want_t))
+    p.free()
+
+
+def test_more_counts_than_one_block_of_host_memory():
+    rng = np.random.default_rng(0)
+    K, N, G = 4200, 3200, 32                                         # 66 x 100 counts
+    keep = rng.random((K, N // G)) < 0.03
+    mask = np.repeat(keep, G, axis=1).astype(np.uint8)
+    mask[0] = 1
+    B = wl.rng_fp16(3, (K, N))
+    p, h = _pack_dev(B, mask, G, tw.PATTERN_TW), tw.tw_pack_host(B, mask, G, tw.PATTERN_TW)
+    _same(p.export(), h.export())
+    assert p.flop_counts() == h.flop_counts()
+    p.free()
+    h.free()
+
+
+def test_several_threads_pack_at_once():
+    """More threads than blocks of host memory are kept, each on a stream of its own, over and over."""
+    import threading
+    import torch
+    rng = np.random.default_rng(1)
+    jobs = []
+    for i in range(6):
+        K, N, G = 100 + 37 * i, 90 + 51 * i, 32
+        keep = rng.random((K, (N + G - 1) // G)) < 0.4
+        keep[0] = True
+        mask = np.repeat(keep, G, axis=1)[:, :N].astype(np.uint8)
+        B = wl.rng_fp16(i, (K, N))
+        jobs.append((B, mask, G, opk.ref_pack(B, mask, G, opk.PATTERN_TW)))
+    errors = []
+
+    def work(B, mask, G, want):
+        try:
+            with torch.cuda.stream(torch.cuda.Stream()):
+                for _ in range(5):
+                    p = _pack_dev(B, mask, G, tw.PATTERN_TW)
+                    _same(p.export(), want)
+                    p.free()
+        except Exception as e:                                       # noqa: BLE001 (handed to the main thread)
+            errors.append(e)
+    threads = [threading.Thread(target=work, args=j) for j in jobs]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not errors, errors
+
+
+def test_packing_while_the_stream_is_captured_is_an_error():
+    import torch
+    B, mask = wl.rng_fp16(0, (64, 64)), np.ones((64, 64), np.uint8)
+    Bd, md, x = torch.from_numpy(B).cuda(), torch.from_numpy(mask).cuda(), torch.zeros(8, device="cuda")
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, capture_error_mode="relaxed"):
+        x += 1
+        with pytest.raises(tw.TwError) as ei:
+            tw.tw_pack_dev(Bd.data_ptr(), 64, md.data_ptr(), None, 64, 64, 64, tw.PATTERN_TW,
+                           torch.cuda.current_stream().cuda_stream)
+    assert ei.value.status == 5
+    g.replay()
+    torch.cuda.synchronize()
+    assert float(x[0]) == 1.0
