@@ -394,7 +394,8 @@ static tw_status gemm_launch(const Opts& o, const void* A, int M, int lda, int l
   g.meta = h->img.d_meta;
   g.ew_ptr = h->img.d_ew_ptr; g.ew_pairs = h->img.d_ew_pairs;
   g.ew_last = h->img.ew_pairs.empty() ? 0 : (int)h->img.ew_pairs.size() - 1;
-  g.n_tiles = h->n_tiles; g.K = h->K; g.N = h->N; g.xcd_map = o.xcd_map;
+  const int n_tiles = h->img.n_tiles;
+  g.n_tiles = n_tiles; g.K = h->K; g.N = h->N; g.xcd_map = o.xcd_map;
   g.wg_split = 1;
   g.tiles_per_wg = 1;
   if (layout == TW_LAYOUT_MK) {
@@ -407,33 +408,37 @@ static tw_status gemm_launch(const Opts& o, const void* A, int M, int lda, int l
   // Few output blocks.  A weight with nothing pruned adds up in the order of the dense baseline (same
   // bits), and a TEW weight without restored elements in the order of its TW twin.  (sum_kw counts a TVW
   // weight before its 2:4 step, so one that keeps every row and column stays with the pipelined kernel too.)
-  const bool plain = h->pattern != TW_PATTERN_TEW || (h->img.ew_pairs.empty() && h->G != 32 && a_fits32);
-  if (plain && automatic(o) && h->sum_kw < (int64_t)h->K * h->N &&
-      twg::small_km_pays(h->G, h->pattern == TW_PATTERN_TVW, M, h->n_tiles, h->max_kp)) {
-    hipError_t e = twg::launch_small_km(h->G, h->pattern == TW_PATTERN_TVW, h->max_kp, g, (hipStream_t)stream);
+  const bool small = h->pattern != TW_PATTERN_TEW || (h->G != 32 && a_fits32);
+  if (small && automatic(o) && h->sum_kw < (int64_t)h->K * h->N &&
+      twg::small_km_pays(h->G, h->pattern == TW_PATTERN_TVW, M, n_tiles, h->max_kp)) {
+    hipError_t e = twg::launch_small_km(h->G, h->pattern == TW_PATTERN_TVW, !h->img.ew_pairs.empty(), h->max_kp, g,
+                                        (hipStream_t)stream);
     return e == hipSuccess ? TW_OK : TW_ERR_HIP;
   }
   if (h->pattern == TW_PATTERN_TVW) {
-    const int tvw_tm = pick_tile_m_tvw(o, h->G, M, h->n_tiles > 0 ? h->n_tiles : 1, h->max_kp);
+    const int tvw_tm = pick_tile_m_tvw(o, h->G, M, n_tiles > 0 ? n_tiles : 1, h->max_kp);
     hipError_t e = twg::launch_tvw_km(h->G, tvw_tm, o.depth > 4 ? 4 : o.depth, g, (hipStream_t)stream);
     if (e == hipErrorInvalidValue) return TW_ERR_UNSUPPORTED;
     return e == hipSuccess ? TW_OK : TW_ERR_HIP;
   }
-  int tm = pick_tile_m(o, M, h->n_tiles > 0 ? h->n_tiles : 1, h->G, h->max_kp);
+  int tm = pick_tile_m(o, M, n_tiles > 0 ? n_tiles : 1, h->G, h->max_kp);
   // no 64 x 64 instance of the asynchronous kernel (tried: one matrix instruction per wave and
   // k-step is too little work per barrier; plain TW falls back to the register-staged kernel)
   if ((h->pattern == TW_PATTERN_TEW || conv) && h->G == 64 && tm == 64) tm = 128;
+  // TEW: the 256-row instance of G = 128 has no register to spare for its second way to the result (768 x 3072 at M =
+  // 4096, 1.5 % restored: 29.4 / 26.4 us with 256 / 128 rows; 3072 x 768: 26.4 / 26.7)
+  if (h->pattern == TW_PATTERN_TEW && h->G == 128 && tm == 256 && o.tile_m != 256) tm = 128;
   hipError_t e = hipErrorInvalidValue;
   // TEW: the same kernels with the restored elements added in the epilogue (3 stages only)
   const bool tew = h->pattern == TW_PATTERN_TEW;
   auto launch_dma = tew ? twg::launch_tew_km_dma : twg::launch_tw_km_dma;
   const int depth = tew ? 3 : o.depth;
   // K split across workgroups: few tiles, long kept-row lists, and a workspace to reduce through
-  if (!tew && o.kernel != 1 && h->G != 32 && a_fits32 && o.ws && o.wg_split != 1 && h->n_tiles > 0) {
+  if (!tew && o.kernel != 1 && h->G != 32 && a_fits32 && o.ws && o.wg_split != 1 && n_tiles > 0) {
     int stm = 0, S = 0;
-    pick_wg_split(o, M, h->n_tiles, h->G, h->max_kp, &stm, &S);
+    pick_wg_split(o, M, n_tiles, h->G, h->max_kp, &stm, &S);
     if (S > 1) {
-      const long pairs = (long)((M + stm - 1) / stm) * h->n_tiles;
+      const long pairs = (long)((M + stm - 1) / stm) * n_tiles;
       const size_t need = WS_COUNTER_BYTES + (size_t)pairs * S * stm * h->G * 4;
       if (pairs <= WS_MAX_PAIRS && need <= o.ws_bytes) {
         g.wg_split = S;
@@ -454,11 +459,11 @@ static tw_status gemm_launch(const Opts& o, const void* A, int M, int lda, int l
     int variant = (o.waves == 8 || (tm == 256 && h->G == 128)) ? twg::DMA_WAVES8 : twg::DMA_WAVES4;
     int tmk = tm;
     const int ks = o.ksplit;
-    if (ks == 2 || (ks == 0 && use_ksplit(M, h->n_tiles, h->max_kp, &tmk))) variant = twg::DMA_KSPLIT2;
+    if (ks == 2 || (ks == 0 && use_ksplit(M, n_tiles, h->max_kp, &tmk))) variant = twg::DMA_KSPLIT2;
     if (variant == twg::DMA_KSPLIT2 && ks == 2) tmk = tm == 256 ? 128 : tm;
     if (variant == twg::DMA_KSPLIT2 && h->G == 64) tmk = 128;   // the one K-split instance for G = 64
     const int tmu = variant == twg::DMA_KSPLIT2 ? tmk : tm;
-    g.scalar_rows = !tew && variant == twg::DMA_WAVES4 && scalar_rows(o, M, h->n_tiles, h->G, tmu, h->max_kp, conv);
+    g.scalar_rows = !tew && variant == twg::DMA_WAVES4 && scalar_rows(o, M, n_tiles, h->G, tmu, h->max_kp, conv);
     // several tiles per workgroup (plain TW, 4 waves, 64- or 128-row tiles of G = 128, 3 stages): on request
     if (!tew && variant == twg::DMA_WAVES4 && o.tiles_per_wg > 1) g.tiles_per_wg = o.tiles_per_wg;
     e = launch_dma(h->G, tmu, depth, variant, g, (hipStream_t)stream);

@@ -119,62 +119,38 @@ __device__ __forceinline__ void wait_stage(int newer) {
 // (in fp32, before the single rounding).  It gives a tile two waves per SIMD,
 // which long-K problems with few tiles need to keep the matrix cores busy.
 
-// ---- TEW: restored elements (Section III-A "TEW": the element-wise part is kept in
-// compressed sparse column form and, the product being linear, computed apart from the
-// TW part).  Here it is added to the fp32 sums of the thread that stores the 8 values
-// C^T[col][m .. m+8): for every restored (k, v) of the column, s += v * A^T[k][m .. m+8).
-// Pairs travel as k << 16 | fp16 bits; the list is padded in registers with
-// (row 0, +0), which adds nothing.  Every load is unconditional (index clamped to the
-// list, value selected afterwards): a load under a branch would be waited for on its own.  A rows are lda >= round-up-8(M) halves long, so the
-// 16-byte read at m < M stays inside the row; lanes at or past M are not stored.
-template <int P>      // P columns at a time: P times the loads in flight per round trip
-__device__ __forceinline__ void ew_accumulate(const GemmArgs& g, const int (&lo)[P], const int (&hi)[P],
-                                              const _Float16* A_m, float (&s)[P][8]) {
-  constexpr int U = 8 / P;     // elements per column and round trip; the next ones are fetched meanwhile
-  int e[P];
-  uint32_t nx[P][U];
-  bool more = false;
-#pragma unroll
-  for (int p = 0; p < P; ++p) {
-    e[p] = lo[p];
-    more |= lo[p] < hi[p];
+// ---- TEW: restored elements (Section III-A "TEW").  The rows that hold any in a tile's columns have joined the tile's
+// list (see the packer) and are multiplied by the matrix cores with the rest: 1.5 % restored elements are in 85 % of the
+// rows of a 128-column tile, 1.9 in a row, and reading those rows once through the pipeline costs half of what the
+// elements cost one by one (256 bytes of A each, lists of different length side by side).  From HBM, M = 4096, 75 %:
+// 768 x 3072 with 0.5 / 1.5 / 3 % restored 23.8 / 34.8 / 49.8 -> 19.3 / 23.3 / 24.1 us, 3072 x 768 22.4 / 34.6 / 52.3 ->
+// 21.6 / 27.0 / 28.0.  What bounds it now: what bounds a TW launch of that many rows.
+// A zero of a joined row is not a term of the product, though, and an infinity of A would make it one: a workgroup whose
+// sums are not all finite starts again with the kept rows alone and adds the restored elements one by one, as the CSC part
+// has them (which has to be right, not fast), to the fp32 sums of the thread that stores the 8 values C^T[col][m .. m+8):
+// for every restored (k, v) of the column, s += v * A^T[k][m .. m+8).  Pairs travel as k << 16 | fp16 bits; the list is
+// padded in registers with (row 0, +0).  A rows are lda >= round-up-8(M) halves long, so the 16-byte read at m < M stays
+// inside the row.
+__device__ __forceinline__ void ew_accumulate(const GemmArgs& g, int lo, int hi, const _Float16* A_m, float (&s)[8]) {
+  constexpr int U = 4;                   // elements per round trip
+  for (int e = lo; e < hi; e += U) {
+    uint32_t w[U];
+    half8 a[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const uint32_t w = g.ew_pairs[min(lo[p] + u, g.ew_last)];
-      nx[p][u] = lo[p] + u < hi[p] ? w : 0u;
-    }
-  }
-  while (more) {
-    uint32_t pr[P][U];
-    half8 a[P][U];
-#pragma unroll
-    for (int p = 0; p < P; ++p)
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        pr[p][u] = nx[p][u];
-        a[p][u] = *(const half8*)(A_m + (size_t)(pr[p][u] >> 16) * g.lda);
-      }
-    more = false;
-#pragma unroll
-    for (int p = 0; p < P; ++p) {
-      e[p] += U;
-      more |= e[p] < hi[p];
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const uint32_t w = g.ew_pairs[min(e[p] + u, g.ew_last)];
-        nx[p][u] = e[p] + u < hi[p] ? w : 0u;
-      }
+      w[u] = g.ew_pairs[min(e + u, g.ew_last)];
+      if (e + u >= hi) w[u] = 0u;
     }
 #pragma unroll
-    for (int p = 0; p < P; ++p)
+    for (int u = 0; u < U; ++u) a[u] = *(const half8*)(A_m + (size_t)(w[u] >> 16) * g.lda);
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        union { uint16_t b; _Float16 h; } cv;
-        cv.b = (uint16_t)(pr[p][u] & 0xffffu);
-        const float v = (float)cv.h;
+    for (int u = 0; u < U; ++u) {
+      union { uint16_t b; _Float16 h; } cv;
+      cv.b = (uint16_t)(w[u] & 0xffffu);
+      const float v = (float)cv.h;
 #pragma unroll
-        for (int q = 0; q < 8; ++q) s[p][q] = __builtin_fmaf(v, (float)a[p][u][q], s[p][q]);
-      }
+      for (int q = 0; q < 8; ++q) s[q] = __builtin_fmaf(v, (float)a[u][q], s[q]);
+    }
   }
 }
 
@@ -184,23 +160,6 @@ __device__ __forceinline__ void store_row_chunk(const GemmArgs& g, _Float16* dst
   for (int q = 0; q < 8; ++q) h[q] = (_Float16)s[q];
   if (m + 8 <= g.M) __builtin_nontemporal_store(h, (half8*)dst);
   else for (int q = 0; m + q < g.M; ++q) dst[q] = h[q];
-}
-
-// A column the TW step dropped: nothing but its restored elements (usually none: +0).
-__device__ __forceinline__ void ew_fill_column(const GemmArgs& g, int which) {
-  const int col = g.zero_cols[which];
-  const int lo = g.ew_ptr[col], hi = g.ew_ptr[col + 1];
-  if (lo == hi) {                        // the usual case (uniform over the workgroup)
-    zero_fill_column(g, which);
-    return;
-  }
-  _Float16* row = g.C + (size_t)col * g.ldc;
-  for (int m = threadIdx.x * 8; m < g.M; m += (int)blockDim.x * 8) {
-    float s[1][8] = {{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}};
-    const int lo1[1] = {lo}, hi1[1] = {hi};
-    ew_accumulate<1>(g, lo1, hi1, g.A + m, s);
-    store_row_chunk(g, row + m, m, s[0]);
-  }
 }
 
 // SPLIT: K split across workgroups.  g.wg_split workgroups own the same (M-tile, N-tile) pair,
@@ -219,7 +178,7 @@ template <int TM, int TN, int WAVES_M, int D, bool DENSE, int NWAVES = 4, int KS
           bool SPLIT = false, bool MULTI = false, bool SCALAR = false>
 // (the TEW epilogue, the loop over jobs and the rows in flight must not cost an instance a wave per
 // SIMD: the second launch-bound asks the compiler to keep the register count within that occupancy)
-__global__ __launch_bounds__(NWAVES * 64, ((MULTI && TM * TN <= 64 * 128) || (!DENSE && !EW && KSPLIT == 1 && NWAVES == 8 && TM == 256)) ? 4 : ((EW || MULTI) && TM <= 128 && TN <= 128 && NWAVES == 4) ? 3 : 1)
+__global__ __launch_bounds__(NWAVES * 64, ((MULTI && TM * TN <= 64 * 128) || (!DENSE && KSPLIT == 1 && NWAVES == 8 && TM == 256)) ? 4 : ((EW || MULTI) && TM <= 128 && TN <= 128 && NWAVES == 4) ? 3 : 1)
 void tw_gemm_km_dma_kernel(GemmArgs g_arg) {
   constexpr bool LIDX = D > 3;             // how the kept-row list reaches the lanes (see fetch_rows)
   static_assert(!SCALAR || (!LIDX && !DENSE && KSPLIT == 1), "");
@@ -245,11 +204,12 @@ void tw_gemm_km_dma_kernel(GemmArgs g_arg) {
   static_assert(D >= 3 && D <= 8, "stages in flight");
   constexpr int NPS = NIA + NIB;
   constexpr int CA = TM / 8;
-  // epilogue row bytes: fp16, 66 dwords mod 64 banks = 2; with restored elements to add (EW) the
-  // tile is staged in fp32 so that their products join the sum before the one rounding
-  constexpr int CS = EW ? (TM + 4) * 4 : (TM + 4) * 2;
+  // epilogue row bytes: fp16, 66 dwords mod 64 banks = 2; with restored elements to add one by one (EW) the
+  // tile is staged in fp32, half at a time, so that their products join the sum before the one rounding
+  constexpr int CS = (TM + 4) * 2, CS32 = (TM + 4) * 4;
   static_assert(!(EW && DENSE), "");
-  constexpr int PIPE_BYTES = D * STAGE, EPI_BYTES = (EW ? TN / 2 : TN) * CS;   // EW stages half a tile at a time
+  constexpr int PIPE_BYTES = D * STAGE, EPI_BYTES = TN * CS;
+  static_assert(!EW || TN / 2 * CS32 <= EPI_BYTES, "");
   constexpr int RED_BYTES = KSPLIT > 1 ? TM * TN * 4 : 0;      // partial accumulators of group 1
   static_assert(RED_BYTES <= PIPE_BYTES, "the reduction reuses the pipeline buffers");
   // kept-row lists travel through LDS as well: a ring of two chunks of 8 stages' indices behind
@@ -270,8 +230,7 @@ void tw_gemm_km_dma_kernel(GemmArgs g_arg) {
   const int S = SPLIT ? g.wg_split : 1;
   const int n_gemm = g.n_mtiles * g.n_tiles * S;
   if (bid >= n_gemm) {
-    if constexpr (EW) ew_fill_column(g, bid - n_gemm);
-    else zero_fill_column(g, bid - n_gemm);
+    zero_fill_column(g, bid - n_gemm);
     return;
   }
   int mt, t;                             // t: launch position of the tile, then the tile itself
@@ -290,14 +249,17 @@ void tw_gemm_km_dma_kernel(GemmArgs g_arg) {
   const int m0 = mt * TM;
 
   int kp0, ns32;                                       // ns32: stages of 32 rows
+  int ns32_kept = 0, w_kept = 0;                       // EW: of these, stages of kept rows (joined rows follow); kept columns
   if constexpr (DENSE) { kp0 = 0; ns32 = g.K / KS; }   // host guarantees K % (32 KSPLIT) == 0
   else {
     // equal tiles in column order (the usual per-tile pruning recipe): the record follows from
     // the launch position, which saves the first of the kernel's dependent round trips
-    if (g.uniform_kp > 0) { kp0 = t * g.uniform_kp; ns32 = g.uniform_kp / KS; }
+    if (g.uniform_kp > 0) { kp0 = t * g.uniform_kp; ns32 = ns32_kept = g.uniform_kp / KS; }
     else {
       const int4v rec = scalar_load4(g.tile_sched + 4 * t);
       t = rec[0]; kp0 = rec[1]; ns32 = rec[2] / KS;
+      ns32_kept = (rec[3] & 0xffffff) / KS;
+      w_kept = (int)((uint32_t)rec[3] >> 24);
     }
   }
   if constexpr (SPLIT) {                               // this workgroup's share of the stages
@@ -305,7 +267,7 @@ void tw_gemm_km_dma_kernel(GemmArgs g_arg) {
     kp0 += first * KS;
     ns32 = last - first;
   }
-  const int ns = (ns32 + KSPLIT - 1) / KSPLIT;         // pipeline stages of KSS rows
+  int ns = (ns32 + KSPLIT - 1) / KSPLIT;               // pipeline stages of KSS rows
   const _Float16* Bt = DENSE ? g.vals + (size_t)t * TN : g.vals + (size_t)kp0 * TN;
   const int ldb = DENSE ? g.ldb : TN;
 
@@ -441,13 +403,6 @@ void tw_gemm_km_dma_kernel(GemmArgs g_arg) {
   };
 
   floatx16 acc[MB][NB];
-#pragma unroll
-  for (int i = 0; i < MB; ++i)
-#pragma unroll
-    for (int j = 0; j < NB; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-
   const int grp = wave / WPG, wl = wave % WPG;         // K-split group, wave inside the group
   const int wm = wl % WAVES_M, wn = wl / WAVES_M;
   // per-lane LDS byte address of each operand block at stage buffer 0, k-step 0
@@ -494,6 +449,16 @@ void tw_gemm_km_dma_kernel(GemmArgs g_arg) {
   using K0 = std::integral_constant<int, 0>;
   using K16 = std::integral_constant<int, 16>;
 
+  // EW: once with the joined rows, and, if that came out infinite or NaN anywhere in the tile, again with the kept rows
+  // alone and the restored elements one by one: a zero of a joined row times an infinity of A is no part of the product.
+  bool joined = EW;
+  for (;;) {
+#pragma unroll
+  for (int i = 0; i < MB; ++i)
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
   bool live_prev = false;
   // What an iteration does once stage s is in LDS: `cur` are the rows of stage s+D-1.
   auto consume = [&](int s, const Rows& cur, auto after_first_reads) {
@@ -597,6 +562,33 @@ void tw_gemm_km_dma_kernel(GemmArgs g_arg) {
     wait_vm<0>();                        // (nothing is outstanding: every copy has been waited for)
   }
   if (KSPLIT == 1 && !BRANCH ? ns > 0 : live_prev) mfma_step(f1);
+  if constexpr (EW) {
+    if (joined) {                                      // (uniform over the workgroup)
+      float z = 0.f;                                   // NaN unless everything is finite
+#pragma unroll
+      for (int i = 0; i < MB; ++i)
+#pragma unroll
+        for (int j = 0; j < NB; ++j)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) z = __builtin_fmaf(acc[i][j][r], 0.f, z);
+      const bool bad = __any(!(z == 0.f));
+      __syncthreads();                                 // everybody is done with the pipeline buffers
+      if (lane == 0) ((int*)lds)[wave] = bad;
+      __syncthreads();
+      int any = 0;
+#pragma unroll
+      for (int w = 0; w < NWAVES; ++w) any |= ((const int*)lds)[w];
+      if (any) {
+        joined = false;
+        ns32 = ns32_kept;
+        ns = (ns32 + KSPLIT - 1) / KSPLIT;
+        __syncthreads();                               // everybody has read the flags
+        continue;
+      }
+    }
+  }
+  break;
+  }
 
   if constexpr (SPLIT) {
     if (S > 1) {
@@ -677,23 +669,12 @@ void tw_gemm_km_dma_kernel(GemmArgs g_arg) {
     }
     __syncthreads();
   }
-  if constexpr (EW) {
-    // Restored elements of this thread's columns: [ew_lo, ew_hi) in the pair list.  Loaded here,
-    // not at kernel start, where the dependent loads would hold up the first copies.
-    int ew_lo[NPASS], ew_hi[NPASS];
-#pragma unroll
-    for (int i = 0; i < NPASS; ++i) {
-      const int col = cols[i] < 0 ? 0 : cols[i];          // unconditional loads, selected afterwards
-      const int p0 = g.ew_ptr[col], p1 = g.ew_ptr[col + 1];
-      const bool live = dst_off[i] >= 0;
-      ew_lo[i] = live ? p0 : 0;
-      ew_hi[i] = live ? p1 : 0;
-    }
+  if (EW && !joined) {
+    if constexpr (EW) {
     // fp32 staging, half of the tile's columns at a time (the staging area then fits the
     // pipeline buffers and does not cost occupancy); every thread finishes its
     // (column, 8 x m) pieces: restored elements added, one rounding, streaming store
     static_assert(NPASS % 2 == 0 && (TN / 2) % 32 == 0, "");
-    constexpr int P = (NPASS / 2) % 2 == 0 ? 2 : 1;      // columns finished together
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
       if (h) __syncthreads();
@@ -711,30 +692,28 @@ void tw_gemm_km_dma_kernel(GemmArgs g_arg) {
               floatx4 v;
 #pragma unroll
               for (int r = 0; r < 4; ++r) v[r] = acc[i][j][rq * 4 + r];
-              *(floatx4*)(lds + n * CS + mm * 4) = v;
+              *(floatx4*)(lds + n * CS32 + mm * 4) = v;
             }
           }
       }
       __syncthreads();
 #pragma unroll
-      for (int i = h * (NPASS / 2); i < (h + 1) * (NPASS / 2); i += P) {
-        float sum[P][8];
-        int lo2[P], hi2[P];
+      for (int i = h * (NPASS / 2); i < (h + 1) * (NPASS / 2); ++i) {
+        float sum[8];
+        const int n = r0 + i * ROWS_PER_PASS - h * (TN / 2);
+        const floatx4 lo4 = *(const floatx4*)(lds + n * CS32 + c * 32);
+        const floatx4 hi4 = *(const floatx4*)(lds + n * CS32 + c * 32 + 16);
 #pragma unroll
-        for (int p = 0; p < P; ++p) {
-          const int n = r0 + (i + p) * ROWS_PER_PASS - h * (TN / 2);
-          const floatx4 lo4 = *(const floatx4*)(lds + n * CS + c * 32);
-          const floatx4 hi4 = *(const floatx4*)(lds + n * CS + c * 32 + 16);
+        for (int q = 0; q < 4; ++q) { sum[q] = lo4[q]; sum[4 + q] = hi4[q]; }
+        if (dst_off[i] < 0) continue;
+        if (g.uniform_kp == 0 && r0 + i * ROWS_PER_PASS >= w_kept) {   // a dropped column: not even zeros of the kept rows
 #pragma unroll
-          for (int q = 0; q < 4; ++q) { sum[p][q] = lo4[q]; sum[p][4 + q] = hi4[q]; }
-          lo2[p] = ew_lo[i + p];
-          hi2[p] = ew_hi[i + p];
+          for (int q = 0; q < 8; ++q) sum[q] = 0.f;
         }
-        ew_accumulate<P>(g, lo2, hi2, g.A + (m < g.M ? m : 0), sum);
-#pragma unroll
-        for (int p = 0; p < P; ++p)
-          if (dst_off[i + p] >= 0) store_row_chunk(g, g.C + dst_off[i + p], m, sum[p]);
+        ew_accumulate(g, g.ew_ptr[cols[i]], g.ew_ptr[cols[i] + 1], g.A + m, sum);
+        store_row_chunk(g, g.C + dst_off[i], m, sum);
       }
+    }
     }
   } else {
     if (grp == 0) {

@@ -1,4 +1,4 @@
-// TW and TVW products with few output blocks (one sequence, decoding, small layers): bound by latency.
+// TW, TVW and TEW products with few output blocks (one sequence, decoding, small layers): bound by latency.
 //
 // The pipelined kernels give a workgroup a whole N-tile; a launch of a few dozen such workgroups
 // walks its kept rows stage by stage on a quarter of the chip, one barrier and one wait per stage.
@@ -16,6 +16,7 @@
 // Microseconds per launch in a stream of launches, pipelined kernels against this one, K x N:
 //   TW 75 %,    M = 128: 768 x 2304 4.1 / 3.2, 768 x 768 4.0 / 2.7, 768 x 3072 4.4 / 3.3, 3072 x 768 7.2 / 4.1
 //   TVW 87.5 %, M = 128: 768 x 2304 3.9 / 3.0, 3072 x 768 7.4 / 3.6, 1024 x 4096 4.3 / 3.4
+//   TEW 1 ... 1.5 %: 3784 x 1257 at 88 %, M = 11 23.8 / 8.5; 2048 x 512 at 90 %, M = 200 21 / 5.0; 320 x 64, G = 64, M = 59 8.6 / 2.9
 //   3 x 3 convolution 512 -> 512 at 14 x 14, one image, TW 75 %, G = 64: 10.8 / 4.7
 // 64 rows of A per workgroup (half the weight reads) gained at most 8 %, only next to the line where
 // the pipelined kernels take over, and lost up to 30 % elsewhere; 16 waves lost 20 % on short lists.
@@ -41,8 +42,27 @@ __device__ __forceinline__ int2v tr_read(uint32_t addr) {
 
 }  // namespace
 
-// SP: 2:4 inside the kept rows (TVW).  NW: waves.  U: k-steps of a wave in flight.
-template <bool SP, int NW, int U>
+// C^T[col][m] of a TEW weight term by term: the kept rows (row list and weights of the tile from kp0 on, column c), if the
+// column is a kept one, and the column's restored elements.  For results that came out infinite or NaN: there the zeros
+// of the joined rows must not count.
+__device__ __forceinline__ float ew_term_by_term(const GemmArgs& g, int G, int kp0, int kept, int c, int col, int m) {
+  float s = 0.f;
+  const _Float16* w = g.vals + (size_t)kp0 * G + (c / 32) * 512 + (c % 32) * 8;
+#pragma unroll 1
+  for (int j = 0; j < kept; ++j)
+    s = __builtin_fmaf((float)g.A[(size_t)g.row_idx[kp0 + j] * g.lda + m],
+                       (float)w[(size_t)(j / 16) * G * 16 + (j % 16) / 8 * 256 + j % 8], s);
+#pragma unroll 1
+  for (int e = g.ew_ptr[col]; e < g.ew_ptr[col + 1]; ++e) {
+    union { uint16_t b; _Float16 h; } v;
+    v.b = (uint16_t)g.ew_pairs[e];
+    s = __builtin_fmaf((float)g.A[(size_t)(g.ew_pairs[e] >> 16) * g.lda + m], (float)v.h, s);
+  }
+  return s;
+}
+
+// SP: 2:4 inside the kept rows (TVW).  NW: waves.  U: k-steps of a wave in flight.  EW: restored elements (TEW).
+template <bool SP, int NW, int U, bool EW>
 __global__ __launch_bounds__(NW * 64) void tw_gemm_small_kernel(GemmArgs g, int G, int n_blocks, int zero_cols_per_wg) {
   constexpr int NT = NW * 64;
   constexpr int KR = SP ? 32 : 16;                  // condensed rows per k-step
@@ -82,12 +102,12 @@ __global__ __launch_bounds__(NW * 64) void tw_gemm_small_kernel(GemmArgs g, int 
     }
   }
   const int CB = G / 32;
-  int t = nb / CB, kp0, kp;
+  int t = nb / CB, kp0, kp, kept = 0;
   const int cb = nb - t * CB;
   if (g.uniform_kp > 0) { kp0 = t * g.uniform_kp; kp = g.uniform_kp; }
   else {
     const int4v rec = *(const int4v*)(g.tile_sched + 4 * t);
-    t = rec[0]; kp0 = rec[1]; kp = rec[2];
+    t = rec[0]; kp0 = rec[1]; kp = rec[2]; kept = rec[3];
   }
   const int m0 = mt * 32;
   const int nk = kp / KR;
@@ -223,13 +243,24 @@ __global__ __launch_bounds__(NW * 64) void tw_gemm_small_kernel(GemmArgs g, int 
       if (++x == P) { x = 0; if (++y == L) y = 0; }
       if (x >= (uint32_t)g.conv_W || y >= (uint32_t)g.conv_H) s1 = 0.f;
     }
+    if constexpr (EW) {
+      if (!(s0 * 0.f == 0.f && s1 * 0.f == 0.f)) {  // infinite or NaN
+        const int c = cb * 32 + n, rows_kept = c < (int)((uint32_t)kept >> 24) ? kept & 0xffffff : 0;
+#pragma unroll 1
+        for (int h = 0; h < 2 && m + h < g.M; ++h) {
+          const float x = ew_term_by_term(g, G, kp0, rows_kept, c, cols[i], m + h);
+          if (h == 0) s0 = x;
+          else s1 = x;
+        }
+      }
+    }
     _Float16* dst = g.C + (size_t)cols[i] * g.ldc + m;
     if (m + 1 < g.M) *(half2v*)dst = half2v{(_Float16)s0, (_Float16)s1};
     else *dst = (_Float16)s0;
   }
 }
 
-template <bool SP, int NW, int U>
+template <bool SP, int NW, int U, bool EW = false>
 static hipError_t launch_small(int G, GemmArgs& g, hipStream_t stream) {
   g.n_mtiles = (g.M + 31) / 32;
   const int n_blocks = g.n_tiles * (G / 32);
@@ -238,7 +269,7 @@ static hipError_t launch_small(int G, GemmArgs& g, hipStream_t stream) {
   const int grid = n_blocks * g.n_mtiles + (g.n_zero + zper - 1) / zper;
   if (grid <= 0) return hipSuccess;
   (void)hipGetLastError();   // an error left behind by an earlier call of this thread is not this launch's
-  hipLaunchKernelGGL((tw_gemm_small_kernel<SP, NW, U>), dim3(grid), dim3(NW * 64), 0, stream, g, G, n_blocks, zper);
+  hipLaunchKernelGGL((tw_gemm_small_kernel<SP, NW, U, EW>), dim3(grid), dim3(NW * 64), 0, stream, g, G, n_blocks, zper);
   return hipGetLastError();
 }
 
@@ -247,12 +278,13 @@ static hipError_t launch_small(int G, GemmArgs& g, hipStream_t stream) {
 // 4.1 against 4.9).  TVW, k-steps of twice the rows: 4 waves for short lists and for more than two
 // workgroups per CU (768 x 3072 at M = 256: 3.5 against 4.6), else 8 (3072 x 768 at M = 128: 3.6
 // against 4.4).
-hipError_t launch_small_km(int G, bool sparse, int max_kp, GemmArgs g, hipStream_t stream) {
+hipError_t launch_small_km(int G, bool sparse, bool restored, int max_kp, GemmArgs g, hipStream_t stream) {
   const long blocks = (long)g.n_tiles * (G / 32) * ((g.M + 31) / 32);
   if (sparse) {
     if (max_kp <= 12 * 32 || blocks > 512) return launch_small<true, 4, 4>(G, g, stream);
     return launch_small<true, 8, 4>(G, g, stream);
   }
+  if (restored) return max_kp > 8 * 4 * 16 ? launch_small<false, 8, 8, true>(G, g, stream) : launch_small<false, 8, 4, true>(G, g, stream);
   if (max_kp > 8 * 4 * 16) return launch_small<false, 8, 8>(G, g, stream);
   return launch_small<false, 8, 4>(G, g, stream);
 }

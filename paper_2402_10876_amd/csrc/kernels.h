@@ -17,7 +17,8 @@ struct GemmArgs {
   const int32_t* tile_kp_off;    // TW: n_tiles+1 offsets into row_idx
   const int32_t* col_idx;        // TW: n_tiles*G kept-column indices, -1 = none (CTO_n)
   const int32_t* tile_order;     // TW: launch order of tiles (longest first) or null
-  const int32_t* tile_sched;     // TW: per launch position {tile, kp offset, Kp_t, width}, 16-byte records
+  const int32_t* tile_sched;     // TW: per launch position {tile, kp offset, Kp_t, of that kept rows | kept columns << 24},
+                                 // 16-byte records
   int uniform_kp;                // > 0: every tile has this padded K_t and launch position = tile, so the
                                  // record is (pos, pos * uniform_kp, uniform_kp) and need not be loaded
   const int32_t* zero_cols;      // pruned columns of C, written as +0
@@ -97,8 +98,9 @@ hipError_t launch_dense_km_dma(int tn, int tm, int depth, int variant, GemmArgs 
 hipError_t launch_zero_words(uint32_t* p, int n, hipStream_t stream);
 // TVW (2:4 inside the kept rows) on the sparse matrix instruction (gemm_tvw.hip).
 hipError_t launch_tvw_km(int G, int tm, int depth, GemmArgs g, hipStream_t stream);
-// Few 32 x 32 blocks of C: TW and TVW (sparse), any G (gemm_small.hip); max_kp: longest padded kept-row list.
-hipError_t launch_small_km(int G, bool sparse, int max_kp, GemmArgs g, hipStream_t stream);
+// Few 32 x 32 blocks of C: TW, TVW (sparse) and TEW (restored: with restored elements), any G (gemm_small.hip); max_kp:
+// longest padded row list.
+hipError_t launch_small_km(int G, bool sparse, bool restored, int max_kp, GemmArgs g, hipStream_t stream);
 bool small_km_pays(int G, bool sparse, int M, int n_tiles, int max_kp);
 
 }  // namespace twg

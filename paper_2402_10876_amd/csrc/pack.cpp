@@ -147,13 +147,19 @@ tw_status pack_host(const uint16_t* B, const uint8_t* mask, const uint8_t* tile_
     for (size_t i = 0, e = (size_t)K * N; i < e; ++i)
       if (tile_mask[i] && !mask[i]) return TW_ERR_MASK;
     h->ew_col_ptr.assign(N + 1, 0);
-    for (int n = 0; n < N; ++n) {
-      for (int k = 0; k < K; ++k) {
+    for (size_t i = 0, e = (size_t)K * N; i < e;)        // (rows of the masks one after the other, twice)
+      for (int n = 0; n < N; ++n, ++i) h->ew_col_ptr[n + 1] += mask[i] && !tile_mask[i];
+    for (int n = 0; n < N; ++n) h->ew_col_ptr[n + 1] += h->ew_col_ptr[n];
+    h->ew_row.resize(h->ew_col_ptr[N]);
+    h->ew_val.resize(h->ew_col_ptr[N]);
+    std::vector<int32_t> at(h->ew_col_ptr.begin(), h->ew_col_ptr.end() - 1);
+    for (int k = 0; k < K; ++k)
+      for (int n = 0; n < N; ++n) {
         const size_t i = (size_t)k * N + n;
-        if (mask[i] && !tile_mask[i]) { h->ew_row.push_back(k); h->ew_val.push_back(B[i]); }
+        if (!mask[i] || tile_mask[i]) continue;
+        h->ew_row[at[n]] = k;
+        h->ew_val[at[n]++] = B[i];
       }
-      h->ew_col_ptr[n + 1] = (int32_t)h->ew_row.size();
-    }
   }
   finish_lists(h);
   h->values.assign((size_t)h->val_off[h->n_tiles], 0);
@@ -330,39 +336,87 @@ static int kstep_of(const tw_handle_s* h) {
   return h->dtype == TW_DTYPE_I8 ? (tvw ? KSTEP_I8_TVW : KSTEP_I8) : tvw ? KSTEP_TVW : KSTEP_TW;
 }
 
-// What follows from the tiles' kept-row counts and widths alone: padded heights, launch order,
+// TEW: the tiles of the image.  Rows with restored elements join the tile's kept rows; the dropped columns that
+// have any follow the kept ones.
+static void plan_image_tiles(tw_handle_s* h) {
+  DeviceImage& d = h->img;
+  const int G = h->G;
+  d.n_tiles = h->n_tiles;
+  d.join_off.clear(); d.join_row.clear();
+  d.zero_cols.clear();
+  // (concatenated weights have narrow tiles in the middle as well)
+  d.col_idx.assign((size_t)h->n_tiles * G, -1);
+  for (int t = 0; t < h->n_tiles; ++t)
+    std::copy(h->col_idx.begin() + h->tile_col_off[t], h->col_idx.begin() + h->tile_col_off[t + 1],
+              d.col_idx.begin() + (size_t)t * G);
+  if (h->n_tiles > 0) d.col_idx.resize((size_t)(h->n_tiles - 1) * G + h->tile_col_off[h->n_tiles] - h->tile_col_off[h->n_tiles - 1]);
+  const bool join = !h->ew_row.empty() && G != 32;       // (no kernel for G = 32)
+  size_t j = 0;
+  for (int n = 0; n < h->N; ++n) {
+    if (j < h->col_idx.size() && h->col_idx[j] == n) { ++j; continue; }
+    if (join && h->ew_col_ptr[n + 1] > h->ew_col_ptr[n]) d.col_idx.push_back(n);
+    else d.zero_cols.push_back(n);
+  }
+  d.n_tiles = (int32_t)((d.col_idx.size() + G - 1) / G);
+  d.col_idx.resize((size_t)d.n_tiles * G, -1);
+  if (!join) return;
+  d.join_off.assign(1, 0);
+  std::vector<uint8_t> holds(h->K);
+  for (int t = 0; t < d.n_tiles; ++t) {
+    std::fill(holds.begin(), holds.end(), 0);
+    for (int c = 0; c < G; ++c) {
+      const int n = d.col_idx[(size_t)t * G + c];
+      if (n < 0) continue;
+      for (int e = h->ew_col_ptr[n]; e < h->ew_col_ptr[n + 1]; ++e) holds[h->ew_row[e]] = 1;
+    }
+    if (t < h->n_tiles)                                  // (a dropped column may use the kept rows)
+      for (int i = h->tile_k_off[t]; i < h->tile_k_off[t + 1]; ++i) holds[h->row_idx[i]] = 0;
+    for (int k = 0; k < h->K; ++k)
+      if (holds[k]) d.join_row.push_back(k);
+    d.join_off.push_back((int32_t)d.join_row.size());
+  }
+}
+
+// What follows from the tiles' kept-row counts and widths alone (TEW: and from the joined rows): padded heights, launch order,
 // sizes of the parts (so that a device image can be allocated before its contents exist).
 void plan_tiles(tw_handle_s* h) {
   DeviceImage& d = h->img;
-  const int G = h->G, nt = h->n_tiles;
+  if (h->pattern == TW_PATTERN_TEW) plan_image_tiles(h);
+  else {
+    d.n_tiles = h->n_tiles;
+    d.n_zero = h->N - h->n_kept;
+  }
+  const int G = h->G, nt = d.n_tiles;
   const bool tvw = h->pattern == TW_PATTERN_TVW;
   const bool i8 = h->dtype == TW_DTYPE_I8;
   const int kstep = kstep_of(h);
+  auto padded = [&](int k) { return (k + kstep - 1) / kstep * kstep; };
+  auto kept = [&](int t) { return t < h->n_tiles ? h->tile_k_off[t + 1] - h->tile_k_off[t] : 0; };
+  auto joined = [&](int t) { return d.join_off.empty() ? 0 : d.join_off[t + 1] - d.join_off[t]; };
+  if (h->pattern == TW_PATTERN_TEW) d.n_zero = (int32_t)d.zero_cols.size();
   d.tile_kp_off.assign(nt + 1, 0);
   h->max_kp = 0;
   for (int t = 0; t < nt; ++t) {
-    const int kt = h->tile_k_off[t + 1] - h->tile_k_off[t];
-    const int kp = (kt + kstep - 1) / kstep * kstep;
+    const int kp = padded(kept(t)) + padded(joined(t));
     d.tile_kp_off[t + 1] = d.tile_kp_off[t] + kp;
     h->max_kp = std::max(h->max_kp, kp);
   }
-  d.n_zero = h->N - h->n_kept;
   d.tile_order.resize(nt);
   for (int t = 0; t < nt; ++t) d.tile_order[t] = t;
   if (longest_first.load())
-    std::stable_sort(d.tile_order.begin(), d.tile_order.end(), [&](int a, int b) {
-      return h->tile_k_off[a + 1] - h->tile_k_off[a] > h->tile_k_off[b + 1] - h->tile_k_off[b];
-    });
+    std::stable_sort(d.tile_order.begin(), d.tile_order.end(),
+                     [&](int a, int b) { return kept(a) + joined(a) > kept(b) + joined(b); });
   d.tile_sched.resize((size_t)nt * 4);
   for (int pos = 0; pos < nt; ++pos) {
     const int t = d.tile_order[pos];
     d.tile_sched[4 * pos + 0] = t;
     d.tile_sched[4 * pos + 1] = d.tile_kp_off[t];
     d.tile_sched[4 * pos + 2] = d.tile_kp_off[t + 1] - d.tile_kp_off[t];
-    d.tile_sched[4 * pos + 3] = h->tile_col_off[t + 1] - h->tile_col_off[t];
+    const int width = t < h->n_tiles ? h->tile_col_off[t + 1] - h->tile_col_off[t] : 0;
+    d.tile_sched[4 * pos + 3] = h->pattern == TW_PATTERN_TEW ? padded(kept(t)) | width << 24 : 0;
   }
   // equal tiles launched in column order: the kernels can form the record from the position
-  d.uniform_kp = nt > 0 ? d.tile_sched[2] : 0;
+  d.uniform_kp = nt > 0 && d.join_off.empty() ? d.tile_sched[2] : 0;
   for (int pos = 0; pos < nt && d.uniform_kp; ++pos)
     if (d.tile_sched[4 * pos] != pos || d.tile_sched[4 * pos + 2] != d.uniform_kp ||
         d.tile_sched[4 * pos + 1] != pos * d.uniform_kp)
@@ -377,28 +431,32 @@ void plan_tiles(tw_handle_s* h) {
 void build_device_lists(tw_handle_s* h) {
   plan_tiles(h);
   DeviceImage& d = h->img;
-  const int G = h->G, nt = h->n_tiles;
-  d.col_idx.assign((size_t)nt * G, -1);
-  for (int t = 0; t < nt; ++t)
-    std::copy(h->col_idx.begin() + h->tile_col_off[t], h->col_idx.begin() + h->tile_col_off[t + 1],
-              d.col_idx.begin() + (size_t)t * G);
-  // slack behind the last tile (valid row 0): the K-split kernel copies stages of 64 rows and
-  // may run one 32-row stage past a tile's end (it never multiplies it), and the TW kernel with more than
-  // three stages in flight copies the list into LDS in chunks of 8 stages, up to two past a short tile
-  d.row_idx.assign((size_t)d.tile_kp_off[nt] + ROW_IDX_SLACK, 0);
-  for (int t = 0; t < nt; ++t) {
-    const int k0 = h->tile_k_off[t], kt = h->tile_k_off[t + 1] - k0;
-    const int kp0 = d.tile_kp_off[t], kp = d.tile_kp_off[t + 1] - kp0;
-    for (int j = 0; j < kp; ++j)
-      d.row_idx[kp0 + j] = kt ? h->row_idx[k0 + std::min(j, kt - 1)] : 0;
-  }
-  d.zero_cols.clear();
-  {
+  const int G = h->G, nt = d.n_tiles;
+  if (h->pattern != TW_PATTERN_TEW) {                    // (TEW: done with the plan)
+    d.col_idx.assign((size_t)nt * G, -1);
+    for (int t = 0; t < nt; ++t)
+      std::copy(h->col_idx.begin() + h->tile_col_off[t], h->col_idx.begin() + h->tile_col_off[t + 1],
+                d.col_idx.begin() + (size_t)t * G);
+    d.zero_cols.clear();
     size_t j = 0;
     for (int n = 0; n < h->N; ++n) {
       if (j < h->col_idx.size() && h->col_idx[j] == n) { ++j; continue; }
       d.zero_cols.push_back(n);
     }
+  }
+  // slack behind the last tile (valid row 0): the K-split kernel copies stages of 64 rows and
+  // may run one 32-row stage past a tile's end (it never multiplies it), and the TW kernel with more than
+  // three stages in flight copies the list into LDS in chunks of 8 stages, up to two past a short tile
+  d.row_idx.assign((size_t)d.tile_kp_off[nt] + ROW_IDX_SLACK, 0);
+  for (int t = 0; t < nt; ++t) {
+    const int k0 = t < h->n_tiles ? h->tile_k_off[t] : 0, kt = t < h->n_tiles ? h->tile_k_off[t + 1] - k0 : 0;
+    const int joined = d.join_off.empty() ? 0 : d.join_off[t + 1] - d.join_off[t];
+    const int kp0 = d.tile_kp_off[t], kp = d.tile_kp_off[t + 1] - kp0;
+    const int ktp = joined ? kp - (joined + KSTEP_TW - 1) / KSTEP_TW * KSTEP_TW : kp;
+    for (int j = 0; j < ktp; ++j)
+      d.row_idx[kp0 + j] = kt ? h->row_idx[k0 + std::min(j, kt - 1)] : 0;
+    for (int j = ktp; j < kp; ++j)
+      d.row_idx[kp0 + j] = d.join_row[d.join_off[t] + std::min(j - ktp, joined - 1)];
   }
   d.ew_ptr = h->ew_col_ptr;
   d.ew_pairs.resize(h->ew_row.size());
@@ -409,7 +467,7 @@ void build_device_lists(tw_handle_s* h) {
 // Where the parts lie in the one allocation of an image, 256-byte aligned.
 void layout_image(const tw_handle_s* h, ImageLayout* L) {
   const DeviceImage& d = h->img;
-  const size_t nt = (size_t)h->n_tiles;
+  const size_t nt = (size_t)d.n_tiles;
   size_t* b = L->bytes;
   b[IMG_TILE_KP_OFF] = (nt + 1) * 4;
   b[IMG_TILE_ORDER] = nt * 4;
@@ -449,7 +507,7 @@ void bind_image(tw_handle_s* h, void* blob, const ImageLayout& L, int device) {
 // The value parts of the device image, from the logical values (layouts above).
 void build_device_values(tw_handle_s* h) {
   DeviceImage& d = h->img;
-  const int G = h->G, nt = h->n_tiles;
+  const int G = h->G, nt = d.n_tiles;
   const bool tvw = h->pattern == TW_PATTERN_TVW;
   const bool i8 = h->dtype == TW_DTYPE_I8;
   if (i8 && tvw) {
@@ -509,7 +567,7 @@ void build_device_values(tw_handle_s* h) {
   }
   if (!tvw) {
     d.vals.assign(((size_t)d.tile_kp_off[nt] + KSTEP_TW) * G, 0);
-    for (int t = 0; t < nt; ++t) {
+    for (int t = 0; t < h->n_tiles; ++t) {
       const int kt = h->tile_k_off[t + 1] - h->tile_k_off[t];
       const int w = h->tile_col_off[t + 1] - h->tile_col_off[t];
       const uint16_t* v = h->values.data() + h->val_off[t];
@@ -519,6 +577,24 @@ void build_device_values(tw_handle_s* h) {
         const int jn = std::min(8, kt - j0);
         for (int c = 0; c < w; ++c)
           for (int j = 0; j < jn; ++j) ob[(c / 32) * 512 + (c % 32) * 8 + j] = v[(size_t)(j0 + j) * w + c];
+      }
+    }
+    if (!d.join_off.empty()) {                           // TEW: the restored elements in their rows
+      std::vector<int32_t> place(h->K);
+      for (int t = 0; t < nt; ++t) {
+        const int kt = t < h->n_tiles ? h->tile_k_off[t + 1] - h->tile_k_off[t] : 0;
+        const int ktp = (kt + KSTEP_TW - 1) / KSTEP_TW * KSTEP_TW;
+        uint16_t* o = d.vals.data() + (size_t)d.tile_kp_off[t] * G;
+        for (int i = 0; i < kt; ++i) place[h->row_idx[h->tile_k_off[t] + i]] = i;
+        for (int i = d.join_off[t]; i < d.join_off[t + 1]; ++i) place[d.join_row[i]] = ktp + i - d.join_off[t];
+        for (int c = 0; c < G; ++c) {
+          const int n = d.col_idx[(size_t)t * G + c];
+          if (n < 0) continue;
+          for (int e = h->ew_col_ptr[n]; e < h->ew_col_ptr[n + 1]; ++e) {
+            const int j = place[h->ew_row[e]];
+            o[(size_t)(j / 16) * G * 16 + (c / 32) * 512 + (j % 16 / 8 * 32 + c % 32) * 8 + j % 8] = h->ew_val[e];
+          }
+        }
       }
     }
     d.meta.clear();

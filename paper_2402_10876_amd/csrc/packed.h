@@ -23,19 +23,25 @@ constexpr int ROW_IDX_SLACK = 1024 + KSTEP_I8_TVW;   // readable entries behind 
 
 struct DeviceImage {
   // host staging (filled by the packer)
-  std::vector<int32_t> col_idx;      // n_tiles*G, -1 = no column (narrow last tile)
+  std::vector<int32_t> col_idx;      // n_tiles*G, -1 = no column (narrow last tile; TEW: n_tiles of the image)
   std::vector<int32_t> tile_kp_off;  // n_tiles+1, prefix sums of padded K_t
   std::vector<int32_t> row_idx;      // sum Kp_t; pads repeat the tile's last kept row (0 if none)
-  std::vector<int32_t> zero_cols;    // original indices of pruned columns
+  std::vector<int32_t> zero_cols;    // original indices of the columns of C that are +0
   std::vector<int32_t> tile_order;   // tiles by descending K_t (longest first)
-  std::vector<int32_t> tile_sched;   // per launch position: {tile, kp offset, Kp_t, width}
+  std::vector<int32_t> tile_sched;   // per launch position: {tile, kp offset, Kp_t, padded kept rows (TEW: without the
+                                     // joined ones) | kept columns << 24}
   std::vector<uint16_t> vals;        // TW: condensed rows, TVW: compressed values; both in register order
   std::vector<int8_t> vals8;         // int8: TW [sum Kp_t][G] bytes, TVW swizzled compressed bytes (vals is empty then)
   std::vector<uint32_t> meta;        // TVW: swizzled 2-bit position words
   std::vector<int32_t> ew_ptr;       // TEW: N+1 offsets into ew_pairs, by original column
   std::vector<uint32_t> ew_pairs;    // TEW: restored elements, row << 16 | fp16 bits
+  // TEW: in row_idx and vals a tile's kept rows are followed by the rows that hold restored elements in its columns
+  // ("joined": zeros elsewhere), and dropped columns with restored elements follow the kept ones, in what the last
+  // tile has left and in tiles of their own
+  std::vector<int32_t> join_off, join_row;           // per tile of the image: its joined rows
+  int32_t n_tiles = 0;                               // tiles of the image
   int32_t uniform_kp = 0;            // > 0: all tiles have this padded K_t and are launched in column order
-  int32_t n_zero = 0;                // pruned columns
+  int32_t n_zero = 0;                // columns of C that are +0: the pruned ones (TEW: without restored elements)
   size_t n_vals = 0, n_meta = 0;     // elements of the value / position-word parts (set with the lists)
   // device copies (one allocation, sub-pointers)
   void* blob = nullptr;

@@ -145,6 +145,76 @@ def test_tew_random_masks_and_M_tails(M, G, _opts):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("G,tile_m,ksplit", [(128, 64, 1), (128, 128, 1), (128, 256, 1), (128, 128, 2), (128, 64, 2), (64, 128, 1),
+                                             (64, 256, 1)])
+def test_tew_infinities_stay_in_the_columns_that_refer_to_them(G, tile_m, ksplit, _opts):
+    """Rows with several restored elements are multiplied whole, zeros included; an infinity or NaN of A in such a row
+    must reach the columns that hold one of its elements and no other."""
+    rng = np.random.default_rng(G + tile_m + ksplit)
+    K, N, M = 210, 300, 270
+    m, tm = random_tew_mask(rng, K, N, G, extra=0.05, col_keep=0.9, row_keep=0.3)
+    A, B = wl.make_A(4, M, K), wl.make_B(4, K, N, 1.0)
+    B[B == 0] = 1
+    restored = (m != 0) & (tm == 0)
+    # (row 0 and the tiles' last kept rows also stand in, times +0, where a list is padded)
+    padding = np.append(K - 1 - tm[::-1].argmax(0)[tm.any(0)], 0)
+    ks = np.setdiff1d(np.flatnonzero(restored.any(1)), padding)[[0, 7, -1]]
+    A[3, ks[0]], A[4, ks[1]], A[M - 1, ks[2]] = np.inf, np.nan, -np.inf
+    tw.tw_set_option("tile_m", tile_m)
+    tw.tw_set_option("ksplit", ksplit)
+    print(f"case tew infinities G={G} tile_m={tile_m} ksplit={ksplit}", flush=True)
+    _check_infinities(A, B, m, *_gpu_run(B, m, tm, G, A))
+
+
+def _check_infinities(A, B, m, C, _raw):
+    N = B.shape[1]
+    with np.errstate(invalid="ignore"):
+        want = np.stack([A[:, m[:, n] != 0].astype(np.float64) @ B[m[:, n] != 0, n].astype(np.float64) for n in range(N)], axis=1)
+    fin = np.isfinite(want)
+    assert not fin.all() and (~fin).sum() < fin.sum()
+    assert np.array_equal(np.isfinite(C), fin) and np.array_equal(np.isnan(C), np.isnan(want))
+    assert np.array_equal(C[~fin & ~np.isnan(want)], want[~fin & ~np.isnan(want)])
+    F = np.where(np.isfinite(A), A, np.float16(0))
+    ref, S = og.gemm_oracle(F, B, m), og.abs_bound(F, B, m)
+    assert_C_close(np.where(fin, C, ref), ref, S)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("G,M,K,N,col_keep", [(128, 40, 210, 300, 0.9), (64, 5, 900, 190, 0.6), (64, 33, 100, 64, 1.0),
+                                              (128, 1, 2000, 100, 0.1)])
+def test_tew_few_blocks(G, M, K, N, col_keep, _opts):
+    """The kernel for few output blocks, finite (also A = I, bit for bit) and with infinities."""
+    rng = np.random.default_rng(G + M)
+    m, tm = random_tew_mask(rng, K, N, G, extra=0.03, col_keep=col_keep, row_keep=0.3)
+    A, B = wl.make_A(6, M, K), wl.make_B(6, K, N, 1.0)
+    print(f"case tew few blocks G={G} M={M}", flush=True)
+    C, _ = _gpu_run(B, m, tm, G, A)
+    assert_C_close(C, og.gemm_oracle(A, B, m), og.abs_bound(A, B, m))
+    eye = np.zeros((M, K), np.float16)
+    at = rng.choice(K, M, replace=False)
+    eye[np.arange(M), at] = 1
+    _, raw = _gpu_run(B, m, tm, G, eye)
+    want = np.where(m != 0, B, np.float16(0)).astype(np.float16)[at]
+    assert np.array_equal(raw[:, :M].T.view(np.uint16), want.view(np.uint16))
+    padding = np.append(K - 1 - tm[::-1].argmax(0)[tm.any(0)], 0)
+    ks = np.setdiff1d(np.flatnonzero(((m != 0) & (tm == 0)).any(1)), padding)[[0, -1]]
+    A[0, ks[0]], A[M - 1, ks[1]] = np.inf, -np.inf
+    B[B == 0] = 1
+    _check_infinities(A, B, m, *_gpu_run(B, m, tm, G, A))
+
+
+def test_tew_image_join_counts_only_shape_the_device_form():
+    """tw_flop_counts, tw_export and tw_unpack know nothing of the rows that are multiplied whole."""
+    rng = np.random.default_rng(31)
+    m, tm = random_tew_mask(rng, 300, 200, 64, extra=0.05)
+    B = wl.make_B(31, 300, 200, 1.0)
+    p = tw.tw_pack_host(B, m, 64, tw.PATTERN_TEW, tile_mask=tm)
+    assert p.flop_counts()[0] == int(tm.sum())
+    _same_tew(p.export(), opk.ref_pack(B, m, 64, opk.PATTERN_TEW, tile_mask=tm))
+    p.free()
+
+
+@pytest.mark.gpu
 def test_tew_without_restored_elements_equals_tw(_opts):
     from tests import gpu_util as gu
     rng = np.random.default_rng(77)
