@@ -19,10 +19,14 @@
 //             for, pruned ones as +0, and stored in whole 16-byte pieces of C's rows; a piece at
 //             the end of the range that belongs to two workgroups is stored element by element.
 //
-// What bounds it: with one workgroup of 8 waves per CU the phases of a group (K loop 2 us, bound by
-// the LDS reads of gathered rows; staging 0.6 us; stores 1.2 us) do not overlap, and the first band
-// takes 4 us to arrive.  75 %, M = 4096, K x N: 768 x 2304 21.2 us, 768 x 768 11.2, 768 x 3072 23.0,
-// 3072 x 768 27.8 us, against 82, 55, 88 and 55 us with 2-byte gathers and scatters.
+// What bounds it: with one workgroup of 8 waves per CU the phases of a group do not overlap.  768 x 2304 at M = 4096, 75 %,
+// by timestamps: the first band 3.8 us, then per group of two tiles the K loop 2.0 to 2.6 us (1.3 to 1.7 without the next
+// tile's loads, which share the CU's 64 bytes a clock), 0.3 to 0.9 waiting for the slowest wave, staging 0.45, stores 0.55 to
+// 0.85.  75 %, M = 4096, K x N: 768 x 2304 17.2 us, 768 x 768 8.8, 768 x 3072 18.7, 3072 x 768 20.2.
+// Tried on that and not kept: staging condensed columns and reading them back with the transposing read (17.4, fewer LDS
+// instructions, no faster), stores through a buffer descriptor whose number the compiler can count (18.6 with it), reads of
+// the rows two k-steps ahead (17.3), 12 k-steps of weights in flight for a long K (3072 x 768 21.9), two bands on their
+// way (26.3).
 #include <type_traits>
 
 #include "device_common.h"
@@ -35,21 +39,13 @@ namespace {
 constexpr uint32_t MK_ZERO = MK_KC;    // row of zeros behind the band
 constexpr int MK_NW = 8, MK_NT = MK_NW * 64;
 
-// LDS offset of row k of the band, in units of 16 bytes (above: row, low bits: XOR mask of the
-// row's 16-byte chunks).  The 8 x 8 blocks are written with k = 8 kc + j, one j at a time for
-// consecutive kc: bits 3 and up of k permute neighbouring rows and the chunks inside a row, so that a
-// wave's writes cover the 256-byte bank period evenly; the low bits of k send the four
-// consecutive rows of a read to the four quarters of the period.
+// LDS offset of row k of the band: rows of TM * 2 bytes, and 16 bytes more after every 8 of them.  The 8 x 8 blocks are
+// written with k = 8 kc + j, one j at a time for consecutive kc, which the 16 bytes spread evenly over the banks; the
+// rows that a read gathers are any rows, so no order would help it.  Two instructions, for the K loop was bound by
+// their number: with rows and chunks permuted by exclusive-or (eleven, 21 of vector arithmetic per k-step in all) 75 %, M =
+// 4096 took 18.5 us for 768 x 2304, now 17.2; 768 x 768 9.4, 8.8; 768 x 3072 20.0, 18.7; 3072 x 768 22.2, 20.2.
 template <int TM>
-__device__ __forceinline__ uint32_t mk_row_unit(uint32_t k) {
-  if constexpr (TM == 64) {
-    const uint32_t row = k ^ ((k >> 3) & 1u);
-    const uint32_t x = ((k >> 3) & 3u) | ((((k >> 5) ^ (k >> 1)) & 1u) << 2);
-    return row << 3 | x;
-  } else {
-    return (k ^ ((k >> 3) & 3u)) << 2 | ((k >> 5) & 3u);
-  }
-}
+constexpr __device__ __forceinline__ uint32_t mk_row(uint32_t k) { return ((k & 0xffffffu) * (TM * 2 + 2)) & ~15u; }   // (24-bit multiply)
 
 __device__ __forceinline__ half8 mk_operand(const char* lo, const char* hi) {
   union { short4v s[2]; half8 h; } u;
@@ -71,7 +67,7 @@ __global__ __launch_bounds__(MK_NT, TM == 32 ? 4 : 2) void tw_gemm_mk_kernel(Gem
   constexpr int SLOTS = MK_NW / SW;
   constexpr int NM = TM / 32;                       // blocks of 32 rows
   constexpr int KB = MK_KB<TM>;                     // columns of A a wave turns round at a time
-  constexpr int A_BYTES = (MK_KC + 8) * TM * 2;     // LDS bytes of the band, TM * 2 per k
+  constexpr int A_BYTES = (int)mk_row<TM>(MK_ZERO) + TM * 2;        // LDS bytes of the band, the row of zeros the last
   constexpr int RW = TM / MK_NW;                    // rows of C a wave stores
   constexpr int PF = TM == 32 ? 6 : LONG ? 8 : 14;                 // k-steps of weights and kept rows in flight
   // output staging: 64 rows of 368 columns (256 kept ones and the pruned ones between them, usually);
@@ -111,8 +107,7 @@ __global__ __launch_bounds__(MK_NT, TM == 32 ? 4 : 2) void tw_gemm_mk_kernel(Gem
       u32x4 w;
 #pragma unroll
       for (int d = 0; d < 4; ++d) w[d] = __builtin_amdgcn_perm(v[2 * d + 1][j >> 1], v[2 * d][j >> 1], sel);
-      const uint32_t unit = mk_row_unit<TM>((uint32_t)(kb * KB + kc * 8 + j)) ^ (uint32_t)mg;
-      *(u32x4*)(lds + unit * 16) = w;
+      *(u32x4*)(lds + mk_row<TM>((uint32_t)(kb * KB + kc * 8)) + mg * 16 + j * (TM * 2)) = w;
     }
   };
   char* stg = lds + A_BYTES;
@@ -189,7 +184,7 @@ __global__ __launch_bounds__(MK_NT, TM == 32 ? 4 : 2) void tw_gemm_mk_kernel(Gem
     for (int u = 0; u < PF; ++u) fetch(cur, u < cur.nk ? u : 0, u);
     load_head(group_of(gr_n > 1 ? 1 : 0));
     for (int i = tid; i < TM * PITCH / 16; i += MK_NT) *(u32x4*)(stg + i * 16) = u32x4{0u, 0u, 0u, 0u};
-    if (tid < TM / 8) *(u32x4*)(lds + (mk_row_unit<TM>(MK_ZERO) ^ (uint32_t)tid) * 16) = u32x4{0u, 0u, 0u, 0u};
+    if (tid < TM / 8) *(u32x4*)(lds + mk_row<TM>(MK_ZERO) + tid * 16) = u32x4{0u, 0u, 0u, 0u};
     if (wave * KB < (LONG ? kc_max : MK_KC)) store_block(wave, v0);
     if (two) store_block(wave + 8, v1);
   }
@@ -226,11 +221,11 @@ __global__ __launch_bounds__(MK_NT, TM == 32 ? 4 : 2) void tw_gemm_mk_kernel(Gem
       // operands of a k-step: rows of the other bands read the row of zeros
       auto operands = [&](int u, half8 (&a)[NM]) {
         const uint32_t k = (uint32_t)(r[u] - k0);
-        const int unit = (int)(mk_row_unit<TM>(k < (uint32_t)kn ? k : MK_ZERO) << 4);
-        const uint32_t lo = (uint32_t)__builtin_amdgcn_mov_dpp(unit, 0xA0, 0xf, 0xf, false) ^ xa;   // lanes 0,0,2,2 of each four
-        const uint32_t hi = (uint32_t)__builtin_amdgcn_mov_dpp(unit, 0xF5, 0xf, 0xf, false) ^ xa;   // lanes 1,1,3,3
+        const int row = (int)mk_row<TM>(!LONG || k < (uint32_t)kn ? k : MK_ZERO);
+        const uint32_t lo = (uint32_t)__builtin_amdgcn_mov_dpp(row, 0xA0, 0xf, 0xf, false) + xa;   // lanes 0,0,2,2 of each four
+        const uint32_t hi = (uint32_t)__builtin_amdgcn_mov_dpp(row, 0xF5, 0xf, 0xf, false) + xa;   // lanes 1,1,3,3
         a[0] = mk_operand(lds + lo, lds + hi);
-        if constexpr (NM == 2) a[1] = mk_operand(lds + (lo ^ 64u), lds + (hi ^ 64u));
+        if constexpr (NM == 2) a[1] = mk_operand(lds + lo + 64, lds + hi + 64);
       };
       auto multiply = [&](int u, const half8 (&a)[NM]) {
         acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[0], b[u], acc[0], 0, 0, 0);
