@@ -790,10 +790,8 @@ static hipError_t launch(const GemmArgs& g, hipStream_t stream) {
   if (jobs <= 0) return hipSuccess;
   const int tpw = MULTI && g.tiles_per_wg > 1 ? g.tiles_per_wg : 1;
   const int grid = MULTI ? ((jobs + tpw - 1) / tpw + 7) / 8 * 8 : jobs;
-  (void)hipGetLastError();   // an error left behind by an earlier call of this thread is not this launch's
-  hipLaunchKernelGGL((tw_gemm_km_dma_kernel<TM, TN, WAVES_M, D, DENSE, NWAVES, KSPLIT, EW, SPLIT, MULTI, SCALAR>), dim3(grid),
-                     dim3(NWAVES * 64), 0, stream, g);
-  return hipGetLastError();
+  return launch_kernel(tw_gemm_km_dma_kernel<TM, TN, WAVES_M, D, DENSE, NWAVES, KSPLIT, EW, SPLIT, MULTI, SCALAR>, dim3(grid),
+                       dim3(NWAVES * 64), stream, g);
 }
 
 // TEW instances: three stages in flight only.
@@ -871,9 +869,7 @@ static __global__ void zero_words(uint32_t* p, int n) {
 }
 hipError_t launch_zero_words(uint32_t* p, int n, hipStream_t stream) {
   if (n <= 0) return hipSuccess;
-  (void)hipGetLastError();
-  hipLaunchKernelGGL(zero_words, dim3((n + 255) / 256), dim3(256), 0, stream, p, n);
-  return hipGetLastError();
+  return launch_kernel(zero_words, dim3((n + 255) / 256), dim3(256), stream, p, n);
 }
 
 hipError_t launch_tw_km_dma_split(int G, int tm, GemmArgs g, hipStream_t stream) {

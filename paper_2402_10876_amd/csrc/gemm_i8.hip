@@ -531,26 +531,21 @@ template <int TM, int TN, int WAVES_M, bool DENSE, int NWAVES = 4, int KSPLIT = 
 static hipError_t launch8(const GemmI8Args& g, hipStream_t stream) {
   const int grid = g.n_mtiles * g.n_tiles + g.n_zero;
   if (grid <= 0) return hipSuccess;
-  (void)hipGetLastError();   // an error left behind by an earlier call of this thread is not this launch's
   auto go = [&](auto VEC_) {
     constexpr bool VEC = decltype(VEC_)::value;
     if (g.c_i8)
-      hipLaunchKernelGGL((tw_gemm_i8_kernel<TM, TN, WAVES_M, DENSE, true, NWAVES, KSPLIT, VEC>), dim3(grid),
-                         dim3(NWAVES * 64), 0, stream, g);
+      return launch_kernel(tw_gemm_i8_kernel<TM, TN, WAVES_M, DENSE, true, NWAVES, KSPLIT, VEC>, dim3(grid), dim3(NWAVES * 64), stream, g);
     else
-      hipLaunchKernelGGL((tw_gemm_i8_kernel<TM, TN, WAVES_M, DENSE, false, NWAVES, KSPLIT, VEC>), dim3(grid),
-                         dim3(NWAVES * 64), 0, stream, g);
+      return launch_kernel(tw_gemm_i8_kernel<TM, TN, WAVES_M, DENSE, false, NWAVES, KSPLIT, VEC>, dim3(grid), dim3(NWAVES * 64), stream, g);
   };
   // Row indices by vector loads with at most two workgroups per CU (same buffers, scalar / vector, TW 75 %,
   // int8 output: 3072 x 768 at M = 4096 9.2 / 8.4 us, 768 x 768 5.5 / 5.3, 2048 x 2048 x 2048 of G = 64 at 80 %
   // 7.1 / 6.0, 64 x 4096 x 4096 8.5 / 6.7); with more the scalar round trip is hidden and the extra request to the
   // copy unit is not (768 x 2304 at M = 4096, 576 workgroups 7.6 / 8.2; 768 x 3072 8.1 / 8.6; 750
   // workgroups of 64-wide tiles 5.8 / 6.0).
-  if constexpr (DENSE) go(std::false_type{});
-  else if constexpr (KSPLIT > 1) go(std::true_type{});
-  else if ((long)g.n_mtiles * g.n_tiles <= 512) go(std::true_type{});
-  else go(std::false_type{});
-  return hipGetLastError();
+  if constexpr (DENSE) return go(std::false_type{});
+  else if constexpr (KSPLIT > 1) return go(std::true_type{});
+  else return (long)g.n_mtiles * g.n_tiles <= 512 ? go(std::true_type{}) : go(std::false_type{});
 }
 
 template <bool DENSE>

@@ -362,10 +362,8 @@ static hipError_t launch_mk(GemmArgs& g, hipStream_t stream) {
   parts = (groups + per - 1) / per;
   const dim3 grid((unsigned)(g.n_mtiles * parts));
   if (g.K > MK_KC)
-    hipLaunchKernelGGL((tw_gemm_mk_kernel<G, true, TM, CAREFUL>), grid, dim3(MK_NT), 0, stream, g, groups, parts, per, MK_KC_LONG<TM>);
-  else
-    hipLaunchKernelGGL((tw_gemm_mk_kernel<G, false, TM, CAREFUL>), grid, dim3(MK_NT), 0, stream, g, groups, parts, per, MK_KC);
-  return hipGetLastError();
+    return launch_kernel(tw_gemm_mk_kernel<G, true, TM, CAREFUL>, grid, dim3(MK_NT), stream, g, groups, parts, per, MK_KC_LONG<TM>);
+  return launch_kernel(tw_gemm_mk_kernel<G, false, TM, CAREFUL>, grid, dim3(MK_NT), stream, g, groups, parts, per, MK_KC);
 }
 
 // Rows of a band.  32: twice the workgroups, two per CU, which overlap their phases and give few blocks
@@ -384,11 +382,8 @@ static hipError_t launch_mk_rows(int max_kp, bool nonfinite, GemmArgs& g, hipStr
 }
 
 hipError_t launch_tw_mk(int G, int max_kp, bool nonfinite, GemmArgs g, hipStream_t stream) {
-  (void)hipGetLastError();   // an error left behind by an earlier call of this thread is not this launch's
-  if (g.n_tiles == 0) {
-    hipLaunchKernelGGL(zero_mk, dim3((g.N + 255) / 256, g.M < 1024 ? g.M : 1024), dim3(256), 0, stream, g.C, g.M, g.N, g.ldc);
-    return hipGetLastError();
-  }
+  if (g.n_tiles == 0)
+    return launch_kernel(zero_mk, dim3((g.N + 255) / 256, g.M < 1024 ? g.M : 1024), dim3(256), stream, g.C, g.M, g.N, g.ldc);
   if (G == 128) return launch_mk_rows<128>(max_kp, nonfinite, g, stream);
   if (G == 64) return launch_mk_rows<64>(max_kp, nonfinite, g, stream);
   if (G == 32) return launch_mk_rows<32>(max_kp, nonfinite, g, stream);

@@ -268,9 +268,7 @@ static hipError_t launch_small(int G, GemmArgs& g, hipStream_t stream) {
   const int zper = chunks < NW * 64 ? NW * 64 / chunks : 1;       // pruned columns per workgroup that clears them
   const int grid = n_blocks * g.n_mtiles + (g.n_zero + zper - 1) / zper;
   if (grid <= 0) return hipSuccess;
-  (void)hipGetLastError();   // an error left behind by an earlier call of this thread is not this launch's
-  hipLaunchKernelGGL((tw_gemm_small_kernel<SP, NW, U, EW>), dim3(grid), dim3(NW * 64), 0, stream, g, G, n_blocks, zper);
-  return hipGetLastError();
+  return launch_kernel(tw_gemm_small_kernel<SP, NW, U, EW>, dim3(grid), dim3(NW * 64), stream, g, G, n_blocks, zper);
 }
 
 // Waves and k-steps in flight.  TW: 8 waves; 8 k-steps where the lists are longer than 8 x 4 of them

@@ -412,10 +412,7 @@ static hipError_t launch(const GemmArgs& g, hipStream_t stream) {
   constexpr bool VEC = D == 3;           // (a deeper pipeline would wait for its index loads)
   const int grid = g.n_mtiles * g.n_tiles + g.n_zero;
   if (grid <= 0) return hipSuccess;
-  (void)hipGetLastError();   // an error left behind by an earlier call of this thread is not this launch's
-  hipLaunchKernelGGL((tvw_gemm_km_kernel<TM, TN, WAVES_N, D, NW, VEC>), dim3(grid), dim3(NW * 64), 0,
-                     stream, g);
-  return hipGetLastError();
+  return launch_kernel(tvw_gemm_km_kernel<TM, TN, WAVES_N, D, NW, VEC>, dim3(grid), dim3(NW * 64), stream, g);
 }
 
 hipError_t launch_tvw_km(int G, int tm, int depth, GemmArgs g, hipStream_t stream) {

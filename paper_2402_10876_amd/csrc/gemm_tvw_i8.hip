@@ -354,12 +354,8 @@ template <int TM, int TN, int WAVES_N>
 static hipError_t launch_tvw8(const GemmI8Args& g, hipStream_t stream) {
   const int grid = g.n_mtiles * g.n_tiles + g.n_zero;
   if (grid <= 0) return hipSuccess;
-  (void)hipGetLastError();   // an error left behind by an earlier call of this thread is not this launch's
-  if (g.c_i8)
-    hipLaunchKernelGGL((tvw_gemm_i8_kernel<TM, TN, WAVES_N, true>), dim3(grid), dim3(256), 0, stream, g);
-  else
-    hipLaunchKernelGGL((tvw_gemm_i8_kernel<TM, TN, WAVES_N, false>), dim3(grid), dim3(256), 0, stream, g);
-  return hipGetLastError();
+  if (g.c_i8) return launch_kernel(tvw_gemm_i8_kernel<TM, TN, WAVES_N, true>, dim3(grid), dim3(256), stream, g);
+  return launch_kernel(tvw_gemm_i8_kernel<TM, TN, WAVES_N, false>, dim3(grid), dim3(256), stream, g);
 }
 
 hipError_t launch_tvw_i8(int G, int tm, GemmI8Args g, hipStream_t stream) {

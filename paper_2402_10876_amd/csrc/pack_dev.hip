@@ -30,6 +30,7 @@
 #include <new>
 #include <vector>
 
+#include "launch.h"
 #include "mk_band.h"
 #include "packed.h"
 
@@ -502,8 +503,7 @@ size_t up(size_t x) { return (x + 255) / 256 * 256; }
 #define TWG_TRY(expr) do { if ((expr) != hipSuccess) { (void)hipGetLastError(); return TW_ERR_HIP; } } while (0)
 #define TWG_LAUNCH(kernel, grid, block, ...)                                  \
   do {                                                                        \
-    hipLaunchKernelGGL(kernel, grid, block, 0, s, __VA_ARGS__);               \
-    if (hipGetLastError() != hipSuccess) return TW_ERR_HIP;                   \
+    if (launch_kernel(kernel, grid, block, s, __VA_ARGS__) != hipSuccess) return TW_ERR_HIP; \
   } while (0)
 
 }  // namespace

@@ -567,12 +567,10 @@ hipError_t prune_device(const uint16_t* B, int K, int N, int ldb, int G, bool tv
   int32_t* row_list = (int32_t*)w;
   const int lg = G == 128 ? 7 : G == 64 ? 6 : 5;
   auto aligned = [](const void* p, size_t a) { return ((uintptr_t)p & (a - 1)) == 0; };
-  (void)hipGetLastError();   // an error left behind by an earlier call of this thread is not this call's
   // a failed launch ends the call: later kernels would read workspace nobody wrote
 #define TWG_LAUNCH(kernel, grid, block, ...)                                  \
   do {                                                                        \
-    hipLaunchKernelGGL(kernel, grid, block, 0, stream, __VA_ARGS__);          \
-    const hipError_t e_ = hipGetLastError();                                  \
+    const hipError_t e_ = launch_kernel(kernel, grid, block, stream, __VA_ARGS__); \
     if (e_ != hipSuccess) return e_;                                          \
   } while (0)
   TWG_LAUNCH(column_scores, dim3((unsigned)((N + SCORE_CW - 1) / SCORE_CW)), dim3(1024), B, K, N, ldb,
