@@ -17,7 +17,7 @@ PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 LIB = os.path.join(PKG, "libtwgemm.so")
 HASH_FILE = LIB + ".srchash"
-SOURCES = ["api.cpp", "pack.cpp", "gemm_kernels.hip", "gemm_dma.hip", "gemm_mk.hip", "gemm_small.hip", "gemm_tvw.hip", "gemm_i8.hip", "gemm_tvw_i8.hip", "prune.hip", "pack_dev.hip", "calibrate.hip"]
+SOURCES = ["api.cpp", "pack.cpp", "gemm_kernels.hip", "gemm_dma.hip", "gemm_mk.hip", "gemm_small.hip", "gemm_small_i8.hip", "gemm_tvw.hip", "gemm_i8.hip", "gemm_tvw_i8.hip", "prune.hip", "pack_dev.hip", "calibrate.hip"]
 # the launch calls as a CPython module (csrc/pycall.cpp), for this interpreter (its tag is in the name); optional:
 # without it the binding makes these calls through ctypes
 CALL = os.path.join(PKG, "_twcall" + (sysconfig.get_config_var("EXT_SUFFIX") or ".so"))

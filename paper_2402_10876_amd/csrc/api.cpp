@@ -657,6 +657,10 @@ static tw_status gemm_i8_launch(const void* A, int M, int lda, tw_handle_t h, vo
   g.n_tiles = h->n_tiles; g.K = h->K; g.N = h->N; g.xcd_map = o.xcd_map ? 1 : 0;
   g.meta = h->img.d_meta;
   hipError_t e;
+  if (automatic(o) && twg::small_i8_pays(h->G, h->pattern == TW_PATTERN_TVW, M, h->n_tiles, h->max_kp)) {
+    e = twg::launch_small_i8(h->G, h->pattern == TW_PATTERN_TVW, h->max_kp, g, (hipStream_t)stream);
+    return e == hipSuccess ? TW_OK : TW_ERR_HIP;
+  }
   if (h->pattern == TW_PATTERN_TVW) {
     // 64-row tiles where 128-row tiles would not give every CU a workgroup
     const int forced = o.tile_m;

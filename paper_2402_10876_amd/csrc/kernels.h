@@ -102,5 +102,8 @@ hipError_t launch_tvw_km(int G, int tm, int depth, GemmArgs g, hipStream_t strea
 // longest padded row list.
 hipError_t launch_small_km(int G, bool sparse, bool restored, int max_kp, GemmArgs g, hipStream_t stream);
 bool small_km_pays(int G, bool sparse, int M, int n_tiles, int max_kp);
+// The same for int8 operands, TW and TVW (sparse), G in {64, 128} (gemm_small_i8.hip).
+hipError_t launch_small_i8(int G, bool sparse, int max_kp, GemmI8Args g, hipStream_t stream);
+bool small_i8_pays(int G, bool sparse, int M, int n_tiles, int max_kp);
 
 }  // namespace twg

@@ -53,3 +53,39 @@ def test_tvw_width_32_stays_refused():
         gu.run_tw(tw, p, np.ones((8, 8), np.float16), 32)
     assert ei.value.status == 3
     p.free()
+
+
+I8_CASES = [  # pattern, M, K, N, G, col_keep, row_keep, c_dtype
+    ("tw", 1, 2, 1, 64, 1.0, 0.6, 0), ("tw", 15, 128, 64, 64, 0.9, 1.0, 1), ("tw", 31, 513, 129, 128, 0.9, 1.0, 0),
+    ("tw", 33, 520, 300, 128, 0.8, 1.0, 1), ("tw", 97, 1500, 130, 64, 0.9, 1.0, 0), ("tw", 200, 300, 500, 64, 0.9, 0.01, 1),
+    ("tw", 130, 768, 2304, 128, 0.9, 0.28, 1), ("tw", 700, 100, 70, 64, 0.9, 0.5, 0), ("tw", 704, 256, 1000, 128, 0.9, 0.5, 1),
+    ("tvw", 1, 4, 1, 64, 1.0, 1.0, 1), ("tvw", 16, 256, 65, 64, 1.0, 1.0, 0), ("tvw", 47, 1030, 300, 128, 0.8, 1.0, 1),
+    ("tvw", 64, 2100, 257, 64, 0.9, 1.0, 0), ("tvw", 290, 768, 600, 128, 0.9, 0.25, 1), ("tvw", 60, 200, 300, 64, 0.9, 0.02, 0),
+    ("tvw", 1300, 500, 60, 64, 0.9, 0.5, 1),
+]
+
+
+@pytest.mark.parametrize("pattern,M,K,N,G,col_keep,row_keep,c_dtype", I8_CASES)
+def test_few_blocks_i8_edges(pattern, M, K, N, G, col_keep, row_keep, c_dtype):
+    """Sums are whole numbers: the same as the oracle's, and as the pipelined kernels' (which a forced tile size takes)."""
+    rng = np.random.default_rng(M * 7919 + K + N)
+    if pattern == "tw":
+        mask = tmask = random_tw_mask(rng, K, N, G, col_keep, row_keep)
+    else:
+        mask, tmask = random_tvw_mask(rng, K, N, G, col_keep, row_keep, full=False)
+    A, B, scale = wl.rng_i8(K, (M, K)), wl.rng_i8(K + 1, (K, N)), 1.0 / 331.0
+    print(f"case few blocks i8 {pattern} M={M} K={K} N={N} G={G} keep={col_keep}/{row_keep} out={c_dtype}", flush=True)
+    p = tw.tw_pack_i8(B, mask, G, tw.PATTERN_TW if pattern == "tw" else tw.PATTERN_TVW, tile_mask=tmask)
+    lda, ldc = (M + 15) // 16 * 16 + 16, (M + 15) // 16 * 16 + 32
+    C, raw = gu.run_tw_i8(tw, p, A, N, c_dtype=c_dtype, scale=scale, lda=lda, ldc=ldc)
+    tw.tw_set_option("tile_m", 128)
+    try:
+        C2, _ = gu.run_tw_i8(tw, p, A, N, c_dtype=c_dtype, scale=scale, lda=lda, ldc=ldc)
+    finally:
+        tw.tw_set_option("tile_m", 0)
+    p.free()
+    want = og.gemm_i8_oracle(A, B, mask)
+    if c_dtype:
+        want = og.requantize_i8(want, scale).astype(np.int64)
+    assert np.array_equal(C, want) and np.array_equal(C2, want)
+    assert (raw[:, M:] == -77).all()                                   # nothing written past row M
