@@ -87,16 +87,18 @@ __global__ __launch_bounds__(NW * 64) void tw_gemm_small_kernel(GemmArgs g, int 
     }
     return;
   }
-  // the M-tiles of a column block are 8 ids apart: the same XCD, whose L2 then holds its weights
+  // The M-tiles of a column block are 8 ids apart: the same XCD, whose L2 then holds its weights.  With more M-tiles than
+  // column blocks, and for the last few of these, an XCD takes a range of M-tiles and all column blocks: A, of which a line
+  // of memory serves two M-tiles, then comes once (TVW 75 %, 2304 x 128, M = 3520: 13.3 / 6.7 us; TW 75 %, M = 1600 4.7 / 3.6).
   int nb, mt;
   {
-    const int whole = n_blocks / 8 * 8, rem = n_blocks - whole;
+    const int whole = g.n_mtiles > n_blocks ? 0 : n_blocks / 8 * 8, rem = n_blocks - whole;
     if (bid < whole * g.n_mtiles) {
       const int r = bid >> 3, grp = r / g.n_mtiles;
       mt = r - grp * g.n_mtiles;
       nb = grp * 8 + (bid & 7);
     } else {
-      const int r = bid - whole * g.n_mtiles;
+      const int r = xcd_remap(bid - whole * g.n_mtiles, rem * g.n_mtiles);
       mt = r / rem;
       nb = whole + r - mt * rem;
     }
@@ -287,19 +289,21 @@ hipError_t launch_small_km(int G, bool sparse, bool restored, int max_kp, GemmAr
   return launch_small<false, 8, 4>(G, g, stream);
 }
 
-// Where it beats the pipelined kernels, by the number of 32 x 32 blocks of C (sweeps over M at some
-// twenty K x N, G and sparsities, TW and TVW, and eight convolutions).  Short lists: one workgroup per
-// CU (256 x 256 of G = 64 at 50 %: 256 blocks 2.7 against 3.1 us, 512 blocks 3.5 against 3.2).  Medium
-// ones: 768 x 768 at 75 %, 576 blocks 4.3 against 4.5, 768 blocks 4.9 against 4.3.  Long ones, bound by
-// the LDS reads and copies again: 3072 x 768, 384 blocks 7.4 against 7.7, 576 blocks 8.8 against 7.8;
-// 4096 x 4096, 464 blocks 7.4 against 8.9, 928 blocks 11.9 against 9.5.  TVW: 768 x 768 at 87.5 %, 384
-// blocks 3.3 against 3.9, 576 blocks 4.1 against 4.0; lists of more than 12 k-steps 704 blocks and more
-// (1024 x 1024, G = 64: 720 blocks 6.9 against 8.3; 4096 x 4096: 928 blocks 13.9 against 18.8).
+// Where it beats the pipelined kernels, by the number of 32 x 32 blocks of C and the length of the lists (sweeps over M at some
+// forty K x N, G and sparsities, TW and TVW, and eleven convolutions).  TW, this kernel / pipelined.  Short lists, G = 64, whose
+// pipelined launches have twice the workgroups: 256 x 256 at 50 %, 256 blocks 3.0 / 3.3 us, 480 blocks 3.5 / 3.4; G = 128:
+// 768 x 768 at 87.5 %, 480 blocks 3.4 / 3.8, 648 blocks 3.9 / 3.8.  Medium ones: 768 x 768 at 75 %, 672 blocks 4.0 / 4.4,
+// 792 blocks 4.4 / 4.4; 2048 x 1024 at 80 %, 672 blocks 5.6 / 6.1, 800 blocks 6.7 / 6.1.  Long ones, bound by the LDS reads and
+// copies again: 3072 x 768, 432 blocks 6.7 / 7.9, 552 blocks 9.1 / 8.2; 4096 x 1024 at 50 %, 448 blocks 12.3 / 15.2, 576 blocks
+// 16.7 / 15.4.  TVW: 768 x 768 at 87.5 %, 720 blocks 3.9 / 4.4; 1024 x 1024 at 80 %, 704 blocks 5.1 / 5.7, 800 blocks 5.6 / 5.7;
+// 4096 x 1024 at 75 %, 672 blocks 14.7 / 14.6, 800 blocks 18.6 / 14.5.
 bool small_km_pays(int G, bool sparse, int M, int n_tiles, int max_kp) {
   const long blocks = (long)n_tiles * (G / 32) * (((long)M + 31) / 32);
   if (sparse && G == 32) return false;              // TVW is not offered for this width at any size
-  if (sparse) return blocks <= (max_kp > 12 * 32 ? 704 : 512);
-  return blocks <= (max_kp < 12 * 16 ? 256 : max_kp <= 32 * 16 ? 576 : 464);
+  if (sparse) return blocks <= 704;
+  if (max_kp < 12 * 16) return blocks <= (G == 128 ? 480 : 256);
+  if (max_kp <= 32 * 16) return blocks <= (G == 128 ? 704 : 576);
+  return blocks <= 464;
 }
 
 }  // namespace twg
