@@ -144,14 +144,18 @@ bool scalar_rows(const Opts& o, int M, int n_tiles, int G, int tm, int max_k, bo
 
 // K-split inside the workgroup pays when 128-row tiles cannot give every CU a
 // workgroup and the K loop is long enough to amortise the final reduction.  64-row tiles
-// only where 128-row tiles would leave more than half of the CUs idle: they move half as much
+// only where 128-row tiles would leave half of the CUs idle or more: they move half as much
 // again from L2 into LDS per product and read A in 128-byte pieces (3072 x 768 at M = 4096 from
 // cold HBM: 15.9 us with 64-row tiles, 13.7 with 128-row tiles; 4608 x 512 at M = 1568, 52
 // tiles of 128 rows: 11.1 against 14.2 us the other way).
 bool use_ksplit(int M, int n_tiles, int max_k, int* tm) {
   const long wgs128 = (long)((M + 127) / 128) * n_tiles;
   if (max_k < 12 * 32 || wgs128 > 320) return false;
-  *tm = wgs128 < 128 ? 64 : 128;
+  // 64 rows as long as every workgroup has a CU to itself: it is done in about three quarters of the time of 128 rows (256 / 258
+  // workgroups of 64 and half as many of 128, 64 / 128 rows: 4096 x 1024 at 50 %, G = 128, 17.5 / 22.9 and 24.6 / 23.2 us;
+  // 2048 x 1024 at 80 % 7.2 / 9.0 and 9.2 / 9.1; TEW 2048 x 2048 at 60 % 17.0 / 21.3 and 23.5 / 21.5; int8 4096 x 1024 at 50 %
+  // 11.3 / 14.1 and 16.5 / 14.6)
+  *tm = (long)((M + 63) / 64) * n_tiles <= 256 ? 64 : 128;
   return true;
 }
 

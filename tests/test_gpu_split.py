@@ -233,3 +233,29 @@ def test_one_handle_two_threads_different_options_and_geometries():
     for b in bind:
         b.free()
     p.free()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("pattern,M", [(p, M) for p in ("tw", "tew", "i8") for M in (4032, 4033, 4096, 4097)])
+def test_k_groups_around_one_workgroup_per_cu(pattern, M):
+    """Two K groups in a workgroup, four column tiles: 252, 256, 256 and 260 workgroups of 64 rows, the last of which
+    are too many (128 rows then); 1024 and some rows kept."""
+    K, N, G = 1300, 512, 128
+    rng = np.random.default_rng(M)
+    tmask = mask = random_tw_mask(rng, K, N, G, col_keep=1.0, row_keep=0.8)
+    print(f"case k groups {pattern} M={M}", flush=True)
+    if pattern == "i8":
+        A, B = wl.rng_i8(M, (M, K)), wl.rng_i8(5, (K, N))
+        p = tw.tw_pack_i8(B, mask, G, tw.PATTERN_TW)
+        C, _ = gu.run_tw_i8(tw, p, A, N, c_dtype=0, scale=1.0, lda=(M + 15) // 16 * 16, ldc=(M + 15) // 16 * 16)
+        p.free()
+        assert np.array_equal(C, og.gemm_i8_oracle(A, B, mask))
+        return
+    if pattern == "tew":
+        mask = (tmask | (rng.random((K, N)) < 0.01)).astype(np.uint8)
+    A, B = wl.make_A(K, M, K), wl.make_B(K, K, N, 0.1)
+    p = tw.tw_pack(B, mask, G, tw.PATTERN_TEW if pattern == "tew" else tw.PATTERN_TW, tile_mask=tmask)
+    C, raw = gu.run_tw(tw, p, A, N, lda=(M + 7) // 8 * 8, ldc=(M + 7) // 8 * 8 + 8, fill=5.0)
+    p.free()
+    assert_C_close(C, og.gemm_oracle(A, B, mask), og.abs_bound(A, B, mask))
+    assert (raw[:, M:] == 5.0).all()                                   # nothing written past row M
