@@ -426,7 +426,7 @@ static tw_status gemm_launch(const Opts& o, const void* A, int M, int lda, int l
     return e == hipSuccess ? TW_OK : TW_ERR_HIP;
   }
   int tm = pick_tile_m(o, M, n_tiles > 0 ? n_tiles : 1, h->G, h->max_kp);
-  // no 64 x 64 instance of the asynchronous kernel (tried: one matrix instruction per wave and
+  // no 64 x 64 instance of the asynchronous kernel without K groups (tried: one matrix instruction per wave and
   // k-step is too little work per barrier; plain TW falls back to the register-staged kernel)
   if ((h->pattern == TW_PATTERN_TEW || conv) && h->G == 64 && tm == 64) tm = 128;
   // TEW: the 256-row instance of G = 128 has no register to spare for its second way to the result (768 x 3072 at M =
@@ -465,7 +465,7 @@ static tw_status gemm_launch(const Opts& o, const void* A, int M, int lda, int l
     const int ks = o.ksplit;
     if (ks == 2 || (ks == 0 && use_ksplit(M, n_tiles, h->max_kp, &tmk))) variant = twg::DMA_KSPLIT2;
     if (variant == twg::DMA_KSPLIT2 && ks == 2) tmk = tm == 256 ? 128 : tm;
-    if (variant == twg::DMA_KSPLIT2 && h->G == 64) tmk = 128;   // the one K-split instance for G = 64
+    if (variant == twg::DMA_KSPLIT2 && h->G == 64 && (tew || ks == 2)) tmk = 128;   // (TEW has no other instance; on request)
     const int tmu = variant == twg::DMA_KSPLIT2 ? tmk : tm;
     g.scalar_rows = !tew && variant == twg::DMA_WAVES4 && scalar_rows(o, M, n_tiles, h->G, tmu, h->max_kp, conv);
     // several tiles per workgroup (plain TW, 4 waves, 64- or 128-row tiles of G = 128, 3 stages): on request

@@ -830,6 +830,13 @@ static hipError_t dispatch(int G, int tm, int depth, int variant, GemmArgs& g, h
     if (G == 128 && tm == 64 && depth == 3) return launch<64, 128, 1, 3, DENSE, 8, 2>(g, stream);
     if (G == 128 && tm == 64 && depth == 4) return launch<64, 128, 1, 4, DENSE, 8, 2>(g, stream);
     if (G == 64 && tm == 128 && depth == 3) return launch<128, 64, 2, 3, DENSE, 8, 2>(g, stream);
+    // One 32 x 32 block per wave and k-step is little work per barrier, but twice the workgroups where half of the chip
+    // is idle: 64 / 128 rows, 3072 x 768 at 75 %, M = 1403, 242 workgroups of 64 7.5 / 8.8 us; 4608 x 512, M = 1915 9.3 / 10.7;
+    // 3 x 3 convolutions 512 -> 512 of eight 14 x 14 images 9.9 / 11.8, 256 -> 256 of four 28 x 28 6.6 / 7.9; short lists even
+    // (768 x 768 at 40 %, M = 1019 6.3 / 6.4).  (More workgroups than CUs: 3072 x 768, M = 1531 9.0 / 8.7.)
+    if constexpr (!DENSE) {
+      if (G == 64 && tm == 64 && depth == 3) return launch<64, 64, 2, 3, false, 8, 2>(g, stream);
+    }
     return hipErrorInvalidValue;
   }
   if (variant == DMA_WAVES8) {    // 512-thread workgroups: 64 x 32 (m x n) per wave

@@ -236,14 +236,14 @@ def test_one_handle_two_threads_different_options_and_geometries():
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("pattern,M", [(p, M) for p in ("tw", "tew", "i8") for M in (4032, 4033, 4096, 4097)])
-def test_k_groups_around_one_workgroup_per_cu(pattern, M):
+@pytest.mark.parametrize("pattern,G,M", [(p, G, M) for p, G in (("tw", 128), ("tw", 64), ("tew", 128), ("i8", 128)) for M in (4032, 4033, 4096, 4097)])
+def test_k_groups_around_one_workgroup_per_cu(pattern, G, M):
     """Two K groups in a workgroup, four column tiles: 252, 256, 256 and 260 workgroups of 64 rows, the last of which
     are too many (128 rows then); 1024 and some rows kept."""
-    K, N, G = 1300, 512, 128
+    K, N = 1300, 4 * G
     rng = np.random.default_rng(M)
     tmask = mask = random_tw_mask(rng, K, N, G, col_keep=1.0, row_keep=0.8)
-    print(f"case k groups {pattern} M={M}", flush=True)
+    print(f"case k groups {pattern} G={G} M={M}", flush=True)
     if pattern == "i8":
         A, B = wl.rng_i8(M, (M, K)), wl.rng_i8(5, (K, N))
         p = tw.tw_pack_i8(B, mask, G, tw.PATTERN_TW)
@@ -259,3 +259,21 @@ def test_k_groups_around_one_workgroup_per_cu(pattern, M):
     p.free()
     assert_C_close(C, og.gemm_oracle(A, B, mask), og.abs_bound(A, B, mask))
     assert (raw[:, M:] == 5.0).all()                                   # nothing written past row M
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("row_keep", [0.33, 0.5])
+@pytest.mark.parametrize("K,N,M", [(2500, 449, 1000), (1200, 130, 5000)])
+def test_k_groups_of_64_by_64_uneven_lists(K, N, M, row_keep):
+    """Lists of an odd and an even number of 32-row steps, a last tile of one or two columns."""
+    rng = np.random.default_rng(K + N)
+    mask = random_tw_mask(rng, K, N, 64, col_keep=1.0, row_keep=row_keep)
+    mask[:, 64:128] = 0
+    mask[7, 64:128] = 1                                                # one tile of a single row
+    A, B = wl.make_A(K, M, K), wl.make_B(K, K, N, 0.1)
+    print(f"case k groups 64x64 K={K} N={N} M={M}", flush=True)
+    p = tw.tw_pack(B, mask, 64, tw.PATTERN_TW)
+    C, raw = gu.run_tw(tw, p, A, N, lda=M + 8, ldc=M + 16, fill=5.0)
+    p.free()
+    assert_C_close(C, og.gemm_oracle(A, B, mask), og.abs_bound(A, B, mask))
+    assert (raw[:, M:] == 5.0).all()
