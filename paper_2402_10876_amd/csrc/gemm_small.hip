@@ -264,7 +264,7 @@ __global__ __launch_bounds__(NW * 64) void tw_gemm_small_kernel(GemmArgs g, int 
 
 template <bool SP, int NW, int U, bool EW = false>
 static hipError_t launch_small(int G, GemmArgs& g, hipStream_t stream) {
-  g.n_mtiles = (g.M + 31) / 32;
+  g.n_mtiles = (int)(((long)g.M + 31) / 32);
   const int n_blocks = g.n_tiles * (G / 32);
   const int chunks = (g.M + 7) / 8;
   const int zper = chunks < NW * 64 ? NW * 64 / chunks : 1;       // pruned columns per workgroup that clears them

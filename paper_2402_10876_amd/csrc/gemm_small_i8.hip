@@ -16,6 +16,7 @@
 
 #include "device_common.h"
 #include "i8_common.h"
+#include "zero_cols.h"
 
 namespace twg {
 
@@ -51,13 +52,14 @@ __global__ __launch_bounds__(NW * 64) void tw_gemm_small_i8_kernel(GemmI8Args g,
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int bid = blockIdx.x, n_gemm = n_blocks * g.n_mtiles;
   if (bid >= n_gemm) {                              // 0 into zero_cols_per_wg pruned columns
-    const int bytes = g.M * ES, chunks = (bytes + 15) / 16, z0 = (bid - n_gemm) * zero_cols_per_wg;
-    const int n = min(zero_cols_per_wg, g.n_zero - z0) * chunks;
+    const int64_t bytes = (int64_t)g.M * ES;
+    const int chunks = zero_chunks(bytes), z0 = (bid - n_gemm) * zero_cols_per_wg;
+    const int n = min(zero_cols_per_wg, g.n_zero - z0) * chunks;      // (several columns: at most NT chunks)
     for (int i = tid; i < n; i += NT) {
-      const int z = i / chunks, b = (i - z * chunks) * 16;
-      char* row = (char*)g.C + (size_t)g.zero_cols[z0 + z] * g.ldc * ES;
-      if (b + 16 <= bytes) *(u32x4*)(row + b) = u32x4{0u, 0u, 0u, 0u};
-      else for (int e = b; e < bytes; ++e) row[e] = 0;
+      const ZeroChunk x = zero_chunk(i, chunks);
+      char* row = (char*)g.C + (size_t)g.zero_cols[z0 + x.column] * g.ldc * ES;
+      if (x.at + 16 <= bytes) *(u32x4*)(row + x.at) = u32x4{0u, 0u, 0u, 0u};
+      else for (int64_t e = x.at; e < bytes; ++e) row[e] = 0;
     }
     return;
   }
@@ -224,9 +226,9 @@ __global__ __launch_bounds__(NW * 64) void tw_gemm_small_i8_kernel(GemmI8Args g,
 
 template <bool SP, int NW>
 static hipError_t launch_small8(int G, GemmI8Args& g, hipStream_t stream) {
-  g.n_mtiles = (g.M + 31) / 32;
+  g.n_mtiles = (int)(((long)g.M + 31) / 32);
   const int n_blocks = g.n_tiles * (G / 32);
-  const int chunks = (int)(((long)g.M * (g.c_i8 ? 1 : 4) + 15) / 16);
+  const int chunks = zero_chunks((int64_t)g.M * (g.c_i8 ? 1 : 4));
   const int zper = chunks < NW * 64 ? NW * 64 / chunks : 1;       // pruned columns per workgroup that clears them
   const int grid = n_blocks * g.n_mtiles + (g.n_zero + zper - 1) / zper;
   if (grid <= 0) return hipSuccess;

@@ -303,3 +303,16 @@ def test_i8_k_split_is_chosen_for_long_k_few_tiles():
     want = og.requantize_i8(og.gemm_i8_oracle(A[rows], B, mask), 1.0 / 2000.0)
     assert (np.abs(want) > 10).any()
     assert np.array_equal(C[rows], want.astype(np.int64))
+
+
+@pytest.mark.parametrize("M,c_dtype", [((1 << 29) + 16, 0), ((1 << 31) - 16, 1)])
+def test_i8_nothing_kept_and_a_column_of_more_bytes_than_an_int_counts(M, c_dtype):
+    import torch
+    print(f"i8 nothing kept M={M} out={c_dtype}", flush=True)
+    p = tw.tw_pack_i8(np.ones((1, 1), np.int8), np.zeros((1, 1), np.uint8), 64)
+    A = torch.ones((1, M), dtype=torch.int8, device="cuda")
+    C = torch.full((1, M), -77, dtype=torch.int8 if c_dtype else torch.int32, device="cuda")
+    tw.tw_gemm_i8(A.data_ptr(), M, M, p, C.data_ptr(), M, c_dtype, 1.0, torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    p.free()
+    assert not C.view(torch.int64).any().item()
