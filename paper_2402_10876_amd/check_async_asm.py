@@ -18,6 +18,10 @@ The vector loads are also followed along every branch, up to the first wait for 
 path: there the compiler's own instructions are reported (whether a path can reach one of
 the kernels' own uses without a wait depends on the conditions of its branches).
 
+A vector memory instruction needs five wait states behind a vector instruction that wrote a scalar register of its
+address (v_readlane of a spilled one, say).  The compiler sees to that for its own instructions and does not look into
+inline assembly: such an instruction there is reported unless the block itself waits.
+
     python -m paper_2402_10876_amd.check_async_asm          # exit status 1 on a finding
 """
 from __future__ import annotations
@@ -143,6 +147,42 @@ def check_branches(asm_text: str):
     return findings
 
 
+_VMEM = re.compile(r"^(global|flat|buffer|scratch)_\w+$")
+_TWO_DST = re.compile(r"^v_(add|sub|subrev|addc|subb|subbrev)_co_|^v_mad_[ui]64_|^v_div_scale_")
+_WAIT_STATES = 5
+
+
+def check_scalar_addresses(asm_text: str):
+    """Findings as check_assembly's: inline-assembly vector memory instructions too close behind a vector instruction
+    that wrote a scalar register of theirs (in layout order)."""
+    findings, kernel, in_app, age = [], None, False, {}     # age: wait states since the register was written
+    for ln, raw in enumerate(asm_text.split("\n"), 1):
+        line = raw.strip()
+        if line.startswith(";;#ASM"):
+            in_app = line.startswith(";;#ASMSTART")
+            continue
+        code = line.split(";")[0].strip()
+        if code.endswith(":"):
+            if not code.startswith(".") and not raw[0].isspace():
+                kernel, age = code[:-1], {}
+            continue
+        if not code or code.startswith("."):
+            continue
+        op, _, args = code.partition(" ")
+        operands = re.split(r",\s*", args)
+        if in_app and _VMEM.match(op):
+            bad = {r for r in _regs(args) if r[0] == "s" and age.get(r, _WAIT_STATES) < _WAIT_STATES}
+            if bad:
+                findings.append((kernel, ln, code, sorted(bad)))
+        states = int(args, 0) + 1 if op == "s_nop" else 1
+        age = {r: a + states for r, a in age.items() if a + states < _WAIT_STATES}
+        if op.startswith("v_"):
+            for r in _regs(",".join(operands[:2 if _TWO_DST.match(op) else 1])):
+                if r[0] == "s":
+                    age[r] = 0
+    return findings
+
+
 def compile_to_asm(src: str) -> str:
     with tempfile.TemporaryDirectory() as td:
         out = os.path.join(td, "k.s")
@@ -158,7 +198,7 @@ def check_sources(sources=KERNEL_SOURCES):
         texts = list(ex.map(compile_to_asm, sources))
     res = []
     for src, text in zip(sources, texts):
-        res += [(src,) + f for f in check_assembly(text) + check_branches(text)]
+        res += [(src,) + f for f in check_assembly(text) + check_branches(text) + check_scalar_addresses(text)]
     return res
 
 

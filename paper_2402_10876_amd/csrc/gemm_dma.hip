@@ -359,6 +359,7 @@ void tw_gemm_km_dma_kernel(GemmArgs g_arg) {
       }
     }
   };
+  // (the address must not come from a vector instruction within five wait states: a spilled one would; the build checks it)
   auto fetch_quad = [&](int s, int& dst) {       // else: of the quad; valid once the load has been waited for
     if constexpr (!DENSE && !LIDX && !SCALAR)
       asm volatile("global_load_dword %0, %1, %2" : "=v"(dst) : "v"(idx_lane), "s"(g.row_idx + kp0 + s * KSS));

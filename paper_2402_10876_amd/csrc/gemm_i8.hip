@@ -197,6 +197,7 @@ __global__ __launch_bounds__(NWAVES * 64, (TM * TN >= 256 * 128) ? 2 : 1) void t
     }
   };
   const uint32_t idx_lane = (uint32_t)((wave * NIA + (lane & (NIA - 1))) * RPIA + a_rloc) * 4u;
+  // (the address must not come from a vector instruction within five wait states: a spilled one would; the build checks it)
   auto fetch_quad = [&](int s, int& dst) {       // VEC: of the quad; valid once the load has been waited for
     if constexpr (VEC)
       asm volatile("global_load_dword %0, %1, %2" : "=v"(dst) : "v"(idx_lane), "s"(g.row_idx + kp0 + s * KSS));

@@ -145,6 +145,7 @@ __global__ __launch_bounds__(256) void tvw_gemm_i8_kernel(GemmI8Args g) {
   // 768 x 768 5.9 / 5.0, 768 x 3072 10.6 / 10.3, 1200 x 3000 x 2000 at 75 % 15.1 / 11.9, 64 x 4096 x 4096 16.3 / 8.9.
   struct Rows { int r[NIA]; };
   const uint32_t idx_lane = (uint32_t)((wave * NIA + (lane & (NIA - 1))) * RPIA + a_rloc) * 4u;
+  // (the address must not come from a vector instruction within five wait states: a spilled one would; the build checks it)
   auto fetch_quad = [&](int s, int& dst) {       // of the quad; valid once the load has been waited for
     asm volatile("global_load_dword %0, %1, %2" : "=v"(dst) : "v"(idx_lane), "s"(g.row_idx + kp0 + s * KSV));
   };

@@ -64,6 +64,34 @@ _Z1kv:
 """
 
 
+# a spilled address comes back through v_readlane, and the load in the assembly block reads it five wait states too early
+BAD_SPILL = """
+_Z1kv:
+	v_readlane_b32 s14, v105, 12
+	v_readlane_b32 s15, v105, 13
+	;;#ASMSTART
+	global_load_dword v35, v92, s[14:15]
+	;;#ASMEND
+	;;#ASMSTART
+	s_waitcnt vmcnt(0)
+	;;#ASMEND
+	s_endpgm
+"""
+
+
+def test_scanner_flags_a_scalar_address_that_a_vector_instruction_just_wrote():
+    f = chk.check_scalar_addresses(BAD_SPILL)
+    assert len(f) == 1 and f[0][0] == "_Z1kv" and f[0][3] == [("s", 14), ("s", 15)]
+    load = "\tglobal_load_dword v35"
+    assert len(chk.check_scalar_addresses(BAD_SPILL.replace(load, "\ts_nop 3\n" + load))) == 1
+    assert chk.check_scalar_addresses(BAD_SPILL.replace(load, "\ts_nop 4\n" + load)) == []
+    assert chk.check_scalar_addresses(BAD_SPILL.replace("v_readlane_b32 s1", "s_mov_b32 s1")) == []
+    # the compiler's own instructions are its own business; a carry goes to the second operand, a mask to the first
+    assert chk.check_scalar_addresses(BAD_SPILL.replace("\t;;#ASMSTART\n" + load, load)) == []
+    for write in ("v_cmp_gt_i32_e64 s[14:15], v1, v2", "v_mad_u64_u32 v[2:3], s[14:15], v1, v2, v[4:5]"):
+        assert len(chk.check_scalar_addresses(BAD_SPILL.replace("v_readlane_b32 s15, v105, 13", write))) == 1
+
+
 def test_scanner_follows_the_vector_loads_along_branches():
     f = chk.check_branches(BAD_SKIP)
     assert len(f) == 1 and f[0][0] == "_Z1kv" and "v136, 0" in f[0][2]
