@@ -565,13 +565,23 @@ void tw_gemm_km_dma_kernel(GemmArgs g_arg) {
   if (KSPLIT == 1 && !BRANCH ? ns > 0 : live_prev) mfma_step(f1);
   if constexpr (EW) {
     if (joined) {                                      // (uniform over the workgroup)
-      float z = 0.f;                                   // NaN unless everything is finite
+      // NaN unless everything that is stored is finite (rows past M come from the padding of A, which may hold anything)
+      float z = 0.f;
+      int m_lane = m0 + wm * WM + 4 * (lane >> 5);
+      // (otherwise the comparisons move to the kernel's start and their masks push the scalar registers of the K loop out)
+      asm volatile("" : "+v"(m_lane));
+      auto look = [&](auto WHOLE) {
 #pragma unroll
-      for (int i = 0; i < MB; ++i)
+        for (int i = 0; i < MB; ++i)
 #pragma unroll
-        for (int j = 0; j < NB; ++j)
+          for (int r = 0; r < 16; ++r) {
+            if (!decltype(WHOLE)::value && m_lane + i * 32 + 8 * (r / 4) + r % 4 >= g.M) continue;
 #pragma unroll
-          for (int r = 0; r < 16; ++r) z = __builtin_fmaf(acc[i][j][r], 0.f, z);
+            for (int j = 0; j < NB; ++j) z = __builtin_fmaf(acc[i][j][r], 0.f, z);
+          }
+      };
+      if (m0 + TM <= g.M) look(std::true_type{});
+      else look(std::false_type{});
       const bool bad = __any(!(z == 0.f));
       __syncthreads();                                 // everybody is done with the pipeline buffers
       if (lane == 0) ((int*)lds)[wave] = bad;

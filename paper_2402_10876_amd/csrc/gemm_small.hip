@@ -246,10 +246,12 @@ __global__ __launch_bounds__(NW * 64) void tw_gemm_small_kernel(GemmArgs g, int 
       if (x >= (uint32_t)g.conv_W || y >= (uint32_t)g.conv_H) s1 = 0.f;
     }
     if constexpr (EW) {
-      if (!(s0 * 0.f == 0.f && s1 * 0.f == 0.f)) {  // infinite or NaN
+      const bool bad0 = !(s0 * 0.f == 0.f), bad1 = m + 1 < g.M && !(s1 * 0.f == 0.f);      // infinite or NaN, and stored
+      if (bad0 || bad1) {
         const int c = cb * 32 + n, rows_kept = c < (int)((uint32_t)kept >> 24) ? kept & 0xffffff : 0;
 #pragma unroll 1
-        for (int h = 0; h < 2 && m + h < g.M; ++h) {
+        for (int h = 0; h < 2; ++h) {
+          if (!(h ? bad1 : bad0)) continue;
           const float x = ew_term_by_term(g, G, kp0, rows_kept, c, cols[i], m + h);
           if (h == 0) s0 = x;
           else s1 = x;

@@ -203,6 +203,39 @@ def test_tew_few_blocks(G, M, K, N, col_keep, _opts):
     _check_infinities(A, B, m, *_gpu_run(B, m, tm, G, A))
 
 
+@pytest.mark.gpu
+@pytest.mark.parametrize("G,M,K,N,tile_m,ksplit", [
+    (128, 1, 1500, 3000, 0, 0), (64, 33, 500, 2000, 0, 0),                                        # few output blocks
+    (128, 333, 410, 900, 64, 1), (128, 333, 410, 900, 128, 1), (128, 333, 410, 900, 256, 1), (64, 333, 410, 900, 128, 1),
+    (64, 333, 410, 900, 256, 1), (128, 129, 900, 900, 64, 2), (128, 131, 900, 900, 128, 2), (64, 1, 900, 2000, 128, 2)])
+def test_tew_padding_of_A_is_no_input(G, M, K, N, tile_m, ksplit, _opts):
+    """Rows past M of the last tile come from columns M .. round-up-8(M) of A, which a caller may leave as they are: the
+    same bits whatever lies there, and those of the sums with the joined rows."""
+    import torch
+    rng = np.random.default_rng(G + M + tile_m)
+    m, tm = random_tew_mask(rng, K, N, G, extra=0.04, col_keep=0.8, row_keep=0.3)
+    A, B = wl.make_A(9, M, K), wl.make_B(9, K, N, 1.0)
+    tw.tw_set_option("tile_m", tile_m)
+    tw.tw_set_option("ksplit", ksplit)
+    ld = (M + 7) // 8 * 8
+    p = tw.tw_pack(B, m, G, tw.PATTERN_TEW, tile_mask=tm)
+    out = []
+    for pad in (0.0, 7.0, np.nan, -np.inf):
+        print(f"case tew padding G={G} M={M} tile_m={tile_m} ksplit={ksplit} pad={pad}", flush=True)
+        At = np.full((K, ld), pad, np.float16)
+        At[:, :M] = A.T
+        Ad = torch.from_numpy(At).cuda()
+        C = torch.full((N, ld), 3.0, dtype=torch.float16, device="cuda")
+        tw.tw_gemm(Ad.data_ptr(), M, ld, tw.LAYOUT_KM, p, C.data_ptr(), ld, torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+        out.append(C.cpu().numpy())
+    p.free()
+    assert_C_close(out[0][:, :M].T.astype(np.float64), og.gemm_oracle(A, B, m), og.abs_bound(A, B, m))
+    assert (out[0][:, M:] == 3.0).all()
+    for other in out[1:]:
+        assert np.array_equal(out[0].view(np.uint16), other.view(np.uint16))
+
+
 def test_tew_image_join_counts_only_shape_the_device_form():
     """tw_flop_counts, tw_export and tw_unpack know nothing of the rows that are multiplied whole."""
     rng = np.random.default_rng(31)
