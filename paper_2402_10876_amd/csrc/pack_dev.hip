@@ -518,6 +518,11 @@ tw_status pack_device(const uint16_t* B, int ldb, const uint8_t* mask, const uin
   const size_t ntmax = (size_t)(N + G - 1) / G;
   const int blocks = (K + 63) / 64;
   (void)hipGetLastError();
+  // A stream under capture: nothing would run before the wait below.  Asked first, because an allocation can end the
+  // caller's capture.
+  hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
+  TWG_TRY(hipStreamIsCapturing(s, &capturing));
+  if (capturing != hipStreamCaptureStatusNone) return TW_ERR_HIP;
 
   // ---- structure: kept columns, kept rows per tile --------------------------------------
   DevBuf ws;
@@ -530,9 +535,6 @@ tw_status pack_device(const uint16_t* B, int ldb, const uint8_t* mask, const uin
     (void)hipGetLastError();
     return TW_ERR_ALLOC;
   }
-  hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
-  TWG_TRY(hipStreamIsCapturing(s, &capturing));
-  if (capturing != hipStreamCaptureStatusNone) return TW_ERR_HIP;    // (nothing would run before the wait below)
   char* w = (char*)ws.p;
   const uint32_t tag = next_tag.fetch_add(1);
   TWG_LAUNCH(column_bits, dim3(nb), dim3(1024), S, K, N, (uint16_t*)w);

@@ -137,12 +137,14 @@ def test_several_threads_pack_at_once():
     assert not errors, errors
 
 
-def test_packing_while_the_stream_is_captured_is_an_error():
+@pytest.mark.parametrize("mode", ["relaxed", "thread_local", "global"])
+def test_packing_while_the_stream_is_captured_is_an_error(mode):
+    """Refused before anything is allocated: outside the relaxed mode an allocation would end the caller's capture."""
     import torch
     B, mask = wl.rng_fp16(0, (64, 64)), np.ones((64, 64), np.uint8)
     Bd, md, x = torch.from_numpy(B).cuda(), torch.from_numpy(mask).cuda(), torch.zeros(8, device="cuda")
     g = torch.cuda.CUDAGraph()
-    with torch.cuda.graph(g, capture_error_mode="relaxed"):
+    with torch.cuda.graph(g, capture_error_mode=mode):
         x += 1
         with pytest.raises(tw.TwError) as ei:
             tw.tw_pack_dev(Bd.data_ptr(), 64, md.data_ptr(), None, 64, 64, 64, tw.PATTERN_TW,
