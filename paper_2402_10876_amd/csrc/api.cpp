@@ -147,15 +147,23 @@ bool scalar_rows(const Opts& o, int M, int n_tiles, int G, int tm, int max_k, bo
 // only where 128-row tiles would leave half of the CUs idle or more: they move half as much
 // again from L2 into LDS per product and read A in 128-byte pieces (3072 x 768 at M = 4096 from
 // cold HBM: 15.9 us with 64-row tiles, 13.7 with 128-row tiles; 4608 x 512 at M = 1568, 52
-// tiles of 128 rows: 11.1 against 14.2 us the other way).
-bool use_ksplit(int M, int n_tiles, int max_k, int* tm) {
+// tiles of 128 rows: 11.1 against 14.2 us the other way).  el: bytes per weight (0: the dense baseline).
+bool use_ksplit(int M, int n_tiles, int G, int max_k, int el, int* tm) {
   const long wgs128 = (long)((M + 127) / 128) * n_tiles;
   if (max_k < 12 * 32 || wgs128 > 320) return false;
   // 64 rows as long as every workgroup has a CU to itself: it is done in about three quarters of the time of 128 rows (256 / 258
   // workgroups of 64 and half as many of 128, 64 / 128 rows: 4096 x 1024 at 50 %, G = 128, 17.5 / 22.9 and 24.6 / 23.2 us;
   // 2048 x 1024 at 80 % 7.2 / 9.0 and 9.2 / 9.1; TEW 2048 x 2048 at 60 % 17.0 / 21.3 and 23.5 / 21.5; int8 4096 x 1024 at 50 %
-  // 11.3 / 14.1 and 16.5 / 14.6)
-  *tm = (long)((M + 63) / 64) * n_tiles <= 256 ? 64 : 128;
+  // 11.3 / 14.1 and 16.5 / 14.6).  Weights of uneven tiles would gain from 64 rows further on (1003 x 2491, G = 64: 288 to 864
+  // workgroups 7.8 / 8.3, 8.1 / 9.3, 8.1 / 9.5 and 9.2 / 10.1, then 11.3 / 11.1), which none of these numbers tells.
+  if ((long)((M + 63) / 64) * n_tiles > 256) { *tm = 128; return true; }
+  // Not with many column tiles of 128, from half a round of 128-row workgroups on: few rows of A then share a long list of
+  // weights, and every 64 of them fetch it again (64 / 128 rows, 64 x 32 tiles: 4096 rows, 50 %, 22.5 / 19.2 us, 2048 rows
+  // 13.3 / 12.1, TEW 4096 rows, 75 %, 30.5 / 25.8, int8 4096 rows 13.7 / 12.3, dense 4096 rows 40.1 / 32.2, 1024 rows 12.9 / 11.3;
+  // 26 tiles 19.8 / 19.2 and dense 33.3 / 31.1; 22 tiles 17.8 / 19.2 and 29.1 / 31.2).  Lists of 1 KiB a column gain all the same
+  // (512 rows, 32 and 64 tiles 7.3 / 8.3, 7.5 / 8.2 us; int8, 1024 rows, 8.3 / 8.4).
+  const bool few_or_short = n_tiles <= 24 || (el > 0 && max_k * el <= 1024);
+  *tm = wgs128 < 128 || G == 64 || few_or_short ? 64 : 128;
   return true;
 }
 
@@ -463,7 +471,7 @@ static tw_status gemm_launch(const Opts& o, const void* A, int M, int lda, int l
     int variant = (o.waves == 8 || (tm == 256 && h->G == 128)) ? twg::DMA_WAVES8 : twg::DMA_WAVES4;
     int tmk = tm;
     const int ks = o.ksplit;
-    if (ks == 2 || (ks == 0 && use_ksplit(M, n_tiles, h->max_kp, &tmk))) variant = twg::DMA_KSPLIT2;
+    if (ks == 2 || (ks == 0 && use_ksplit(M, n_tiles, h->G, h->max_kp, 2, &tmk))) variant = twg::DMA_KSPLIT2;
     if (variant == twg::DMA_KSPLIT2 && ks == 2) tmk = tm == 256 ? 128 : tm;
     if (variant == twg::DMA_KSPLIT2 && h->G == 64 && (tew || ks == 2)) tmk = 128;   // (TEW has no other instance; on request)
     const int tmu = variant == twg::DMA_KSPLIT2 ? tmk : tm;
@@ -620,7 +628,7 @@ tw_status tw_dense_gemm(const void* A, const void* B, void* C, int M, int K, int
     int variant = (o.waves == 8 || tm == 256) ? twg::DMA_WAVES8 : twg::DMA_WAVES4;
     int tmk = tm;
     const int ks = o.ksplit;
-    if (K % 64 == 0 && (ks == 2 || (ks == 0 && use_ksplit(M, g.n_tiles, K, &tmk)))) variant = twg::DMA_KSPLIT2;
+    if (K % 64 == 0 && (ks == 2 || (ks == 0 && use_ksplit(M, g.n_tiles, tn, K, 0, &tmk)))) variant = twg::DMA_KSPLIT2;
     if (variant == twg::DMA_KSPLIT2 && ks == 2) tmk = tm == 256 ? 128 : tm;
     e = twg::launch_dense_km_dma(tn, variant == twg::DMA_KSPLIT2 ? tmk : tm, o.depth, variant, g,
                                  (hipStream_t)stream);
@@ -678,7 +686,7 @@ static tw_status gemm_i8_launch(const void* A, int M, int lda, tw_handle_t h, vo
     int tmk = tm;
     e = hipErrorInvalidValue;
     // (from 12 stages of 64 rows on: below that the reduction through LDS costs more than it saves)
-    if (ks == 2 || (ks == 0 && h->max_kp >= 768 && use_ksplit(M, h->n_tiles, h->max_kp, &tmk))) {
+    if (ks == 2 || (ks == 0 && h->max_kp >= 768 && use_ksplit(M, h->n_tiles, h->G, h->max_kp, 1, &tmk))) {
       if (ks == 2) tmk = tm == 256 ? 128 : tm;
       if (h->G == 64) tmk = 128;
       e = twg::launch_tw_i8(h->G, tmk, 2, g, (hipStream_t)stream);
