@@ -437,13 +437,14 @@ static tw_status gemm_launch(const Opts& o, const void* A, int M, int lda, int l
   // no 64 x 64 instance of the asynchronous kernel without K groups (tried: one matrix instruction per wave and
   // k-step is too little work per barrier; plain TW falls back to the register-staged kernel)
   if ((h->pattern == TW_PATTERN_TEW || conv) && h->G == 64 && tm == 64) tm = 128;
-  // TEW: the 256-row instance of G = 128 has no register to spare for its second way to the result (768 x 3072 at M =
-  // 4096, 1.5 % restored: 29.4 / 26.4 us with 256 / 128 rows; 3072 x 768: 26.4 / 26.7)
-  if (h->pattern == TW_PATTERN_TEW && h->G == 128 && tm == 256 && o.tile_m != 256) tm = 128;
-  hipError_t e = hipErrorInvalidValue;
-  // TEW: the same kernels with the restored elements added in the epilogue (3 stages only)
   const bool tew = h->pattern == TW_PATTERN_TEW;
-  auto launch_dma = tew ? twg::launch_tew_km_dma : twg::launch_tw_km_dma;
+  // TEW: the kernels with restored elements, three stages only; without any, the TW kernels
+  const bool restored = !h->img.ew_pairs.empty();
+  // The 256-row instance of G = 128 has no register to spare for its second way to the result (768 x 3072 at M =
+  // 4096, 1.5 % restored: 29.4 / 26.4 us with 256 / 128 rows; 3072 x 768: 26.4 / 26.7)
+  if (restored && h->G == 128 && tm == 256 && o.tile_m != 256) tm = 128;
+  hipError_t e = hipErrorInvalidValue;
+  auto launch_dma = restored ? twg::launch_tew_km_dma : twg::launch_tw_km_dma;
   const int depth = tew ? 3 : o.depth;
   // K split across workgroups: few tiles, long kept-row lists, and a workspace to reduce through
   if (!tew && o.kernel != 1 && h->G != 32 && a_fits32 && o.ws && o.wg_split != 1 && n_tiles > 0) {
@@ -473,9 +474,9 @@ static tw_status gemm_launch(const Opts& o, const void* A, int M, int lda, int l
     const int ks = o.ksplit;
     if (ks == 2 || (ks == 0 && use_ksplit(M, n_tiles, h->G, h->max_kp, 2, &tmk))) variant = twg::DMA_KSPLIT2;
     if (variant == twg::DMA_KSPLIT2 && ks == 2) tmk = tm == 256 ? 128 : tm;
-    if (variant == twg::DMA_KSPLIT2 && h->G == 64 && (tew || ks == 2)) tmk = 128;   // (TEW has no other instance; on request)
+    if (variant == twg::DMA_KSPLIT2 && h->G == 64 && (restored || ks == 2)) tmk = 128;   // (no other instance; on request)
     const int tmu = variant == twg::DMA_KSPLIT2 ? tmk : tm;
-    g.scalar_rows = !tew && variant == twg::DMA_WAVES4 && scalar_rows(o, M, n_tiles, h->G, tmu, h->max_kp, conv);
+    g.scalar_rows = !restored && variant == twg::DMA_WAVES4 && scalar_rows(o, M, n_tiles, h->G, tmu, h->max_kp, conv);
     // several tiles per workgroup (plain TW, 4 waves, 64- or 128-row tiles of G = 128, 3 stages): on request
     if (!tew && variant == twg::DMA_WAVES4 && o.tiles_per_wg > 1) g.tiles_per_wg = o.tiles_per_wg;
     e = launch_dma(h->G, tmu, depth, variant, g, (hipStream_t)stream);

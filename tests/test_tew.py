@@ -248,10 +248,10 @@ def test_tew_image_join_counts_only_shape_the_device_form():
 
 
 @pytest.mark.gpu
-def test_tew_without_restored_elements_equals_tw(_opts):
+@pytest.mark.parametrize("K,N,G,M", [(300, 260, 128, 200), (900, 1500, 128, 1700), (900, 1500, 64, 1333), (150, 3000, 128, 4100)])
+def test_tew_without_restored_elements_equals_tw(K, N, G, M, _opts):
     from tests import gpu_util as gu
     rng = np.random.default_rng(77)
-    K, N, G, M = 300, 260, 128, 200
     tm = random_tw_mask(rng, K, N, G)
     A, B = wl.make_A(7, M, K), wl.make_B(7, K, N, 1.0)
     _, raw = _gpu_run(B, tm, tm, G, A)
