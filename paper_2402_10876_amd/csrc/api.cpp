@@ -188,6 +188,26 @@ void pick_wg_split(const Opts& o, int M, int n_tiles, int G, int max_k, int* tm,
   *S = s;
 }
 
+// TEW: restored elements one by one behind the K loop instead of in the rows that join it.  32 joined rows cost a workgroup
+// as much as 2 elements in each of its columns, plus the time of 7 elements to come to its lists (fitted to 476 launches: 17 K x N,
+// 60 to 95 %, 0.02 to 2 % restored, M = 256 to 8192), where joined rows are dear: up to half a workgroup of 128 rows per CU, when the
+// K loop is a chain with nothing beside it and joined rows are most of it, and with many column tiles, whose weights no
+// longer fit an XCD's L2, unless two workgroups are on every CU and no more.  Joined / one by one, K x N x M, sparsity, restored:
+// 4096 x 1024 x 512, 90 %, 0.5 % 16.6 / 13.1 us, x 8192 37.3 / 48.1; 2048 x 3072 x 512, 75 %, 0.5 % 14.7 / 12.1, x 1024 16.5 / 16.8;
+// 2560 x 4096 x 384, 85 %, 0.6 % 16.9 / 12.8, x 1024 22.1 / 19.1, x 2048 31.1 / 33.3, x 6144 103 / 83; 4096 x 4096 x 8192, 95 %,
+// 0.5 % 169 / 125, 2 % 282 / 315; 2048 x 2048, 60 %, 768 x 3072 and G = 64: 5 to 40 % for joined rows.  A's rows have to start on lines
+// of 128 bytes: an element's 256 bytes are three of them otherwise (2048 x 3072 x 1957, 0.5 % 25.2 / 29.6).
+bool ew_elements(const tw_handle_s* h, int M, int lda) {
+  const twg::DeviceImage& d = h->img;
+  if (h->G != 128 || d.join_off.empty() || h->n_tiles == 0 || lda % 64) return false;
+  const long wgs128 = (long)((M + 127) / 128) * d.n_tiles;
+  const double rows = (double)d.join_row.size() / d.n_tiles, kept = (double)h->sum_k / h->n_tiles;   // of a tile
+  const double per_column = (double)d.ew_pairs.size() / h->N;
+  if (wgs128 > 256) return d.n_tiles >= 24 && wgs128 > 640 && rows / 32 > 5 + 2.1 * per_column;
+  if (wgs128 > 128) return d.n_tiles >= 24 && rows / 32 > 8 + 2.1 * per_column && rows >= 1.5 * kept;
+  return rows / 32 > 7 + 1.8 * per_column && rows >= (d.n_tiles >= 24 && wgs128 > 64 ? 0.9 : 1.5) * kept;
+}
+
 }  // namespace
 
 // A convolution geometry bound to a packed weight: the kept-row lists of the handle's device
@@ -433,13 +453,15 @@ static tw_status gemm_launch(const Opts& o, const void* A, int M, int lda, int l
     if (e == hipErrorInvalidValue) return TW_ERR_UNSUPPORTED;
     return e == hipSuccess ? TW_OK : TW_ERR_HIP;
   }
-  int tm = pick_tile_m(o, M, n_tiles > 0 ? n_tiles : 1, h->G, h->max_kp);
+  const bool restored = !h->img.ew_pairs.empty();
+  g.ew_elements = restored && ew_elements(h, M, lda);
+  const int max_kp = g.ew_elements ? h->img.max_kept_kp : h->max_kp;
+  int tm = pick_tile_m(o, M, n_tiles > 0 ? n_tiles : 1, h->G, max_kp);
   // no 64 x 64 instance of the asynchronous kernel without K groups (tried: one matrix instruction per wave and
   // k-step is too little work per barrier; plain TW falls back to the register-staged kernel)
   if ((h->pattern == TW_PATTERN_TEW || conv) && h->G == 64 && tm == 64) tm = 128;
   const bool tew = h->pattern == TW_PATTERN_TEW;
   // TEW: the kernels with restored elements, three stages only; without any, the TW kernels
-  const bool restored = !h->img.ew_pairs.empty();
   // The 256-row instance of G = 128 has no register to spare for its second way to the result (768 x 3072 at M =
   // 4096, 1.5 % restored: 29.4 / 26.4 us with 256 / 128 rows; 3072 x 768: 26.4 / 26.7)
   if (restored && h->G == 128 && tm == 256 && o.tile_m != 256) tm = 128;
@@ -449,7 +471,7 @@ static tw_status gemm_launch(const Opts& o, const void* A, int M, int lda, int l
   // K split across workgroups: few tiles, long kept-row lists, and a workspace to reduce through
   if (!tew && o.kernel != 1 && h->G != 32 && a_fits32 && o.ws && o.wg_split != 1 && n_tiles > 0) {
     int stm = 0, S = 0;
-    pick_wg_split(o, M, n_tiles, h->G, h->max_kp, &stm, &S);
+    pick_wg_split(o, M, n_tiles, h->G, max_kp, &stm, &S);
     if (S > 1) {
       const long pairs = (long)((M + stm - 1) / stm) * n_tiles;
       const size_t need = WS_COUNTER_BYTES + (size_t)pairs * S * stm * h->G * 4;
@@ -472,11 +494,11 @@ static tw_status gemm_launch(const Opts& o, const void* A, int M, int lda, int l
     int variant = (o.waves == 8 || (tm == 256 && h->G == 128)) ? twg::DMA_WAVES8 : twg::DMA_WAVES4;
     int tmk = tm;
     const int ks = o.ksplit;
-    if (ks == 2 || (ks == 0 && use_ksplit(M, n_tiles, h->G, h->max_kp, 2, &tmk))) variant = twg::DMA_KSPLIT2;
+    if (ks == 2 || (ks == 0 && use_ksplit(M, n_tiles, h->G, max_kp, 2, &tmk))) variant = twg::DMA_KSPLIT2;
     if (variant == twg::DMA_KSPLIT2 && ks == 2) tmk = tm == 256 ? 128 : tm;
     if (variant == twg::DMA_KSPLIT2 && h->G == 64 && (restored || ks == 2)) tmk = 128;   // (no other instance; on request)
     const int tmu = variant == twg::DMA_KSPLIT2 ? tmk : tm;
-    g.scalar_rows = !restored && variant == twg::DMA_WAVES4 && scalar_rows(o, M, n_tiles, h->G, tmu, h->max_kp, conv);
+    g.scalar_rows = !restored && variant == twg::DMA_WAVES4 && scalar_rows(o, M, n_tiles, h->G, tmu, max_kp, conv);
     // several tiles per workgroup (plain TW, 4 waves, 64- or 128-row tiles of G = 128, 3 stages): on request
     if (!tew && variant == twg::DMA_WAVES4 && o.tiles_per_wg > 1) g.tiles_per_wg = o.tiles_per_wg;
     e = launch_dma(h->G, tmu, depth, variant, g, (hipStream_t)stream);

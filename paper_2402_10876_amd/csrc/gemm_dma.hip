@@ -127,30 +127,52 @@ __device__ __forceinline__ void wait_stage(int newer) {
 // 21.6 / 27.0 / 28.0.  What bounds it now: what bounds a TW launch of that many rows.
 // A zero of a joined row is not a term of the product, though, and an infinity of A would make it one: a workgroup whose
 // sums are not all finite starts again with the kept rows alone and adds the restored elements one by one, as the CSC part
-// has them (which has to be right, not fast), to the fp32 sums of the thread that stores the 8 values C^T[col][m .. m+8):
-// for every restored (k, v) of the column, s += v * A^T[k][m .. m+8).  Pairs travel as k << 16 | fp16 bits; the list is
-// padded in registers with (row 0, +0).  A rows are lda >= round-up-8(M) halves long, so the 16-byte read at m < M stays
-// inside the row.
-__device__ __forceinline__ void ew_accumulate(const GemmArgs& g, int lo, int hi, const _Float16* A_m, float (&s)[8]) {
-  constexpr int U = 4;                   // elements per round trip
-  for (int e = lo; e < hi; e += U) {
-    uint32_t w[U];
-    half8 a[U];
+// has them, to the fp32 sums of the thread that stores the 8 values C^T[col][m .. m+8): for every restored (k, v) of the
+// column, s += v * A^T[k][m .. m+8).  EW_ELEMENTS does that at once, for lists of many joined rows with few elements each (the
+// host's rule has the figures).  Pairs travel as k << 16 | fp16 bits; the list is padded in registers with (row 0, +0).  A rows
+// are lda >= round-up-8(M) halves long, so the 16-byte read at m < M stays inside the row.
+// P columns at a time (P times the loads in flight per round trip), U elements of each; the next ones are fetched meanwhile.
+// Every load is unconditional (index clamped to the list, value selected afterwards): one under a branch would be waited
+// for on its own.
+template <int P, int U>
+__device__ __forceinline__ void ew_accumulate(const GemmArgs& g, const int (&lo)[P], const int (&hi)[P],
+                                              const _Float16* A_m, float (&s)[P][8]) {
+  int e[P];
+  uint32_t nx[P][U];
+  bool more = false;
+  auto fetch = [&](int p) {
+    more |= e[p] < hi[p];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      w[u] = g.ew_pairs[min(e + u, g.ew_last)];
-      if (e + u >= hi) w[u] = 0u;
+      const uint32_t w = g.ew_pairs[min(e[p] + u, g.ew_last)];
+      nx[p][u] = e[p] + u < hi[p] ? w : 0u;
     }
+  };
 #pragma unroll
-    for (int u = 0; u < U; ++u) a[u] = *(const half8*)(A_m + (size_t)(w[u] >> 16) * g.lda);
+  for (int p = 0; p < P; ++p) { e[p] = lo[p]; fetch(p); }
+  while (more) {
+    uint32_t w[P][U];
+    half8 a[P][U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      union { uint16_t b; _Float16 h; } cv;
-      cv.b = (uint16_t)(w[u] & 0xffffu);
-      const float v = (float)cv.h;
+    for (int p = 0; p < P; ++p)
 #pragma unroll
-      for (int q = 0; q < 8; ++q) s[q] = __builtin_fmaf(v, (float)a[u][q], s[q]);
-    }
+      for (int u = 0; u < U; ++u) {
+        w[p][u] = nx[p][u];
+        a[p][u] = *(const half8*)(A_m + (size_t)(w[p][u] >> 16) * g.lda);
+      }
+    more = false;
+#pragma unroll
+    for (int p = 0; p < P; ++p) { e[p] += U; fetch(p); }
+#pragma unroll
+    for (int p = 0; p < P; ++p)
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        union { uint16_t b; _Float16 h; } cv;
+        cv.b = (uint16_t)(w[p][u] & 0xffffu);
+        const float v = (float)cv.h;
+#pragma unroll
+        for (int q = 0; q < 8; ++q) s[p][q] = __builtin_fmaf(v, (float)a[p][u][q], s[p][q]);
+      }
   }
 }
 
@@ -174,9 +196,9 @@ __device__ __forceinline__ void store_row_chunk(const GemmArgs& g, _Float16* dst
 // stores as older operations, which only makes them wait longer).  Per job the kernel
 // arguments are read again through a pointer the compiler cannot see through and the lane id is
 // made opaque, so that nothing derived from them stays in registers across jobs.
-template <int TM, int TN, int WAVES_M, int D, bool DENSE, int NWAVES = 4, int KSPLIT = 1, bool EW = false,
+template <int TM, int TN, int WAVES_M, int D, bool DENSE, int NWAVES = 4, int KSPLIT = 1, int EW = EW_NONE,
           bool SPLIT = false, bool MULTI = false, bool SCALAR = false>
-// (the TEW epilogue, the loop over jobs and the rows in flight must not cost an instance a wave per
+// (TEW's second way to the result, the loop over jobs and the rows in flight must not cost an instance a wave per
 // SIMD: the second launch-bound asks the compiler to keep the register count within that occupancy)
 __global__ __launch_bounds__(NWAVES * 64, ((MULTI && TM * TN <= 64 * 128) || (!DENSE && KSPLIT == 1 && NWAVES == 8 && TM == 256)) ? 4 : ((EW || MULTI) && TM <= 128 && TN <= 128 && NWAVES == 4) ? 3 : 1)
 void tw_gemm_km_dma_kernel(GemmArgs g_arg) {
@@ -204,7 +226,7 @@ void tw_gemm_km_dma_kernel(GemmArgs g_arg) {
   static_assert(D >= 3 && D <= 8, "stages in flight");
   constexpr int NPS = NIA + NIB;
   constexpr int CA = TM / 8;
-  // epilogue row bytes: fp16, 66 dwords mod 64 banks = 2; with restored elements to add one by one (EW) the
+  // epilogue row bytes: fp16, 66 dwords mod 64 banks = 2; with restored elements to add one by one the
   // tile is staged in fp32, half at a time, so that their products join the sum before the one rounding
   constexpr int CS = (TM + 4) * 2, CS32 = (TM + 4) * 4;
   static_assert(!(EW && DENSE), "");
@@ -249,7 +271,7 @@ void tw_gemm_km_dma_kernel(GemmArgs g_arg) {
   const int m0 = mt * TM;
 
   int kp0, ns32;                                       // ns32: stages of 32 rows
-  int ns32_kept = 0, w_kept = 0;                       // EW: of these, stages of kept rows (joined rows follow); kept columns
+  int ns32_kept = 0, w_kept = 0;                       // TEW: of these, stages of kept rows (joined rows follow); kept columns
   if constexpr (DENSE) { kp0 = 0; ns32 = g.K / KS; }   // host guarantees K % (32 KSPLIT) == 0
   else {
     // equal tiles in column order (the usual per-tile pruning recipe): the record follows from
@@ -260,6 +282,7 @@ void tw_gemm_km_dma_kernel(GemmArgs g_arg) {
       t = rec[0]; kp0 = rec[1]; ns32 = rec[2] / KS;
       ns32_kept = (rec[3] & 0xffffff) / KS;
       w_kept = (int)((uint32_t)rec[3] >> 24);
+      if constexpr (EW == EW_ELEMENTS) ns32 = ns32_kept;
     }
   }
   if constexpr (SPLIT) {                               // this workgroup's share of the stages
@@ -450,9 +473,9 @@ void tw_gemm_km_dma_kernel(GemmArgs g_arg) {
   using K0 = std::integral_constant<int, 0>;
   using K16 = std::integral_constant<int, 16>;
 
-  // EW: once with the joined rows, and, if that came out infinite or NaN anywhere in the tile, again with the kept rows
+  // EW_JOINED: once with the joined rows, and, if that came out infinite or NaN anywhere in the tile, again with the kept rows
   // alone and the restored elements one by one: a zero of a joined row times an infinity of A is no part of the product.
-  bool joined = EW;
+  bool joined = EW == EW_JOINED;
   for (;;) {
 #pragma unroll
   for (int i = 0; i < MB; ++i)
@@ -563,7 +586,7 @@ void tw_gemm_km_dma_kernel(GemmArgs g_arg) {
     wait_vm<0>();                        // (nothing is outstanding: every copy has been waited for)
   }
   if (KSPLIT == 1 && !BRANCH ? ns > 0 : live_prev) mfma_step(f1);
-  if constexpr (EW) {
+  if constexpr (EW == EW_JOINED) {
     if (joined) {                                      // (uniform over the workgroup)
       // NaN unless everything that is stored is finite (rows past M come from the padding of A, which may hold anything)
       float z = 0.f;
@@ -708,21 +731,30 @@ void tw_gemm_km_dma_kernel(GemmArgs g_arg) {
           }
       }
       __syncthreads();
+      constexpr int P = EW == EW_ELEMENTS && (NPASS / 2) % 2 == 0 ? 2 : 1;       // columns finished together
 #pragma unroll
-      for (int i = h * (NPASS / 2); i < (h + 1) * (NPASS / 2); ++i) {
-        float sum[8];
-        const int n = r0 + i * ROWS_PER_PASS - h * (TN / 2);
-        const floatx4 lo4 = *(const floatx4*)(lds + n * CS32 + c * 32);
-        const floatx4 hi4 = *(const floatx4*)(lds + n * CS32 + c * 32 + 16);
+      for (int i = h * (NPASS / 2); i < (h + 1) * (NPASS / 2); i += P) {
+        float sum[P][8];
+        int lo[P], hi[P];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) { sum[q] = lo4[q]; sum[4 + q] = hi4[q]; }
-        if (dst_off[i] < 0) continue;
-        if (g.uniform_kp == 0 && r0 + i * ROWS_PER_PASS >= w_kept) {   // a dropped column: not even zeros of the kept rows
+        for (int p = 0; p < P; ++p) {
+          const int n = r0 + (i + p) * ROWS_PER_PASS - h * (TN / 2);
+          const floatx4 lo4 = *(const floatx4*)(lds + n * CS32 + c * 32);
+          const floatx4 hi4 = *(const floatx4*)(lds + n * CS32 + c * 32 + 16);
+          // a dropped column: not even zeros of the kept rows
+          const bool dropped = g.uniform_kp == 0 && r0 + (i + p) * ROWS_PER_PASS >= w_kept;
 #pragma unroll
-          for (int q = 0; q < 8; ++q) sum[q] = 0.f;
+          for (int q = 0; q < 4; ++q) { sum[p][q] = dropped ? 0.f : lo4[q]; sum[p][4 + q] = dropped ? 0.f : hi4[q]; }
+          const bool live = dst_off[i + p] >= 0;
+          const int col = live ? cols[i + p] : 0;
+          const int p0 = g.ew_ptr[col], p1 = g.ew_ptr[col + 1];
+          lo[p] = live ? p0 : 0;
+          hi[p] = live ? p1 : 0;
         }
-        ew_accumulate(g, g.ew_ptr[cols[i]], g.ew_ptr[cols[i] + 1], g.A + m, sum);
-        store_row_chunk(g, g.C + dst_off[i], m, sum);
+        ew_accumulate<P, EW == EW_ELEMENTS ? 8 / P : 4>(g, lo, hi, g.A + (m < g.M ? m : 0), sum);
+#pragma unroll
+        for (int p = 0; p < P; ++p)
+          if (dst_off[i + p] >= 0) store_row_chunk(g, g.C + dst_off[i + p], m, sum[p]);
       }
     }
     }
@@ -794,7 +826,7 @@ void tw_gemm_km_dma_kernel(GemmArgs g_arg) {
   }
 }
 
-template <int TM, int TN, int WAVES_M, int D, bool DENSE, int NWAVES = 4, int KSPLIT = 1, bool EW = false,
+template <int TM, int TN, int WAVES_M, int D, bool DENSE, int NWAVES = 4, int KSPLIT = 1, int EW = EW_NONE,
           bool SPLIT = false, bool MULTI = false, bool SCALAR = false>
 static hipError_t launch(const GemmArgs& g, hipStream_t stream) {
   const int jobs = g.n_mtiles * g.n_tiles * (SPLIT ? g.wg_split : 1) + g.n_zero;
@@ -806,21 +838,22 @@ static hipError_t launch(const GemmArgs& g, hipStream_t stream) {
 }
 
 // TEW instances: three stages in flight only.
+template <int EW>
 static hipError_t dispatch_ew(int G, int tm, int variant, GemmArgs& g, hipStream_t stream) {
   g.n_mtiles = (g.M + tm - 1) / tm;
   if (variant == DMA_KSPLIT2) {
-    if (G == 128 && tm == 128) return launch<128, 128, 2, 3, false, 8, 2, true>(g, stream);
-    if (G == 128 && tm == 64) return launch<64, 128, 1, 3, false, 8, 2, true>(g, stream);
+    if (G == 128 && tm == 128) return launch<128, 128, 2, 3, false, 8, 2, EW>(g, stream);
+    if (G == 128 && tm == 64) return launch<64, 128, 1, 3, false, 8, 2, EW>(g, stream);
     return hipErrorInvalidValue;
   }
   if (variant == DMA_WAVES8) {
-    if (G == 128 && tm == 256) return launch<256, 128, 4, 3, false, 8, 1, true>(g, stream);
+    if (G == 128 && tm == 256) return launch<256, 128, 4, 3, false, 8, 1, EW_JOINED>(g, stream);   // (no registers left for elements)
     return hipErrorInvalidValue;
   }
-  if (G == 128 && tm == 64) return launch<64, 128, 1, 3, false, 4, 1, true>(g, stream);
-  if (G == 128 && tm == 128) return launch<128, 128, 2, 3, false, 4, 1, true>(g, stream);
-  if (G == 64 && tm == 128) return launch<128, 64, 2, 3, false, 4, 1, true>(g, stream);
-  if (G == 64 && tm == 256) return launch<256, 64, 4, 3, false, 4, 1, true>(g, stream);
+  if (G == 128 && tm == 64) return launch<64, 128, 1, 3, false, 4, 1, EW>(g, stream);
+  if (G == 128 && tm == 128) return launch<128, 128, 2, 3, false, 4, 1, EW>(g, stream);
+  if (G == 64 && tm == 128) return launch<128, 64, 2, 3, false, 4, 1, EW_JOINED>(g, stream);     // (never faster one by one)
+  if (G == 64 && tm == 256) return launch<256, 64, 4, 3, false, 4, 1, EW_JOINED>(g, stream);
   return hipErrorInvalidValue;
 }
 
@@ -828,7 +861,7 @@ static hipError_t dispatch_ew(int G, int tm, int variant, GemmArgs& g, hipStream
 template <int TM, int TN, int WAVES_M, int D, bool DENSE, int NWAVES = 4>
 static hipError_t launch_multi(const GemmArgs& g, hipStream_t stream) {
   if constexpr (!DENSE) {
-    if (g.tiles_per_wg > 1) return launch<TM, TN, WAVES_M, D, false, NWAVES, 1, false, false, true>(g, stream);
+    if (g.tiles_per_wg > 1) return launch<TM, TN, WAVES_M, D, false, NWAVES, 1, EW_NONE, false, true>(g, stream);
   }
   return launch<TM, TN, WAVES_M, D, DENSE, NWAVES>(g, stream);
 }
@@ -858,8 +891,8 @@ static hipError_t dispatch(int G, int tm, int depth, int variant, GemmArgs& g, h
   }
   if constexpr (!DENSE) {
     if (g.scalar_rows && depth == 3 && g.tiles_per_wg <= 1) {
-      if (G == 128 && tm == 128) return launch<128, 128, 2, 3, false, 4, 1, false, false, false, true>(g, stream);
-      if (G == 64 && tm == 256) return launch<256, 64, 4, 3, false, 4, 1, false, false, false, true>(g, stream);
+      if (G == 128 && tm == 128) return launch<128, 128, 2, 3, false, 4, 1, EW_NONE, false, false, true>(g, stream);
+      if (G == 64 && tm == 256) return launch<256, 64, 4, 3, false, 4, 1, EW_NONE, false, false, true>(g, stream);
     }
   }
 #define TWG_CASE(TM_, TN_, WM_, D_) \
@@ -893,14 +926,14 @@ hipError_t launch_zero_words(uint32_t* p, int n, hipStream_t stream) {
 hipError_t launch_tw_km_dma_split(int G, int tm, GemmArgs g, hipStream_t stream) {
   if (g.wg_split < 1 || !g.ws_partials || !g.ws_counters) return hipErrorInvalidValue;
   g.n_mtiles = (g.M + tm - 1) / tm;
-  if (G == 128 && tm == 128) return launch<128, 128, 2, 3, false, 4, 1, false, true>(g, stream);
-  if (G == 128 && tm == 64) return launch<64, 128, 1, 3, false, 4, 1, false, true>(g, stream);
-  if (G == 64 && tm == 128) return launch<128, 64, 2, 3, false, 4, 1, false, true>(g, stream);
+  if (G == 128 && tm == 128) return launch<128, 128, 2, 3, false, 4, 1, EW_NONE, true>(g, stream);
+  if (G == 128 && tm == 64) return launch<64, 128, 1, 3, false, 4, 1, EW_NONE, true>(g, stream);
+  if (G == 64 && tm == 128) return launch<128, 64, 2, 3, false, 4, 1, EW_NONE, true>(g, stream);
   return hipErrorInvalidValue;
 }
 hipError_t launch_tew_km_dma(int G, int tm, int depth, int variant, GemmArgs g, hipStream_t stream) {
   if (depth != 3) return hipErrorInvalidValue;
-  return dispatch_ew(G, tm, variant, g, stream);
+  return g.ew_elements ? dispatch_ew<EW_ELEMENTS>(G, tm, variant, g, stream) : dispatch_ew<EW_JOINED>(G, tm, variant, g, stream);
 }
 hipError_t launch_dense_km_dma(int tn, int tm, int depth, int variant, GemmArgs g, hipStream_t stream) {
   return dispatch<true>(tn, tm, depth, variant, g, stream);

@@ -38,6 +38,7 @@ struct GemmArgs {
   // disjoint ranges of the kept rows; fp32 partial tiles go to ws_partials, the workgroup that
   // arrives last at ws_counters[pair] adds them up in split order and runs the epilogue.
   int scalar_rows;               // asynchronous TW kernel: kept-row indices by scalar loads (host side only)
+  int ew_elements;               // TEW: restored elements one by one instead of with the joined rows (host side only)
   int tiles_per_wg;              // asynchronous TW kernel: jobs per workgroup (> 1: the instances that loop)
   int wg_split;
   float* ws_partials;            // [pair][split][tile] fp32
@@ -87,11 +88,13 @@ hipError_t launch_dense_mk(GemmArgs g, hipStream_t stream);
 // (tm in {128, 256}, G = 128); DMA_KSPLIT2 = two groups of 4 waves splitting K inside
 // the workgroup (dense: K % 64 == 0).
 enum { DMA_WAVES4 = 0, DMA_WAVES8 = 1, DMA_KSPLIT2 = 2 };
+// Restored elements (TEW): in rows that join the tile's list, or one by one behind the K loop.
+enum { EW_NONE = 0, EW_JOINED = 1, EW_ELEMENTS = 2 };
 hipError_t launch_tw_km_dma(int G, int tm, int depth, int variant, GemmArgs g, hipStream_t stream);
 // The same with K split across g.wg_split workgroups per tile (4 waves, 3 stages): (G, tm) in
 // {(128, 128), (128, 64), (64, 128)}.
 hipError_t launch_tw_km_dma_split(int G, int tm, GemmArgs g, hipStream_t stream);
-// The same with the restored elements of a TEW weight added in the epilogue (g.ew_*).
+// The same for a TEW weight with restored elements (g.ew_*; three stages only).
 hipError_t launch_tew_km_dma(int G, int tm, int depth, int variant, GemmArgs g, hipStream_t stream);
 hipError_t launch_dense_km_dma(int tn, int tm, int depth, int variant, GemmArgs g, hipStream_t stream);
 // Zero fill of n 32-bit words (the counters of a workspace).

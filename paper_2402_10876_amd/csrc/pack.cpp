@@ -395,11 +395,12 @@ void plan_tiles(tw_handle_s* h) {
   auto joined = [&](int t) { return d.join_off.empty() ? 0 : d.join_off[t + 1] - d.join_off[t]; };
   if (h->pattern == TW_PATTERN_TEW) d.n_zero = (int32_t)d.zero_cols.size();
   d.tile_kp_off.assign(nt + 1, 0);
-  h->max_kp = 0;
+  h->max_kp = d.max_kept_kp = 0;
   for (int t = 0; t < nt; ++t) {
     const int kp = padded(kept(t)) + padded(joined(t));
     d.tile_kp_off[t + 1] = d.tile_kp_off[t] + kp;
     h->max_kp = std::max(h->max_kp, kp);
+    d.max_kept_kp = std::max(d.max_kept_kp, padded(kept(t)));
   }
   d.tile_order.resize(nt);
   for (int t = 0; t < nt; ++t) d.tile_order[t] = t;

@@ -40,6 +40,7 @@ struct DeviceImage {
   // tile has left and in tiles of their own
   std::vector<int32_t> join_off, join_row;           // per tile of the image: its joined rows
   int32_t n_tiles = 0;                               // tiles of the image
+  int32_t max_kept_kp = 0;                           // largest padded K_t without the joined rows
   int32_t uniform_kp = 0;            // > 0: all tiles have this padded K_t and are launched in column order
   int32_t n_zero = 0;                // columns of C that are +0: the pruned ones (TEW: without restored elements)
   size_t n_vals = 0, n_meta = 0;     // elements of the value / position-word parts (set with the lists)

@@ -236,6 +236,48 @@ def test_tew_padding_of_A_is_no_input(G, M, K, N, tile_m, ksplit, _opts):
         assert np.array_equal(out[0].view(np.uint16), other.view(np.uint16))
 
 
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,N,tile_m,ksplit", [(512, 384, 64, 1), (500, 384, 128, 1), (129, 640, 64, 2), (1, 256, 128, 2), (700, 1024, 256, 1),
+                                              (384, 3100, 0, 0)])
+def test_tew_elements_one_by_one(M, N, tile_m, ksplit, _opts):
+    """Long lists of joined rows with few elements each: the elements are added one by one (the host's rule holds for these
+    shapes); A = I, bit for bit, random values and infinities."""
+    import torch
+    rng = np.random.default_rng(M + N)
+    K, G = 3000, 128
+    m, tm = random_tew_mask(rng, K, N, G, extra=0.003, col_keep=0.9, row_keep=0.1)
+    A, B = wl.make_A(10, M, K), wl.make_B(10, K, N, 1.0)
+    B[B == 0] = 1
+    tw.tw_set_option("tile_m", tile_m)
+    tw.tw_set_option("ksplit", ksplit)
+    lda = (M + 63) // 64 * 64
+    p = tw.tw_pack(B, m, G, tw.PATTERN_TEW, tile_mask=tm)
+
+    def run(X):
+        At = np.full((K, lda), np.nan, np.float16)
+        At[:, :M] = X.T
+        Ad = torch.from_numpy(At).cuda()
+        C = torch.full((N, lda), 3.0, dtype=torch.float16, device="cuda")
+        tw.tw_gemm(Ad.data_ptr(), M, lda, tw.LAYOUT_KM, p, C.data_ptr(), lda, torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+        raw = C.cpu().numpy()
+        assert (raw[:, M:] == 3.0).all()
+        return raw[:, :M].T
+
+    print(f"case tew one by one M={M} N={N} tile_m={tile_m} ksplit={ksplit}", flush=True)
+    assert_C_close(run(A).astype(np.float64), og.gemm_oracle(A, B, m), og.abs_bound(A, B, m))
+    at = rng.choice(K, M, replace=False)
+    eye = np.zeros((M, K), np.float16)
+    eye[np.arange(M), at] = 1
+    want = np.where(m != 0, B, np.float16(0)).astype(np.float16)[at]
+    assert np.array_equal(run(eye).view(np.uint16), want.view(np.uint16))
+    padding = np.append(K - 1 - tm[::-1].argmax(0)[tm.any(0)], 0)
+    ks = np.setdiff1d(np.flatnonzero(((m != 0) & (tm == 0)).any(1)), padding)[[0, -1]]
+    A[0, ks[0]], A[M - 1, ks[1]] = np.inf, -np.inf
+    _check_infinities(A, B, m, run(A).astype(np.float64), None)
+    p.free()
+
+
 def test_tew_image_join_counts_only_shape_the_device_form():
     """tw_flop_counts, tw_export and tw_unpack know nothing of the rows that are multiplied whole."""
     rng = np.random.default_rng(31)
