@@ -356,10 +356,9 @@ template <bool TVW>
 __global__ __launch_bounds__(512) void build_image(ImageArgs a) {
   constexpr int STEP = TVW ? KSTEP_TVW : KSTEP_TW;
   __shared__ int32_t rows[64];
-  __shared__ unsigned long long words[512];
-  __shared__ int front[512], part[8];
+  __shared__ int part[8];
   __shared__ int last;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, T4 = 4 * a.G, waves = T4 >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, T4 = 4 * a.G;
   const int t = (int)(blockIdx.x / (unsigned)a.stages), stage = (int)(blockIdx.x - (unsigned)t * (unsigned)a.stages);
   const unsigned long long* bits = a.row_bits;
   if (t >= a.n_tiles) {                  // slack behind the lists and values, pruned columns, the host's tables
@@ -388,28 +387,31 @@ __global__ __launch_bounds__(512) void build_image(ImageArgs a) {
   if (stage * STEP >= kp) return;
   bits += (size_t)t * a.blocks;
   if (tid == 0) last = 0;
-  int kt = 0, top = 0;                   // kept rows so far; the last one this wave has seen
+  const int lo = stage * STEP;           // the stage holds kept rows number lo .. lo + STEP - 1
+  int kt = 0, top = 0;                   // kept rows so far; the last one this thread has seen
   for (int b0 = 0; b0 < a.blocks; b0 += T4) {
     const unsigned long long x = b0 + tid < a.blocks ? bits[b0 + tid] : 0ull;
     int all;
-    front[tid] = kt + sum_before(__popcll(x), part, &all);
-    words[tid] = x;
-    __syncthreads();
-    const int n = min(T4, a.blocks - b0);
-    for (int i = wave; i < n; i += waves) {            // a lane per row
-      const unsigned long long w = words[i];
-      const int p = front[i] + __popcll(w & ((1ull << lane) - 1ull)) - stage * STEP;
-      if (w >> lane & 1ull) {
-        top = (b0 + i) * 64 + lane;
-        if (p >= 0 && p < STEP) rows[p] = top;
-      }
+    const int front = kt + sum_before(__popcll(x), part, &all);
+    // the words of this wave that hold rows of the stage, a few whatever K is: a lane per row
+    for (unsigned long long hit = __ballot(x != 0 && front < lo + STEP && front + __popcll(x) > lo); hit; hit &= hit - 1) {
+      const int i = __ffsll(hit) - 1;
+      const unsigned long long w = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)x, i) |
+                                   (unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(x >> 32), i) << 32;
+      const int p = __builtin_amdgcn_readlane(front, i) + __popcll(w & ((1ull << lane) - 1ull)) - lo;
+      if ((w >> lane & 1ull) && p >= 0 && p < STEP) rows[p] = (b0 + tid - lane + i) * 64 + lane;
     }
+    if (x) top = (b0 + tid) * 64 + 63 - __clzll((long long)x);
     kt += all;
-    __syncthreads();
+    if (b0 + T4 < a.blocks) __syncthreads();           // `part` may be used again
   }
-  if (top > 0) atomicMax(&last, top);
+  const int left = kt - lo;              // of the stage's rows, those that are kept rows
+  if (left < STEP) {                     // the rest repeat the last kept row
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) top = max(top, __shfl_xor(top, d));
+    if (lane == 0) atomicMax(&last, top);
+  }
   __syncthreads();
-  const int left = kt - stage * STEP;    // of the stage's rows, those that are kept rows
   if (tid < STEP) {
     const int row = tid < left ? rows[tid] : last;
     if (tid >= left) rows[tid] = row;
