@@ -432,9 +432,10 @@ struct DevBuf {               // device allocation freed on scope exit
 
 // Pinned host memory through which the kernels and the host of one call talk: a part for numbers and tables, and a
 // part that only ever holds tagged words (so that a word with this call's tag was written by this call).
-// Allocating it costs more than everything else the host does here, so up to four blocks of the usual size are kept, for
-// calls on up to four threads at once; they are given back when the process ends.
-constexpr size_t PIN_PLAIN = 16 << 10, PIN_WORDS = 48 << 10;
+// Allocating it costs more than everything else the host does here (70 us and more), so up to four blocks of the usual size
+// are kept, for calls on up to four threads at once; they are given back when the process ends.  The usual size holds the counts of
+// 32768 x 32768 at G = 128 and of 16384 x 16384 at G = 32; above that the kernels take ten times as long as the allocation.
+constexpr size_t PIN_PLAIN = 64 << 10, PIN_WORDS = 1 << 20;
 struct PinnedPool {
   std::mutex m;
   std::vector<char*> idle;

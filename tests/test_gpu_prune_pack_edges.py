@@ -91,11 +91,11 @@ def test_a_tile_of_more_columns_than_fit_in_lds():
     p.free()
 
 
-def test_more_counts_than_one_block_of_host_memory():
+@pytest.mark.parametrize("K,N,G", [(4200, 3200, 32), (40, 90000, 32)])   # 66 x 100 counts; tables of 2813 tiles: a block of its own
+def test_more_counts_than_one_block_of_host_memory(K, N, G):
     rng = np.random.default_rng(0)
-    K, N, G = 4200, 3200, 32                                         # 66 x 100 counts
-    keep = rng.random((K, N // G)) < 0.03
-    mask = np.repeat(keep, G, axis=1).astype(np.uint8)
+    keep = rng.random((K, -(-N // G))) < 0.03
+    mask = np.repeat(keep, G, axis=1)[:, :N].astype(np.uint8)
     mask[0] = 1
     B = wl.rng_fp16(3, (K, N))
     p, h = _pack_dev(B, mask, G, tw.PATTERN_TW), tw.tw_pack_host(B, mask, G, tw.PATTERN_TW)
