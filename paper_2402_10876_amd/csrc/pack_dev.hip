@@ -31,6 +31,7 @@
 #include <vector>
 
 #include "launch.h"
+#include "grid.h"
 #include "mk_band.h"
 #include "packed.h"
 
@@ -153,7 +154,7 @@ struct RowArgs {
   int32_t *kept, *dropped;             // the two column lists
   unsigned long long* row_bits;        // [tile][block]: rows that have an entry among the tile's columns
   unsigned long long* host;            // [0]: kept columns, [1 + tile * blocks + block]: the above
-  uint32_t tag;
+  uint32_t tag, n_wgs;
 };
 
 // Workgroup (tile, block of 64 rows).  The tile's columns reach from its first kept one (tile 0: from column 0) to
@@ -165,7 +166,9 @@ __global__ __launch_bounds__(T) void tile_rows(RowArgs a) {
   __shared__ unsigned long long word_part[T / 64];
   __shared__ int flags[T / 64];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int t = blockIdx.x / a.blocks, kb = blockIdx.x - t * a.blocks;
+  const uint32_t wg = blockIdx.y * gridDim.x + blockIdx.x;
+  if (wg >= a.n_wgs) return;
+  const int t = (int)(wg / (uint32_t)a.blocks), kb = (int)(wg - (uint32_t)t * (uint32_t)a.blocks);
   const int G = 1 << a.lg, words = (a.N + 63) / 64;
   // ---- columns ----
   const int per = (words + T - 1) / T, w0 = min(tid * per, words), w1 = min(w0 + per, words);
@@ -185,7 +188,7 @@ __global__ __launch_bounds__(T) void tile_rows(RowArgs a) {
   }
   __syncthreads();
   const int n_tiles = (n_kept + G - 1) >> a.lg;
-  if (blockIdx.x == 0 && tid == 0) tell(a.host, a.tag, (uint32_t)n_kept);
+  if (wg == 0 && tid == 0) tell(a.host, a.tag, (uint32_t)n_kept);
   const bool live = t < max(n_tiles, 1); // (nothing kept at all: tile 0 still lists the dropped columns and looks at `element`)
   const int lo = t == 0 ? 0 : range[0], hi = (t + 1) << a.lg < n_kept ? range[1] : a.N;
   if (kb == 0 && live) {
@@ -202,7 +205,7 @@ __global__ __launch_bounds__(T) void tile_rows(RowArgs a) {
     }
   }
   if (!live) {
-    if (tid == 0) tell(a.host + 1 + blockIdx.x, a.tag, 0u);
+    if (tid == 0) tell(a.host + 1 + wg, a.tag, 0u);
     return;
   }
   // ---- rows ----
@@ -250,8 +253,8 @@ __global__ __launch_bounds__(T) void tile_rows(RowArgs a) {
   __syncthreads();
   if (tid == 0) {
     word = (word_part[0] | word_part[1]) | (word_part[2] | word_part[3]);
-    a.row_bits[blockIdx.x] = word;
-    tell(a.host + 1 + blockIdx.x, a.tag,
+    a.row_bits[wg] = word;
+    tell(a.host + 1 + wg, a.tag,
          (uint32_t)((entries[0] + entries[1]) + (entries[2] + entries[3])) | (uint32_t)__popcll(word) << ROWS_KEPT_SHIFT |
              (uint32_t)(flags[0] | flags[1] | flags[2] | flags[3]));
   }
@@ -359,9 +362,11 @@ __global__ __launch_bounds__(512) void build_image(ImageArgs a) {
   __shared__ int part[8];
   __shared__ int last;
   const int tid = threadIdx.x, lane = tid & 63, T4 = 4 * a.G;
-  const int t = (int)(blockIdx.x / (unsigned)a.stages), stage = (int)(blockIdx.x - (unsigned)t * (unsigned)a.stages);
+  const uint32_t wg = blockIdx.y * gridDim.x + blockIdx.x;
+  const int t = (int)(wg / (uint32_t)a.stages), stage = (int)(wg - (uint32_t)t * (uint32_t)a.stages);
+  if (t > a.n_tiles || (t == a.n_tiles && stage > 0)) return;
   const unsigned long long* bits = a.row_bits;
-  if (t >= a.n_tiles) {                  // slack behind the lists and values, pruned columns, the host's tables
+  if (t == a.n_tiles) {                  // slack behind the lists and values, pruned columns, the host's tables
     const int kp_end = a.tables[a.n_tiles];
     for (int i = tid; i < ROW_IDX_SLACK; i += T4) a.row_idx[kp_end + i] = 0;
     if constexpr (!TVW)
@@ -553,8 +558,9 @@ tw_status pack_device(const uint16_t* B, int ldb, const uint8_t* mask, const uin
   r.row_bits = (unsigned long long*)(w + o_rbits);
   r.kept = (int32_t*)(w + o_kept); r.dropped = (int32_t*)(w + o_drop);
   r.host = pin.words; r.tag = tag;
-  const dim3 row_grid((unsigned)(ntmax * blocks));
-  TWG_LAUNCH(tile_rows, row_grid, dim3(T), r);
+  r.n_wgs = (uint32_t)(ntmax * blocks);
+  const Grid2 rg = grid_of(ntmax * blocks, T);
+  TWG_LAUNCH(tile_rows, dim3(rg.x, rg.y), dim3(T), r);
 
   // ---- plan: the counts visit the host ----------------------------------------------------
   if (!wait_for_tags(pin.words, 1 + ntmax * blocks, tag, s)) { (void)hipGetLastError(); return TW_ERR_HIP; }
@@ -612,7 +618,8 @@ tw_status pack_device(const uint16_t* B, int ldb, const uint8_t* mask, const uin
   m.row_idx = (int32_t*)d.d_row_idx; m.col_idx = (int32_t*)d.d_col_idx; m.zero_cols = (int32_t*)d.d_zero_cols;
   m.vals = (uint16_t*)d.d_vals; m.meta = (uint16_t*)d.d_meta; m.valid = (uint8_t*)d.d_valid;
   m.result = (uint32_t*)pin.p;
-  const dim3 grid((unsigned)n_tiles * (unsigned)m.stages + 1u), block(4 * G);
+  const Grid2 ig = grid_of((uint64_t)n_tiles * (uint64_t)m.stages + 1, 4 * G);
+  const dim3 grid(ig.x, ig.y), block(4 * G);
   if (tvw) TWG_LAUNCH(build_image<true>, grid, block, m);
   else TWG_LAUNCH(build_image<false>, grid, block, m);
   // The handle may be used on any stream from now on.  (The one wait for the stream: 9 us with up to seven launches
