@@ -63,18 +63,20 @@ __device__ __forceinline__ u32x4 load_mask16(const uint8_t* S, int k, int n0, in
 
 __device__ __forceinline__ bool any_byte(const u32x4& v) { return (v[0] | v[1] | v[2] | v[3]) != 0; }
 
-// Bit n of `bits` = column n of the K x N byte mask S has a non-zero entry (bits past N: 0).  A workgroup of 1024
-// threads takes 128 columns and all rows: 8 lanes of 16 columns, 128 rows at a time.
-__global__ __launch_bounds__(1024) void column_bits(const uint8_t* S, int K, int N, uint16_t* bits) {
+// Bit n of slice blockIdx.y of `bits` = column n of the K x N byte mask S has a non-zero entry among the slice's rows (bits
+// past N: 0).  A workgroup of 1024 threads takes 128 columns: 8 lanes of 16 columns, 128 rows at a time.  Narrow weights are cut
+// into slices of `rows` rows, which the readers put together: 25088 x 64 on one CU took 42 us, in 16
+// slices 4.9 (two slices of 1024 x 4096 save nothing and cost the readers a microsecond).
+__global__ __launch_bounds__(1024) void column_bits(const uint8_t* S, int K, int N, int rows, uint16_t* bits) {
   __shared__ u32x4 part[16][8];
   const int tid = threadIdx.x, c = tid & 7;
-  const int n0 = blockIdx.x * 128 + c * 16;
+  const int n0 = blockIdx.x * 128 + c * 16, k_end = min(K, ((int)blockIdx.y + 1) * rows);
   u32x4 a = {0u, 0u, 0u, 0u};
   if (n0 < N)
-    for (int k0 = tid >> 3; k0 < K; k0 += 4 * 128) {
+    for (int k0 = blockIdx.y * rows + (tid >> 3); k0 < k_end; k0 += 4 * 128) {
       u32x4 v[4];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) v[i] = load_mask16(S, min(k0 + i * 128, K - 1), n0, K, N);
+      for (int i = 0; i < 4; ++i) v[i] = load_mask16(S, min(k0 + i * 128, k_end - 1), n0, K, N);
       a |= (v[0] | v[1]) | (v[2] | v[3]);
     }
 #pragma unroll
@@ -89,7 +91,7 @@ __global__ __launch_bounds__(1024) void column_bits(const uint8_t* S, int K, int
   uint32_t b = 0;
 #pragma unroll
   for (int j = 0; j < 4; ++j) b |= (a[j] * 0x01020408u) >> 24 << (4 * j);          // bytes 0 / 1 -> four bits
-  bits[blockIdx.x * 8 + c] = (uint16_t)b;
+  bits[(blockIdx.y * gridDim.x + blockIdx.x) * 8 + c] = (uint16_t)b;
 }
 
 // Position of set bit number n (from 0) of x.
@@ -150,12 +152,21 @@ struct RowArgs {
   const uint8_t *S, *element;          // structure mask; element mask to compare with it (or null)
   const uint16_t* B;                   // weights to look at for infinities (or null)
   int ldb, K, N, lg, blocks;           // blocks of 64 rows
-  const unsigned long long* col_bits;
+  const unsigned long long* col_bits;  // `slices` times `stride` words
+  int slices, stride;
   int32_t *kept, *dropped;             // the two column lists
   unsigned long long* row_bits;        // [tile][block]: rows that have an entry among the tile's columns
   unsigned long long* host;            // [0]: kept columns, [1 + tile * blocks + block]: the above
   uint32_t tag, n_wgs;
 };
+
+// Word w of the column bits.
+__device__ __forceinline__ unsigned long long col_word(const RowArgs& a, int w) {
+  unsigned long long x = 0;
+#pragma unroll 4
+  for (int s = 0; s < a.slices; ++s) x |= a.col_bits[s * a.stride + w];
+  return x;
+}
 
 // Workgroup (tile, block of 64 rows).  The tile's columns reach from its first kept one (tile 0: from column 0) to
 // the next tile's (the last tile: to column N); which they are follows from the column bits.  16 lanes of 16 columns
@@ -173,14 +184,14 @@ __global__ __launch_bounds__(T) void tile_rows(RowArgs a) {
   // ---- columns ----
   const int per = (words + T - 1) / T, w0 = min(tid * per, words), w1 = min(w0 + per, words);
   int mine = 0, n_kept;
-  for (int w = w0; w < w1; ++w) mine += __popcll(a.col_bits[w]);
+  for (int w = w0; w < w1; ++w) mine += __popcll(col_word(a, w));
   const int front = sum_before(mine, part[0], &n_kept);
 #pragma unroll
   for (int e = 0; e < 2; ++e) {          // column of kept column number (t + e) G
     int n = ((t + e) << a.lg) - front;
     if (n < 0 || n >= mine) continue;
     for (int w = w0; w < w1; ++w) {
-      const unsigned long long x = a.col_bits[w];
+      const unsigned long long x = col_word(a, w);
       const int c = __popcll(x);
       if (n < c) { range[e] = w * 64 + nth_bit(x, n); break; }
       n -= c;
@@ -195,7 +206,7 @@ __global__ __launch_bounds__(T) void tile_rows(RowArgs a) {
     int base = t << a.lg;
     for (int n0 = lo; n0 < hi; n0 += T) {
       const int n = n0 + tid;
-      const bool v = n < hi && (a.col_bits[n >> 6] >> (n & 63) & 1ull);
+      const bool v = n < hi && (col_word(a, n >> 6) >> (n & 63) & 1ull);
       int all;
       const int p = base + sum_before(v, part[1], &all);
       if (v) a.kept[p] = n;
@@ -537,7 +548,9 @@ tw_status pack_device(const uint16_t* B, int ldb, const uint8_t* mask, const uin
   Pinned pin;
   Launched ours{s};
   const unsigned nb = (unsigned)((N + 127) / 128);
-  const size_t o_rbits = up((size_t)nb * 16), o_kept = o_rbits + up(ntmax * blocks * 8), o_drop = o_kept + up((size_t)N * 4);
+  // column bits: a workgroup per CU at most, 1024 rows at least for each
+  const int slices = std::max(1, std::min({16, 256 / (int)std::min(nb, 256u), (K + 1023) / 1024})), slice_rows = (K + slices - 1) / slices;
+  const size_t o_rbits = up((size_t)nb * 16 * slices), o_kept = o_rbits + up(ntmax * blocks * 8), o_drop = o_kept + up((size_t)N * 4);
   const size_t plain = 64 + (6 * ntmax + 256) * 4;                   // two numbers, then the tables (each 256-byte aligned)
   if (ws.alloc(o_drop + (size_t)N * 4) != hipSuccess || pin.get(plain, 1 + ntmax * blocks) != hipSuccess) {
     (void)hipGetLastError();
@@ -545,7 +558,7 @@ tw_status pack_device(const uint16_t* B, int ldb, const uint8_t* mask, const uin
   }
   char* w = (char*)ws.p;
   const uint32_t tag = next_tag.fetch_add(1);
-  TWG_LAUNCH(column_bits, dim3(nb), dim3(1024), S, K, N, (uint16_t*)w);
+  TWG_LAUNCH(column_bits, dim3(nb, (unsigned)slices), dim3(1024), S, K, N, slice_rows, (uint16_t*)w);
   ours.running = true;
   RowArgs r{};
   r.S = S;
@@ -555,6 +568,7 @@ tw_status pack_device(const uint16_t* B, int ldb, const uint8_t* mask, const uin
   r.ldb = ldb;
   r.K = K; r.N = N; r.lg = lg; r.blocks = blocks;
   r.col_bits = (const unsigned long long*)w;
+  r.slices = slices; r.stride = (int)nb * 2;
   r.row_bits = (unsigned long long*)(w + o_rbits);
   r.kept = (int32_t*)(w + o_kept); r.dropped = (int32_t*)(w + o_drop);
   r.host = pin.words; r.tag = tag;

@@ -105,6 +105,32 @@ def test_more_counts_than_one_block_of_host_memory(K, N, G):
     h.free()
 
 
+@pytest.mark.parametrize("K,N,G,pattern", [(1025, 70, 64, "tw"), (5000, 130, 32, "tvw"), (20011, 64, 64, "tw"), (2049, 700, 128, "tvw"),
+                                           (17000, 17, 32, "tw")])
+def test_tall_weights_in_slices(K, N, G, pattern):
+    """Narrow and tall: the columns' bits come from several slices of the rows, a column from one of them or a few."""
+    rng = np.random.default_rng(K + N)
+    B = wl.rng_fp16(K, (K, N))
+    tm = np.zeros((K, N), np.uint8)
+    cols = np.sort(rng.choice(N, max(1, N * 2 // 3), replace=False))
+    for t in range(0, len(cols), G):
+        at = rng.integers(0, K, 5)                                   # rows of a tile in few places, the ends among them
+        rows = np.unique(np.concatenate([at, (at + 1) % K, [0, K - 1] if t == 0 else at]))
+        tm[np.ix_(rows, cols[t:t + G])] = 1
+    mask, tile_mask, P = tm, None, tw.PATTERN_TW
+    if pattern == "tvw":                                             # two of four: the first two rows of every group
+        mask, tile_mask, P = np.zeros_like(tm), tm, tw.PATTERN_TVW
+        for t in range(0, len(cols), G):
+            rows = np.flatnonzero(tm[:, cols[t]])
+            mask[np.ix_(rows[np.arange(len(rows)) % 4 < 2], cols[t:t + G])] = 1
+    p = _pack_dev(B, mask, G, P, tile_mask=tile_mask)
+    h = tw.tw_pack_host(B, mask, G, P, tile_mask=tile_mask)
+    _same(p.export(), h.export())
+    assert p.flop_counts() == h.flop_counts()
+    p.free()
+    h.free()
+
+
 def test_several_threads_pack_at_once():
     """More threads than blocks of host memory are kept, each on a stream of its own, over and over."""
     import threading
