@@ -18,6 +18,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <mutex>
 
 #include "device_common.h"
@@ -317,6 +318,7 @@ struct PruneArgs {
   const int32_t *row_pos, *row_list;   // K > REG_MAX: the same for the rows of each tile
   uint8_t *tiles, *element;            // masks (tiles: or null)
   int blocks, rows;                    // workgroups per tile, rows of each (a multiple of 64)
+  int shares;                          // masks: workgroups that share a tile's columns
 };
 constexpr int REG_MAX = 4 * SCAN_T;    // longest segment that is selected in registers
 // The workgroups of neighbouring tiles, which share 128-byte lines of the weight and the masks, run on one XCD: its L2
@@ -417,25 +419,26 @@ __device__ __forceinline__ void store_piece(uint8_t* p, const u32x4_t& v, int fr
 // The masks.  tiles[k][n] = column n kept and row k kept in n's tile (may be null).  TVW: element[k][n], of those,
 // 2:4 along the condensed kept rows of the tile: in every group of 4 consecutive kept rows and every column
 // the 2 largest |w| stay; equal magnitudes: the lower position stays.
-// Workgroup (tile, block of rows): the tile answers for the columns from its first kept one (tile 0: from 0) to the next
-// tile's (the last: to N).  R > 0: the workgroup first selects the tile's kept rows for itself.  Then 16 lanes take
-// a row, 16 bytes of the mask each, aligned whatever N is; in a kept row (TVW) a lane reads the weights of the group's
-// four rows and ranks its own row among them.  1024 x 4096: 16 us; selection, masks of zeros and a kernel that filled in
-// single bytes took 6.7 + 5.4 + 4.1 us and two launches more.  1003 x 2491: 20 against 45.  What bounds it: the selection
-// (4 us), then the number of store instructions: the pieces that two tiles share are written in up to four parts.
-constexpr int COL_BITS = 8192;                 // columns a tile may answer for with their bits in LDS
-template <int R, bool TVW>
+// Workgroup (tile, block of rows, share of the columns): the tile answers for the columns from its first kept one (tile 0:
+// from 0) to the next tile's (the last: to N).  R > 0: the workgroup first selects the tile's kept rows for itself.  Then a team of
+// G / 8 lanes takes a row, 16 bytes of the mask each, aligned whatever N is.  TVW by rows: in a kept row a lane reads the
+// weights of the group's four rows and ranks its own row among them; by groups: a team reads and ranks the four rows once.  What bounds it: the selection (4 us), then
+// the number of store instructions: the pieces that two tiles share are written in up to four parts.
+constexpr int COL_BITS = 65536;                // columns a tile may answer for with their bits in LDS
+enum { MASKS_TW = 0, MASKS_TVW_ROWS = 1, MASKS_TVW_GROUPS = 2 };
+template <int R, int MODE>
 __global__ __launch_bounds__(1024) void emit_masks(PruneArgs a, int lg) {
   __shared__ SelectLds lds;
   __shared__ int32_t pos_lds[R > 0 ? R * SCAN_T : 1], list_lds[R > 0 ? R * SCAN_T : 1];
   __shared__ uint32_t bits[COL_BITS / 32 + 2];
   const int K = a.K, N = a.N, tid = threadIdx.x;
-  int t, b;
-  tile_and_block(a, t, b);
+  const int lid = xcd_remap(blockIdx.x, gridDim.x), tiles = (int)gridDim.x / (a.blocks * a.shares);
+  const int t = lid % tiles, share = lid / tiles % a.shares, b = lid / (tiles * a.shares);
   const int c0 = t << lg, c1 = min((t + 1) << lg, a.n_kept);
   const int lo = t == 0 ? 0 : a.kept_cols[c0], hi = c1 < a.n_kept ? a.kept_cols[c1] : N;
   const bool few = hi - lo <= COL_BITS;        // (uniform)
-  for (int i = tid; i < COL_BITS / 32 + 2; i += 1024) bits[i] = 0;
+  if (few)
+    for (int i = tid; i < (hi - lo) / 32 + 2; i += 1024) bits[i] = 0;
   __syncthreads();
   if (few && c0 + tid < c1) {
     const int at = a.kept_cols[c0 + tid] - lo;
@@ -488,30 +491,95 @@ __global__ __launch_bounds__(1024) void emit_masks(PruneArgs a, int lg) {
     }
   };
   const bool same = !a.tiles || (((uintptr_t)a.tiles ^ (uintptr_t)a.element) & 15) == 0;
-  const int k_end = min(K, (b + 1) * a.rows);
-  for (int k = b * a.rows + (tid >> 4); k < k_end; k += 64) {
-    const int at = c0 < c1 ? pos[k] : -1;
-    uint8_t* row = a.element + (size_t)k * N;
-    const int off = (int)((uintptr_t)row & 15);
-    for (int n = ((lo + off) & ~15) - off + 16 * (tid & 15); n < hi; n += 256) {
-      const uint32_t x = at >= 0 ? kept16(n) : 0u;
-      u32x4_t tb, eb;
+  const int team = lg - 3, lane = tid & ((1 << team) - 1), first_team = tid >> team, teams = 1024 >> team;
+  auto expand = [](uint32_t x) {               // four bits each -> bytes 0 / 1
+    u32x4_t v;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {            // four bits -> bytes 0 / 1
-        const uint32_t y = x >> (4 * j) & 15u;
-        tb[j] = (y * 0x00204081u) & 0x01010101u;
+    for (int j = 0; j < 4; ++j) v[j] = ((x >> (4 * j) & 15u) * 0x00204081u) & 0x01010101u;
+    return v;
+  };
+  auto store = [&](int k, int n, uint32_t x, const u32x4_t& tb, const u32x4_t& eb) {
+    const int from = lo - n, to = hi - n;
+    store_piece(a.element + (size_t)k * N + n, eb, from, to);
+    if (!a.tiles) return;
+    uint8_t* other = a.tiles + (size_t)k * N + n;
+    if (same) store_piece(other, tb, from, to);
+    else
+      for (int c = max(from, 0); c < min(to, 16); ++c) other[c] = (uint8_t)(x >> c & 1u);
+  };
+  // this lane's columns of a row whose mask starts `off` bytes behind a multiple of 16
+  auto first_column = [&](int off) { return ((lo + off) & ~15) - off + 16 * (lane + (share << team)); };
+  const int step = 16 * a.shares << team;
+  auto offset = [&](int k) { return (int)((uintptr_t)(a.element + (size_t)k * N) & 15); };
+  constexpr uint32_t H = 0x80008000u;          // top bits of the halves
+  if constexpr (MODE == MASKS_TVW_GROUPS) {
+    const int groups = c0 < c1 ? (a.rows_kept + 3) / 4 : 0;
+    const int g0 = (int)((int64_t)groups * b / a.blocks), g_end = (int)((int64_t)groups * (b + 1) / a.blocks);
+    // (the groups first: while some teams are at them, the others write the rows that are not kept)
+    for (int g = g0 + first_team; g < g_end; g += teams) {
+      const int cnt = min(4, a.rows_kept - 4 * g);
+      int row[4], off[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) { row[q] = list[4 * g + min(q, cnt - 1)]; off[q] = offset(row[q]); }
+      const bool alike = off[0] == off[1] && off[0] == off[2] && off[0] == off[3];   // (N a multiple of 16, usually)
+#pragma unroll 1
+      for (int only = 0; only < (alike ? 1 : cnt); ++only) {
+        const int o = only == 0 ? off[0] : only == 1 ? off[1] : only == 2 ? off[2] : off[3];
+        for (int n = first_column(o); n < hi; n += step) {             // the masks of all rows from column n on, or of one of them
+          const uint32_t x = kept16(n);
+          const u32x4_t tb = expand(x);
+          u32x4_t eb[4] = {tb, tb, tb, tb};
+          if (x) {
+            uint32_t v[4][8];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) load16(row[q], n, v[q]);
+#pragma unroll
+            for (int q = 1; q < 4; ++q)
+              if (q >= cnt)                    // past the end of the list: ahead of nobody
+#pragma unroll
+                for (int j = 0; j < 8; ++j) v[q][j] = 0;
+            // top bit of a half: the row in front is as large or larger, so it comes ahead; a row stays unless two come ahead
+            auto two = [](uint32_t p, uint32_t q, uint32_t r) { return (p & q) | (r & (p | q)); };   // of three, two at least
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+              uint32_t keep[4][2];
+#pragma unroll
+              for (int h = 0; h < 2; ++h) {
+                auto ahead = [&](int p, int q) { return (v[p][2 * j + h] | H) - v[q][2 * j + h]; };
+                const uint32_t p01 = ahead(0, 1), p02 = ahead(0, 2), p03 = ahead(0, 3), p12 = ahead(1, 2), p13 = ahead(1, 3), p23 = ahead(2, 3);
+                keep[0][h] = two(p01, p02, p03);
+                keep[1][h] = two(~p01, p12, p13);
+                keep[2][h] = two(~p02, ~p12, p23);
+                keep[3][h] = two(~p03, ~p13, ~p23);
+              }
+#pragma unroll
+              for (int q = 0; q < 4; ++q) eb[q][j] &= __builtin_amdgcn_perm(keep[q][1], keep[q][0], 0x07050301u) >> 7;
+            }
+          }
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+            if (q < cnt && (alike || q == only)) store(row[q], n, x, tb, eb[q]);
+        }
       }
-      eb = tb;
-      if constexpr (TVW) {
+    }
+  }
+  const int k_end = min(K, (b + 1) * a.rows);
+  for (int k = b * a.rows + first_team; k < k_end; k += teams) {
+    const int at = c0 < c1 ? pos[k] : -1;
+    if (MODE == MASKS_TVW_GROUPS && at >= 0) continue;
+    for (int n = first_column(offset(k)); n < hi; n += step) {
+      const uint32_t x = at >= 0 ? kept16(n) : 0u;
+      const u32x4_t tb = expand(x);
+      u32x4_t eb = tb;
+      if constexpr (MODE == MASKS_TVW_ROWS) {
         if (x) {
-          const int g0 = at & ~3, mine = at & 3;
+          const int g = at & ~3, mine = at & 3;
           uint32_t own[8], v[4][8];
           load16(k, n, own);
 #pragma unroll
           for (int q = 0; q < 4; ++q)          // past the end of the list: the row itself, which is not ahead of itself
-            load16(g0 + q < a.rows_kept ? list[g0 + q] : k, n, v[q]);
+            load16(g + q < a.rows_kept ? list[g + q] : k, n, v[q]);
           // top bit of a half: row q comes ahead, being larger, or (in front) as large
-          constexpr uint32_t H = 0x80008000u;
           uint32_t keep[8];
 #pragma unroll
           for (int j = 0; j < 8; ++j) {
@@ -526,14 +594,7 @@ __global__ __launch_bounds__(1024) void emit_masks(PruneArgs a, int lg) {
             eb[j] &= __builtin_amdgcn_perm(keep[2 * j + 1], keep[2 * j], 0x07050301u) >> 7;
         }
       }
-      const int from = lo - n, to = hi - n;
-      store_piece(row + n, eb, from, to);
-      if (a.tiles) {
-        uint8_t* other = a.tiles + (size_t)k * N + n;
-        if (same) store_piece(other, tb, from, to);
-        else
-          for (int c = max(from, 0); c < min(to, 16); ++c) other[c] = (uint8_t)(x >> c & 1u);
-      }
+      store(k, n, x, tb, eb);
     }
   }
 }
@@ -575,13 +636,13 @@ hipError_t prune_device(const uint16_t* B, int K, int N, int ldb, int G, bool tv
   } while (0)
   TWG_LAUNCH(column_scores, dim3((unsigned)((N + SCORE_CW - 1) / SCORE_CW)), dim3(1024), B, K, N, ldb,
              (int)(ldb % 4 == 0 && aligned(B, 8)), col_score);
-  PruneArgs a{B, K, N, ldb, n_kept, rows_per_tile, col_score, row_score, col_pos, kept_cols, row_pos, row_list, tile_mask, mask, 0, 0};
+  PruneArgs a{B, K, N, ldb, n_kept, rows_per_tile, col_score, row_score, col_pos, kept_cols, row_pos, row_list, tile_mask, mask, 0, 0, 1};
   // Workgroups of 1024 threads for the tiles, about one per CU: each selects for itself.
   const int tiles = nt > 0 ? nt : 1;
   a.blocks = 256 / tiles > 1 ? 256 / tiles : 1;
   a.rows = ((K + a.blocks - 1) / a.blocks + 63) / 64 * 64;
   a.blocks = (K + a.rows - 1) / a.rows;
-  const dim3 grid((unsigned)tiles * (unsigned)a.blocks), block(1024);
+  dim3 grid((unsigned)tiles * (unsigned)a.blocks), block(1024);
   // Columns: entries per thread of a selection in registers, or (0) a kernel that selects.
   const int rc = N <= SCAN_T ? 1 : N <= REG_MAX ? 4 : 0, rk = K <= SCAN_T ? 1 : K <= REG_MAX ? 4 : 0;
   if (!rc) TWG_LAUNCH(select_kept, dim3(1), block, col_score, N, n_cols_pruned, col_pos, kept_cols);
@@ -595,15 +656,24 @@ hipError_t prune_device(const uint16_t* B, int K, int N, int ldb, int G, bool tv
   else if (G == 64) TWG_ROWS(64);
   else TWG_ROWS(32);
   if (!rk && nt > 0) TWG_LAUNCH(select_kept, dim3(nt), block, row_score, K, K - rows_per_tile, row_pos, row_list);
-  if (!tvw) {                                  // the element mask is the tile mask
-    if (rk == 1) TWG_LAUNCH((emit_masks<1, false>), grid, block, a, lg);
-    else if (rk == 4) TWG_LAUNCH((emit_masks<4, false>), grid, block, a, lg);
-    else TWG_LAUNCH((emit_masks<0, false>), grid, block, a, lg);
-  } else {
-    if (rk == 1) TWG_LAUNCH((emit_masks<1, true>), grid, block, a, lg);
-    else if (rk == 4) TWG_LAUNCH((emit_masks<4, true>), grid, block, a, lg);
-    else TWG_LAUNCH((emit_masks<0, true>), grid, block, a, lg);
-  }
+  // Few tiles with many columns each and few rows: their columns in shares.
+  const int room = 256 / (tiles * a.blocks), wide = N / (tiles * 256);
+  a.shares = std::max(1, std::min(room, wide));
+  grid.x *= (unsigned)a.shares;
+  // TVW, few groups of four rows for a workgroup's teams: a team per row, which reads its group and ranks itself (768 x 768
+  // 25.2 us, a team per group 28.5; 4096 x 4096 78 and 68).
+  const int groups = ((rows_per_tile + 3) / 4 + a.blocks - 1) / a.blocks, teams = 1024 >> (lg - 3);
+  const int mode = !tvw ? MASKS_TW : 4 * groups <= teams ? MASKS_TVW_ROWS : MASKS_TVW_GROUPS;
+#define TWG_MASKS(R_)                                                                                  \
+  do {                                                                                                 \
+    if (mode == MASKS_TW) TWG_LAUNCH((emit_masks<R_, MASKS_TW>), grid, block, a, lg);                  \
+    else if (mode == MASKS_TVW_ROWS) TWG_LAUNCH((emit_masks<R_, MASKS_TVW_ROWS>), grid, block, a, lg); \
+    else TWG_LAUNCH((emit_masks<R_, MASKS_TVW_GROUPS>), grid, block, a, lg);                           \
+  } while (0)
+  if (rk == 1) TWG_MASKS(1);
+  else if (rk == 4) TWG_MASKS(4);
+  else TWG_MASKS(0);
+#undef TWG_MASKS
 #undef TWG_ROWS
 #undef TWG_LAUNCH
   return hipSuccess;

@@ -18,7 +18,7 @@ pytestmark = pytest.mark.gpu
 CASES = [  # K, N, G, columns pruned, rows kept per tile
     (1024, 64, 64, 5, 300), (1025, 48, 32, 0, 256), (6, 4096, 128, 400, 4), (8, 4112, 64, 1, 8),
     (4100, 16, 32, 2, 1000), (33, 1040, 128, 1039, 1), (5, 17, 32, 3, 5), (64, 160, 32, 16, 32),
-    (1, 1, 32, 0, 1), (130, 3, 64, 1, 70), (4097, 5, 128, 0, 4097), (2, 9000, 64, 8990, 1), (70, 143, 128, 143, 5),
+    (600, 3008, 32, 8, 557), (601, 3001, 32, 1, 558), (400, 6016, 128, 0, 390), (130, 9000, 64, 8950, 20), (1, 1, 32, 0, 1), (130, 3, 64, 1, 70), (4097, 5, 128, 0, 4097), (2, 9000, 64, 8990, 1), (70, 143, 128, 143, 5),
 ]
 
 
@@ -75,9 +75,11 @@ def test_masks_at_any_address(K, N, G, at, tile_at):
     p.free()
 
 
-def test_a_tile_of_more_columns_than_fit_in_lds():
-    """100 kept columns among 20000: the last tile answers for more than 8192 columns."""
-    K, N, G = 6, 20000, 32
+@pytest.mark.parametrize("N", [20000, 90000])
+def test_a_tile_of_very_many_columns(N):
+    """100 kept columns: the last tile answers for all columns from 9000 on, shared by several workgroups, 90000 are more than
+    its bits in LDS hold."""
+    K, G = 6, 32
     B = np.zeros((K, N), np.float16)
     cols = np.r_[5:90, 9000:9015]
     B[:, cols] = wl.rng_fp16(1, (K, len(cols)), 0.5)
