@@ -21,7 +21,7 @@ struct GemmArgs {
                                  // 16-byte records
   int uniform_kp;                // > 0: every tile has this padded K_t and launch position = tile, so the
                                  // record is (pos, pos * uniform_kp, uniform_kp) and need not be loaded
-  const int32_t* zero_cols;      // pruned columns of C, written as +0
+  const int32_t* zero_cols;      // columns of C that are +0: the pruned ones (TEW: without restored elements)
   const uint32_t* meta;          // TVW: 2:4 position words
   const int32_t* ew_ptr;         // TEW: N+1 offsets into ew_pairs by original column of C
   const uint32_t* ew_pairs;      // TEW: restored elements, K row << 16 | fp16 bits (at least one readable word)
@@ -88,13 +88,14 @@ hipError_t launch_dense_mk(GemmArgs g, hipStream_t stream);
 // (tm in {128, 256}, G = 128); DMA_KSPLIT2 = two groups of 4 waves splitting K inside
 // the workgroup (dense: K % 64 == 0).
 enum { DMA_WAVES4 = 0, DMA_WAVES8 = 1, DMA_KSPLIT2 = 2 };
-// Restored elements (TEW): in rows that join the tile's list, or one by one behind the K loop.
-enum { EW_NONE = 0, EW_JOINED = 1, EW_ELEMENTS = 2 };
 hipError_t launch_tw_km_dma(int G, int tm, int depth, int variant, GemmArgs g, hipStream_t stream);
 // The same with K split across g.wg_split workgroups per tile (4 waves, 3 stages): (G, tm) in
 // {(128, 128), (128, 64), (64, 128)}.
 hipError_t launch_tw_km_dma_split(int G, int tm, GemmArgs g, hipStream_t stream);
-// The same for a TEW weight with restored elements (g.ew_*; three stages only).
+// The same as launch_tw_km_dma for a TEW weight with restored elements (g.ew_*; three stages only): they are multiplied in
+// rows that join the tile's list, or one by one behind the K loop (g.ew_elements, and where a tile's sums with the joined rows
+// are not all finite).
+enum { EW_NONE = 0, EW_JOINED = 1, EW_ELEMENTS = 2 };
 hipError_t launch_tew_km_dma(int G, int tm, int depth, int variant, GemmArgs g, hipStream_t stream);
 hipError_t launch_dense_km_dma(int tn, int tm, int depth, int variant, GemmArgs g, hipStream_t stream);
 // Zero fill of n 32-bit words (the counters of a workspace).

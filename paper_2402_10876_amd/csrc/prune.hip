@@ -23,7 +23,6 @@
 
 #include "device_common.h"
 #include "prune.h"
-#include "scan.h"
 
 namespace twg {
 
@@ -32,6 +31,7 @@ namespace {
 typedef unsigned __int128 u128;
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 typedef int32_t i32x4_t __attribute__((ext_vector_type(4)));
+constexpr int SCAN_T = 1024, SCAN_WAVES = SCAN_T / 64;   // threads and waves of a workgroup that selects
 
 __device__ __forceinline__ uint64_t magnitude24(uint16_t h) {   // |value| in units of 2^-24
   const uint32_t e = (h >> 10) & 31u, m = h & 1023u;

@@ -278,6 +278,39 @@ def test_tew_elements_one_by_one(M, N, tile_m, ksplit, _opts):
     p.free()
 
 
+@pytest.mark.gpu
+@pytest.mark.parametrize("G,M,K,tile_m,ksplit", [
+    (64, 5, 210, 0, 0), (128, 5, 210, 0, 0),                                                      # few output blocks
+    (64, 333, 210, 128, 1), (64, 333, 900, 128, 2), (128, 333, 210, 64, 1), (128, 333, 210, 256, 1), (128, 333, 900, 64, 2)])
+def test_tew_concat_gemm(G, M, K, tile_m, ksplit, _opts):
+    """Members' rows with restored elements join the tiles of the concatenated weight: narrow tiles in the middle, a member without
+    restored elements and one without kept columns; random values, and A = I, bit for bit."""
+    rng = np.random.default_rng(G + M + K)
+    mem = []
+    for i, (N, extra, kw) in enumerate([(150, 0.04, {}), (300, 0.0, {}), (77, 0.02, dict(col_keep=0.0)), (190, 0.08, dict(row_keep=0.1))]):
+        m, tm = random_tew_mask(rng, K, N, G, extra=extra, **kw)
+        mem.append((wl.make_B(60 + i, K, N, 1.0), m, tm))
+    parts = [tw.tw_pack_host(B, m, G, tw.PATTERN_TEW, tile_mask=t) for B, m, t in mem]
+    cat = tw.tw_concat(parts)
+    B, m = (np.concatenate([x[i] for x in mem], axis=1) for i in (0, 1))
+    A = wl.make_A(11, M, K)
+    eye = np.zeros((M, K), np.float16)
+    at = rng.permutation(np.arange(M) % K)
+    eye[np.arange(M), at] = 1
+    tw.tw_set_option("tile_m", tile_m)
+    tw.tw_set_option("ksplit", ksplit)
+    from tests import gpu_util as gu
+    print(f"case tew concat G={G} M={M} tile_m={tile_m} ksplit={ksplit}", flush=True)
+    C, _ = gu.run_tw(tw, cat, A, B.shape[1])
+    _, raw = gu.run_tw(tw, cat, eye, B.shape[1])
+    assert_C_close(C, og.gemm_oracle(A, B, m), og.abs_bound(A, B, m))
+    want = np.where(m != 0, B, np.float16(0)).astype(np.float16)[at]
+    want[want == 0] = 0                                                # (+0: a sum that starts at +0)
+    assert np.array_equal(raw[:, :M].T.view(np.uint16), want.view(np.uint16))
+    for p in parts + [cat]:
+        p.free()
+
+
 def test_tew_image_join_counts_only_shape_the_device_form():
     """tw_flop_counts, tw_export and tw_unpack know nothing of the rows that are multiplied whole."""
     rng = np.random.default_rng(31)
