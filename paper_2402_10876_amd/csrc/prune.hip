@@ -87,27 +87,30 @@ __device__ __forceinline__ u128 sum_over_lanes(const Sum& s) {
   return total;
 }
 
-// TW-C scores, exact and independent of any order (integer sums).  A workgroup of 1024 threads takes 16 columns
-// and all rows: 4 lanes of 4 columns, 256 rows at a time, 4 loads of 8 bytes in flight per thread.  Neighbouring
+// TW-C scores, exact and independent of any order (integer sums).  A workgroup of 1024 threads takes CW columns:
+// lanes of 4 columns, 4 loads of 8 bytes in flight per thread.  CW = 16: all rows, 256 at a time; neighbouring
 // workgroups, which share the 128-byte lines, run on one XCD and meet in its L2.  One kernel, where slices of the
-// rows and a second kernel to add them up took 9.8 us and a launch more for 1024 x 4096.
-constexpr int SCORE_CW = 16, SCORE_LANES = SCORE_CW / 4, SCORE_STEP = 1024 / SCORE_LANES;
-__global__ __launch_bounds__(1024) void column_scores(const uint16_t* B, int K, int N, int ldb, int vec, u128* score) {
-  constexpr int CW = SCORE_CW, LANES = SCORE_LANES, ROWS = SCORE_STEP, U = 4;
+// rows and a second kernel to add them up took 9.8 us and a launch more for 1024 x 4096.  CW = 64, tall weights: blockIdx.y is a
+// slice of `slice` rows with scores of its own, which add_slices() adds up.  (With 25088 rows of 4096 columns the workgroups that share
+// lines drift apart: 144 us in one piece, 91 in slices.)
+template <int CW>
+__global__ __launch_bounds__(1024) void column_scores(const uint16_t* B, int K, int N, int ldb, int vec, int slice, u128* score) {
+  constexpr int LANES = CW / 4, ROWS = 1024 / LANES, U = 4;
   __shared__ u128 part[16][CW];
   const int tid = threadIdx.x, c4 = tid % LANES;
   const int n_block = xcd_remap(blockIdx.x, gridDim.x) * CW;
   const int n = n_block + c4 * 4;
   Sum s[4];
   int rows = 0;
-  for (int k0 = tid / LANES; k0 < K; k0 += U * ROWS) {
+  const int k_end = min(K, ((int)blockIdx.y + 1) * slice);
+  for (int k0 = (int)blockIdx.y * slice + tid / LANES; k0 < k_end; k0 += U * ROWS) {
     union { uint2 v; uint16_t e[4]; } x[U];
     uint32_t big = 0;
 #pragma unroll
     for (int i = 0; i < U; ++i) {
       x[i].v = uint2{0u, 0u};
       const int k = k0 + i * ROWS;
-      if (k >= K) continue;
+      if (k >= k_end) continue;
       const uint16_t* p = B + (size_t)k * ldb + n;
       if (vec && n + 4 <= N) x[i].v = *(const uint2*)p;
       else
@@ -136,7 +139,7 @@ __global__ __launch_bounds__(1024) void column_scores(const uint16_t* B, int K, 
   }
 #pragma unroll
   for (int c = 0; c < 4; ++c) {
-    if (K > (1 << 15)) s[c].carry();           // (the lanes' 64-bit sums together would not fit)
+    if (slice > (1 << 15)) s[c].carry();       // (the lanes' 64-bit sums together would not fit)
     const u128 w = sum_over_lanes<LANES, 32>(s[c]);
     if ((tid & 63) < LANES) part[tid >> 6][c4 * 4 + c] = w;
   }
@@ -146,7 +149,15 @@ __global__ __launch_bounds__(1024) void column_scores(const uint16_t* B, int K, 
   u128 t = 0;
 #pragma unroll
   for (int w = 0; w < 16; ++w) t += part[w][tid];
-  score[col] = t;
+  score[(size_t)blockIdx.y * N + col] = t;
+}
+__global__ void add_slices(const u128* partial, int slices, int N, u128* score) {
+  const int n = blockIdx.x * blockDim.x + threadIdx.x;
+  if (n >= N) return;
+  u128 t = 0;
+#pragma unroll 16
+  for (int y = 0; y < slices; ++y) t += partial[(size_t)y * N + n];
+  score[n] = t;
 }
 
 // Which entries of a segment of scores are kept: all but the n_pruned lowest in (score, index) order.  For the
@@ -606,7 +617,7 @@ size_t align_up(size_t x) { return (x + 255) / 256 * 256; }
 size_t prune_workspace_bytes(int K, int N, int G) {
   const size_t nt = (size_t)(N + G - 1) / G;
   // The size is part of the interface: more than the kernels use (one spare list per column and per row, and
-  // room for the column scores of `slices` slices of the rows).
+  // room for the column scores of `slices` slices of the rows, of which prune_device() takes fewer).
   const int blocks = (N + 255) / 256, slices = K < 512 / blocks ? K : 512 / blocks > 1 ? 512 / blocks : 1;
   return align_up((size_t)N * 16) + 3 * align_up((size_t)N * 4) +          // column score, pos, list
          align_up(nt * K * 16) + 3 * align_up(nt * K * 4) +                 // row score, pos, list
@@ -625,7 +636,8 @@ hipError_t prune_device(const uint16_t* B, int K, int N, int ldb, int G, bool tv
   int32_t* kept_cols = (int32_t*)w;      w += align_up((size_t)N * 4);
   u128* row_score = (u128*)w;            w += align_up(ntmax * K * 16) + align_up(ntmax * K * 4);
   int32_t* row_pos = (int32_t*)w;        w += align_up(ntmax * K * 4);
-  int32_t* row_list = (int32_t*)w;
+  int32_t* row_list = (int32_t*)w;       w += align_up(ntmax * K * 4);
+  u128* partial = (u128*)w;
   const int lg = G == 128 ? 7 : G == 64 ? 6 : 5;
   auto aligned = [](const void* p, size_t a) { return ((uintptr_t)p & (a - 1)) == 0; };
   // a failed launch ends the call: later kernels would read workspace nobody wrote
@@ -634,8 +646,18 @@ hipError_t prune_device(const uint16_t* B, int K, int N, int ldb, int G, bool tv
     const hipError_t e_ = launch_kernel(kernel, grid, block, stream, __VA_ARGS__); \
     if (e_ != hipSuccess) return e_;                                          \
   } while (0)
-  TWG_LAUNCH(column_scores, dim3((unsigned)((N + SCORE_CW - 1) / SCORE_CW)), dim3(1024), B, K, N, ldb,
-             (int)(ldb % 4 == 0 && aligned(B, 8)), col_score);
+  // From 4096 rows on: slices of at least 512, 64 columns (a line) wide, one workgroup per CU in all.  In slices / not, whole
+  // call: 65536 x 64 124 / 274 us, 25088 x 512 86 / 150, 16384 x 2048 96 / 129, 25088 x 4096 246 / 302, 4096 x 1024 32 / 34,
+  // 4608 x 4096 67 / 70; 2304 x 256 29 / 28, 3072 x 768 30 / 31.
+  const int vec = (int)(ldb % 4 == 0 && aligned(B, 8)), wide_wgs = (N + 63) / 64;
+  const int slices = K >= 4096 ? std::max(1, std::min(256 / wide_wgs, K / 512)) : 1;
+  if (slices > 1) {
+    TWG_LAUNCH(column_scores<64>, dim3((unsigned)wide_wgs, (unsigned)slices), dim3(1024), B, K, N, ldb, vec,
+               (K + slices - 1) / slices, partial);
+    TWG_LAUNCH(add_slices, dim3((unsigned)wide_wgs), dim3(64), partial, slices, N, col_score);
+  } else {
+    TWG_LAUNCH(column_scores<16>, dim3((unsigned)((N + 15) / 16)), dim3(1024), B, K, N, ldb, vec, K, col_score);
+  }
   PruneArgs a{B, K, N, ldb, n_kept, rows_per_tile, col_score, row_score, col_pos, kept_cols, row_pos, row_list, tile_mask, mask, 0, 0, 1};
   // Workgroups of 1024 threads for the tiles, about one per CU: each selects for itself.
   const int tiles = nt > 0 ? nt : 1;
@@ -656,6 +678,15 @@ hipError_t prune_device(const uint16_t* B, int K, int N, int ldb, int G, bool tv
   else if (G == 64) TWG_ROWS(64);
   else TWG_ROWS(32);
   if (!rk && nt > 0) TWG_LAUNCH(select_kept, dim3(nt), block, row_score, K, K - rows_per_tile, row_pos, row_list);
+  // No selection in each workgroup and many rows for each: more of them, with about 768 rows, TW 384 (25088 x 4096 TVW 396 -> 371
+  // us, TW 249 -> 240, G = 32, 11008 x 4096 251 -> 214 and 151 -> 138; shorter ones gain nothing: 14336 x 4096 TVW with 1344 rows
+  // 192 -> 196, 4608 x 4096 84 -> 91).
+  if (!rk && a.rows >= 1536) {
+    a.blocks = std::max(1, std::min(K / (tvw ? 768 : 384), 1024 / tiles));
+    a.rows = ((K + a.blocks - 1) / a.blocks + 63) / 64 * 64;
+    a.blocks = (K + a.rows - 1) / a.rows;
+    grid.x = (unsigned)tiles * (unsigned)a.blocks;
+  }
   // Few tiles with many columns each and few rows: their columns in shares.
   const int room = 256 / (tiles * a.blocks), wide = N / (tiles * 256);
   a.shares = std::max(1, std::min(room, wide));

@@ -133,6 +133,45 @@ def test_tall_weights_in_slices(K, N, G, pattern):
     h.free()
 
 
+@pytest.mark.parametrize("K,N,G,cp,rk,pattern", [
+    (4095, 66, 64, 3, 900, "tw"), (4096, 64, 64, 0, 1300, "tw"), (4097, 130, 32, 20, 700, "tvw"), (9001, 33, 32, 1, 4000, "tvw"),
+    (40000, 5, 32, 1, 13, "tw")])
+def test_tall_weights_are_scored_in_slices(K, N, G, cp, rk, pattern):
+    """Around the line where columns are scored in slices, with values on both sides of 1 (sums of 64 and of 128 bits)."""
+    B = wl.rng_fp16(K + N, (K, N), 0.5)
+    B[::37] *= np.float16(40)
+    print(f"case tall prune {pattern} K={K} N={N} G={G} cp={cp} rk={rk}", flush=True)
+    mask, tmask, _ = _prune_on_device(B, G, tw.PATTERN_TVW if pattern == "tvw" else tw.PATTERN_TW, cp, rk, ldb=N + 3)
+    want_t = op.tw(B, G, n_cols_pruned=cp, rows_kept_per_tile=rk, exact=True)
+    assert np.array_equal(tmask, want_t)
+    assert np.array_equal(mask, op.vw24_condensed(B, want_t, G) if pattern == "tvw" else want_t)
+
+
+@pytest.mark.parametrize("pattern", ["tw", "tvw"])
+def test_many_rows_for_each_workgroup_of_the_masks(pattern):
+    """2560 rows for a workgroup, which are divided again; the selection as a whole is compared with one on the host in integers."""
+    import torch
+    K, N, G, rk = 5003, 3072, 32, 2000
+    q = torch.randint(-7, 8, (K, N), generator=torch.Generator().manual_seed(5), dtype=torch.int8)
+    q[:, 0::2] *= 2
+    B = (q.to(torch.float16) / 16).numpy()
+    print(f"case masks with many rows {pattern} K={K} N={N}", flush=True)
+    mask, tmask, _ = _prune_on_device(B, G, tw.PATTERN_TVW if pattern == "tvw" else tw.PATTERN_TW, 5, rk)
+    sq = q.to(torch.int32) ** 2
+    cols = torch.sort(torch.argsort(sq.sum(0), stable=True)[5:]).values
+    want_t = np.zeros((K, N), np.uint8)
+    want = np.zeros((K, N), np.uint8)
+    for t in range(0, len(cols), G):
+        c = cols[t:t + G]
+        rows = torch.sort(torch.argsort(sq[:, c].sum(1), stable=True)[K - rk:]).values
+        want_t[np.ix_(rows.numpy(), c.numpy())] = 1
+        v = sq[rows][:, c].reshape(rk // 4, 4, len(c))                        # of four, the two largest; equal: the lower position
+        two = torch.argsort(v, dim=1, descending=True, stable=True)[:, :2]
+        keep = torch.zeros(v.shape, dtype=torch.uint8).scatter_(1, two, 1).reshape(rk, len(c))
+        want[np.ix_(rows.numpy(), c.numpy())] = keep.numpy()
+    assert np.array_equal(tmask, want_t) and np.array_equal(mask, want if pattern == "tvw" else want_t)
+
+
 def test_several_threads_pack_at_once():
     """More threads than blocks of host memory are kept, each on a stream of its own, over and over."""
     import threading
