@@ -368,10 +368,11 @@ static hipError_t launch_mk(GemmArgs& g, hipStream_t stream) {
 
 // Rows of a band.  32: twice the workgroups, two per CU, which overlap their phases and give few blocks
 // a CU each, but read every weight twice as often.  They win where 64-row bands would leave half of
-// the CUs idle, and where the lists are short (band 64 / 32): 768 x 768 at 75 %, M = 2048 9.2 / 7.2 us,
-// M = 4096 9.8 / 11.0; 768 x 3072, M = 512 9.4 / 7.3, M = 1024 10.1 / 11.0; 3072 x 768, M = 2048 23.7 /
-// 21.3; 2000 x 1500 with G = 64, 144 of the larger blocks 16.2 / 20.4; lists of at most 96 rows at M = 4096:
-// 768 x 3072 at 90 % 20.8 / 18.4, 128 x 512 at 50 % 8.0 / 5.9; of 128 rows 9.3 / 9.8 (200 x 1000, 50 %).
+// the CUs idle, and where the lists are short (band 64 / 32): 768 x 768 at 75 %, 128 of the larger blocks 10.6 / 8.5 us, 256
+// 12.3 / 14.1; 768 x 2304, 120 blocks 10.8 / 8.7, 160 11.1 / 12.8; 3072 x 768, 128 blocks 25.1 / 24.2, 256 27.6 / 41.0; 2000 x
+// 1500 with G = 64, 96 blocks 20.1 / 18.7, 144 20.4 / 29.9; lists of 96 rows: 768 x 3072, 640 blocks 18.2 / 16.6, 768 x 2304 with
+// G = 64, 256 blocks 9.5 / 8.9; of 128 rows 18.5 / 20.1, 640 blocks.  Where the rule is wrong: two bands of K and many column
+// groups (1024 x 4096 at 50 %, 48 blocks 13.4 / 16.0), a last round that is nearly empty (768 x 3072, 288 blocks 20.2 / 17.9).
 template <int G>
 static hipError_t launch_mk_rows(int max_kp, bool nonfinite, GemmArgs& g, hipStream_t stream) {
   constexpr int SLOTS = MK_NW / (G / 32);

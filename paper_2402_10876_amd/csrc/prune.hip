@@ -13,8 +13,8 @@
 // first.
 //
 // What bounds it: three launches one after the other on a weight of a few MB, each of them a
-// few dependent trips to memory.  1024 x 4096 at 87.5 % (TVW): 35.4 us of kernels,
-// against 39.4 with seven launches; 64 x 64 20 against 25.5; 3136 x 192 30 against 59.
+// few dependent trips to memory (four for tall weights, 4096 rows and more).  Whole call, seven launches / now: 1024 x 4096 at
+// 87.5 % (TVW) 39.8 / 34.0 us, 64 x 64 25.6 / 14.4, 3072 x 768 44.0 / 33.7, 4096 x 4096 66.0 / 61.2, 25088 x 512 120 / 97.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
