@@ -90,7 +90,7 @@ __device__ __forceinline__ u128 sum_over_lanes(const Sum& s) {
 // TW-C scores, exact and independent of any order (integer sums).  A workgroup of 1024 threads takes CW columns:
 // lanes of 4 columns, 4 loads of 8 bytes in flight per thread.  CW = 16: all rows, 256 at a time; neighbouring
 // workgroups, which share the 128-byte lines, run on one XCD and meet in its L2.  One kernel, where slices of the
-// rows and a second kernel to add them up took 9.8 us and a launch more for 1024 x 4096.  CW = 64, tall weights: blockIdx.y is a
+// rows and a second kernel to add them up took 9.8 us and a launch more for 1024 x 4096.  CW = 64, tall or wide weights: blockIdx.y is a
 // slice of `slice` rows with scores of its own, which add_slices() adds up.  (With 25088 rows of 4096 columns the workgroups that share
 // lines drift apart: 144 us in one piece, 91 in slices.)
 template <int CW>
@@ -648,13 +648,14 @@ hipError_t prune_device(const uint16_t* B, int K, int N, int ldb, int G, bool tv
   } while (0)
   // From 4096 rows on: slices of at least 512, 64 columns (a line) wide, one workgroup per CU in all.  In slices / not, whole
   // call: 65536 x 64 124 / 274 us, 25088 x 512 86 / 150, 16384 x 2048 96 / 129, 25088 x 4096 246 / 302, 4096 x 1024 32 / 34,
-  // 4608 x 4096 67 / 70; 2304 x 256 29 / 28, 3072 x 768 30 / 31.
+  // 4608 x 4096 67 / 70; 2304 x 256 29 / 28, 3072 x 768 30 / 31.  Wide weights have enough workgroups of whole lines without
+  // (lines / quarters of lines, the kernel alone: 272 x 34912 14 / 32 us, 4096 x 14336 41 / 58, 5120 x 13824 56 / 80).
   const int vec = (int)(ldb % 4 == 0 && aligned(B, 8)), wide_wgs = (N + 63) / 64;
   const int slices = K >= 4096 ? std::max(1, std::min(256 / wide_wgs, K / 512)) : 1;
-  if (slices > 1) {
+  if (slices > 1 || wide_wgs >= 128) {
     TWG_LAUNCH(column_scores<64>, dim3((unsigned)wide_wgs, (unsigned)slices), dim3(1024), B, K, N, ldb, vec,
-               (K + slices - 1) / slices, partial);
-    TWG_LAUNCH(add_slices, dim3((unsigned)wide_wgs), dim3(64), partial, slices, N, col_score);
+               (K + slices - 1) / slices, slices > 1 ? partial : col_score);
+    if (slices > 1) TWG_LAUNCH(add_slices, dim3((unsigned)wide_wgs), dim3(64), partial, slices, N, col_score);
   } else {
     TWG_LAUNCH(column_scores<16>, dim3((unsigned)((N + 15) / 16)), dim3(1024), B, K, N, ldb, vec, K, col_score);
   }
@@ -678,11 +679,13 @@ hipError_t prune_device(const uint16_t* B, int K, int N, int ldb, int G, bool tv
   else if (G == 64) TWG_ROWS(64);
   else TWG_ROWS(32);
   if (!rk && nt > 0) TWG_LAUNCH(select_kept, dim3(nt), block, row_score, K, K - rows_per_tile, row_pos, row_list);
-  // No selection in each workgroup and many rows for each: more of them, with about 768 rows, TW 384 (25088 x 4096 TVW 396 -> 371
-  // us, TW 249 -> 240, G = 32, 11008 x 4096 251 -> 214 and 151 -> 138; shorter ones gain nothing: 14336 x 4096 TVW with 1344 rows
-  // 192 -> 196, 4608 x 4096 84 -> 91).
-  if (!rk && a.rows >= 1536) {
-    a.blocks = std::max(1, std::min(K / (tvw ? 768 : 384), 1024 / tiles));
+  // Many rows for each workgroup and no selection in them: more workgroups, with about 768 rows, TW 384 (25088 x 4096 TVW
+  // 396 -> 371 us, TW 249 -> 240, G = 32, 11008 x 4096 251 -> 214 and 151 -> 138; shorter ones gain nothing: 14336 x 4096 TVW with
+  // 1344 rows 192 -> 196, 4608 x 4096 84 -> 91).  With a selection only where one per tile leaves CUs idle, TVW (the masks alone,
+  // 3904 x 13520, G = 64, 150 tiles 125 -> 106; TW 50 -> 53, and 4096 x 14336, 80 tiles of three 95 -> 101).
+  const bool idle = rk && tvw && a.blocks == 1 && tiles < 256 && a.rows >= 1024;
+  if (idle || (!rk && a.rows >= 1536)) {
+    a.blocks = std::max(1, idle ? 512 / tiles : std::min(K / (tvw ? 768 : 384), 1024 / tiles));
     a.rows = ((K + a.blocks - 1) / a.blocks + 63) / 64 * 64;
     a.blocks = (K + a.rows - 1) / a.rows;
     grid.x = (unsigned)tiles * (unsigned)a.blocks;

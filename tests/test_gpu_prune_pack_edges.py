@@ -135,9 +135,9 @@ def test_tall_weights_in_slices(K, N, G, pattern):
 
 @pytest.mark.parametrize("K,N,G,cp,rk,pattern", [
     (4095, 66, 64, 3, 900, "tw"), (4096, 64, 64, 0, 1300, "tw"), (4097, 130, 32, 20, 700, "tvw"), (9001, 33, 32, 1, 4000, "tvw"),
-    (40000, 5, 32, 1, 13, "tw")])
+    (40000, 5, 32, 1, 13, "tw"), (70, 8129, 128, 3000, 20, "tvw"), (33, 8128, 64, 5000, 9, "tw")])
 def test_tall_weights_are_scored_in_slices(K, N, G, cp, rk, pattern):
-    """Around the line where columns are scored in slices, with values on both sides of 1 (sums of 64 and of 128 bits)."""
+    """Around the lines where columns are scored in slices and in whole lines of memory, with values on both sides of 1 (sums of 64 and of 128 bits)."""
     B = wl.rng_fp16(K + N, (K, N), 0.5)
     B[::37] *= np.float16(40)
     print(f"case tall prune {pattern} K={K} N={N} G={G} cp={cp} rk={rk}", flush=True)
@@ -147,11 +147,11 @@ def test_tall_weights_are_scored_in_slices(K, N, G, cp, rk, pattern):
     assert np.array_equal(mask, op.vw24_condensed(B, want_t, G) if pattern == "tvw" else want_t)
 
 
-@pytest.mark.parametrize("pattern", ["tw", "tvw"])
-def test_many_rows_for_each_workgroup_of_the_masks(pattern):
-    """2560 rows for a workgroup, which are divided again; the selection as a whole is compared with one on the host in integers."""
+@pytest.mark.parametrize("pattern,K,N,rk", [("tw", 5003, 3072, 2000), ("tvw", 5003, 3072, 2000), ("tvw", 1100, 4500, 500)])
+def test_many_rows_for_each_workgroup_of_the_masks(pattern, K, N, rk):
+    """2560 rows for a workgroup, or all of a tile, which are divided again; the selection as a whole is compared with one on the host in integers."""
     import torch
-    K, N, G, rk = 5003, 3072, 32, 2000
+    G = 32
     q = torch.randint(-7, 8, (K, N), generator=torch.Generator().manual_seed(5), dtype=torch.int8)
     q[:, 0::2] *= 2
     B = (q.to(torch.float16) / 16).numpy()
